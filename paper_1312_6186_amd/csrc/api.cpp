@@ -69,6 +69,8 @@ struct Stage {
     long pool_bands = 0;       // CONV directly under a pool whose backward kernel leaves those band sums: their number
     bool bands_ready = false;  // ... and whether the pool's backward pass of this call has left them
     GemmPlan p_fwd, p_dgrad, p_wgrad;
+    DirectPlan d_fwd, d_dgrad;   // CONV: set where the forward pass / the data gradient (of one group) runs as conv_direct
+    size_t wf_elems = 0, wd_elems = 0;   // packed filters of one group
     size_t out_elems() const { return kind == ST_FC ? (size_t)out_ld : (size_t)outH * outW * outCp; }
 };
 
@@ -147,8 +149,8 @@ size_t carve(asgd_net &n, char *base)
         s.dout = at(oe * es + 256);
         if (s.kind == ST_POOL) s.argmax = static_cast<uint8_t *>(at(oe));
         if (s.kind == ST_CONV) {
-            s.wf = at((size_t)s.outCp * s.k * (s.rw ? s.rwKW : s.k * s.inCp) * es);
-            s.wd = i > 0 ? at((size_t)s.inCp * s.k * s.k * s.outCp * es) : nullptr;
+            s.wf = at(s.wf_elems * s.groups * es);
+            s.wd = i > 0 ? at(s.wd_elems * s.groups * es) : nullptr;
         }
         if (s.has_params()) s.colsum_ws = static_cast<float *>(at(s.colsum_floats * 4));
         if (s.kind == ST_FC && s.in_is_spatial) {
@@ -164,6 +166,7 @@ size_t carve(asgd_net &n, char *base)
 }
 
 Gather conv_gather(const Stage &s, const void *x, int B, int dt, int group = 0);
+Gather dgrad_gather(const Stage &s, const void *dy, int B, int dt, int group);
 
 int plan_net(asgd_net &n)
 {
@@ -320,6 +323,13 @@ int plan_net(asgd_net &n)
                 // the first layer's filter gradient as one persistent kernel wants a partial result per workgroup
                 if (s.rw) s.p_wgrad.ws_floats = std::max(s.p_wgrad.ws_floats, rows_wgrad_ws_floats(n.dtype, s.outCp, conv_gather(s, nullptr, (int)B, n.dtype)));
             }
+            const int Ng = s.groups > 1 ? s.outC / s.groups : s.outCp, Cg = s.groups > 1 ? s.inC / s.groups : s.inCp;
+            s.d_fwd = plan_direct(n.dtype, conv_gather(s, nullptr, (int)B, n.dtype), Ng);
+            s.wf_elems = s.d_fwd.ks ? s.d_fwd.pack_elems : (size_t)Ng * s.k * (s.rw ? s.rwKW : s.k * Cg);
+            if (si > 0) {
+                s.d_dgrad = plan_direct(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg);
+                s.wd_elems = s.d_dgrad.ks ? s.d_dgrad.pack_elems : (size_t)Cg * s.k * s.k * Ng;
+            }
             scratch_side = std::max(scratch_side, s.p_wgrad.ws_floats);
             s.colsum_floats = colsum_ws_floats(n.dtype, M, s.outCp);
             if (si + 1 < n.stages.size() && n.stages[si + 1].kind == ST_POOL) {
@@ -465,6 +475,21 @@ Gather conv_gather(const Stage &s, const void *x, int B, int dt, int group)
     return g;
 }
 
+// The data gradient of a convolution stage as a gather over its output gradient dy (one group's channels of it), to be
+// multiplied with the flipped filters.
+Gather dgrad_gather(const Stage &s, const void *dy, int B, int dt, int group)
+{
+    const size_t es = dtype_size(dt);
+    const int Og = s.groups > 1 ? s.outC / s.groups : s.outCp;
+    Gather d;
+    d.x = static_cast<const char *>(dy) + (size_t)group * Og * es; d.N = B; d.H = s.outH; d.W = s.outW; d.C = Og;
+    d.Ho = s.inH; d.Wo = s.inW;
+    d.kh = d.kw = s.k; d.sm = 1; d.ds = s.stride; d.pad = s.k - 1 - s.pad;
+    d.pix = (size_t)s.outCp * es; d.rowb = (size_t)s.outW * s.outCp * es;
+    d.bytes = (size_t)B * s.outH * s.outW * s.outCp * es - (size_t)group * Og * es;
+    return d;
+}
+
 const char *param_ptr(const asgd_net *n, const void *params, size_t off) { return static_cast<const char *>(params) + off * dtype_size(n->dtype); }
 
 int forward(asgd_net *n, const void *params, const void *images, const int32_t *labels, uint64_t seed, uint64_t step, uint32_t worker,
@@ -499,22 +524,15 @@ int forward(asgd_net *n, const void *params, const void *images, const int32_t *
             Stage &s = n->stages[si];
             if (s.kind != ST_CONV) continue;
             if (s.groups > 1) {
-                // forward pack of all groups at once (rows are output channels, each over its group's Cg inputs);
-                // one flipped data-gradient pack per group
                 const int Cg = s.inC / s.groups, Og = s.outC / s.groups;
-                const size_t gw = (size_t)Og * Cg * s.k * s.k;          // canonical filters / packed elements of one group
-                {
+                const size_t gw = (size_t)Og * Cg * s.k * s.k;          // canonical filters of one group
+                for (int g = 0; g < s.groups; ++g) {
                     PackJob &J = jobs.j[jobs.n++];
-                    J.w = param_ptr(n, params, s.w_off); J.wf = s.wf; J.wd = nullptr;
-                    J.cout = s.outC; J.cin = Cg; J.k = s.k; J.coutp = s.outC; J.cinp = Cg; J.rw = 0; J.KW = 0;
-                    bytes += (double)s.w_cnt * es * 2;
-                    if (jobs.n == 12) { const int rc = flush(); if (rc != ASGD_OK) return rc; }
-                }
-                for (int g = 0; g < s.groups && s.wd; ++g) {
-                    PackJob &J = jobs.j[jobs.n++];
-                    J.w = param_ptr(n, params, s.w_off + g * gw); J.wf = nullptr; J.wd = static_cast<char *>(s.wd) + g * gw * dtype_size(dt);
+                    J.w = param_ptr(n, params, s.w_off + g * gw); J.wf = static_cast<char *>(s.wf) + g * s.wf_elems * dtype_size(dt);
+                    J.wd = s.wd ? static_cast<char *>(s.wd) + g * s.wd_elems * dtype_size(dt) : nullptr;
                     J.cout = Og; J.cin = Cg; J.k = s.k; J.coutp = Og; J.cinp = Cg; J.rw = 0; J.KW = 0;
-                    bytes += (double)gw * es * 2;
+                    J.fks = s.d_fwd.ks; J.fch = s.d_fwd.nchunks; J.dks = s.d_dgrad.ks; J.dch = s.d_dgrad.nchunks;
+                    bytes += (double)gw * es * (J.wd ? 3 : 2);
                     if (jobs.n == 12) { const int rc = flush(); if (rc != ASGD_OK) return rc; }
                 }
                 continue;
@@ -522,6 +540,7 @@ int forward(asgd_net *n, const void *params, const void *images, const int32_t *
             PackJob &J = jobs.j[jobs.n++];
             J.w = param_ptr(n, params, s.w_off); J.wf = s.wf; J.wd = s.rw ? nullptr : s.wd;
             J.cout = s.outC; J.cin = s.inC; J.k = s.k; J.coutp = s.outCp; J.cinp = s.inCp; J.rw = s.rw ? s.rwC : 0; J.KW = s.rwKW;
+            J.fks = s.d_fwd.ks; J.fch = s.d_fwd.nchunks; J.dks = s.d_dgrad.ks; J.dch = s.d_dgrad.nchunks;
             bytes += (double)s.w_cnt * es * (J.wd ? 3 : 2);
             if (jobs.n == 12) { const int rc = flush(); if (rc != ASGD_OK) return rc; }
         }
@@ -539,23 +558,15 @@ int forward(asgd_net *n, const void *params, const void *images, const int32_t *
             const double Mo = Bd * s.outH * s.outW;
             ProfScope ps(n, st, ASGD_K_CONV_FWD, 2 * Mo * s.outC * (s.inC / s.groups) * s.k * s.k,
                          (Bd * s.inH * s.inW * s.inC + (double)s.w_cnt + Mo * s.outC) * es);
-            if (s.groups > 1) {
-                const int Cg = s.inC / s.groups, Og = s.outC / s.groups;
-                const long Kg = (long)s.k * s.k * Cg;
-                for (int gi = 0; gi < s.groups; ++gi) {
-                    const Gather g = conv_gather(s, cur, B, dt, gi);
-                    Epilogue ep;
-                    ep.out = static_cast<char *>(s.out) + (size_t)gi * Og * dtype_size(dt); ep.ld = s.outCp;
-                    ep.bias = param_ptr(n, params, s.b_off + (size_t)gi * Og); ep.bias_n = Og; ep.relu = s.relu;
-                    CHECK_LAUNCH(gemm_gather_plain(dt, g, static_cast<const char *>(s.wf) + (size_t)gi * Og * Kg * dtype_size(dt), Kg, Og, ep, s.p_fwd,
-                                                   n->scratch, st),
-                                 "conv forward");
-                }
-            } else {
-                const Gather g = conv_gather(s, cur, B, dt);
+            const int Og = s.groups > 1 ? s.outC / s.groups : s.outCp;   // columns of one group
+            for (int gi = 0; gi < s.groups; ++gi) {
+                const Gather g = conv_gather(s, cur, B, dt, gi);
+                const void *wf = static_cast<const char *>(s.wf) + gi * s.wf_elems * dtype_size(dt);
                 Epilogue ep;
-                ep.out = s.out; ep.ld = s.outCp; ep.bias = param_ptr(n, params, s.b_off); ep.bias_n = s.outC; ep.relu = s.relu;
-                CHECK_LAUNCH(gemm_gather_plain(dt, g, s.wf, (long)g.kh * g.kw * g.C, s.outCp, ep, s.p_fwd, n->scratch, st), "conv forward");
+                ep.out = static_cast<char *>(s.out) + (size_t)gi * Og * dtype_size(dt); ep.ld = s.outCp;
+                ep.bias = param_ptr(n, params, s.b_off + (size_t)gi * Og); ep.bias_n = s.outC / s.groups; ep.relu = s.relu;
+                if (s.d_fwd.ks) CHECK_LAUNCH(conv_direct(dt, g, wf, Og, ep, s.d_fwd, st), "conv forward");
+                else CHECK_LAUNCH(gemm_gather_plain(dt, g, wf, (long)g.kh * g.kw * g.C, Og, ep, s.p_fwd, n->scratch, st), "conv forward");
             }
         } else if (s.kind == ST_LRN) {
             ProfScope ps(n, st, ASGD_K_LRN, 0, 2 * Bd * s.outC * s.outH * s.outW * es);
@@ -810,17 +821,13 @@ int backward(asgd_net *n, const void *params, float *grads, hipStream_t st, cons
                 for (int gi = 0; gi < s.groups; ++gi) {
                     // the group's slice of the output gradient, gathered with the flipped filters of that group
                     const int Ogp = s.groups > 1 ? Og : s.outCp, Cgp = s.groups > 1 ? Cg : s.inCp;
-                    Gather d;
-                    d.x = static_cast<const char *>(s.dout) + (size_t)gi * Og * esz; d.N = B; d.H = s.outH; d.W = s.outW; d.C = Ogp;
-                    d.Ho = s.inH; d.Wo = s.inW;
-                    d.kh = d.kw = s.k; d.sm = 1; d.ds = s.stride; d.pad = s.k - 1 - s.pad;
-                    d.pix = (size_t)s.outCp * esz; d.rowb = (size_t)s.outW * s.outCp * esz;
-                    d.bytes = (size_t)B * s.outH * s.outW * s.outCp * esz - (size_t)gi * Og * esz;
+                    const Gather d = dgrad_gather(s, s.dout, B, dt, gi);
                     Epilogue ed;
                     ed.out = static_cast<char *>(prev->dout) + (size_t)gi * Cg * esz; ed.ld = s.inCp;
                     if (masked) { ed.mask_src = static_cast<const char *>(prev->out) + (size_t)gi * Cg * esz; ed.mask_ld = s.inCp; ed.mask_scale = 1.f; }
-                    const void *wd = static_cast<const char *>(s.wd) + (size_t)gi * Og * Cg * s.k * s.k * esz;
-                    CHECK_LAUNCH(gemm_gather_plain(dt, d, wd, (long)s.k * s.k * Ogp, Cgp, ed, s.p_dgrad, n->scratch, st), "conv data gradient");
+                    const void *wd = static_cast<const char *>(s.wd) + gi * s.wd_elems * esz;
+                    if (s.d_dgrad.ks) CHECK_LAUNCH(conv_direct(dt, d, wd, Cgp, ed, s.d_dgrad, st), "conv data gradient");
+                    else CHECK_LAUNCH(gemm_gather_plain(dt, d, wd, (long)s.k * s.k * Ogp, Cgp, ed, s.p_dgrad, n->scratch, st), "conv data gradient");
                 }
             }
         }

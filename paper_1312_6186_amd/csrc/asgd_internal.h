@@ -73,6 +73,17 @@ struct GemmPlan {
     size_t ws_floats = 0;    // fp32 scratch needed when splits > 1
 };
 
+// Stride-1 convolutions over equal grids (forward, and the data gradient as a convolution with flipped filters): K steps
+// of 16 channels per chunk (0: the convolution does not run this way), chunks, tile shape, and the size of the packed
+// filters.  Packed element (n, pos, c): blocks of 32 output columns, then chunks, window positions and K steps, each K
+// step 64 lanes x 8 channels in the order the matrix cores take them (see direct_index).
+struct DirectPlan {
+    int ks = 0, nchunks = 0, tile = 0;
+    size_t nblk_elems = 0, pack_elems = 0;
+};
+DirectPlan plan_direct(int dtype, const Gather &a, int N);
+int conv_direct(int dtype, const Gather &a, const void *wpack, int N, const Epilogue &ep, const DirectPlan &plan, hipStream_t s);
+
 // Every operand must fit in 1 GiB.
 // C[M][N] = A[M][K] * B[N][K]^T; A gathered (direct), B plain K-contiguous.
 GemmPlan plan_gemm(long M, long N, long K, int dtype, int max_splits);
@@ -118,9 +129,11 @@ int launch_stage_input_rw(int dtype, const void *src, void *dst, int B, int C, i
 // Filter packing for all convolution layers of a net in one launch.  Per layer: canonical filters
 // [cout][cin][k][k] -> forward pack wf [coutp][k][k][cinp] and, if wd is given, the flipped data-gradient pack
 // wd [cinp][k][k][coutp]; or (rw = channels per stored pixel > 0) the window-row pack wf [coutp][k][KW], element (ky, kx*rw + ci), zeros elsewhere.
+// fks / dks > 0: that pack is in the order of conv_direct instead.
 struct PackJob {
     const void *w; void *wf; void *wd;
     int cout, cin, k, coutp, cinp, rw, KW;
+    int fks, fch, dks, dch;   // K steps per chunk and chunks of wf / wd where they are packed for conv_direct (0: rows)
     unsigned start, nf;   // filled by launch_pack_conv
 };
 struct PackJobs { PackJob j[12]; int n; unsigned total; };

@@ -24,10 +24,8 @@
 // raised priority while it multiplies a tile, and a wave whose part of the tile
 // lies outside C does not multiply at all.
 //
-// Stride-1 convolutions whose output grid equals their input grid have a second
-// kernel (conv_patch_kernel, further down): the run of input pixels that the 128
-// output pixels of a tile need is staged in LDS once per 128 bytes of channels
-// and serves every window position from there.
+// Stride-1 convolutions whose output grid equals their input grid run
+// conv_direct_kernel (conv_direct.h) instead.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -35,16 +33,9 @@
 #include <type_traits>
 
 #include "asgd_internal.h"
+#include "mfma_common.h"
 
 namespace asgd {
-
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16_t;
-
-template <typename T> struct Geo;
-template <> struct Geo<bf16_t> { enum { CH = 8, BK = 64, KSTEPS = 4 }; };
-template <> struct Geo<float> { enum { CH = 4, BK = 32, KSTEPS = 2 }; };
 
 // Tile configuration: block tile BM x BN, WAVES_M x WAVES_N wave64s, DEPTH K tiles in flight in registers,
 // MINB workgroups per CU the register budget is sized for.
@@ -56,18 +47,6 @@ template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, int DEPTH_, int MINB_> s
 };
 using Cfg128 = TileCfg<128, 128, 2, 2, 2, 2>;   // 256 threads (wave tile 64x64), two workgroups per CU: two waves per SIMD
 using Cfg128w8 = TileCfg<128, 128, 2, 4, 2, 2>; // 512 threads (wave tile 64x32), two workgroups per CU: four waves per SIMD
-using Cfg64n = TileCfg<128, 64, 2, 2, 2, 4>;     // 256 threads (wave tile 64x32), four workgroups per CU: four waves per SIMD
-#define ASGD_INLINE __attribute__((always_inline))
-
-// Compile-time loop: indices reach the body as constants, so register arrays are never addressed dynamically.
-template <int I, int N, class F> __device__ __forceinline__ void static_for(F &&f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
-
 
 FastDiv make_fastdiv(uint32_t d)
 {
@@ -81,34 +60,7 @@ FastDiv make_fastdiv(uint32_t d)
     return f;
 }
 
-__device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv &f) { return (__umulhi(n, f.mul) + n) >> f.sh; }
-__device__ __forceinline__ int swz(int row) { return (row ^ (row >> 3)) & 7; }
-
-__device__ __forceinline__ float to_f32(float v) { return v; }
-__device__ __forceinline__ float to_f32(bf16_t v) { return (float)v; }
-
 // ------------------------------------------------------------------ loaders
-// All operand fetches are 16-byte buffer loads: the operand tensor is described to the hardware as a byte range,
-// a lane passes a 32-bit byte offset, and an offset outside the range returns zeros.  A loader therefore never
-// builds a 64-bit address and never branches: pieces that must read as zero (rows or K positions past the end,
-// window positions outside the image) get an offset with the top two bits set.  Offsets of valid pieces stay
-// below 1 GiB (checked on the host), so the sum of a valid and an invalid part is still out of range.
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-constexpr unsigned kInv = 0xC0000000u;
-constexpr unsigned kMaxOperandBytes = 0x40000000u;
-
-struct Operand {
-    const void *base; unsigned bytes;
-    __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc() const
-    {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
-    }
-};
-__device__ __forceinline__ uint4 buf_ld16(__amdgpu_buffer_rsrc_t rs, unsigned off)
-{
-    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0);
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
 // value of lane S of the caller's quad (4 consecutive lanes)
 template <int S> __device__ __forceinline__ unsigned quad_bcast(unsigned v)
 {
@@ -354,13 +306,6 @@ template <typename T, class L, int ROWS, int NT, int DEPTH> struct Stage<T, L, R
     }
 };
 
-// LDS tile of a row-contiguous operand: BK lines of ROWS elements.  A transposing read makes half a wave touch
-// 4 K lines x 64 bytes; with lines 64 bytes (mod 256) apart those eight 32-byte groups cover all banks once.
-template <typename T, int ROWS> struct TransTile {
-    static constexpr int LINE = ROWS * (int)sizeof(T) + (sizeof(T) == 2 ? 64 : 32);   // bytes
-    static constexpr int BYTES = Geo<T>::BK * LINE;
-};
-
 template <typename T, class L, int ROWS, int NT, int DEPTH> struct Stage<T, L, ROWS, NT, DEPTH, true> {
     static constexpr int CPL = ROWS * (int)sizeof(T) / 16;   // 16-byte pieces per K line
     static constexpr int LPP = NT / CPL;                     // K lines covered by one pass of the workgroup
@@ -404,224 +349,6 @@ template <typename T, class L, int ROWS, int NT, int DEPTH> struct Stage<T, L, R
         });
     }
 };
-
-// ------------------------------------------------------------------ MFMA step
-// A fragment is the 8 consecutive K elements of one row that a lane feeds to the
-// MFMA.  FragOff holds, per K step, the LDS byte offset of that piece for the
-// lane's row in row block 0 and in row block 1 (blocks 64 rows apart share it), so
-// the inner loop issues its LDS reads with no address arithmetic.
-template <typename T> struct Frag;
-template <typename T, bool TRANS, int ROWS> struct FragOff;
-template <int ROWS> struct FragOff<bf16_t, false, ROWS> {
-    unsigned o[Geo<bf16_t>::KSTEPS][2];
-    __device__ __forceinline__ void init(int row0, int lane)
-    {
-        const int lrow = lane & 31, half = lane >> 5;
-        static_for<0, Geo<bf16_t>::KSTEPS>([&](auto ks) ASGD_INLINE {
-            static_for<0, 2>([&](auto par) ASGD_INLINE {
-                const int row = row0 + par * 32 + lrow;
-                o[ks][par] = (unsigned)(row * 8 + ((ks * 2 + half) ^ swz(row))) * 16u;
-            });
-        });
-    }
-};
-template <int ROWS> struct FragOff<float, false, ROWS> {
-    unsigned o[Geo<float>::KSTEPS][2][2];
-    __device__ __forceinline__ void init(int row0, int lane)
-    {
-        const int lrow = lane & 31, half = lane >> 5;
-        static_for<0, Geo<float>::KSTEPS>([&](auto ks) ASGD_INLINE {
-            static_for<0, 2>([&](auto par) ASGD_INLINE {
-                const int row = row0 + par * 32 + lrow, q = ks * 4 + half * 2, z = swz(row);
-                o[ks][par][0] = (unsigned)(row * 8 + (q ^ z)) * 16u;
-                o[ks][par][1] = (unsigned)(row * 8 + ((q + 1) ^ z)) * 16u;
-            });
-        });
-    }
-};
-// Row-contiguous tiles.  16-bit data: ds_read_b64_tr_b16 works on blocks of 16 lanes; when lane j of a block
-// points at K line (j >> 2) and row piece (j & 3) of a 4 x 16 patch, lane i receives row i of the patch for the
-// four K lines in order.  Lane L = 16*b + i of the wave wants row 16*(b & 1) + i and K lines 8*(b >> 1) + 0..7
-// of the K step, i.e. two such reads.  32-bit data needs no hardware help: eight 4-byte reads down the K axis.
-template <int ROWS> struct FragOff<bf16_t, true, ROWS> {
-    unsigned base;
-    __device__ __forceinline__ void init(int row0, int lane)
-    {
-        const int b = lane >> 4, i = lane & 15;
-        base = (unsigned)((8 * (b >> 1) + (i >> 2)) * TransTile<bf16_t, ROWS>::LINE + (row0 + 16 * (b & 1) + 4 * (i & 3)) * 2);
-    }
-};
-template <int ROWS> struct FragOff<float, true, ROWS> {
-    unsigned base;
-    __device__ __forceinline__ void init(int row0, int lane)
-    {
-        base = (unsigned)(8 * (lane >> 5) * TransTile<float, ROWS>::LINE + (row0 + (lane & 31)) * 4);
-    }
-};
-// Fragment offsets into an activation patch (see conv_patch_kernel): the byte address of the lane's pixel for
-// row block 0 / 1, K-half included, at each of the PPT window positions of the K tile; the K steps of one
-// position are 32 (bf16) or 64 (fp32) bytes apart.
-template <int PPT> struct PatchOff { unsigned a[2][PPT]; };
-typedef short short4v __attribute__((ext_vector_type(4)));
-template <> struct Frag<bf16_t> {
-    uint4 v;
-    template <int KS, int BLK, int PPT> __device__ __forceinline__ void read(const char *sm, const PatchOff<PPT> &fo)
-    {
-        constexpr int SPP = Geo<bf16_t>::KSTEPS / PPT;   // K steps per window position
-        v = *reinterpret_cast<const uint4 *>(sm + fo.a[BLK][KS / SPP] + (KS % SPP) * 32);
-    }
-    template <int KS, int BLK, int ROWS> __device__ __forceinline__ void read(const char *sm, const FragOff<bf16_t, false, ROWS> &fo)
-    {
-        v = *reinterpret_cast<const uint4 *>(sm + fo.o[KS][BLK % 2] + (BLK / 2) * (64 * 128));
-    }
-    template <int KS, int BLK, int ROWS> __device__ __forceinline__ void read(const char *sm, const FragOff<bf16_t, true, ROWS> &fo)
-    {
-        constexpr int LINE = TransTile<bf16_t, ROWS>::LINE;
-        typedef __attribute__((address_space(3))) short4v lds_s4;
-        const char *p = sm + fo.base + KS * 16 * LINE + BLK * 64;
-        const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(p));
-        const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(p + 4 * LINE));
-        const uint2 a = __builtin_bit_cast(uint2, lo), b = __builtin_bit_cast(uint2, hi);
-        v = make_uint4(a.x, a.y, b.x, b.y);
-    }
-};
-template <> struct Frag<float> {
-    uint4 v[2];
-    template <int KS, int BLK, int PPT> __device__ __forceinline__ void read(const char *sm, const PatchOff<PPT> &fo)
-    {
-        constexpr int SPP = Geo<float>::KSTEPS / PPT;
-        v[0] = *reinterpret_cast<const uint4 *>(sm + fo.a[BLK][KS / SPP] + (KS % SPP) * 64);
-        v[1] = *reinterpret_cast<const uint4 *>(sm + fo.a[BLK][KS / SPP] + (KS % SPP) * 64 + 16);
-    }
-    template <int KS, int BLK, int ROWS> __device__ __forceinline__ void read(const char *sm, const FragOff<float, false, ROWS> &fo)
-    {
-        v[0] = *reinterpret_cast<const uint4 *>(sm + fo.o[KS][BLK % 2][0] + (BLK / 2) * (64 * 128));
-        v[1] = *reinterpret_cast<const uint4 *>(sm + fo.o[KS][BLK % 2][1] + (BLK / 2) * (64 * 128));
-    }
-    template <int KS, int BLK, int ROWS> __device__ __forceinline__ void read(const char *sm, const FragOff<float, true, ROWS> &fo)
-    {
-        constexpr int LINE = TransTile<float, ROWS>::LINE;
-        const char *p = sm + fo.base + KS * 16 * LINE + BLK * 128;
-        uint32_t e[8];
-        static_for<0, 8>([&](auto j) ASGD_INLINE { e[j] = *reinterpret_cast<const uint32_t *>(p + j * LINE); });
-        v[0] = make_uint4(e[0], e[1], e[2], e[3]);
-        v[1] = make_uint4(e[4], e[5], e[6], e[7]);
-    }
-};
-
-__device__ __forceinline__ void mma(f32x16 &acc, const Frag<bf16_t> &first, const Frag<bf16_t> &second)
-{
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, first.v), __builtin_bit_cast(bf16x8, second.v),
-                                                  acc, 0, 0, 0);
-}
-__device__ __forceinline__ void mma(f32x16 &acc, const Frag<float> &first, const Frag<float> &second)
-{
-    const uint32_t a[8] = {first.v[0].x, first.v[0].y, first.v[0].z, first.v[0].w, first.v[1].x, first.v[1].y, first.v[1].z, first.v[1].w};
-    const uint32_t b[8] = {second.v[0].x, second.v[0].y, second.v[0].z, second.v[0].w, second.v[1].x, second.v[1].y, second.v[1].z, second.v[1].w};
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[e]), __uint_as_float(b[e]), acc, 0, 0, 0);
-}
-
-// ------------------------------------------------------------------ epilogue
-__device__ __forceinline__ uint64_t mix64(uint64_t z)
-{
-    z ^= z >> 30; z *= 0xBF58476D1CE4E5B9ull;
-    z ^= z >> 27; z *= 0x94D049BB133111EBull;
-    z ^= z >> 31;
-    return z;
-}
-
-// Store of 8 consecutive output elements (32 bytes fp32 / 16 bytes bf16) as 16-byte vectors: every output
-// row starts 16-byte aligned and has a multiple of 8 elements (checked on the host).
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-template <typename T> __device__ __forceinline__ void store8(T *p, const float (&v)[8]);
-template <> __device__ __forceinline__ void store8<float>(float *p, const float (&v)[8])
-{
-    f32x4 *q = reinterpret_cast<f32x4 *>(__builtin_assume_aligned(p, 16));
-    q[0] = f32x4{v[0], v[1], v[2], v[3]};
-    q[1] = f32x4{v[4], v[5], v[6], v[7]};
-}
-template <> __device__ __forceinline__ void store8<bf16_t>(bf16_t *p, const float (&v)[8])
-{
-    union { bf16_t h[8]; u32x4 u; } t;
-#pragma unroll
-    for (int r = 0; r < 8; ++r) t.h[r] = (bf16_t)v[r];
-    *reinterpret_cast<u32x4 *>(__builtin_assume_aligned(p, 16)) = t.u;
-}
-
-template <typename T> struct Vec8;
-template <> struct Vec8<float> { union { float4 u[2]; float e[8]; }; };
-template <> struct Vec8<bf16_t> { union { uint4 u[1]; bf16_t e[8]; }; };
-
-// Eight consecutive columns n0..n0+7 of row m (n0 a multiple of 8, all in range).
-// The bias of these 8 columns, as fp32 (zeros past bias_n or without a bias).
-template <typename T> __device__ __forceinline__ void load_bias8(const Epilogue &ep, int n0, float (&b8)[8])
-{
-#pragma unroll
-    for (int r = 0; r < 8; ++r) b8[r] = 0.f;
-    if (ep.bias) {
-        const T *b = static_cast<const T *>(ep.bias);
-#pragma unroll
-        for (int r = 0; r < 8; ++r)
-            if (n0 + r < ep.bias_n) b8[r] = to_f32(b[n0 + r]);
-    }
-}
-
-template <typename T> __device__ __forceinline__ void epilogue8(const Epilogue &ep, int m, int n0, float (&v)[8], const float (&b8)[8])
-{
-    if (ep.mode == 1) {  // conv filter gradient: (cout, (ky,kx,ci_padded)) -> canonical [cout][cin][kh][kw]
-        if (m >= ep.cw_cout) return;
-        const int t = n0 / ep.cw_cinp, ci0 = n0 - t * ep.cw_cinp;
-        const int ky = t / ep.cw_kw, kx = t - ky * ep.cw_kw;
-        float *o = static_cast<float *>(ep.out);
-#pragma unroll
-        for (int r = 0; r < 8; ++r)
-            if (ci0 + r < ep.cw_cin) o[(((long)m * ep.cw_cin + ci0 + r) * ep.cw_kh + ky) * ep.cw_kw + kx] = v[r];
-        return;
-    }
-    if (ep.mode == 2) {  // the same for window rows: columns are (ky, j), j = kx*cw_rwc + ci over a padded row of cw_cinp elements
-        if (m >= ep.cw_cout) return;
-        const int ky = n0 / ep.cw_cinp, j0 = n0 - ky * ep.cw_cinp;
-        float *o = static_cast<float *>(ep.out);
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const int kx = (j0 + r) / ep.cw_rwc, ci = (j0 + r) - kx * ep.cw_rwc;
-            if (ci < ep.cw_cin && kx < ep.cw_kw) o[(((long)m * ep.cw_cin + ci) * ep.cw_kh + ky) * ep.cw_kw + kx] = v[r];
-        }
-        return;
-    }
-    if (ep.bias) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r) v[r] += b8[r];
-    }
-    if (ep.relu) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r) v[r] = v[r] > 0.f ? v[r] : 0.f;
-    }
-    if (ep.drop) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const uint64_t idx = (uint64_t)m * (uint64_t)ep.drop_F + (uint64_t)(n0 + r);
-            const uint32_t u = (uint32_t)(mix64(ep.drop_key + 0x9E3779B97F4A7C15ull * (idx + 1)) >> 32);
-            v[r] = (u >= ep.drop_thr) ? v[r] * ep.drop_scale : 0.f;
-        }
-    }
-    if (ep.mask_src) {
-        Vec8<T> ms;   // the mask tensor is a workspace tensor: rows and column groups are 16-byte aligned
-        const T *mp = static_cast<const T *>(ep.mask_src) + (long)m * ep.mask_ld + n0;
-        static_for<0, sizeof(ms.u) / 16>([&](auto i) ASGD_INLINE { ms.u[i] = reinterpret_cast<const std::remove_reference_t<decltype(ms.u[0])> *>(mp)[i]; });
-#pragma unroll
-        for (int r = 0; r < 8; ++r) v[r] = to_f32(ms.e[r]) > 0.f ? v[r] * ep.mask_scale : 0.f;
-    }
-    if (ep.out_f32) {
-        // fp32 output = a parameter gradient: read again only by the update, long after it has left every cache
-        f32x4 *q = reinterpret_cast<f32x4 *>(__builtin_assume_aligned(static_cast<float *>(ep.out) + (long)m * ep.ld + n0, 16));
-        __builtin_nontemporal_store(f32x4{v[0], v[1], v[2], v[3]}, q);
-        __builtin_nontemporal_store(f32x4{v[4], v[5], v[6], v[7]}, q + 1);
-    }
-    else store8<T>(static_cast<T *>(ep.out) + (long)m * ep.ld + n0, v);
-}
 
 // ------------------------------------------------------------------ kernel
 // One K tile out of LDS.  The fragments of K step ks+1 are requested before the
@@ -838,7 +565,7 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::MINB) void gemm_kernel(LA la, LB lb, 
     output_tile<T, Cfg, (int)sizeof(smem), Cfg::NT, LA::kTrans && LB::kTrans>(smem, acc, ep, tm, tn, split, M, N, ws, bias8, tid, wm, wn);
 }
 
-// gemm_kernel with the waves of a workgroup in two roles, as in conv_patch_ws_kernel further down: Cfg::NT / 64 waves read
+// gemm_kernel with the waves of a workgroup in two roles: Cfg::NT / 64 waves read
 // fragments and multiply (wave tiles of 64 x 64), four more fetch both operands and move them into LDS.  Step t of
 // a fetching wave: after the barrier, tile t+1 (fetched two steps ago) goes from its register set into the LDS stage
 // that was multiplied in step t-1, and the set is refilled with tile t+3.
@@ -885,7 +612,7 @@ __global__ __launch_bounds__(Cfg::NT + kFetchThreads, 2) void gemm_ws_kernel(LA 
             }
         }
         // A wave that has ended no longer counts at the barriers of the output phase.  (Letting these waves help to take
-        // the tile out of LDS, as in the patch kernel, makes the filter gradient 3.5 % slower.)
+        // the tile out of LDS makes the filter gradient 3.5 % slower.)
         return;
     }
 
@@ -911,426 +638,11 @@ __global__ __launch_bounds__(Cfg::NT + kFetchThreads, 2) void gemm_ws_kernel(LA 
     output_tile<T, Cfg, (int)sizeof(smem)>(smem, acc, ep, tm, tn, split, M, N, ws, bias8, tid, wm, wn);
 }
 
-// ------------------------------------------------------------------ patch convolution
-// Stride-1 convolutions whose output grid equals the input grid (and their data gradients, which have the
-// same form).  With channel-last storage the input pixel that output pixel m needs at window position
-// (ky, kx) is pixel m + (ky - pad) * W + (kx - pad) of the flattened tensor, whenever it is inside the image.
-// So the 128 output pixels of a block tile need, for ALL window positions, one contiguous run of
-// 128 + (kh-1) * W + (kw-1) input pixels.  The K loop therefore runs channel chunk by channel chunk (one
-// chunk = one K tile = 128 bytes of channels): the run of pixels of the chunk (the patch) is brought into LDS
-// once and serves the kh * kw K tiles of the chunk, the A fragment of a window position being the same LDS
-// read at a shifted address.  Only the weights are fetched and written to LDS per K tile, which about halves
-// what a workgroup pulls through the L2-to-CU path and takes a quarter off its LDS traffic compared with the
-// im2col-style gather.  Window positions outside the image (zero padding, and rows past M) are handled per
-// lane: its fragment address is redirected to a pixel of zeros kept behind the patch.  Pixels sit 144 bytes
-// apart in LDS: 16 consecutive pixels' 16-byte pieces then fall into 16 different groups of four banks,
-// whatever pixel the run starts at.
-// A chunk is a whole K tile of channels (PPT = 1) or half a K tile (PPT = 2: a K tile then holds two window
-// positions of the half-wide chunk, pixels sit 80 bytes apart).  Channel counts of 1.5, 2.5, ... K tiles
-// (96 channels in 16-bit data) lose nothing in the second form, where the first would multiply a third more K
-// tiles than there are.
-template <int PPT> constexpr int kPatchPitch = PPT == 1 ? 144 : 80;
-
-// The weights [rows][npos][C] as the B operand when K tiles enumerate (chunk, group of PPT window positions).
-template <typename T, int PPT> struct ChunkK {
-    static constexpr bool kTrans = false;
-    static constexpr int CW = Geo<T>::BK / PPT;   // channels of a chunk
-    Operand op; unsigned ldb, posb; int rows, C, npos, ntc;   // posb: bytes from one window position to the next; ntc: K tiles of a chunk
-    FastDiv dntc;
-    struct Row { unsigned off; };
-    struct KPos { int pos, c; unsigned koff; };   // window position and channel of this thread's piece
-    __device__ __forceinline__ Row row(int r) const { return Row{r < rows ? (unsigned)r * ldb : kInv}; }
-    __device__ __forceinline__ unsigned off_of(int pos, int c) const
-    {
-        return (c < C && pos < npos) ? (unsigned)pos * posb + (unsigned)c * (unsigned)sizeof(T) : kInv;
-    }
-    // k = K tile * BK + element inside the tile
-    __device__ __forceinline__ KPos kpos(int k) const
-    {
-        const int t = k / (int)Geo<T>::BK, e = k % (int)Geo<T>::BK;
-        const int ch = (int)fdiv((uint32_t)t, dntc), pos = (t - ch * ntc) * PPT + e / CW, c = ch * CW + e % CW;
-        return KPos{pos, c, off_of(pos, c)};
-    }
-    __device__ __forceinline__ void advance(KPos &kp, int) const
-    {
-        const bool wrap = kp.pos + PPT >= ntc * PPT;
-        kp.pos = wrap ? kp.pos + PPT - ntc * PPT : kp.pos + PPT;
-        kp.c += wrap ? CW : 0;
-        kp.koff = off_of(kp.pos, kp.c);
-    }
-    __device__ __forceinline__ unsigned voff(const Row &r, const KPos &kp) const { return r.off + kp.koff; }
-};
-
-template <typename T> struct PatchSrc {
-    Operand op; unsigned pix;              // bytes from one pixel to the next
-    int H, W, C, kh, kw, pad, npos, ntc, M;   // ntc: K tiles of a chunk; M: pixels of the tensor = GEMM rows
-    FastDiv dW, dHW, dkw, dntc;
-};
-
-template <typename T, int NPL, class Cfg, int PPT>
-__global__ __launch_bounds__(Cfg::NT, Cfg::MINB) void conv_patch_kernel(PatchSrc<T> pa, ChunkK<T, PPT> lb, Epilogue ep, int M, int N, int nkt,
-                                                                    int kt_per_split, int tiles_m, int tiles_n, float *ws)
-{
-    constexpr int BK = Geo<T>::BK, BM = Cfg::BM, BN = Cfg::BN, NT = Cfg::NT, MB = Cfg::MB, NB = Cfg::NB;
-    constexpr int TB = BN * 128;
-    constexpr int PIECES = 8 / PPT;                       // 16-byte pieces of a pixel's chunk
-    constexpr int PITCH = kPatchPitch<PPT>;
-    constexpr int CW = Geo<T>::BK / PPT;                  // channels of a chunk
-    constexpr int PPMAX = NPL * NT / PIECES;              // pixels the patch buffer holds
-    constexpr int ZBYTES = 256 + 128;                     // zeros behind them: one 16-byte piece per group of four banks, and the reach of a K tile's fragment offsets
-    constexpr int PBYTES = PPMAX * PITCH + ZBYTES;
-    static_assert((PPMAX * PITCH) % 256 == 0 && (2 * TB) % 256 == 0, "the zeros start at bank 0");
-    static_assert(MB == 2 && BM == 128, "two row blocks per wave");
-    constexpr int SMEM = (2 * TB + PBYTES) > BM * BN * 4 ? (2 * TB + PBYTES) : BM * BN * 4;
-    __shared__ uint4 smem[SMEM / 16];        // two stages of B tiles, the patch; reused to stage the whole output tile
-    uint4 (*sB)[TB / 16] = reinterpret_cast<uint4 (*)[TB / 16]>(smem);
-    char *sP = reinterpret_cast<char *>(smem + 2 * TB / 16);
-    const int tid = threadIdx.x;
-    int bid;
-    {
-        const int nb = gridDim.x, q = nb >> 3, r = nb & 7, x = blockIdx.x & 7;
-        bid = x * q + (x < r ? x : r) + (blockIdx.x >> 3);
-    }
-    const int tn = bid % tiles_n; bid /= tiles_n;
-    const int tm = bid % tiles_m;
-    const int split = bid / tiles_m;
-    const int kt0 = split * kt_per_split;
-    const int nt = min(nkt, kt0 + kt_per_split) - kt0;
-
-    Stage<T, ChunkK<T, PPT>, BN, NT, 2> stB;
-    stB.init(lb, tn * BN, kt0 * BK, tid, NT / 2);
-
-    // chunk, first window position and its place in the window for the first K tile (all uniform)
-    int ch = (int)fdiv((uint32_t)kt0, pa.dntc);
-    int pos = (kt0 - ch * pa.ntc) * PPT;
-    int ky = (int)fdiv((uint32_t)pos, pa.dkw), kx = pos - ky * pa.kw;
-
-    // patch pieces of this thread: piece q = tid + j * NT is slot q % PIECES (= tid % PIECES) of patch pixel q / PIECES
-    const __amdgpu_buffer_rsrc_t prs = pa.op.rsrc();
-    const int slot = tid & (PIECES - 1);
-    const int gp0 = tm * BM - pa.pad * pa.W - pa.pad + tid / PIECES;   // tensor pixel of piece 0
-    unsigned poff[NPL];
-    static_for<0, NPL>([&](auto j) ASGD_INLINE {
-        const int gp = gp0 + j * (NT / PIECES);
-        poff[j] = (gp >= 0 && gp < pa.M) ? (unsigned)gp * pa.pix + (unsigned)slot * 16u : kInv;
-    });
-    const unsigned pwo = (unsigned)((tid / PIECES) * PITCH + slot * 16);
-    uint4 pr[NPL];
-    auto patch_load = [&](int chunk) ASGD_INLINE {
-        const unsigned coff = (chunk * CW + slot * (int)Geo<T>::CH < pa.C) ? (unsigned)chunk * (128u / PPT) : kInv;
-        static_for<0, NPL>([&](auto j) ASGD_INLINE { pr[j] = buf_ld16(prs, poff[j] + coff); });
-    };
-    auto patch_store = [&]() ASGD_INLINE {
-        static_for<0, NPL>([&](auto j) ASGD_INLINE {
-            *reinterpret_cast<uint4 *>(sP + pwo + j * (NT / PIECES) * PITCH) = pr[j];
-        });
-    };
-
-    f32x16 acc[NB][MB];
-    static_for<0, NB>([&](auto i) ASGD_INLINE { static_for<0, MB>([&](auto j) ASGD_INLINE { acc[i][j] = f32x16{}; }); });
-
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = (wave % Cfg::WAVES_M) * (BM / Cfg::WAVES_M), wn = (wave / Cfg::WAVES_M) * (BN / Cfg::WAVES_N);
-    const int lrow = lane & 31, half = lane >> 5;
-    FragOff<T, false, BN> foB;
-    foB.init(wn, lane);
-    // a wave whose whole tile lies outside C (96 output columns in a tile of 128: a quarter of the waves) only helps
-    // to move the operands; wave-uniform
-    const bool busy = __builtin_amdgcn_readfirstlane((tm * BM + wm < M && tn * BN + wn < N) ? 1 : 0) != 0;
-    // the two fragment rows of this lane: patch address at window position (0, 0) and the mask of positions inside the image
-    constexpr unsigned kHalfBytes = 8 * (unsigned)sizeof(T);
-    // A lane whose window position lies outside the image reads zeros instead, at the address behind the patch
-    // that falls into the same banks as the pixel it would have read: the lanes that read together hit different
-    // banks among the pixels, and a single shared pixel of zeros would collide with one of them.
-    constexpr unsigned zero_base = (unsigned)(PPMAX * PITCH);
-    unsigned abase[2], amask[2];
-    static_for<0, 2>([&](auto mb) ASGD_INLINE {
-        const int rr = wm + mb * 32 + lrow, m = tm * BM + rr;
-        abase[mb] = (unsigned)(rr * PITCH) + (unsigned)half * kHalfBytes;
-        unsigned mask = 0;
-        if (m < M) {
-            const int n = (int)fdiv((uint32_t)m, pa.dHW);
-            const int rem = m - n * (pa.H * pa.W);
-            const int y = (int)fdiv((uint32_t)rem, pa.dW);
-            const int y0 = y - pa.pad, x0 = rem - y * pa.W - pa.pad;
-            const int ylo = max(0, -y0), yhi = max(ylo, min(pa.kh, pa.H - y0));
-            const int xlo = max(0, -x0), xhi = max(xlo, min(pa.kw, pa.W - x0));
-            const unsigned xm = ((1u << xhi) - 1u) & ~((1u << xlo) - 1u);
-            for (int a = ylo; a < yhi; ++a) mask |= xm << (a * pa.kw);
-        }
-        amask[mb] = mask;
-    });
-
-    if (tid < ZBYTES / 16) *reinterpret_cast<uint4 *>(sP + PPMAX * PITCH + tid * 16) = make_uint4(0u, 0u, 0u, 0u);
-    patch_load(ch);
-    stB.template load<0>(lb);
-    stB.template load<1>(lb);
-    float bias8[8];   // asked for behind the first tiles, which therefore do not wait for it
-    load_bias8<T>(ep, tn * BN + (tid % (BN / 8)) * 8, bias8);
-    patch_store();
-    stB.template store<0>(sB[0], tid);
-    patch_load(ch + 1);
-
-    // One K tile: the B pipeline is that of gemm_kernel; when a tile opens a new chunk, the patch fetched during
-    // the previous chunk replaces the old one between two barriers and the fetch of the next one is issued.
-    auto step = [&](auto par, bool first, bool more) ASGD_INLINE {
-        __syncthreads();
-        if (pos == 0 && !first) {
-            patch_store();
-            __syncthreads();
-            ++ch;
-            patch_load(ch + 1);
-        }
-        stB.template load<par>(lb);
-        PatchOff<PPT> foA;
-        static_for<0, PPT>([&](auto h) ASGD_INLINE {
-            // a position past the last one (odd window sizes with two positions per tile) has no mask bit and no weights
-            const unsigned sh = (unsigned)((ky * pa.W + kx) * PITCH);
-            const unsigned a0 = abase[0] + sh, a1 = abase[1] + sh;
-            foA.a[0][h] = ((amask[0] >> pos) & 1u) ? a0 : zero_base + (a0 & 0xF0u);
-            foA.a[1][h] = ((amask[1] >> pos) & 1u) ? a1 : zero_base + (a1 & 0xF0u);
-            ++pos; ++kx;
-            if (kx == pa.kw) { kx = 0; ++ky; }
-        });
-        __builtin_amdgcn_s_setprio(1);
-        if (busy) compute_tile<T, MB, NB>(reinterpret_cast<const uint4 *>(sP), sB[par], acc, foA, foB);
-        __builtin_amdgcn_s_setprio(0);
-        if (pos >= pa.npos) { pos = 0; ky = 0; kx = 0; }
-        if (more) stB.template store<1 - par>(sB[1 - par], tid);
-    };
-    for (int t = 0; t < nt; t += 2) {
-        step(std::integral_constant<int, 0>{}, t == 0, t + 1 < nt);
-        if (t + 1 < nt) step(std::integral_constant<int, 1>{}, false, t + 2 < nt);
-    }
-
-    output_tile<T, Cfg, (int)sizeof(smem)>(smem, acc, ep, tm, tn, split, M, N, ws, bias8, tid, wm, wn);
-}
-
-// The same convolution with the waves of a workgroup in two roles: the first Cfg::NT / 64 waves read fragments and
-// multiply, four more fetch the weights and the patch and move them into LDS.  The multiplying waves hold no
-// staging registers and no fetch addresses, which leaves room for wave tiles of 64 x 64 (four multiplying waves
-// on a 128 x 128 tile) at four waves per SIMD: a third fewer fragment reads from LDS than with 64 x 32, and the
-// K loop gets 3-7 % faster.  Both kinds of wave go through the same barriers; the fetching waves end after the
-// K loop and then help to take the output tile out of LDS.
-//
-// NSTG = 3: the weights do not pass through registers.  A fetching wave asks for its pieces with buffer loads that
-// write LDS directly (lane l of the instruction fills bytes [16 l, 16 l + 16) behind a wave-uniform LDS address, so
-// one instruction fills eight rows of a tile and the XOR swizzle is applied on the global side: the lane fetches the
-// K piece that belongs into its slot).  Tile t lives in stage t % 3 and is asked for two steps ahead, right after the
-// barrier that retires the stage's previous tile; before the barrier of step t the wave waits until at most the
-// pieces of tile t + 1 are outstanding (the counter retires in order).  Against register staging this takes the
-// fetched bytes off the return path into the register file and removes the LDS store instructions: in a loop of
-// nothing but fragment reads, MFMAs and the fetch of a 16 KB tile per step, 0.60 instead of 0.81 us per step.
-constexpr int kProducers = 256;
+// The barrier of a wave that has buffer loads in flight that write LDS directly: its own LDS stores are waited for, the
+// buffer loads are not (__syncthreads carries a release fence, for which the compiler drains every load that writes LDS);
+// the "memory" clobber keeps the compiler from moving LDS accesses across it.
 typedef __attribute__((address_space(3))) void lds_void;
-// The barrier of a wave that has such loads in flight: its own LDS stores are waited for, the buffer loads are not
-// (__syncthreads carries a release fence, for which the compiler drains every load that writes LDS); the "memory"
-// clobber keeps the compiler from moving LDS accesses across it.
 __device__ __forceinline__ void barrier_keep_loads() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-template <typename T, int NPL, class Cfg, int PPT, int NSTG>
-__global__ __launch_bounds__(Cfg::NT + kProducers, 2) void conv_patch_ws_kernel(PatchSrc<T> pa, ChunkK<T, PPT> lb, Epilogue ep, int M, int N, int nkt,
-                                                                              int kt_per_split, int tiles_m, int tiles_n, float *ws)
-{
-    constexpr int BK = Geo<T>::BK, BM = Cfg::BM, BN = Cfg::BN, NT = Cfg::NT, MB = Cfg::MB, NB = Cfg::NB, NP = kProducers;
-    constexpr int TB = BN * 128;
-    constexpr int PIECES = 8 / PPT;
-    constexpr int PITCH = kPatchPitch<PPT>;
-    constexpr int CW = Geo<T>::BK / PPT;
-    constexpr int PPMAX = NPL * NP / PIECES;
-    constexpr int ZBYTES = 256 + 128;
-    constexpr int PBYTES = PPMAX * PITCH + ZBYTES;
-    static_assert(NSTG == 2 || NSTG == 3, "B stages");
-    static_assert((PPMAX * PITCH) % 256 == 0 && (NSTG * TB) % 256 == 0, "the zeros start at bank 0");
-    static_assert(MB == 2 && BM == 128, "two row blocks per wave");
-    constexpr int SMEM = (NSTG * TB + PBYTES) > BM * BN * 4 ? (NSTG * TB + PBYTES) : BM * BN * 4;
-    static_assert(SMEM <= 81920, "two workgroups per CU");
-    __shared__ uint4 smem[SMEM / 16];
-    uint4 (*sB)[TB / 16] = reinterpret_cast<uint4 (*)[TB / 16]>(smem);
-    char *sP = reinterpret_cast<char *>(smem + NSTG * TB / 16);
-    const int tid = threadIdx.x;
-    int bid;
-    {
-        const int nb = gridDim.x, q = nb >> 3, r = nb & 7, x = blockIdx.x & 7;
-        bid = x * q + (x < r ? x : r) + (blockIdx.x >> 3);
-    }
-    const int tn = bid % tiles_n; bid /= tiles_n;
-    const int tm = bid % tiles_m;
-    const int split = bid / tiles_m;
-    const int kt0 = split * kt_per_split;
-    const int nt = min(nkt, kt0 + kt_per_split) - kt0;
-    int ch = (int)fdiv((uint32_t)kt0, pa.dntc);
-    int pos = (kt0 - ch * pa.ntc) * PPT;
-
-    if (tid >= NT) {
-        // ---- fetching waves.  Step t: after the barrier, tile t+1 (fetched two steps ago) goes from its register set
-        // into the LDS stage that was multiplied in step t-1, and the set is refilled with tile t+3.
-        const int ptid = tid - NT;
-        Stage<T, ChunkK<T, PPT>, BN, NP, 2> stB;
-        if constexpr (NSTG == 2) stB.init(lb, tn * BN, kt0 * BK, ptid, NP / 2);
-        // NSTG == 3: instruction i = s * 4 + fw of a tile fills rows 8 i .. 8 i + 7 (lane l: row 8 i + l / 8, slot l % 8); the
-        // slot holds K piece slot ^ swz(row), and swz(row) = (l / 8 ^ i) & 7 is the same for all s of one parity
-        constexpr int SL = BN * 8 / NP;
-        static_assert(NP == 256 && SL == 4, "four instructions per wave and tile");
-        const int fw = __builtin_amdgcn_readfirstlane(ptid >> 6), fl = ptid & 63;
-        typename ChunkK<T, PPT>::Row brow[SL];
-        typename ChunkK<T, PPT>::KPos bkp[2];
-        const __amdgpu_buffer_rsrc_t brs = lb.op.rsrc();
-        if constexpr (NSTG == 3) {
-            static_for<0, SL>([&](auto sl) ASGD_INLINE { brow[sl] = lb.row(tn * BN + (sl * 4 + fw) * 8 + (fl >> 3)); });
-            const int piece = (fl & 7) ^ (((fl >> 3) ^ fw) & 7);
-            bkp[0] = lb.kpos(kt0 * BK + piece * (int)Geo<T>::CH);
-            bkp[1] = lb.kpos(kt0 * BK + (piece ^ 4) * (int)Geo<T>::CH);
-        }
-        auto issue = [&](auto stage) ASGD_INLINE {   // the tile at the cursor into LDS stage `stage`; advances the cursor
-            static_for<0, SL>([&](auto sl) ASGD_INLINE {
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(brs, (lds_void *)(reinterpret_cast<char *>(smem) + stage * TB + (sl * 4 + fw) * 1024), 16,
-                                                         (int)lb.voff(brow[sl], bkp[sl & 1]), 0, 0, 0);
-            });
-            lb.advance(bkp[0], BK); lb.advance(bkp[1], BK);
-        };
-        const __amdgpu_buffer_rsrc_t prs = pa.op.rsrc();
-        const int slot = ptid & (PIECES - 1);
-        const int gp0 = tm * BM - pa.pad * pa.W - pa.pad + ptid / PIECES;
-        unsigned poff[NPL];
-        static_for<0, NPL>([&](auto j) ASGD_INLINE {
-            const int gp = gp0 + j * (NP / PIECES);
-            poff[j] = (gp >= 0 && gp < pa.M) ? (unsigned)gp * pa.pix + (unsigned)slot * 16u : kInv;
-        });
-        const unsigned pwo = (unsigned)((ptid / PIECES) * PITCH + slot * 16);
-        uint4 pr[NPL];
-        auto patch_load = [&](int chunk) ASGD_INLINE {
-            const unsigned coff = (chunk * CW + slot * (int)Geo<T>::CH < pa.C) ? (unsigned)chunk * (128u / PPT) : kInv;
-            static_for<0, NPL>([&](auto j) ASGD_INLINE { pr[j] = buf_ld16(prs, poff[j] + coff); });
-        };
-        auto patch_store = [&]() ASGD_INLINE {
-            static_for<0, NPL>([&](auto j) ASGD_INLINE {
-                *reinterpret_cast<uint4 *>(sP + pwo + j * (NP / PIECES) * PITCH) = pr[j];
-            });
-        };
-        if constexpr (NSTG == 3) {
-            patch_load(ch);
-            issue(std::integral_constant<int, 0>{});
-            if (nt > 1) issue(std::integral_constant<int, 1>{});
-            patch_store();
-            patch_load(ch + 1);
-            // step t: tile t must have landed (whatever was asked for after tile t + 1's pieces, i.e. nothing, may be
-            // outstanding with them; a patch asked for in step t - 1 precedes them and is waited for too); after the
-            // barrier the stage of tile t - 1 is free and takes tile t + 2
-            auto step = [&](auto stage, int t) ASGD_INLINE {
-                if (t + 1 < nt) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-                else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                barrier_keep_loads();
-                if (pos == 0 && t != 0) {
-                    patch_store();
-                    barrier_keep_loads();
-                    ++ch;
-                    patch_load(ch + 1);
-                }
-                pos += PPT;
-                if (pos >= pa.npos) pos = 0;
-                if (t + 2 < nt) issue(std::integral_constant<int, (stage + 2) % 3>{});
-            };
-            for (int t = 0; t < nt; t += 3) {
-                step(std::integral_constant<int, 0>{}, t);
-                if (t + 1 < nt) step(std::integral_constant<int, 1>{}, t + 1);
-                if (t + 2 < nt) step(std::integral_constant<int, 2>{}, t + 2);
-            }
-        } else {
-        patch_load(ch);
-        stB.template load<0>(lb);
-        stB.template load<1>(lb);
-        patch_store();
-        stB.template store<0>(sB[0], ptid);
-        stB.template load<0>(lb);
-        patch_load(ch + 1);
-        auto step = [&](auto par, bool first, bool more) ASGD_INLINE {
-            __syncthreads();
-            if (pos == 0 && !first) {
-                patch_store();
-                __syncthreads();
-                ++ch;
-                patch_load(ch + 1);
-            }
-            pos += PPT;
-            if (pos >= pa.npos) pos = 0;
-            if (more) stB.template store<1 - par>(sB[1 - par], ptid);
-            stB.template load<1 - par>(lb);
-        };
-        for (int t = 0; t < nt; t += 2) {
-            step(std::integral_constant<int, 0>{}, t == 0, t + 1 < nt);
-            if (t + 1 < nt) step(std::integral_constant<int, 1>{}, false, t + 2 < nt);
-        }
-        }
-            // the fetching waves help to take the output tile out of LDS
-        float bias8[8];
-        load_bias8<T>(ep, tn * BN + (tid % (BN / 8)) * 8, bias8);
-        __syncthreads();
-        __syncthreads();
-        emit_tile<T, Cfg, NT + NP>(smem, ep, tm, tn, split, M, N, ws, bias8, tid);
-        return;
-    }
-
-    // ---- multiplying waves
-    int ky = (int)fdiv((uint32_t)pos, pa.dkw), kx = pos - ky * pa.kw;
-    f32x16 acc[NB][MB];
-    static_for<0, NB>([&](auto i) ASGD_INLINE { static_for<0, MB>([&](auto j) ASGD_INLINE { acc[i][j] = f32x16{}; }); });
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = (wave % Cfg::WAVES_M) * (BM / Cfg::WAVES_M), wn = (wave / Cfg::WAVES_M) * (BN / Cfg::WAVES_N);
-    const int lrow = lane & 31, half = lane >> 5;
-    FragOff<T, false, BN> foB;
-    foB.init(wn, lane);
-    const bool busy = __builtin_amdgcn_readfirstlane((tm * BM + wm < M && tn * BN + wn < N) ? 1 : 0) != 0;
-    constexpr unsigned kHalfBytes = 8 * (unsigned)sizeof(T);
-    constexpr unsigned zero_base = (unsigned)(PPMAX * PITCH);
-    unsigned abase[2], amask[2];
-    static_for<0, 2>([&](auto mb) ASGD_INLINE {
-        const int rr = wm + mb * 32 + lrow, m = tm * BM + rr;
-        abase[mb] = (unsigned)(rr * PITCH) + (unsigned)half * kHalfBytes;
-        unsigned mask = 0;
-        if (m < M) {
-            const int n = (int)fdiv((uint32_t)m, pa.dHW);
-            const int rem = m - n * (pa.H * pa.W);
-            const int y = (int)fdiv((uint32_t)rem, pa.dW);
-            const int y0 = y - pa.pad, x0 = rem - y * pa.W - pa.pad;
-            const int ylo = max(0, -y0), yhi = max(ylo, min(pa.kh, pa.H - y0));
-            const int xlo = max(0, -x0), xhi = max(xlo, min(pa.kw, pa.W - x0));
-            const unsigned xm = ((1u << xhi) - 1u) & ~((1u << xlo) - 1u);
-            for (int a = ylo; a < yhi; ++a) mask |= xm << (a * pa.kw);
-        }
-        amask[mb] = mask;
-    });
-    if (tid < ZBYTES / 16) *reinterpret_cast<uint4 *>(sP + PPMAX * PITCH + tid * 16) = make_uint4(0u, 0u, 0u, 0u);
-    float bias8[8];
-    load_bias8<T>(ep, tn * BN + (tid % (BN / 8)) * 8, bias8);
-    auto step = [&](auto par, bool first) ASGD_INLINE {
-        __syncthreads();
-        if (pos == 0 && !first) __syncthreads();   // the fetching waves replace the patch between these two
-        PatchOff<PPT> foA;
-        static_for<0, PPT>([&](auto h) ASGD_INLINE {
-            const unsigned sh = (unsigned)((ky * pa.W + kx) * PITCH);
-            const unsigned a0 = abase[0] + sh, a1 = abase[1] + sh;
-            foA.a[0][h] = ((amask[0] >> pos) & 1u) ? a0 : zero_base + (a0 & 0xF0u);
-            foA.a[1][h] = ((amask[1] >> pos) & 1u) ? a1 : zero_base + (a1 & 0xF0u);
-            ++pos; ++kx;
-            if (kx == pa.kw) { kx = 0; ++ky; }
-        });
-        if (busy) compute_tile<T, MB, NB>(reinterpret_cast<const uint4 *>(sP), sB[par], acc, foA, foB);
-        if (pos >= pa.npos) { pos = 0; ky = 0; kx = 0; }
-    };
-    if constexpr (NSTG == 3) {
-        for (int t = 0; t < nt; t += 3) {
-            step(std::integral_constant<int, 0>{}, t == 0);
-            if (t + 1 < nt) step(std::integral_constant<int, 1>{}, false);
-            if (t + 2 < nt) step(std::integral_constant<int, 2>{}, false);
-        }
-    } else {
-        for (int t = 0; t < nt; t += 2) {
-            step(std::integral_constant<int, 0>{}, t == 0);
-            if (t + 1 < nt) step(std::integral_constant<int, 1>{}, false);
-        }
-    }
-    output_tile<T, Cfg, (int)sizeof(smem), NT + NP>(smem, acc, ep, tm, tn, split, M, N, ws, bias8, tid, wm, wn);
-}
 
 // ------------------------------------------------------------------ first-layer convolution from staged image rows
 // The window-row form of a first convolution (few input channels: a window row (kx, c) is one contiguous run of the
@@ -1579,7 +891,7 @@ __global__ __launch_bounds__(512, 2) void conv_rows_wgrad_kernel(RowsConv a, int
         issue(v, 0);
         if (v + g < a.total) issue(v + g, 1);
         int buf2 = 2;                                        // buffer of tile it + 2
-        for (int it = 0; v < a.total; ++it, v += g) {
+        for (; v < a.total; v += g) {   // tile `it`
             // tile `it` has landed when at most the next tile's instructions are outstanding (the counter retires in order)
             if (v + g >= a.total) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             else if (rows_wave) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NI) : "memory");
@@ -1869,98 +1181,6 @@ template <typename T> static PlainT<T> make_plain_t(const void *p, long ld, int 
     return PlainT<T>{operand(p, ((size_t)(K - 1) * ld + rows) * sizeof(T)), (unsigned)(ld * sizeof(T)), rows, K};
 }
 
-// The patch form applies to stride-1 convolutions with equal input and output grids over a dense tensor whose
-// run of pixels per block tile fits the patch buffer.  Returns the window positions per K tile to run it with
-// (1 or 2), or 0 where the im2col gather is the better choice.
-template <typename T> static int patch_applies(const Gather &a, long ldb)
-{
-    const size_t pixb = a.pix ? a.pix : (size_t)a.C * sizeof(T);
-    const int npos = a.kh * a.kw;
-    if (!(a.sm == 1 && a.ds == 1 && a.Ho == a.H && a.Wo == a.W && npos > 1 && npos <= 32 && 2 * a.pad == a.kh - 1 &&
-                 2 * a.pad == a.kw - 1 && (a.rowb == 0 || a.rowb == (size_t)a.W * pixb) && pixb % 16 == 0 && a.C % (int)Geo<T>::CH == 0 &&
-                 ((uintptr_t)a.x & 15) == 0 && ldb == (long)npos * a.C && 128 + (a.kh - 1) * a.W + a.kw - 1 <= 256))
-        return 0;
-    // A chunk is a whole K tile of channels, or half of one with two window positions per K tile.  Where the
-    // channel count is not a multiple of the chunk the patch form multiplies more K tiles than the gather, which
-    // packs K densely; beyond 15 % more it loses.  (96 channels in 16-bit data, 5 x 5: 38 K tiles dense, 50 with
-    // whole-tile chunks, 39 with half-tile chunks.)
-    const int BK = (int)Geo<T>::BK;
-    const long nkt_gather = ((long)npos * a.C + BK - 1) / BK;
-    const long nkt1 = (long)((a.C + BK - 1) / BK) * npos, nkt2 = (long)((a.C + BK / 2 - 1) / (BK / 2)) * ((npos + 1) / 2);
-    const int ppt = nkt2 < nkt1 ? 2 : 1;
-    return (ppt == 1 ? nkt1 : nkt2) * 100 <= nkt_gather * 115 ? ppt : 0;
-}
-
-template <typename T, class Cfg, int PPT>
-static int run_patch_cfg(const Gather &a, const void *b, long ldb, int N, const Epilogue &ep, const GemmPlan &plan, float *ws, hipStream_t s);
-template <typename T, int PPT>
-static int run_patch(const Gather &a, const void *b, long ldb, int N, const Epilogue &ep, const GemmPlan &plan, float *ws, hipStream_t s)
-{
-    // Both shapes run wave tiles of 64 x 32 at four waves per SIMD and take the same time per tile; the narrow one
-    // fills the chip better when the wide one would leave more than an eighth of the 512 workgroup slots empty
-    // (conv5 at batch 128: 338 workgroups against 676).
-    // The narrow one holds runs of up to 160 pixels (more pieces per thread cost it its fourth wave per SIMD).
-    const long wide = (long)((a.N * a.H * a.W + 127) / 128) * ((N + 127) / 128) * plan.splits;
-    const int pp = 128 + (a.kh - 1) * a.W + a.kw - 1;
-    if (N > 64 && wide < 448 && pp <= 5 * Cfg64n::NT / 8) return run_patch_cfg<T, Cfg64n, PPT>(a, b, ldb, N, ep, plan, ws, s);
-    return run_patch_cfg<T, Cfg128w8, PPT>(a, b, ldb, N, ep, plan, ws, s);
-}
-template <typename T, class Cfg, int PPT>
-static int run_patch_cfg(const Gather &a, const void *b, long ldb, int N, const Epilogue &ep, const GemmPlan &plan, float *ws, hipStream_t s)
-{
-    constexpr int BK = Geo<T>::BK;
-    const int M = a.N * a.H * a.W, npos = a.kh * a.kw, K = npos * a.C;
-    if (M <= 0 || N <= 0 || (N & 7)) return -1;
-    PatchSrc<T> pa;
-    pa.op = operand(a.x, a.bytes);
-    pa.pix = a.pix ? (unsigned)a.pix : (unsigned)(a.C * sizeof(T));
-    constexpr int CW = BK / PPT;                 // channels of a chunk
-    const int ntc = (npos + PPT - 1) / PPT;      // K tiles of a chunk
-    pa.H = a.H; pa.W = a.W; pa.C = a.C; pa.kh = a.kh; pa.kw = a.kw; pa.pad = a.pad; pa.npos = npos; pa.ntc = ntc; pa.M = M;
-    pa.dW = make_fastdiv(a.W); pa.dHW = make_fastdiv(a.H * a.W); pa.dkw = make_fastdiv(a.kw); pa.dntc = make_fastdiv(ntc);
-    ChunkK<T, PPT> lb;
-    lb.op = operand(b, ((size_t)(N - 1) * ldb + K) * sizeof(T));
-    lb.ldb = (unsigned)(ldb * sizeof(T)); lb.posb = (unsigned)(a.C * sizeof(T)); lb.rows = N; lb.C = a.C; lb.npos = npos; lb.ntc = ntc;
-    lb.dntc = pa.dntc;
-    if (pa.op.bytes == 0 || lb.op.bytes == 0) return -1;
-    const int tiles_m = (M + Cfg::BM - 1) / Cfg::BM, tiles_n = (N + Cfg::BN - 1) / Cfg::BN;
-    const int nkt = ((a.C + CW - 1) / CW) * ntc;
-    int splits = plan.splits;
-    if (splits > 1 && ws == nullptr) return -1;
-    const int per = (nkt + splits - 1) / splits;
-    splits = (nkt + per - 1) / per;
-    const long blocks = (long)tiles_m * tiles_n * splits;
-    if (blocks > 0x7fffffffL) return -1;
-    const int pp = 128 + (a.kh - 1) * a.W + a.kw - 1;   // pixels a block tile needs
-    // The wide shape runs with the two kinds of waves (see conv_patch_ws_kernel).
-    if constexpr (Cfg::NT == 512) {
-        if (pp > 256) return -1;
-        if constexpr (PPT == 2)
-            hipLaunchKernelGGL((conv_patch_ws_kernel<T, 4, Cfg128, 2, 3>), dim3((unsigned)blocks), dim3(Cfg128::NT + kProducers), 0, s, pa, lb, ep, M, N, nkt, per,
-                               tiles_m, tiles_n, splits > 1 ? ws : nullptr);
-        else if (pp <= 192)
-            hipLaunchKernelGGL((conv_patch_ws_kernel<T, 6, Cfg128, 1, 3>), dim3((unsigned)blocks), dim3(Cfg128::NT + kProducers), 0, s, pa, lb, ep, M, N, nkt, per,
-                               tiles_m, tiles_n, splits > 1 ? ws : nullptr);
-        else
-            hipLaunchKernelGGL((conv_patch_ws_kernel<T, 8, Cfg128, 1, 2>), dim3((unsigned)blocks), dim3(Cfg128::NT + kProducers), 0, s, pa, lb, ep, M, N, nkt, per,
-                               tiles_m, tiles_n, splits > 1 ? ws : nullptr);
-    } else if constexpr (PPT == 2) {
-        // the narrow shape, half-wide chunks: four pieces per pixel, three per thread hold 192 pixels with 256 threads
-        constexpr int NPL = 3;
-        if (pp > NPL * Cfg::NT / 4) return -1;
-        hipLaunchKernelGGL((conv_patch_kernel<T, NPL, Cfg, 2>), dim3((unsigned)blocks), dim3(Cfg::NT), 0, s, pa, lb, ep, M, N, nkt, per, tiles_m,
-                           tiles_n, splits > 1 ? ws : nullptr);
-    } else {
-        // the narrow shape, whole-tile chunks: five pieces per thread hold runs of up to 160 pixels with 256 threads
-        constexpr int NPL_S = 5;
-        if (pp > NPL_S * Cfg::NT / 8) return -1;
-        hipLaunchKernelGGL((conv_patch_kernel<T, NPL_S, Cfg, 1>), dim3((unsigned)blocks), dim3(Cfg::NT), 0, s, pa, lb, ep, M, N, nkt, per, tiles_m,
-                           tiles_n, splits > 1 ? ws : nullptr);
-    }
-    if (splits > 1) launch_splitk_reduce<T>(ws, splits, ep, M, N, s);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
 // The window-row form of a first convolution in 16-bit data with up to 96 output columns runs conv_rows_kernel when
 // the filter bank and the image rows of a tile fit its LDS layout; everything else takes the tile engine.
 static bool rows_applies(const Gather &a, long ldb, int N, const Epilogue &ep, const GemmPlan &plan)
@@ -2002,9 +1222,6 @@ static int gather_plain_t(const Gather &a, const void *b, long ldb, int N, const
     if constexpr (sizeof(T) == 2) {
         if (rows_applies(a, ldb, N, ep, plan)) return run_rows(a, b, ldb, N, ep, s);
     }
-    const int ppt = patch_applies<T>(a, ldb);
-    if (ppt == 1) return run_patch<T, 1>(a, b, ldb, N, ep, plan, ws, s);
-    if (ppt == 2) return run_patch<T, 2>(a, b, ldb, N, ep, plan, ws, s);
     if (a.ds == 1 && a.kh * a.kw <= 32)
         return run<T>(make_gather_k<T, false>(a), make_plain_k<T>(b, ldb, N, K), a.N * a.Ho * a.Wo, N, K, ep, plan, ws, s);
     if (a.ds == 1)

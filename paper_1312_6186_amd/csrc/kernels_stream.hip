@@ -477,6 +477,12 @@ int launch_stage_input_rw(int dtype, const void *src, void *dst, int B, int C, i
     return launch_ok();
 }
 
+// Element (row n, window position pos, channel c) of a filter pack in the order of conv_direct.
+__device__ __forceinline__ long direct_index(int n, int pos, int c, int ks, int nch, int npos)
+{
+    const int cw = ks * 16, ch = c / cw, e = c - ch * cw;
+    return ((((long)(n >> 5) * nch + ch) * npos + pos) * ks + (e >> 4)) * 512 + ((n & 31) + 32 * ((e >> 3) & 1)) * 8 + (e & 7);
+}
 // All convolution layers of a net in one launch.  A thread produces 8 consecutive packed elements (the innermost
 // packed index is a multiple of 8 wide in every pack) and stores them as one or two 16-byte vectors; group g
 // belongs to the job whose range holds it.
@@ -509,7 +515,7 @@ template <typename T> __global__ __launch_bounds__(256) void pack_conv_kernel(Pa
         const T *src = w + ((long)co * J.cin + ci0) * kk + ky * k + kx;
 #pragma unroll
         for (int e = 0; e < 8; ++e) out[e] = (co < J.cout && ci0 + e < J.cin) ? src[e * kk] : (T)0.f;
-        dst = static_cast<T *>(J.wf) + li;
+        dst = static_cast<T *>(J.wf) + (J.fks ? direct_index(co, ky * k + kx, ci0, J.fks, J.fch, (int)kk) : (long)li);
     } else {  // wd[ci][ky'][kx'][co] = w[co][ci][k-1-ky'][k-1-kx']
         li -= J.nf;
         const int co0 = (int)(li % (unsigned)J.coutp); unsigned t = li / (unsigned)J.coutp;
@@ -519,7 +525,7 @@ template <typename T> __global__ __launch_bounds__(256) void pack_conv_kernel(Pa
         const long cstride = (long)J.cin * kk;
 #pragma unroll
         for (int e = 0; e < 8; ++e) out[e] = (co0 + e < J.cout && ci < J.cin) ? src[e * cstride] : (T)0.f;
-        dst = static_cast<T *>(J.wd) + li;
+        dst = static_cast<T *>(J.wd) + (J.dks ? direct_index(ci, ky * k + kx, co0, J.dks, J.dch, (int)kk) : (long)li);
     }
     uint4 *d4 = reinterpret_cast<uint4 *>(dst);
     const uint4 *o4 = reinterpret_cast<const uint4 *>(out);
@@ -573,7 +579,8 @@ template <typename T> __global__ __launch_bounds__(1024) void pack_conv_lds_kern
             const int cg = i % cv, t = i / cv, pp = t % kk, c = t / kk;
 #pragma unroll
             for (int e = 0; e < V; ++e) o.e[e] = at(c, cg * V + e, pp);
-            *reinterpret_cast<uint4 *>(static_cast<T *>(J.wf) + ((long)(co0 + c) * kk + pp) * J.cinp + cg * V) = o.u;
+            const long at_f = J.fks ? direct_index(co0 + c, pp, cg * V, J.fks, J.fch, kk) : ((long)(co0 + c) * kk + pp) * J.cinp + cg * V;
+            *reinterpret_cast<uint4 *>(static_cast<T *>(J.wf) + at_f) = o.u;
         }
     }
     if (J.wd) {  // wd[ci][ky'][kx'][co] = w[co][ci][k-1-ky'][k-1-kx']: this group's 16 bytes of every (ci, ky', kx')
@@ -582,7 +589,8 @@ template <typename T> __global__ __launch_bounds__(1024) void pack_conv_lds_kern
             const int pp = i % kk, ci = i / kk;
 #pragma unroll
             for (int e = 0; e < V; ++e) o.e[e] = at(e, ci, kk - 1 - pp);
-            *reinterpret_cast<uint4 *>(static_cast<T *>(J.wd) + ((long)ci * kk + pp) * J.coutp + co0) = o.u;
+            const long at_d = J.dks ? direct_index(ci, pp, co0, J.dks, J.dch, kk) : ((long)ci * kk + pp) * J.coutp + co0;
+            *reinterpret_cast<uint4 *>(static_cast<T *>(J.wd) + at_d) = o.u;
         }
     }
 }

@@ -255,6 +255,26 @@ def test_minibatch_gradient_matches_oracle(cfg, batch, dtype):
         g.close()
 
 
+# Stride-1 convolutions over equal grids: channel counts around the chunks (a chunk is 16, 32, 48 or 64 channels), output
+# counts around the blocks of 32 columns, and enough pixels for every tile shape to be the cheapest one somewhere.
+DIRECT_SHAPES = [(8, 8, 3, 5, 7, 3), (16, 40, 5, 6, 9, 2), (48, 136, 3, 8, 8, 4), (72, 200, 3, 6, 5, 9), (120, 96, 3, 9, 9, 4), (136, 24, 5, 7, 11, 3),
+                 (24, 128, 3, 33, 31, 64), (24, 128, 3, 31, 31, 50), (24, 96, 3, 31, 31, 80), (24, 96, 3, 31, 31, 53), (24, 192, 3, 31, 31, 26),
+                 (24, 192, 3, 31, 31, 40), (32, 96, 5, 13, 13, 64)]
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("shape", DIRECT_SHAPES, ids=lambda s: "%dto%d_k%d_%dx%dx%d" % s)
+def test_stride1_convolution_shapes(shape, dtype):
+    cin, cout, k, h, w, batch = shape
+    layers = [("conv", cin, 1, 1, 0), ("relu",), ("conv", cout, k, 1, k // 2), ("relu",), ("maxpool", 2, 2), ("fc", 10), ("softmax_ce",)]
+    g, onet, (loss, grads), (ref_loss, ref_grads, _), _ = _net_case({"name": "direct", "in_shape": (3, h, w), "classes": 10, "layers": layers}, batch, dtype, plain=False)
+    try:
+        assert abs(loss - ref_loss) <= TOL[dtype] * abs(ref_loss)
+        compare_grads(onet, grads, ref_grads, TOL[dtype], "direct")
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
 @pytest.mark.parametrize("k,stride", [(2, 2), (3, 2), (3, 1)])
 def test_pooling_positions_are_bit_exact(k, stride, dtype):
