@@ -91,7 +91,7 @@ struct asgd_net {
     void *act0 = nullptr;      // staged input
     float *scratch = nullptr;       // split-K partials of the kernels on the caller's stream
     float *scratch_side = nullptr;  // split-K and column-sum partials of the parameter-gradient kernels (side stream)
-    // The parameter gradients of a layer (and the filter packing of the forward pass) do not feed the next
+    // The parameter gradients of a layer do not feed the next
     // layer: they run on an internal stream beside the caller's, forked and joined with events.
     hipStream_t side = nullptr;
     bool in_replay = false;   // replicas of a replay already run beside each other: no side stream then (measured slower)
@@ -100,8 +100,8 @@ struct asgd_net {
     // first use, released with the plan), so that a replay only enqueues.
     std::vector<hipStream_t> replay_streams;   // one per worker, then the server's
     std::vector<hipEvent_t> replay_events;
-    hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_bias = nullptr;
-    std::vector<hipEvent_t> ev_pack, ev_dy, ev_dg;   // per stage: filters packed, output gradient ready, data gradient issued
+    hipEvent_t ev_join = nullptr, ev_bias = nullptr;
+    std::vector<hipEvent_t> ev_dy, ev_dg;   // per stage: output gradient ready, data gradient issued
     float *row_loss = nullptr;
     int *version_counter = nullptr;  // device-side count of applied updates (A-SGD replay)
     size_t scratch_floats = 0, scratch_side_floats = 0;
@@ -359,13 +359,11 @@ int release_device(asgd_net *n)
     for (hipStream_t st : n->replay_streams) if (st) { (void)hipStreamSynchronize(st); (void)hipStreamDestroy(st); }
     for (hipEvent_t e : n->replay_events) if (e) (void)hipEventDestroy(e);
     n->replay_streams.clear(); n->replay_events.clear();
-    if (n->ev_fork) { (void)hipEventDestroy(n->ev_fork); n->ev_fork = nullptr; }
     if (n->ev_join) { (void)hipEventDestroy(n->ev_join); n->ev_join = nullptr; }
     if (n->ev_bias) { (void)hipEventDestroy(n->ev_bias); n->ev_bias = nullptr; }
-    for (hipEvent_t e : n->ev_pack) if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : n->ev_dy) if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : n->ev_dg) if (e) (void)hipEventDestroy(e);
-    n->ev_pack.clear(); n->ev_dy.clear(); n->ev_dg.clear();
+    n->ev_dy.clear(); n->ev_dg.clear();
     if (n->arena) {
         const hipError_t e = hipFree(n->arena);
         n->arena = nullptr;
@@ -387,15 +385,12 @@ int ensure_prepared(asgd_net *n)
     n->device = dev;
     carve(*n, static_cast<char *>(n->arena));
     e = hipStreamCreateWithFlags(&n->side, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&n->ev_fork, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&n->ev_join, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&n->ev_bias, hipEventDisableTiming);
-    n->ev_pack.assign(n->stages.size(), nullptr);
     n->ev_dy.assign(n->stages.size(), nullptr);
     n->ev_dg.assign(n->stages.size(), nullptr);
     for (size_t i = 0; i < n->stages.size() && e == hipSuccess; ++i) {
-        e = hipEventCreateWithFlags(&n->ev_pack[i], hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&n->ev_dy[i], hipEventDisableTiming);
+        e = hipEventCreateWithFlags(&n->ev_dy[i], hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&n->ev_dg[i], hipEventDisableTiming);
     }
     if (e != hipSuccess) { release_device(n); return hip_fail(e, "creating the internal stream and events"); }
@@ -492,32 +487,22 @@ Gather dgrad_gather(const Stage &s, const void *dy, int B, int dt, int group)
 
 const char *param_ptr(const asgd_net *n, const void *params, size_t off) { return static_cast<const char *>(params) + off * dtype_size(n->dtype); }
 
-int forward(asgd_net *n, const void *params, const void *images, const int32_t *labels, uint64_t seed, uint64_t step, uint32_t worker,
-            float *loss, hipStream_t st)
+int forward(asgd_net *n, const void *params, const void *images, const int32_t *labels, uint64_t seed, uint64_t step, uint32_t worker, hipStream_t st)
 {
     const int B = n->batch, dt = n->dtype;
     const double es = (double)dtype_size(dt), Bd = (double)B;
-    {
-        ProfScope ps(n, st, ASGD_K_LAYOUT, 0, 2 * Bd * n->in_c * n->in_h * n->in_w * es);
-        const Stage &s0 = n->stages[0];
-        if (s0.rw) CHECK_LAUNCH(launch_stage_input_rw(dt, images, n->act0, B, n->in_c, n->in_h, n->in_w, s0.pad, s0.rwWp, s0.rwC, st), "stage_input");
-        else CHECK_LAUNCH(launch_stage_input(dt, images, n->act0, B, n->in_c, n->in_h, n->in_w, n->in_cp, st), "stage_input");
-    }
-    // filter packing: beside the input staging and the first layers (in line when profiling, to be timed alone)
-    const bool fork = !n->prof_on && !n->in_replay && !n->serial;
-    hipStream_t sd = fork ? n->side : st;
-    if (fork) {
-        CHECK_HIP(hipEventRecord(n->ev_fork, st), "hipEventRecord");
-        CHECK_HIP(hipStreamWaitEvent(sd, n->ev_fork, 0), "hipStreamWaitEvent");
-    }
-    {   // all layers' filters in one launch (twelve layers per launch at most)
+    {   // the images, and all layers' filters in the same launch (twelve layers per launch at most)
         PackJobs jobs; jobs.n = 0; jobs.total = 0;
-        double bytes = 0;
+        const Stage &s0 = n->stages[0];
+        StageJob stage = {};
+        stage.src = images; stage.dst = n->act0; stage.B = B; stage.C = n->in_c; stage.H = n->in_h; stage.W = n->in_w; stage.Cp = n->in_cp;
+        if (s0.rw) { stage.pad = s0.pad; stage.Wp = s0.rwWp; stage.pc = s0.rwC; }
+        double bytes = 2 * Bd * n->in_c * n->in_h * n->in_w * es;
         auto flush = [&]() -> int {
-            if (jobs.n == 0) return ASGD_OK;
-            ProfScope ps(n, sd, ASGD_K_LAYOUT, 0, bytes);
-            CHECK_LAUNCH(launch_pack_conv(dt, jobs, sd), "pack_conv");
-            jobs.n = 0; bytes = 0;
+            if (jobs.n == 0 && !stage.src) return ASGD_OK;
+            ProfScope ps(n, st, ASGD_K_LAYOUT, 0, bytes);
+            CHECK_LAUNCH(launch_head(dt, jobs, stage, st), "input staging and filter packing");
+            jobs.n = 0; jobs.total = 0; stage.src = nullptr; bytes = 0;
             return ASGD_OK;
         };
         for (size_t si = 0; si < n->stages.size(); ++si) {
@@ -546,15 +531,11 @@ int forward(asgd_net *n, const void *params, const void *images, const int32_t *
         }
         const int rc = flush();
         if (rc != ASGD_OK) return rc;
-        if (fork) CHECK_HIP(hipEventRecord(n->ev_pack[0], sd), "hipEventRecord");
     }
-    bool packed_seen = false;
     const void *cur = n->act0;
     for (size_t si = 0; si < n->stages.size(); ++si) {
         Stage &s = n->stages[si];
         if (s.kind == ST_CONV) {
-            if (fork && !packed_seen) CHECK_HIP(hipStreamWaitEvent(st, n->ev_pack[0], 0), "hipStreamWaitEvent");
-            packed_seen = true;
             const double Mo = Bd * s.outH * s.outW;
             ProfScope ps(n, st, ASGD_K_CONV_FWD, 2 * Mo * s.outC * (s.inC / s.groups) * s.k * s.k,
                          (Bd * s.inH * s.inW * s.inC + (double)s.w_cnt + Mo * s.outC) * es);
@@ -598,7 +579,7 @@ int forward(asgd_net *n, const void *params, const void *images, const int32_t *
     }
     Stage &last = n->stages.back();
     ProfScope ps(n, st, ASGD_K_SOFTMAX_CE, 0, Bd * n->classes * (4 + es));
-    CHECK_LAUNCH(launch_softmax_ce(dt, static_cast<const float *>(last.out), last.out_ld, labels, B, n->classes, last.dout, loss, n->row_loss, st),
+    CHECK_LAUNCH(launch_softmax_ce(dt, static_cast<const float *>(last.out), last.out_ld, labels, B, n->classes, last.dout, n->row_loss, st),
                  "softmax cross-entropy");
     return ASGD_OK;
 }
@@ -613,13 +594,14 @@ struct ServerArgs {
     bool fuse;           // fully-connected weights: the push happens inside the weight-gradient kernel, which stores no gradient
 };
 
-int backward(asgd_net *n, const void *params, float *grads, hipStream_t st, const ServerArgs *srv)
+int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStream_t st, const ServerArgs *srv)
 {
     const int B = n->batch, dt = n->dtype;
     const double es = (double)dtype_size(dt), Bd = (double)B;
     const bool fork = !n->prof_on && !n->in_replay && !n->serial;
     hipStream_t sd = fork ? n->side : st;   // parameter gradients go here
-    ColsumJobs bias_jobs; bias_jobs.n = 0;  // second stage of the bias gradients: one launch at the end, or per layer when pushing by layer
+    ColsumJobs bias_jobs; bias_jobs.n = 0;  // the loss, and second stage of the bias gradients: one launch at the end, or per layer when pushing by layer
+    loss_job(n->row_loss, B, loss, bias_jobs);
     ColsumS1Jobs bias_s1; bias_s1.n = 0;    // first stages that wait for that launch too (one launch for all of them)
     double bias_s1_bytes = 0;
     int first_param = -1;
@@ -774,7 +756,7 @@ int backward(asgd_net *n, const void *params, float *grads, hipStream_t st, cons
                     CHECK_LAUNCH(launch_colsum_finish(bias_jobs, sd), "conv bias gradient");
                 }
                 ColsumJob &J = bias_jobs.j[bias_jobs.n++];
-                J.ws = s.colsum_ws; J.nblk = (int)s.pool_bands; J.ld = s.outCp; J.N = s.outC; J.db = grads + s.b_off; J.start_block = 0; J.colmajor = 1;
+                J.ws = s.colsum_ws; J.nblk = (int)s.pool_bands; J.ld = s.outCp; J.N = s.outC; J.db = grads + s.b_off; J.start_block = 0; J.colmajor = 1; J.div = 1.f;
                 if (by_layer) CHECK_LAUNCH(launch_colsum_finish(bias_jobs, sd), "conv bias gradient");
                 return ASGD_OK;
             };
@@ -961,10 +943,10 @@ int asgd_fwd_bwd(asgd_net_t *net, const void *params, const void *images, const 
     int rc = ensure_prepared(net);
     if (rc != ASGD_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = forward(net, params, images, labels, dropout_seed, step, worker, loss, st);
+    rc = forward(net, params, images, labels, dropout_seed, step, worker, st);
     if (rc != ASGD_OK) return rc;
     net->last_seed = dropout_seed; net->last_step = step; net->last_worker = worker; net->ran = true;
-    return backward(net, params, grads, st, nullptr);
+    return backward(net, params, loss, grads, st, nullptr);
 }
 
 // ---- the entry point that allocates nothing
@@ -1022,8 +1004,8 @@ int asgd_fwd_bwd_static(asgd_net_t *net, const void *params, const void *images,
     const bool was_serial = net->serial;
     net->serial = true;
     if (launch_fill_zero(base, net->ws_bytes, st) != 0) rc = hip_fail(hipGetLastError(), "fill kernel");
-    if (rc == ASGD_OK) rc = forward(net, params, images, labels, dropout_seed, step, worker, loss, st);
-    if (rc == ASGD_OK) rc = backward(net, params, grads, st, nullptr);
+    if (rc == ASGD_OK) rc = forward(net, params, images, labels, dropout_seed, step, worker, st);
+    if (rc == ASGD_OK) rc = backward(net, params, loss, grads, st, nullptr);
     net->serial = was_serial;
     carve(*net, static_cast<char *>(net->arena));   // back to the plan's own workspace (null pointers if it has none yet)
     net->ran = false;                               // nothing of this call is left where asgd_debug_get looks
@@ -1042,11 +1024,11 @@ int train_step_impl(const char *name, bool fuse, asgd_net_t *net, float *master,
     int rc = ensure_prepared(net);
     if (rc != ASGD_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = forward(net, worker_copy, images, labels, dropout_seed, step, worker, loss, st);
+    rc = forward(net, worker_copy, images, labels, dropout_seed, step, worker, st);
     if (rc != ASGD_OK) return rc;
     net->last_seed = dropout_seed; net->last_step = step; net->last_worker = worker; net->ran = true;
     const ServerArgs srv{master, momentum, worker_copy, lr, mu, wd, fuse};
-    return backward(net, worker_copy, grads, st, &srv);
+    return backward(net, worker_copy, loss, grads, st, &srv);
 }
 }  // namespace
 

@@ -122,10 +122,6 @@ int launch_adadelta(float *w, float *a, float *b, const float *g, size_t n, floa
 int launch_accumulate(float *acc, const float *g, size_t n, bool first, hipStream_t s);
 int launch_snapshot(const float *src, void *dst, size_t n, int dst_dtype, const int *version_counter,
                     int32_t *log_slot, int log_update, int log_worker, hipStream_t s);
-// images [B][C][H][W] (compute type) -> channel-last [B][H][W][Cp], zero padding channels
-int launch_stage_input(int dtype, const void *src, void *dst, int B, int C, int H, int W, int Cp, hipStream_t s);
-// the same into the interior of a bordered [B][H+2*pad][Wp][4] tensor (C <= 4; the border is not written)
-int launch_stage_input_rw(int dtype, const void *src, void *dst, int B, int C, int H, int W, int pad, int Wp, int pc, hipStream_t s);
 // Filter packing for all convolution layers of a net in one launch.  Per layer: canonical filters
 // [cout][cin][k][k] -> forward pack wf [coutp][k][k][cinp] and, if wd is given, the flipped data-gradient pack
 // wd [cinp][k][k][coutp]; or (rw = channels per stored pixel > 0) the window-row pack wf [coutp][k][KW], element (ky, kx*rw + ci), zeros elsewhere.
@@ -137,7 +133,15 @@ struct PackJob {
     unsigned start, nf;   // filled by launch_pack_conv
 };
 struct PackJobs { PackJob j[12]; int n; unsigned total; };
-int launch_pack_conv(int dtype, PackJobs &jobs, hipStream_t s);
+// Input staging: images [B][C][H][W] (compute type) -> channel-last [B][H][W][Cp] with zero padding channels (pc = 0), or
+// into the interior of a bordered [B][H+2*pad][Wp][pc] tensor (pc = 1..4 channels per pixel; the border is not written).
+struct StageJob {
+    const void *src; void *dst;   // src == nullptr: nothing to stage
+    int B, C, H, W, Cp, pad, Wp, pc;
+    unsigned total; FastDiv dHW, dH, dWq;   // filled by launch_head
+};
+// the head of a forward pass: the filters of up to 12 layers packed and the images staged, in one launch where it can be
+int launch_head(int dtype, PackJobs &jobs, const StageJob &st, hipStream_t s);
 int launch_pool_fwd(int dtype, const void *x, void *y, uint8_t *arg, int B, int H, int W, int Cp, int k, int stride,
                     hipStream_t s);
 // dx[pixel] = sum of dy over the windows whose recorded maximum is this pixel; times [x > 0] if relu
@@ -158,7 +162,7 @@ int launch_unflatten(int dtype, const void *dflat, const void *x_for_mask, int r
 // db[n] = sum_m dy[m][n], n < N, fp32, fixed summation order, in two stages: launch_colsum_partial sums bands of
 // rows into ws (colsum_ws_floats floats, not shared with another pending job) and appends a job;
 // launch_colsum_finish adds the bands of all pending jobs (up to 12) in one launch.
-struct ColsumJob { const float *ws; float *db; long ld; int nblk, N; unsigned start_block; int colmajor; };   // ws[band][ld], or ws[column][nblk] if colmajor
+struct ColsumJob { const float *ws; float *db; long ld; int nblk, N; unsigned start_block; int colmajor; float div; };   // ws[band][ld], or ws[column][nblk] if colmajor; sums are divided by div
 struct ColsumJobs { ColsumJob j[12]; int n; };
 int launch_colsum_partial(int dtype, const void *dy, long ld, long M, int N, float *db, float *ws, ColsumJobs &jobs, hipStream_t s);
 // the same with the first stage put off: colsum_partial_defer appends the tensor to s1 (and its second stage to jobs),
@@ -169,9 +173,10 @@ int colsum_partial_defer(int dtype, const void *dy, long ld, long M, int N, floa
 int launch_colsum_stage1(int dtype, ColsumS1Jobs &s1, hipStream_t s);
 int launch_colsum_finish(ColsumJobs &jobs, hipStream_t s);
 size_t colsum_ws_floats(int dtype, long M, long ld);
-// softmax cross-entropy over fp32 logits [B][ld]: loss (mean) and dz (compute type, [B][ld], zero padding columns)
-int launch_softmax_ce(int dtype, const float *z, long ld, const int32_t *labels, int B, int C, void *dz, float *loss,
-                      float *row_loss, hipStream_t s);
+// softmax cross-entropy over fp32 logits [B][ld]: the loss of every row, whose mean loss_job appends to the bias sums' second
+// stage, and dz (compute type, [B][ld], zero padding columns)
+int launch_softmax_ce(int dtype, const float *z, long ld, const int32_t *labels, int B, int C, void *dz, float *row_loss, hipStream_t s);
+void loss_job(const float *row_loss, int B, float *loss, ColsumJobs &jobs);
 int launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 // debug exports (canonical layouts)
 int launch_export_nhwc(int dtype, const void *x, float *dst, int B, int H, int W, int C, int Cp, hipStream_t s);

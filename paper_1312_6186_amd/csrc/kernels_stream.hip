@@ -389,94 +389,59 @@ int launch_fill_zero(void *p, size_t bytes, hipStream_t s)
 }
 
 // ---------------------------------------------------------------- input staging and filter packing
-template <typename T> __global__ __launch_bounds__(256) void stage_input_kernel(const T *__restrict__ src, T *__restrict__ dst, int B, int C, int H,
-                                                                              int W, int Cp)
+__device__ __forceinline__ uint32_t fdiv32(uint32_t n, const FastDiv &f) { return (__umulhi(n, f.mul) + n) >> f.sh; }
+// One element of work of the input staging: images [B][C][H][W] -> the first layer's channel-last input.
+// FORM 0: 16 bytes of channels of one pixel, Cp channels per pixel, zeros past C (reads contiguous along w for each channel).
+// FORM 1..4: FORM channels per pixel into the interior of a bordered tensor, PX neighbouring pixels of one row.  PX = 4 (W and
+// the image base allow 4-element loads): one load per channel; PX = 2 (even W): element loads; PX = 1: any width, element
+// stores.  For PX > 1 the elements make a whole number of dwords at a dword-aligned address (checked by the launcher).
+template <typename T, int FORM, int PX> __device__ __forceinline__ void stage_one(const StageJob &j, unsigned i)
 {
-    // one thread per pixel and 16-byte channel group: reads are contiguous along w for each channel,
-    // the store is one vector
-    constexpr int V = 16 / sizeof(T);
-    const int groups = Cp / V;
-    const long HW = (long)H * W;
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (long)B * HW * groups) return;
-    const long pix = i % ((long)B * HW);       // pixels fastest: neighbouring threads read neighbouring w
-    const int gidx = (int)(i / ((long)B * HW));
-    const long n = pix / HW, hw = pix - n * HW;
-    union { uint4 u; T e[V]; } v;
+    const T *__restrict__ src = static_cast<const T *>(j.src);
+    T *__restrict__ dst = static_cast<T *>(j.dst);
+    if constexpr (FORM == 0) {
+        constexpr int V = 16 / sizeof(T);
+        const unsigned per = (unsigned)j.B * j.H * j.W, gidx = i / per, pix = i - gidx * per;   // pixels fastest
+        const unsigned n = fdiv32(pix, j.dHW), hw = pix - n * (unsigned)(j.H * j.W);
+        union { uint4 u; T e[V]; } v;
 #pragma unroll
-    for (int e = 0; e < V; ++e) {
-        const int c = gidx * V + e;
-        v.e[e] = c < C ? src[(n * C + c) * HW + hw] : (T)0.f;
-    }
-    *reinterpret_cast<uint4 *>(dst + pix * Cp + gidx * V) = v.u;
-}
-int launch_stage_input(int dtype, const void *src, void *dst, int B, int C, int H, int W, int Cp, hipStream_t s)
-{
-    const unsigned blocks = blocks_for((size_t)B * H * W * (Cp / (dtype == kBF16 ? 8 : 4)), 256);
-    if (dtype == kBF16)
-        hipLaunchKernelGGL(stage_input_kernel<bf16_t>, dim3(blocks), dim3(256), 0, s, static_cast<const bf16_t *>(src), static_cast<bf16_t *>(dst), B, C, H, W, Cp);
-    else
-        hipLaunchKernelGGL(stage_input_kernel<float>, dim3(blocks), dim3(256), 0, s, static_cast<const float *>(src), static_cast<float *>(dst), B, C, H, W, Cp);
-    return launch_ok();
-}
-
-template <typename T, int PC> __global__ __launch_bounds__(256) void stage_input_rw_kernel(const T *__restrict__ src, T *__restrict__ dst, int B, int C,
-                                                                                         int H, int W, int pad, int Wp)
-{
-    // a thread moves two neighbouring pixels of a row (W is even, checked by the launcher): 2 * PC elements, which
-    // for every PC and element size make a whole number of dwords at a dword-aligned address
-    const long HW = (long)H * W, HW2 = HW / 2;
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (long)B * HW2) return;
-    const long n = i / HW2, hw = (i - n * HW2) * 2;
-    const int h = (int)(hw / W), w = (int)(hw - (long)h * W);
-    union { T e[2 * PC]; uint32_t u[2 * PC * sizeof(T) / 4]; } v;
+        for (int e = 0; e < V; ++e) {
+            const int c = (int)gidx * V + e;
+            v.e[e] = c < j.C ? src[((size_t)n * j.C + c) * (size_t)(j.H * j.W) + hw] : (T)0.f;
+        }
+        *reinterpret_cast<uint4 *>(dst + (size_t)pix * j.Cp + gidx * V) = v.u;
+    } else {
+        constexpr int PC = FORM;
+        const size_t HW = (size_t)j.H * j.W;
+        const unsigned row = fdiv32(i, j.dWq), w = (i - row * j.dWq.d) * PX;     // row = n * H + h
+        const unsigned n = fdiv32(row, j.dH), h = row - n * (unsigned)j.H;
+        const T *s0 = src + (size_t)n * j.C * HW + (size_t)h * j.W + w;
+        union { T e[PX * PC]; uint32_t u[(PX * PC * sizeof(T) + 3) / 4]; } v;
+        if constexpr (PX == 4) {
+            typedef T t4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
+            for (int c = 0; c < PC; ++c) {
+                const t4 x = c < j.C ? *reinterpret_cast<const t4 *>(s0 + c * HW) : t4{};
 #pragma unroll
-        for (int c = 0; c < PC; ++c) v.e[q * PC + c] = c < C ? src[(n * C + c) * HW + hw + q] : (T)0.f;
-    uint32_t *o = reinterpret_cast<uint32_t *>(dst + ((n * (H + 2 * pad) + h + pad) * Wp + w + pad) * PC);
+                for (int q = 0; q < 4; ++q) v.e[q * PC + c] = x[q];
+            }
+        } else {
 #pragma unroll
-    for (int d = 0; d < (int)(2 * PC * sizeof(T) / 4); ++d) o[d] = v.u[d];
-}
-// one pixel per thread, element stores: any width
-template <typename T> __global__ __launch_bounds__(256) void stage_input_rw_any_kernel(const T *__restrict__ src, T *__restrict__ dst, int B, int C,
-                                                                                     int H, int W, int pad, int Wp, int pc)
-{
-    const long HW = (long)H * W;
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (long)B * HW) return;
-    const long n = i / HW, hw = i - n * HW;
-    const int h = (int)(hw / W), w = (int)(hw - (long)h * W);
-    T *o = dst + ((n * (H + 2 * pad) + h + pad) * Wp + w + pad) * pc;
-    for (int c = 0; c < pc; ++c) o[c] = c < C ? src[(n * C + c) * HW + hw] : (T)0.f;
-}
-template <typename T>
-static void launch_stage_input_rw_t(const void *src, void *dst, int B, int C, int H, int W, int pad, int Wp, int pc, hipStream_t s)
-{
-    const T *a = static_cast<const T *>(src); T *o = static_cast<T *>(dst);
-    // the pair form needs both pixels in one row and every pair dword-aligned: (pad * pc), (Wp * pc) elements even in bytes / 4
-    const bool pairs = (W % 2 == 0) && ((size_t)pad * pc * sizeof(T)) % 4 == 0 && ((size_t)Wp * pc * sizeof(T)) % 4 == 0 &&
-                       ((size_t)2 * pc * sizeof(T)) % 4 == 0;
-    if (pairs) {
-        const unsigned blocks = blocks_for((size_t)B * H * W / 2, 256);
-        switch (pc) {
-        case 1: hipLaunchKernelGGL((stage_input_rw_kernel<T, 1>), dim3(blocks), dim3(256), 0, s, a, o, B, C, H, W, pad, Wp); return;
-        case 2: hipLaunchKernelGGL((stage_input_rw_kernel<T, 2>), dim3(blocks), dim3(256), 0, s, a, o, B, C, H, W, pad, Wp); return;
-        case 3: hipLaunchKernelGGL((stage_input_rw_kernel<T, 3>), dim3(blocks), dim3(256), 0, s, a, o, B, C, H, W, pad, Wp); return;
-        case 4: hipLaunchKernelGGL((stage_input_rw_kernel<T, 4>), dim3(blocks), dim3(256), 0, s, a, o, B, C, H, W, pad, Wp); return;
+            for (int q = 0; q < PX; ++q)
+#pragma unroll
+                for (int c = 0; c < PC; ++c) v.e[q * PC + c] = c < j.C ? s0[c * HW + q] : (T)0.f;
+        }
+        T *o = dst + (((size_t)n * (j.H + 2 * j.pad) + h + j.pad) * j.Wp + w + j.pad) * PC;
+        if constexpr (PX > 1) {
+            uint32_t *o4 = reinterpret_cast<uint32_t *>(o);
+#pragma unroll
+            for (int q = 0; q < (int)(PX * PC * sizeof(T) / 4); ++q) o4[q] = v.u[q];
+        } else {
+#pragma unroll
+            for (int c = 0; c < PC; ++c) o[c] = v.e[c];
         }
     }
-    hipLaunchKernelGGL(stage_input_rw_any_kernel<T>, dim3(blocks_for((size_t)B * H * W, 256)), dim3(256), 0, s, a, o, B, C, H, W, pad, Wp, pc);
 }
-int launch_stage_input_rw(int dtype, const void *src, void *dst, int B, int C, int H, int W, int pad, int Wp, int pc, hipStream_t s)
-{
-    if (C > pc || pc < 1 || pc > 4) return -1;
-    if (dtype == kBF16) launch_stage_input_rw_t<bf16_t>(src, dst, B, C, H, W, pad, Wp, pc, s);
-    else launch_stage_input_rw_t<float>(src, dst, B, C, H, W, pad, Wp, pc, s);
-    return launch_ok();
-}
-
 // Element (row n, window position pos, channel c) of a filter pack in the order of conv_direct.
 __device__ __forceinline__ long direct_index(int n, int pos, int c, int ks, int nch, int npos)
 {
@@ -536,10 +501,9 @@ template <typename T> __global__ __launch_bounds__(256) void pack_conv_kernel(Pa
 // into 64 KB: a workgroup owns such a group of output channels, copies its filters (one contiguous, 16-byte aligned
 // run of the canonical tensor) into LDS with 16-byte loads and writes every packed vector that holds them.  The
 // gather form above reads its 8 elements k*k apart, 2 or 4 bytes at a time.
-template <typename T> __global__ __launch_bounds__(1024) void pack_conv_lds_kernel(PackJobs jobs)
+template <typename T> __device__ __forceinline__ void pack_lds_block(const PackJobs &jobs, uint4 *slab4)
 {
     constexpr int V = 16 / (int)sizeof(T), NT = 1024;
-    __shared__ uint4 slab4[4096];
     T *slab = reinterpret_cast<T *>(slab4);
     int q = 0;
     while (q + 1 < jobs.n && blockIdx.x >= jobs.j[q + 1].start) ++q;
@@ -595,8 +559,56 @@ template <typename T> __global__ __launch_bounds__(1024) void pack_conv_lds_kern
     }
 }
 
-int launch_pack_conv(int dtype, PackJobs &jobs, hipStream_t s)
+// The head of a forward pass in one launch: the first jobs.total workgroups pack filters, the others stage the images, 1024
+// elements of work each.  The packing is a chain of few loads (13 us by itself for 172 workgroups), the staging a stream
+// (20 us for 128 images of 3 x 224 x 224 in bf16); on two streams the events around them cost another 22 us.  Together, with
+// four pixels per thread where the width allows: 54 -> 21 us.
+template <typename T, int FORM, int PX> __global__ __launch_bounds__(1024) void head_kernel(PackJobs jobs, StageJob st)
 {
+    __shared__ uint4 slab4[4096];
+    if (blockIdx.x < jobs.total) { pack_lds_block<T>(jobs, slab4); return; }
+    const unsigned i = (blockIdx.x - jobs.total) * 1024u + threadIdx.x;
+    if (i < st.total) stage_one<T, FORM, PX>(st, i);
+}
+template <typename T> static int launch_head_t(const PackJobs &jobs, StageJob st, hipStream_t s)
+{
+    // elements of work: 32-bit indices (the plan keeps an image tensor below 2^31 elements)
+    const unsigned es = sizeof(T);
+    int form = 0, px = 1;
+    size_t work = st.src ? (size_t)st.B * st.H * st.W : 0;
+    if (st.pc) {
+        form = st.pc;
+        const bool dwords2 = ((size_t)st.pad * st.pc * es) % 4 == 0 && ((size_t)st.Wp * st.pc * es) % 4 == 0 && ((size_t)2 * st.pc * es) % 4 == 0 && ((uintptr_t)st.dst & 3) == 0;
+        if (dwords2 && st.W % 4 == 0 && ((uintptr_t)st.src & (4 * es - 1)) == 0) px = 4;
+        else if (dwords2 && st.W % 2 == 0) px = 2;
+        work /= (size_t)px;
+    } else if (st.src) {
+        work *= (size_t)(st.Cp / (int)(16 / es));
+    }
+    if (work > 0x7fffffffu) return -1;
+    st.total = (unsigned)work;
+    if (st.src) {
+        st.dHW = make_fastdiv((uint32_t)(st.H * st.W)); st.dH = make_fastdiv((uint32_t)st.H); st.dWq = make_fastdiv((uint32_t)(st.W / px));
+    }
+    const unsigned blocks = jobs.total + (st.total + 1023u) / 1024u;
+    if (blocks == 0) return 0;
+#define ASGD_HEAD(F, P) if (form == F && px == P) { hipLaunchKernelGGL((head_kernel<T, F, P>), dim3(blocks), dim3(1024), 0, s, jobs, st); return launch_ok(); }
+    ASGD_HEAD(0, 1)
+    ASGD_HEAD(1, 1) ASGD_HEAD(1, 2) ASGD_HEAD(1, 4)
+    ASGD_HEAD(2, 1) ASGD_HEAD(2, 2) ASGD_HEAD(2, 4)
+    ASGD_HEAD(3, 1) ASGD_HEAD(3, 2) ASGD_HEAD(3, 4)
+    ASGD_HEAD(4, 1) ASGD_HEAD(4, 2) ASGD_HEAD(4, 4)
+#undef ASGD_HEAD
+    return -1;
+}
+
+int launch_head(int dtype, PackJobs &jobs, const StageJob &st, hipStream_t s)
+{
+    if (st.src && ((st.pc && (st.C > st.pc || st.pc > 4)) || (size_t)st.B * st.H * st.W > 0x7fffffffu)) return -1;
+    const auto head = [&](const PackJobs &pack) { return dtype == kBF16 ? launch_head_t<bf16_t>(pack, st, s) : launch_head_t<float>(pack, st, s); };
+    PackJobs none;
+    none.n = 0; none.total = 0;
+    if (jobs.n == 0) return head(none);
     // the LDS form, if every layer qualifies
     {
         const size_t es = dtype_size(dtype), V = 16 / es;
@@ -613,11 +625,10 @@ int launch_pack_conv(int dtype, PackJobs &jobs, hipStream_t s)
             unsigned start = 0;
             for (int q = 0; q < jobs.n; ++q) { jobs.j[q].start = start; start += (unsigned)(jobs.j[q].coutp / (int)V); }
             jobs.total = start;
-            if (dtype == kBF16) hipLaunchKernelGGL(pack_conv_lds_kernel<bf16_t>, dim3(start), dim3(1024), 0, s, jobs);
-            else hipLaunchKernelGGL(pack_conv_lds_kernel<float>, dim3(start), dim3(1024), 0, s, jobs);
-            return launch_ok();
+            return head(jobs);
         }
     }
+    if (head(none) != 0) return -1;
     size_t total = 0;
     for (int q = 0; q < jobs.n; ++q) {
         PackJob &J = jobs.j[q];
@@ -637,7 +648,6 @@ int launch_pack_conv(int dtype, PackJobs &jobs, hipStream_t s)
 }
 
 // ---------------------------------------------------------------- max pooling
-__device__ __forceinline__ uint32_t fdiv32(uint32_t n, const FastDiv &f) { return (__umulhi(n, f.mul) + n) >> f.sh; }
 // Workgroup ids go round-robin over the 8 XCDs; neighbouring pixels share pooling windows, so each XCD is given a
 // contiguous range of blocks (and its L2 fetches a window row once instead of every XCD fetching it).
 __device__ __forceinline__ uint32_t xcd_block()
@@ -1204,7 +1214,7 @@ __global__ __launch_bounds__(256) void colsum_stage2(ColsumJobs jobs)
     if (ty == 0 && n < N) {
         float t = 0.f;
         for (int j = 0; j < L; ++j) t += part[j * cpb + tx];
-        J.db[n] = t;
+        J.db[n] = t / J.div;
     }
 }
 static void colsum_geometry(int dtype, long ld, long M, int &chunks, int &cpb, int &rl, long &rows_per_block, int &nblk)
@@ -1235,7 +1245,7 @@ int colsum_partial_defer(int dtype, const void *dy, long ld, long M, int N, floa
     S.dy = dy; S.ws = ws; S.ld = ld; S.M = M; S.rows_per_block = rpb; S.chunks = chunks; S.cpb = cpb; S.rl = rl;
     S.gx = (chunks + cpb - 1) / cpb; S.gy = nblk; S.start_block = 0;
     ColsumJob &J = jobs.j[jobs.n++];
-    J.ws = ws; J.nblk = nblk; J.ld = ld; J.N = N; J.db = db; J.start_block = 0; J.colmajor = 0;
+    J.ws = ws; J.nblk = nblk; J.ld = ld; J.N = N; J.db = db; J.start_block = 0; J.colmajor = 0; J.div = 1.f;
     return 0;
 }
 int launch_colsum_stage1(int dtype, ColsumS1Jobs &s1, hipStream_t s)
@@ -1337,26 +1347,20 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(const float *__restrict
         stf(&dr[c], g);
     }
 }
-__global__ __launch_bounds__(256) void loss_reduce_kernel(const float *__restrict__ row_loss, int B, float *__restrict__ loss)
-{
-    __shared__ float part[256];
-    float acc = 0.f;
-    for (int i = threadIdx.x; i < B; i += 256) acc += row_loss[i];
-    part[threadIdx.x] = acc;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) part[threadIdx.x] += part[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) loss[0] = part[0] / (float)B;
-}
-int launch_softmax_ce(int dtype, const float *z, long ld, const int32_t *labels, int B, int C, void *dz, float *loss, float *row_loss, hipStream_t s)
+int launch_softmax_ce(int dtype, const float *z, long ld, const int32_t *labels, int B, int C, void *dz, float *row_loss, hipStream_t s)
 {
     const unsigned blocks = (unsigned)B;
     if (dtype == kBF16) hipLaunchKernelGGL(softmax_ce_kernel<bf16_t>, dim3(blocks), dim3(256), 0, s, z, ld, labels, B, C, static_cast<bf16_t *>(dz), row_loss);
     else hipLaunchKernelGGL(softmax_ce_kernel<float>, dim3(blocks), dim3(256), 0, s, z, ld, labels, B, C, static_cast<float *>(dz), row_loss);
-    hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(256), 0, s, row_loss, B, loss);
     return launch_ok();
+}
+
+// The mean of the row losses is one column of B bands: the launch that finishes the bias gradients takes it along (a kernel
+// of its own cost 4 us in the middle of every pass).
+void loss_job(const float *row_loss, int B, float *loss, ColsumJobs &jobs)
+{
+    ColsumJob &J = jobs.j[jobs.n++];
+    J.ws = row_loss; J.nblk = B; J.ld = 1; J.N = 1; J.db = loss; J.start_block = 0; J.colmajor = 1; J.div = (float)B;
 }
 
 // ---------------------------------------------------------------- debug exports

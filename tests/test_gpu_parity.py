@@ -812,6 +812,21 @@ def test_out_of_range_label_gives_nan_loss_and_no_fault():
 
 
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("c,w", [(1, 12), (2, 12), (3, 12), (4, 12), (3, 14), (3, 15), (8, 12), (9, 7)])
+def test_image_staging_takes_any_width(c, w, dtype):
+    """The images of a first convolution are staged four, two or one pixel at a time, by width; more than four channels in
+    groups of 16 bytes.  A channel or a pixel out of place shows in that layer's filter gradient."""
+    layers = [("conv", 8, 3, 2, 2), ("relu",), ("fc", 8), ("softmax_ce",)]
+    cfg, batch = {"name": "staging", "in_shape": (c, 10, w), "classes": 8, "layers": layers}, 5
+    g, onet, (loss, grads), (ref_loss, ref_grads, _), _ = _net_case(cfg, batch, dtype, plain=False)
+    try:
+        assert abs(loss - ref_loss) <= TOL[dtype] * abs(ref_loss)
+        compare_grads(onet, grads, ref_grads, TOL[dtype], "staging")
+    finally:
+        g.close()
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
 def test_serial_plan_gives_the_same_bits(dtype):
     """asgd_net_set_serial keeps every kernel on the caller's stream; the results must not change by a bit."""
     cfg = RAGGED
