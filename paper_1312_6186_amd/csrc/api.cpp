@@ -69,6 +69,7 @@ struct Stage {
     long pool_bands = 0;       // CONV directly under a pool whose backward kernel leaves those band sums: their number
     bool bands_ready = false;  // ... and whether the pool's backward pass of this call has left them
     GemmPlan p_fwd, p_dgrad, p_wgrad;
+    WgradPlan d_wgrad;           // CONV: set where the filter gradient (of all groups) runs as conv_wgrad
     DirectPlan d_fwd, d_dgrad;   // CONV: set where the forward pass / the data gradient (of one group) runs as conv_direct
     size_t wf_elems = 0, wd_elems = 0;   // packed filters of one group
     size_t out_elems() const { return kind == ST_FC ? (size_t)out_ld : (size_t)outH * outW * outCp; }
@@ -300,7 +301,6 @@ int plan_net(asgd_net &n)
     }
     if (n.classes == 0 || n.stages.empty() || !n.stages.back().last) return fail(ASGD_ESHAPE, "the layer list must end with FC, SOFTMAX_CE");
     n.param_count = off;
-
     // sizes, GEMM plans, scratch
     const long B = n.batch;
     size_t scratch = 0, scratch_side = 0;
@@ -324,13 +324,14 @@ int plan_net(asgd_net &n)
                 if (s.rw) s.p_wgrad.ws_floats = std::max(s.p_wgrad.ws_floats, rows_wgrad_ws_floats(n.dtype, s.outCp, conv_gather(s, nullptr, (int)B, n.dtype)));
             }
             const int Ng = s.groups > 1 ? s.outC / s.groups : s.outCp, Cg = s.groups > 1 ? s.inC / s.groups : s.inCp;
+            s.d_wgrad = plan_wgrad(n.dtype, Ng, s.groups, conv_gather(s, nullptr, (int)B, n.dtype));
             s.d_fwd = plan_direct(n.dtype, conv_gather(s, nullptr, (int)B, n.dtype), Ng);
             s.wf_elems = s.d_fwd.ks ? s.d_fwd.pack_elems : (size_t)Ng * s.k * (s.rw ? s.rwKW : s.k * Cg);
             if (si > 0) {
                 s.d_dgrad = plan_direct(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg);
                 s.wd_elems = s.d_dgrad.ks ? s.d_dgrad.pack_elems : (size_t)Cg * s.k * s.k * Ng;
             }
-            scratch_side = std::max(scratch_side, s.p_wgrad.ws_floats);
+            scratch_side = std::max(scratch_side, s.d_wgrad.tile >= 0 ? s.d_wgrad.ws_floats : s.p_wgrad.ws_floats);
             s.colsum_floats = colsum_ws_floats(n.dtype, M, s.outCp);
             if (si + 1 < n.stages.size() && n.stages[si + 1].kind == ST_POOL) {
                 const Stage &pl = n.stages[si + 1];
@@ -774,7 +775,14 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
             }
             {
                 ProfScope ps(n, sd, ASGD_K_CONV_WGRAD, conv_flops, (Mo * s.outC + Bd * s.inH * s.inW * s.inC) * es + (double)s.w_cnt * 4);
-                if (s.groups > 1) {
+                if (s.d_wgrad.tile >= 0) {
+                    const int Ogp = s.groups > 1 ? Og : s.outCp;
+                    Epilogue ew;   // the groups' filters follow each other: one matrix of groups * Og rows
+                    ew.out = grads + s.w_off; ew.mode = 1; ew.out_f32 = 1;
+                    ew.cw_cout = s.outC; ew.cw_cin = Cg; ew.cw_cinp = s.groups > 1 ? Cg : s.inCp; ew.cw_kh = s.k; ew.cw_kw = s.k;
+                    CHECK_LAUNCH(conv_wgrad(s.dout, s.outCp, Ogp, s.groups, conv_gather(s, xin, B, dt), ew, s.d_wgrad, n->scratch_side, sd),
+                                 "conv filter gradient");
+                } else if (s.groups > 1) {
                     for (int gi = 0; gi < s.groups; ++gi) {
                         const Gather g = conv_gather(s, xin, B, dt, gi);
                         Epilogue ew;

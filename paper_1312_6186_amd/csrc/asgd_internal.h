@@ -84,6 +84,18 @@ struct DirectPlan {
 DirectPlan plan_direct(int dtype, const Gather &a, int N);
 int conv_direct(int dtype, const Gather &a, const void *wpack, int N, const Epilogue &ep, const DirectPlan &plan, hipStream_t s);
 
+// Filter gradients of stride-1 convolutions over equal grids in 16-bit data (conv_wgrad.hip): tile shape (-1: does not run
+// this way), pixel ranges.  All groups of a layer run in one launch: dy [pixels][ldy]
+// with M channels per group one after the other, x the gather of the first group.
+struct WgradPlan {
+    int tile = -1, splits = 0;
+    size_t ws_floats = 0;    // fp32 scratch
+};
+WgradPlan plan_wgrad(int dtype, int M, int groups, const Gather &x);
+int conv_wgrad(const void *dy, long ldy, int M, int groups, const Gather &x, const Epilogue &ep, const WgradPlan &plan, float *ws, hipStream_t s);
+// C = ep(sum over splits of ws[split][M][N]), added in a fixed order
+int splitk_reduce(int dtype, const float *ws, int splits, const Epilogue &ep, int M, int N, hipStream_t s);
+
 // Every operand must fit in 1 GiB.
 // C[M][N] = A[M][K] * B[N][K]^T; A gathered (direct), B plain K-contiguous.
 GemmPlan plan_gemm(long M, long N, long K, int dtype, int max_splits);

@@ -1073,6 +1073,13 @@ template <typename T> static void launch_splitk_reduce(const float *ws, int spli
         hipLaunchKernelGGL((splitk_reduce_kernel<T>), dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, s, ws, splits, ep, M, N);
 }
 
+int splitk_reduce(int dtype, const float *ws, int splits, const Epilogue &ep, int M, int N, hipStream_t s)
+{
+    if (dtype == kBF16) launch_splitk_reduce<bf16_t>(ws, splits, ep, M, N, s);
+    else launch_splitk_reduce<float>(ws, splits, ep, M, N, s);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
 // ------------------------------------------------------------------ host side
 GemmPlan plan_gemm(long M, long N, long K, int dtype, int max_splits)
 {

@@ -275,6 +275,27 @@ def test_stride1_convolution_shapes(shape, dtype):
         g.close()
 
 
+# Filter gradients of such layers in bf16: output channels around the tiles of 128, 192 and 256, input channels around the
+# chunks of 32 and 64, two groups, images narrower and wider than a tile of 64 pixels, pixel counts below one tile and around
+# an odd and an even number of tiles, and the largest count of splits.
+WGRAD_SHAPES = [(64, 128, 3, 5, 7, 1, 1), (64, 128, 3, 8, 8, 2, 1), (56, 120, 3, 8, 8, 3, 1), (128, 192, 3, 13, 13, 5, 1), (136, 184, 3, 3, 70, 3, 1),
+                (64, 256, 3, 9, 3, 11, 1), (72, 248, 3, 5, 64, 2, 1), (32, 256, 5, 9, 9, 4, 1), (96, 200, 5, 11, 27, 3, 1), (64, 128, 5, 5, 5, 6, 1),
+                (96, 256, 5, 7, 65, 2, 2), (128, 256, 3, 13, 13, 9, 2), (64, 96, 3, 33, 31, 40, 1)]
+
+
+@pytest.mark.parametrize("shape", WGRAD_SHAPES, ids=lambda s: "%dto%d_k%d_%dx%dx%d_g%d" % s)
+def test_stride1_filter_gradient_shapes(shape):
+    cin, cout, k, h, w, batch, groups = shape
+    layers = [("conv", cin, 1, 1, 0), ("relu",), ("conv", cout, k, 1, k // 2) + ((groups,) if groups > 1 else ()), ("relu",), ("maxpool", 2, 2), ("fc", 10),
+              ("softmax_ce",)]
+    g, onet, (loss, grads), (ref_loss, ref_grads, _), _ = _net_case({"name": "wgrad", "in_shape": (3, h, w), "classes": 10, "layers": layers}, batch, B.BF16, plain=False)
+    try:
+        assert abs(loss - ref_loss) <= TOL[B.BF16] * abs(ref_loss)
+        compare_grads(onet, grads, ref_grads, TOL[B.BF16], "wgrad")
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
 @pytest.mark.parametrize("k,stride", [(2, 2), (3, 2), (3, 1)])
 def test_pooling_positions_are_bit_exact(k, stride, dtype):
