@@ -96,6 +96,7 @@ struct asgd_net {
     // layer: they run on an internal stream beside the caller's, forked and joined with events.
     hipStream_t side = nullptr;
     bool in_replay = false;   // replicas of a replay already run beside each other: no side stream then (measured slower)
+    bool fork_pays = false;   // the side stream is worth its events (plan_net)
     bool serial = false;      // every kernel on the caller's stream (asgd_net_set_serial, or ASGD_SERIAL=1 at creation)
     // Streams and events of the A-SGD replay, kept by the plan of worker 0 from one replay to the next (created on
     // first use, released with the plan), so that a replay only enqueues.
@@ -301,6 +302,14 @@ int plan_net(asgd_net &n)
     }
     if (n.classes == 0 || n.stages.empty() || !n.stages.back().last) return fail(ASGD_ESHAPE, "the layer list must end with FC, SOFTMAX_CE");
     n.param_count = off;
+    // What the side stream hides are the parameter side's partial sums and updates, which grow with the number of weights; what
+    // it costs is a pair of events per layer with parameters and a join, 35 to 60 us a step whatever the batch.  One step with /
+    // without it: 28 x 28 net (16 k parameters) fp32 8 images 129 / 81 us, 256 images 254 / 235; 32 x 32 net (0.1 M) bf16 93
+    // images 234 / 203, 512 images 311 / 303, fp32 512 images 997 / 952; the same with 2.5 M parameters in its first
+    // fully-connected layer 283 / 228.  AlexNet-style bf16 with 6.4 M parameters 32 images 589 / 600, 128 images 1155 / 1213; with
+    // its 62 M 16 images 713 / 754, 128 images 1403 / 1450.
+    n.fork_pays = n.param_count >= (size_t)4 << 20;
+
     // sizes, GEMM plans, scratch
     const long B = n.batch;
     size_t scratch = 0, scratch_side = 0;
@@ -599,7 +608,7 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
 {
     const int B = n->batch, dt = n->dtype;
     const double es = (double)dtype_size(dt), Bd = (double)B;
-    const bool fork = !n->prof_on && !n->in_replay && !n->serial;
+    const bool fork = n->fork_pays && !n->prof_on && !n->in_replay && !n->serial;
     hipStream_t sd = fork ? n->side : st;   // parameter gradients go here
     ColsumJobs bias_jobs; bias_jobs.n = 0;  // the loss, and second stage of the bias gradients: one launch at the end, or per layer when pushing by layer
     loss_job(n->row_loss, B, loss, bias_jobs);

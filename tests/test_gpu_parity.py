@@ -862,3 +862,21 @@ def test_serial_plan_gives_the_same_bits(dtype):
         finally:
             g.close()
     assert out[0][0] == out[1][0] and out[0][1].tobytes() == out[1][1].tobytes()
+
+
+def test_side_stream_gives_the_same_bits():
+    """The same for a net with enough weights that the parameter gradients run on the side stream."""
+    layers = [("conv", 96, 3, 1, 1), ("relu",), ("maxpool", 2, 2), ("fc", 1024), ("relu",), ("fc", 10), ("softmax_ce",)]
+    shape = (3, 16, 16)
+    params = wl.make_params(layers, shape, 3)
+    assert params.size > 4 << 20
+    images, labels = wl.make_batch(shape, 37, 10, 4)
+    out = []
+    for serial in (False, True):
+        g = GpuNet(layers, shape, 37, B.BF16)
+        try:
+            B.asgd_net_set_serial(g.net, serial)
+            out.append(g.fwd_bwd(params, images, labels, 11, 2, 1))
+        finally:
+            g.close()
+    assert out[0][0] == out[1][0] and out[0][1].tobytes() == out[1][1].tobytes()
