@@ -18,7 +18,8 @@
 //
 // us alone, before (128 x 128 tiles of the general engine, both operands in LDS, every window position gathered) -> after,
 // 128 images, 5 x 5 on 27 x 27: 96 -> 256 channels 127 -> 110, in two groups of 48 -> 128 82 -> 74; 3 x 3 on 13 x 13:
-// 256 -> 384 51 -> 46, 384 -> 384 71 -> 60, 384 -> 256 50 -> 53, in two groups 58 -> 38 (384) and 46 -> 32 (256).  Beside the
+// 256 -> 384 51 -> 46, 384 -> 384 71 -> 60, 384 -> 256 50 -> 46 (with 4 x 3 blocks and one
+// workgroup per CU 53), in two groups 58 -> 38 (384) and 46 -> 32 (256).  Beside the
 // data gradients on the other stream they also leave more of the LDS and L2 to those: a step with 128 images 1403 -> 1332.
 #include <hip/hip_runtime.h>
 
@@ -214,8 +215,8 @@ __global__ __launch_bounds__(256, MB * KW <= kWgShared ? 2 : 1) void conv_wgrad_
 
 namespace {
 struct WgTile { int mb, kw, wm, wn; };
-constexpr WgTile kWgTiles[] = {{4, 3, 2, 2}, {3, 3, 2, 2}, {2, 3, 2, 2}, {2, 5, 4, 1}, {2, 5, 2, 2}};
-constexpr int kWgTileCount = 5;
+constexpr WgTile kWgTiles[] = {{3, 3, 2, 2}, {2, 3, 2, 2}, {2, 5, 4, 1}, {2, 5, 2, 2}};
+constexpr int kWgTileCount = 4;
 }
 
 // M: output channels of a group; x: one group's input as a gather
@@ -268,10 +269,9 @@ int conv_wgrad(const void *dy, long ldy, int M, int groups, const Gather &x, con
     if (grid <= 0 || grid > 0x7fffffffL || (long)(plan.splits - 1) * p.per >= p.nkt) return -1;
     const dim3 g((unsigned)grid), b(256);
     switch (plan.tile) {
-    case 0: hipLaunchKernelGGL((conv_wgrad_kernel<4, 3, 2, 2>), g, b, 0, s, p); break;
-    case 1: hipLaunchKernelGGL((conv_wgrad_kernel<3, 3, 2, 2>), g, b, 0, s, p); break;
-    case 2: hipLaunchKernelGGL((conv_wgrad_kernel<2, 3, 2, 2>), g, b, 0, s, p); break;
-    case 3: hipLaunchKernelGGL((conv_wgrad_kernel<2, 5, 4, 1>), g, b, 0, s, p); break;
+    case 0: hipLaunchKernelGGL((conv_wgrad_kernel<3, 3, 2, 2>), g, b, 0, s, p); break;
+    case 1: hipLaunchKernelGGL((conv_wgrad_kernel<2, 3, 2, 2>), g, b, 0, s, p); break;
+    case 2: hipLaunchKernelGGL((conv_wgrad_kernel<2, 5, 4, 1>), g, b, 0, s, p); break;
     default: hipLaunchKernelGGL((conv_wgrad_kernel<2, 5, 2, 2>), g, b, 0, s, p); break;
     }
     return splitk_reduce(kBF16, ws, plan.splits, ep, groups * M, p.N, s);
