@@ -832,6 +832,20 @@ def test_out_of_range_label_gives_nan_loss_and_no_fault():
         g.close()
 
 
+# Bias gradients: bands of rows below and above four rows per lane (a layer without a pool), and of a layer under a pool from
+# fewer bands than the lanes of a workgroup to more than eight times as many.
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("c,h,w,batch", [(8, 5, 7, 1), (40, 9, 11, 3), (200, 13, 13, 7), (40, 31, 33, 40), (136, 41, 43, 60)])
+def test_bias_gradient_shapes(c, h, w, batch, dtype):
+    layers = [("conv", c, 1, 1, 0), ("relu",), ("maxpool", 3, 2), ("conv", c, 1, 1, 0), ("relu",), ("fc", 10), ("softmax_ce",)]
+    g, onet, (loss, grads), (ref_loss, ref_grads, _), _ = _net_case({"name": "bias", "in_shape": (3, h, w), "classes": 10, "layers": layers}, batch, dtype, plain=False)
+    try:
+        assert abs(loss - ref_loss) <= TOL[dtype] * abs(ref_loss)
+        compare_grads(onet, grads, ref_grads, TOL[dtype], "bias")
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
 @pytest.mark.parametrize("c,w", [(1, 12), (2, 12), (3, 12), (4, 12), (3, 14), (3, 15), (8, 12), (9, 7)])
 def test_image_staging_takes_any_width(c, w, dtype):
