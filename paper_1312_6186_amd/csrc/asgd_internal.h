@@ -74,11 +74,11 @@ struct GemmPlan {
 };
 
 // Stride-1 convolutions over equal grids (forward, and the data gradient as a convolution with flipped filters): K steps
-// of 16 channels per chunk (0: the convolution does not run this way), chunks, tile shape, and the size of the packed
-// filters.  Packed element (n, pos, c): blocks of 32 output columns, then chunks, window positions and K steps, each K
+// of 16 channels per chunk (0: the convolution does not run this way), chunks, tile shape, patch loads per thread and chunk,
+// and the size of the packed filters.  Packed element (n, pos, c): blocks of 32 output columns, then chunks, window positions and K steps, each K
 // step 64 lanes x 8 channels in the order the matrix cores take them (see direct_index).
 struct DirectPlan {
-    int ks = 0, nchunks = 0, tile = 0;
+    int ks = 0, nchunks = 0, tile = 0, npl = 0;
     size_t nblk_elems = 0, pack_elems = 0;
 };
 DirectPlan plan_direct(int dtype, const Gather &a, int N);

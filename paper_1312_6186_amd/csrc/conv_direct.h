@@ -9,8 +9,8 @@
 // LDS read at a shifted address; a lane whose window position lies outside the image reads zeros kept behind the patch, in
 // the same banks.  The filters never touch LDS: they are packed in the order in which the matrix cores take them (see
 // direct_index), a wave's fragment of a K step is one 1 KB load from L2, LOOK window positions ahead of its use.  The patch
-// of the next chunk arrives in the other half of LDS, one load per window position, so that a chunk (9 or 25 window
-// positions) has one barrier.
+// of the next chunk arrives in the other half of LDS, one load per window position (see direct_pieces), so that a chunk (9 or
+// 25 window positions) has one barrier.
 //
 // Why: with both operands in LDS (128 x 128 tiles, wave tiles of 64 x 64, a barrier per 64 channels of one window position)
 // LDS reads and writes took as long as the MFMAs.  Here a wave tile of 64 x 64 reads half as much from LDS and writes
@@ -41,6 +41,11 @@ struct DirectConv {
 
 // bytes of LDS behind the patches: zeros for window positions outside the image
 constexpr int kDirectZero = 512;
+
+// Loads per thread that the patch of the next chunk may take.  The load of window position j goes to LDS at position j + 1, that
+// of the last position in its last K step, ahead of the chunk's barrier.  With one K step per chunk that step has the store of
+// the position before ahead of the barrier and issues its own load behind it, so a load there would never arrive.
+constexpr int direct_pieces(int ks, int npos) { return ks == 1 ? npos - 1 : npos; }
 
 template <typename T, int KS> struct DirectGeo {
     static constexpr int PIECES = KS * 16 * (int)sizeof(T) / 16;       // 16-byte pieces of a pixel's chunk
@@ -214,7 +219,8 @@ __global__ __launch_bounds__(64 * WM * WN, (MB * NB > 8 ? 1 : 2)) void conv_dire
             }
             if constexpr (ks == 0) {
                 if constexpr (KS > 1) static_for<0, MB>([&](auto mb) ASGD_INLINE { na[mb] = addr(mb); });
-                // the patch of the next chunk: what the step before asked for goes to LDS, the next loads are issued
+                // the patch of the next chunk: what the step before asked for goes to LDS, the next loads are issued (KS = 1:
+                // that of the last position belongs to no patch, see direct_pieces)
                 if constexpr (!(LAST && KS == 1)) lds_st16(pdst, pr);
                 pr = buf_ld16(xrs, patch_off(gp, pvo, cok));
                 pdst = (pok & (pj < p.npl)) ? pso : dump;

@@ -25,8 +25,7 @@ Fit fit(int es, int ks, int nchunks, const Tile &t, const Gather &a)
     f.npl = (pixels + ppl - 1) / ppl;
     const long patch = ((long)f.npl * ppl * pitch + 255) / 256 * 256;
     const long lds = std::max(patch * (nchunks > 1 ? 2 : 1) + kDirectZero + nt * 16, (long)t.wm * t.wn * t.nb * 4096 + 32L * t.nb * t.wn * 4);
-    // the patch of the next chunk arrives with one load per window position
-    f.ok = lds <= 163840 && (nchunks == 1 || f.npl <= a.kh * a.kw);
+    f.ok = lds <= 163840 && (nchunks == 1 || f.npl <= direct_pieces(ks, a.kh * a.kw));
     f.patch_bytes = (unsigned)patch; f.lds = (unsigned)lds;
     return f;
 }
@@ -70,6 +69,7 @@ DirectPlan plan_direct(int dtype, const Gather &a, int N)
     }
     if (tile < 0) { d.ks = 0; return d; }
     d.tile = tile;
+    d.npl = fit(es, d.ks, d.nchunks, kTiles[tile], a).npl;
     d.nblk_elems = (size_t)d.nchunks * npos * d.ks * 512;
     d.pack_elems = (size_t)((N + 31) / 32) * d.nblk_elems;
     if (d.pack_elems * es > kMaxOperandBytes) { d.ks = 0; return d; }

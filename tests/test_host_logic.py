@@ -157,3 +157,52 @@ def test_replay_rejects_impossible_schedules_without_a_gpu():
     assert run([0, 5], [0, 0]) == B.EINVAL            # no such worker
     for n in nets:
         B.asgd_net_destroy(n)
+
+
+# ---- planning of the stride-1 convolution kernel (internal functions, by their mangled names)
+class _Gather(ctypes.Structure):
+    _fields_ = ([("x", ctypes.c_void_p)] + [(n, ctypes.c_int) for n in ("N", "H", "W", "C", "Ho", "Wo", "kh", "kw", "sm", "ds", "pad")]
+                + [(n, ctypes.c_size_t) for n in ("bytes", "rowb", "pix")])
+
+
+class _DirectPlan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("ks", "nchunks", "tile", "npl")] + [(n, ctypes.c_size_t) for n in ("nblk_elems", "pack_elems")]
+
+
+def _plan_direct(dtype, batch, h, w, cin, cout, k):
+    es = 2 if dtype == B.BF16 else 4
+    f = B.lib()["_ZN4asgd11plan_directEiRKNS_6GatherEi"]
+    f.argtypes, f.restype = [ctypes.c_int, ctypes.POINTER(_Gather), ctypes.c_int], _DirectPlan
+    return f(dtype, ctypes.byref(_Gather(None, batch, h, w, cin, h, w, k, k, 1, 1, k // 2, batch * h * w * cin * es, 0, 0)), cout)
+
+
+def _pieces_stored(ks, npos):
+    """The loads of the next chunk's patch that are in LDS at the barrier that ends a chunk, in the order in which
+    conv_direct_kernel loads and stores them: load j is issued in the first K step of window position j."""
+    stored, on_its_way = set(), None
+    for pos in range(npos):
+        for step in range(ks):
+            if pos == npos - 1 and step == ks - 1:
+                return stored | {on_its_way}          # the last K step stores what has been loaded, then the barrier
+            if step == 0:
+                stored, on_its_way = stored | {on_its_way}, pos
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+def test_stride1_convolution_plans_copy_every_piece_of_a_patch(dtype):
+    wide = chunked = 0
+    for k in (3, 5):
+        for cin in list(range(8, 200, 8)) + [256, 384, 400, 512]:
+            for cout in (8, 48, 64, 96, 128, 256):
+                for w in list(range(5, 64, 9)) + list(range(64, 560, 5)) + [111, 112, 191, 192, 223, 224, 225, 240, 255, 256, 447, 448, 479, 480, 511, 512]:
+                    for h, batch in ((3, 1), (w, 4)):
+                        p = _plan_direct(dtype, batch, h, w, cin, cout, k)
+                        if p.ks == 0:
+                            continue
+                        assert p.nchunks == -(-cin // (16 * p.ks)) and p.npl > 0
+                        if p.nchunks > 1:
+                            chunked += 1
+                            missing = set(range(p.npl)) - _pieces_stored(p.ks, k * k)
+                            assert not missing, (dtype, k, cin, cout, h, w, p.ks, p.npl, missing)
+                            wide += p.npl >= k * k - 1
+    assert chunked > 1000 and wide > 10   # the sweep reaches plans at the limit
