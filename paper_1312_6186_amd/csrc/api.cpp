@@ -170,6 +170,14 @@ size_t carve(asgd_net &n, char *base)
 Gather conv_gather(const Stage &s, const void *x, int B, int dt, int group = 0);
 Gather dgrad_gather(const Stage &s, const void *dy, int B, int dt, int group);
 
+// Bytes of the static workspace of asgd_fwd_bwd_static.
+constexpr size_t kStaticWsBytes = (size_t)64 << 20;
+
+// Chooses the kernels of every stage and sizes the workspace.  partials: floats that the partial sums of a filter gradient may
+// take in conv_wgrad; lean: none of the kernels whose filters are padded to their chunks (conv_direct) or whose partial sums
+// are not the general engine's (conv_wgrad).
+int size_net(asgd_net &n, size_t partials, bool lean);
+
 int plan_net(asgd_net &n)
 {
     const int L = (int)n.layers.size();
@@ -310,7 +318,23 @@ int plan_net(asgd_net &n)
     // its 62 M 16 images 713 / 754, 128 images 1403 / 1450.
     n.fork_pays = n.param_count >= (size_t)4 << 20;
 
-    // sizes, GEMM plans, scratch
+    int rc = size_net(n, SIZE_MAX, false);
+    if (rc != ASGD_OK || n.ws_bytes <= kStaticWsBytes) return rc;
+    // Beyond the static workspace with the kernels chosen for speed: a plan that fits it with fewer partial sums, or else without
+    // the padded filters, is made to (what asgd_fwd_bwd_static accepts does not depend on how the fast kernels are split).
+    const std::vector<Stage> fast = n.stages;
+    const size_t bytes = n.ws_bytes, scratch = n.scratch_floats, scratch_side = n.scratch_side_floats, rest = bytes - scratch_side * 4;
+    if (rest + 512 < kStaticWsBytes) rc = size_net(n, (kStaticWsBytes - rest - 512) / 4, false);
+    if (rc == ASGD_OK && n.ws_bytes > kStaticWsBytes) rc = size_net(n, 0, true);
+    if (rc == ASGD_OK && n.ws_bytes > kStaticWsBytes) {
+        n.stages = fast;
+        n.ws_bytes = bytes; n.scratch_floats = scratch; n.scratch_side_floats = scratch_side;
+    }
+    return rc;
+}
+
+int size_net(asgd_net &n, size_t partials, bool lean)
+{
     const long B = n.batch;
     size_t scratch = 0, scratch_side = 0;
     for (size_t si = 0; si < n.stages.size(); ++si) {
@@ -333,11 +357,11 @@ int plan_net(asgd_net &n)
                 if (s.rw) s.p_wgrad.ws_floats = std::max(s.p_wgrad.ws_floats, rows_wgrad_ws_floats(n.dtype, s.outCp, conv_gather(s, nullptr, (int)B, n.dtype)));
             }
             const int Ng = s.groups > 1 ? s.outC / s.groups : s.outCp, Cg = s.groups > 1 ? s.inC / s.groups : s.inCp;
-            s.d_wgrad = plan_wgrad(n.dtype, Ng, s.groups, conv_gather(s, nullptr, (int)B, n.dtype));
-            s.d_fwd = plan_direct(n.dtype, conv_gather(s, nullptr, (int)B, n.dtype), Ng);
+            s.d_wgrad = lean ? WgradPlan() : plan_wgrad(n.dtype, Ng, s.groups, conv_gather(s, nullptr, (int)B, n.dtype), partials);
+            s.d_fwd = lean ? DirectPlan() : plan_direct(n.dtype, conv_gather(s, nullptr, (int)B, n.dtype), Ng);
             s.wf_elems = s.d_fwd.ks ? s.d_fwd.pack_elems : (size_t)Ng * s.k * (s.rw ? s.rwKW : s.k * Cg);
             if (si > 0) {
-                s.d_dgrad = plan_direct(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg);
+                s.d_dgrad = lean ? DirectPlan() : plan_direct(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg);
                 s.wd_elems = s.d_dgrad.ks ? s.d_dgrad.pack_elems : (size_t)Cg * s.k * s.k * Ng;
             }
             scratch_side = std::max(scratch_side, s.d_wgrad.tile >= 0 ? s.d_wgrad.ws_floats : s.p_wgrad.ws_floats);
@@ -970,7 +994,6 @@ int asgd_fwd_bwd(asgd_net_t *net, const void *params, const void *images, const 
 // Workspace for callers that cannot allocate: one array per GPU, held from the moment the library's code is loaded
 // on that GPU until the process ends.  Host code never uses the array's name as an address (on the host it is
 // only a handle for the runtime): the device address is asked for once per device and kept.
-constexpr size_t kStaticWsBytes = (size_t)64 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticWsBytes];
 
 namespace {

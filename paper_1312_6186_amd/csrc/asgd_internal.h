@@ -91,7 +91,7 @@ struct WgradPlan {
     int tile = -1, splits = 0;
     size_t ws_floats = 0;    // fp32 scratch
 };
-WgradPlan plan_wgrad(int dtype, int M, int groups, const Gather &x);
+WgradPlan plan_wgrad(int dtype, int M, int groups, const Gather &x, size_t max_ws_floats);
 int conv_wgrad(const void *dy, long ldy, int M, int groups, const Gather &x, const Epilogue &ep, const WgradPlan &plan, float *ws, hipStream_t s);
 // C = ep(sum over splits of ws[split][M][N]), added in a fixed order
 int splitk_reduce(int dtype, const float *ws, int splits, const Epilogue &ep, int M, int N, hipStream_t s);

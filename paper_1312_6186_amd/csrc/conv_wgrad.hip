@@ -23,6 +23,8 @@
 // data gradients on the other stream they also leave more of the LDS and L2 to those: a step with 128 images 1403 -> 1332.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "asgd_internal.h"
 #include "mfma_common.h"
 
@@ -219,8 +221,28 @@ constexpr WgTile kWgTiles[] = {{3, 3, 2, 2}, {2, 3, 2, 2}, {2, 5, 4, 1}, {2, 5, 
 constexpr int kWgTileCount = 4;
 }
 
+// us that the workgroups of a launch keep the chip busy: one takes t1 us where it has a CU to itself; where two share a CU
+// both take t2 (0: they never do)
+static double rounds_us(long workgroups, double t1, double t2)
+{
+    const long round = t2 > 0 ? 512 : 256, full = workgroups / round, rest = workgroups - full * round;
+    const double whole = t2 > 0 ? t2 : t1;
+    return full * whole + (rest > 256 ? whole : rest > 0 ? t1 : 0.0);
+}
+// Partial sums are written and read again at the rate of a copy.
+constexpr double kPartialUs = 0.37e-6 * 4;   // us per float
+
 // M: output channels of a group; x: one group's input as a gather
-WgradPlan plan_wgrad(int dtype, int M, int groups, const Gather &x)
+//
+// The tile shape and the number of pixel ranges (splits) with the smallest modelled time: the MFMA blocks of the busiest CU plus
+// the partial sums.  Few pixels want few splits, and a small result many: with the chip filled whatever that cost, 256 -> 384
+// channels on 13 x 13 at 4 images took 33 us in 11 splits (39 MB of partial sums; 17 in 2 splits of the narrower tile), 64 -> 128
+// on 56 x 56 at 16 images 34 us in 157 (27 in 66), 64 -> 128 on 13 x 13 at 32 images 26 in 85.  The general engine (128 x 128
+// tiles, both operands gathered for every window position) keeps the layers for which its modelled time is the smaller one (15,
+// 29 and 15 us of these three), and those whose channels would be more than two fifths padding here: it skips waves that hold
+// nothing but padding.  The times of a block and of a K tile are fits over 3 x 3 and 5 x 5 layers of 32 to 512 channels on 7 to
+// 224 pixels square, 1 to 256 images (90 % of the times within 10 %, the general engine's within 20 %).
+WgradPlan plan_wgrad(int dtype, int M, int groups, const Gather &x, size_t max_ws_floats)
 {
     WgradPlan best;
     const size_t pixb = x.pix ? x.pix : (size_t)x.C * 2;
@@ -228,24 +250,34 @@ WgradPlan plan_wgrad(int dtype, int M, int groups, const Gather &x)
         (x.rowb != 0 && x.rowb != (size_t)x.W * pixb) || pixb % 16 != 0 || x.C % 8 != 0 || M % 8 != 0)
         return best;
     const long npix = (long)x.N * x.H * x.W, nkt = (npix + kWgKT - 1) / kWgKT;
-    double best_cost = 0;
+    const double result = (double)groups * M * x.kh * x.kw * x.C;
+    double best_us = 0;
     for (int v = 0; v < kWgTileCount; ++v) {
         const WgTile &t = kWgTiles[v];
         if (t.kw != x.kw) continue;
-        const int percu = t.mb * t.kw <= kWgShared ? 2 : 1;      // workgroups of this shape that share a CU
+        const int blocks = t.mb * t.kw;
+        const bool shared = blocks <= kWgShared;                 // two workgroups of this shape fit a CU
         const long tiles = (long)groups * ((M + 32 * t.mb * t.wm - 1) / (32 * t.mb * t.wm)) * ((x.C + 32 * t.wn - 1) / (32 * t.wn)) * x.kh;
-        long splits = tiles < 256 * percu ? 256 * percu / tiles : 1;
-        if (splits > nkt) splits = nkt;
-        const long per = (nkt + splits - 1) / splits;
-        splits = (nkt + per - 1) / per;
-        // MFMA blocks of the busiest CU; a workgroup spends about as long as eight tiles outside its loop
-        const double cost = (double)((tiles * splits + 256 * percu - 1) / (256 * percu)) * percu * (per + 8.0) * t.mb * t.kw;
-        // more than two fifths of the multiplications on padding: the general engine skips those waves
         const double useful = (double)groups * M * x.C * x.kh / ((double)tiles * (32.0 * t.mb * t.wm) * (32.0 * t.wn));
         if (useful < 0.6) continue;
-        if (best.tile < 0 || cost < best_cost) { best.tile = v; best.splits = (int)splits; best_cost = cost; }
+        const long most = std::max(1L, std::min(nkt, (shared ? 512 : 256) / tiles));
+        for (long splits = 1, per = nkt; splits <= most && splits * result <= (double)max_ws_floats;) {
+            const double us = rounds_us(tiles * splits, (shared ? 0.11 : 0.085) * blocks * per, shared ? 0.18 * blocks * per : 0) + kPartialUs * splits * result;
+            if (best.tile < 0 || us < best_us) { best.tile = v; best.splits = (int)splits; best_us = us; }
+            if (per == 1) break;
+            splits = (nkt + per - 2) / (per - 1);                // the fewest with fewer tiles each, none of them empty
+            per = (nkt + splits - 1) / splits;
+        }
     }
-    if (best.tile >= 0) best.ws_floats = (size_t)best.splits * groups * M * x.kh * x.kw * x.C;
+    if (best.tile < 0) return best;
+    const long N = (long)x.kh * x.kw * x.C;
+    const GemmPlan g = plan_gemm(M, N, npix, dtype, 128);        // what the general engine would run, once per group
+    const long per = (nkt + g.splits - 1) / g.splits;
+    const double general = groups * (rounds_us(((M + 127) / 128) * ((N + 127) / 128) * g.splits, 0.34 * per, 0.87 * per) + kPartialUs * g.ws_floats);
+    // a launch more per group there, one for the partial sums here; results that are stored where they belong from a whole sum
+    // are scattered there
+    if (general + 9.0 * (groups - 1) + (g.splits == 1 ? 1.0 : -1.0) < best_us) return WgradPlan();
+    best.ws_floats = (size_t)best.splits * groups * M * N;
     return best;
 }
 

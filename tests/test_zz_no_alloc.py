@@ -22,6 +22,32 @@ def test_oversized_plan_is_refused_without_touching_the_gpu():
         B.asgd_net_destroy(net)
 
 
+# Nets that fit the static workspace by the general engine's own needs
+def _conv(cout, k, groups=1):
+    return [("conv", cout, k, 1, k // 2) + ((groups,) if groups > 1 else ()), ("relu",)]
+
+
+STATIC_NETS = {
+    "alexnet": (wl.ALEXNET["layers"], (3, 224, 224), 4, B.BF16),
+    "alexnet5": (wl.ALEXNET["layers"], (3, 224, 224), 5, B.BF16),
+    "alexnet_lrn": (wl.ALEXNET_LRN["layers"], (3, 224, 224), 4, B.BF16),
+    "grouped": (_conv(200, 1) + _conv(448, 1) + _conv(192, 5, 2) + [("maxpool", 2, 2), ("fc", 160), ("softmax_ce",)], (1, 45, 55), 4, B.BF16),
+    "partials": (_conv(360, 3) + _conv(504, 5) + [("maxpool", 2, 2)] + _conv(320, 3) + [("fc", 40), ("softmax_ce",)], (3, 30, 31), 2, B.BF16),
+    "padded_f32": (_conv(80, 1) + _conv(360, 3) + [("maxpool", 2, 2), ("fc", 8), ("softmax_ce",)], (3, 15, 12), 39, B.F32),
+    "padded_bf16": (_conv(40, 5) + _conv(480, 3) + [("maxpool", 2, 2), ("fc", 8), ("softmax_ce",)], (8, 11, 25), 45, B.BF16),
+}
+
+
+@pytest.mark.parametrize("name", list(STATIC_NETS))
+def test_static_workspace_holds_what_fits_it_without_the_fast_convolutions(name):
+    layers, shape, batch, dtype = STATIC_NETS[name]
+    net = B.asgd_net_create(layers, batch, shape, dtype)
+    try:
+        assert B.asgd_workspace_bytes(net) <= B.asgd_static_workspace_bytes()
+    finally:
+        B.asgd_net_destroy(net)
+
+
 def _case(cfg, batch, dtype, seed):
     layers, in_shape = cfg["layers"], cfg["in_shape"]
     tdt = torch.bfloat16 if dtype == B.BF16 else torch.float32
@@ -68,3 +94,27 @@ def test_static_entry_point_matches_fwd_bwd_on_two_calls_in_a_row():
         torch.cuda.synchronize()
         for net in stat_nets:
             B.asgd_net_destroy(net)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", ["alexnet", "grouped", "padded_f32", "padded_bf16"])
+def test_static_entry_point_takes_plans_near_the_size_of_its_workspace(name):
+    """Plans that fit with fewer partial sums, or with the general engine's kernels only: two calls in a row, bit for bit."""
+    layers, in_shape, batch, dtype = STATIC_NETS[name]
+    classes = [l for l in layers if l[0] == "fc"][-1][1]
+    _, _, copy, images, labels = _case({"layers": layers, "in_shape": in_shape, "classes": classes}, batch, dtype, 21)
+    net = B.asgd_net_create(layers, batch, in_shape, dtype)
+    try:
+        n = B.asgd_param_count(net)
+        outs = []
+        for call in (B.asgd_fwd_bwd_static, B.asgd_fwd_bwd_static, B.asgd_fwd_bwd):
+            loss, grads = torch.full((1,), float("nan"), device=DEV), torch.full((n,), float("nan"), device=DEV)
+            call(net, copy, images, labels, 77, 5, 2, loss, grads)
+            outs.append((loss, grads))
+        torch.cuda.synchronize()
+        assert torch.isfinite(outs[2][1]).all()
+        for loss, grads in outs[:2]:
+            assert torch.equal(loss, outs[2][0]) and torch.equal(grads, outs[2][1])
+    finally:
+        torch.cuda.synchronize()
+        B.asgd_net_destroy(net)
