@@ -73,6 +73,13 @@ struct GemmPlan {
     size_t ws_floats = 0;    // fp32 scratch needed when splits > 1
 };
 
+// us that the workgroups of a launch keep the 256 CUs busy, where per_cu of them fit a CU and r on one CU take t(r) us.
+template <class F> double rounds_us(long workgroups, int per_cu, F t)
+{
+    const long round = 256L * per_cu, rest = workgroups % round;
+    return (double)(workgroups / round) * t(per_cu) + (rest ? t((int)((rest + 255) / 256)) : 0.0);
+}
+
 // Stride-1 convolutions over equal grids (forward, and the data gradient as a convolution with flipped filters): K steps
 // of 16 channels per chunk (0: the convolution does not run this way), chunks, tile shape, patch loads per thread and chunk,
 // and the size of the packed filters.  Packed element (n, pos, c): blocks of 32 output columns, then chunks, window positions and K steps, each K

@@ -30,6 +30,41 @@ Fit fit(int es, int ks, int nchunks, const Tile &t, const Gather &a)
     return f;
 }
 
+// Times in us, fits over 3 x 3 and 5 x 5 layers of 8 to 384 channels on 3 to 480 pixels square, 1500 to 400000 pixels (fp32: 90 %
+// of the times within 15 %; bf16: 80 % within 25 %; the general engine within 10 and 15 %).
+struct DirectRates {
+    double launch, load, store;   // the launch; a patch load per thread ahead of the loop; the epilogue of an MFMA block
+    double mma, filters;          // a K step: per MFMA block of a wave, and per block of columns what its filters take from L1 at least
+    double large;                 // what a block takes in a wave tile of eight and more, which reads less per MFMA
+    double pos1, pos3;            // a window position at least, with the filters one and three positions ahead
+    double apart, single;         // what several workgroups on a CU do not hide of one's time; slowdown of chunks of one K step
+};
+constexpr DirectRates kRatesF32 = {4.7, 0.16, 0.5, 0.215, 0, 1, 0, 0, 0.06, 1.2}, kRatesBf16 = {3.3, 0, 1.0, 0.0113, 0.0195, 0.85, 0.155, 0.083, 0.6, 1.8};
+constexpr double kPatchUs = 35e-6;   // a byte of patch: 28 GB/s for each CU while all of them fetch
+
+double direct_us(int es, int ks, int nchunks, const Tile &t, const Gather &a, int N)
+{
+    const DirectRates &q = es == 2 ? kRatesBf16 : kRatesF32;
+    const Fit f = fit(es, ks, nchunks, t, a);
+    const int npos = a.kh * a.kw, blocks = t.mb * t.nb, registers = blocks > 8 ? 1 : blocks >= 3 ? 2 : 4;   // workgroups of four waves per CU
+    const int per_cu = std::max(1, std::min((int)(163840 / f.lds), registers));
+    const double position = ks * t.nb * std::max(q.mma * t.mb * (blocks >= 8 ? q.large : 1.0), q.filters) * (ks == 1 ? q.single : 1.0);
+    const double least = es == 2 && blocks <= 4 && ks >= 2 && npos % 3 == 0 ? q.pos3 : q.pos1;
+    const double alone = (double)nchunks * npos * std::max(position, least) + q.load * f.npl + q.store * blocks;
+    const long M = (long)a.N * a.H * a.W, tiles = ((M + 32 * t.mb * t.wm - 1) / (32 * t.mb * t.wm)) * ((N + 32 * t.nb * t.wn - 1) / (32 * t.nb * t.wn));
+    return q.launch + rounds_us(tiles, per_cu, [&](int r) {
+        return std::max(alone, r * nchunks * (npos * position + kPatchUs * f.patch_bytes) + q.apart * alone);
+    });
+}
+// The general engine: tiles of 128 x 128 (half empty for up to 64 columns), K tiles of 128 bytes.
+double engine_us(int es, const Gather &a, int N)
+{
+    const long M = (long)a.N * a.H * a.W, tiles = ((M + 127) / 128) * ((N + 127) / 128), kt = ((long)a.kh * a.kw * a.C * es + 127) / 128;
+    const double half = N > 64 ? 1.0 : es == 2 ? 0.73 : 0.55;
+    return es == 2 ? 1.9 + rounds_us(tiles, 2, [&](int r) { return 4.5 + half * kt * (r == 1 ? 0.54 : 0.94); })
+                   : 1.2 + rounds_us(tiles, 2, [&](int r) { return 5.2 + half * kt * (r == 1 ? 2.06 : 3.98); });
+}
+
 }  // namespace
 
 DirectPlan plan_direct(int dtype, const Gather &a, int N)
@@ -50,9 +85,13 @@ DirectPlan plan_direct(int dtype, const Gather &a, int N)
         if (d.ks == 0 || steps < best_steps) { d.ks = ks; best_steps = steps; }
     }
     d.nchunks = (a.C + 16 * d.ks - 1) / (16 * d.ks);
+    // In bf16 chunks of one K step are too short to hide a chunk's barrier and its filters: with several of them the general engine
+    // is the faster one (80 -> 192 channels 5 x 5 on 8 x 8, 2591 images 187 us there, 280 here; over 176 such layers the best tile
+    // shape took 0.7 to 2.2 times the engine's time, 1.1 on average).
+    if (es == 2 && d.ks == 1 && d.nchunks > 1) return DirectPlan();
     const long M = (long)a.N * a.H * a.W;
-    double best = 0;
-    int tile = -1;
+    double best_cost = 0, cost_us = 0, best_us = 0;
+    int by_cost = -1, by_time = -1;
     for (int v = 0; v < kDirectTiles; ++v) {
         const Tile &t = kTiles[v];
         if (!direct_has(es, v, d.ks) || !fit(es, d.ks, d.nchunks, t, a).ok) continue;
@@ -64,15 +103,23 @@ DirectPlan plan_direct(int dtype, const Gather &a, int N)
         const double eff_bf16 = t.mb * t.nb >= 6 ? 0.61 : t.mb * t.nb >= 4 ? 0.57 : t.mb * t.nb == 3 ? 0.45 : t.mb == 2 ? 0.47 : t.nb == 2 ? 0.37 : 0.3;
         const double eff = es == 2 ? eff_bf16 : 0.8;
         const long tiles = ((M + 32 * t.mb * t.wm - 1) / (32 * t.mb * t.wm)) * ((N + 32 * t.nb * t.wn - 1) / (32 * t.nb * t.wn));
-        const double cost = (double)((tiles + 255) / 256) * (t.mb * t.nb) * (t.wm * t.wn / 4.0) / eff;
-        if (tile < 0 || cost < best) { tile = v; best = cost; }
+        const double cost = (double)((tiles + 255) / 256) * (t.mb * t.nb) * (t.wm * t.wn / 4.0) / eff, us = direct_us(es, d.ks, d.nchunks, t, a, N);
+        if (by_cost < 0 || cost < best_cost) { by_cost = v; best_cost = cost; cost_us = us; }
+        if (by_time < 0 || us < best_us) { by_time = v; best_us = us; }
     }
-    if (tile < 0) { d.ks = 0; return d; }
+    // That shape is measured inside steps, but knows neither the patch nor how many workgroups share a CU: where another one's
+    // modelled time is a tenth shorter, that one (192 -> 96 channels 3 x 3 on 32 x 32, 272 images: 144 us in 192 x 128, one
+    // workgroup to a CU, 117 in 128 x 128, two).  And the general engine keeps the layers for which its modelled time is the shortest:
+    // a patch has kh - 1 more image rows than its tile, so on wide images it is many times as large, costs the workgroups that
+    // would share the CU and is late (us, engine / here: fp32 48 -> 32 channels 3 x 3 on 128 x 192, 5 images 69 / 165; bf16
+    // 96 -> 16 on 32 x 255, 26 images 47 / 110, 64 -> 128 on 64 x 480, 6 images 44 / 102).
+    const int tile = cost_us > 1.1 * best_us ? by_time : by_cost;
+    if (tile < 0 || engine_us(es, a, N) < (tile == by_time ? best_us : cost_us)) return DirectPlan();
     d.tile = tile;
     d.npl = fit(es, d.ks, d.nchunks, kTiles[tile], a).npl;
     d.nblk_elems = (size_t)d.nchunks * npos * d.ks * 512;
     d.pack_elems = (size_t)((N + 31) / 32) * d.nblk_elems;
-    if (d.pack_elems * es > kMaxOperandBytes) { d.ks = 0; return d; }
+    if (d.pack_elems * es > kMaxOperandBytes) return DirectPlan();
     return d;
 }
 

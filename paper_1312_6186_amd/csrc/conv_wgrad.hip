@@ -221,14 +221,6 @@ constexpr WgTile kWgTiles[] = {{3, 3, 2, 2}, {2, 3, 2, 2}, {2, 5, 4, 1}, {2, 5, 
 constexpr int kWgTileCount = 4;
 }
 
-// us that the workgroups of a launch keep the chip busy: one takes t1 us where it has a CU to itself; where two share a CU
-// both take t2 (0: they never do)
-static double rounds_us(long workgroups, double t1, double t2)
-{
-    const long round = t2 > 0 ? 512 : 256, full = workgroups / round, rest = workgroups - full * round;
-    const double whole = t2 > 0 ? t2 : t1;
-    return full * whole + (rest > 256 ? whole : rest > 0 ? t1 : 0.0);
-}
 // Partial sums are written and read again at the rate of a copy.
 constexpr double kPartialUs = 0.37e-6 * 4;   // us per float
 
@@ -262,7 +254,7 @@ WgradPlan plan_wgrad(int dtype, int M, int groups, const Gather &x, size_t max_w
         if (useful < 0.6) continue;
         const long most = std::max(1L, std::min(nkt, (shared ? 512 : 256) / tiles));
         for (long splits = 1, per = nkt; splits <= most && splits * result <= (double)max_ws_floats;) {
-            const double us = rounds_us(tiles * splits, (shared ? 0.11 : 0.085) * blocks * per, shared ? 0.18 * blocks * per : 0) + kPartialUs * splits * result;
+            const double us = rounds_us(tiles * splits, shared ? 2 : 1, [&](int r) { return (!shared ? 0.085 : r == 1 ? 0.11 : 0.18) * blocks * per; }) + kPartialUs * splits * result;
             if (best.tile < 0 || us < best_us) { best.tile = v; best.splits = (int)splits; best_us = us; }
             if (per == 1) break;
             splits = (nkt + per - 2) / (per - 1);                // the fewest with fewer tiles each, none of them empty
@@ -273,7 +265,7 @@ WgradPlan plan_wgrad(int dtype, int M, int groups, const Gather &x, size_t max_w
     const long N = (long)x.kh * x.kw * x.C;
     const GemmPlan g = plan_gemm(M, N, npix, dtype, 128);        // what the general engine would run, once per group
     const long per = (nkt + g.splits - 1) / g.splits;
-    const double general = groups * (rounds_us(((M + 127) / 128) * ((N + 127) / 128) * g.splits, 0.34 * per, 0.87 * per) + kPartialUs * g.ws_floats);
+    const double general = groups * (rounds_us(((M + 127) / 128) * ((N + 127) / 128) * g.splits, 2, [&](int r) { return (r == 1 ? 0.34 : 0.87) * per; }) + kPartialUs * g.ws_floats);
     // a launch more per group there, one for the partial sums here; results that are stored where they belong from a whole sum
     // are scattered there
     if (general + 9.0 * (groups - 1) + (g.splits == 1 ? 1.0 : -1.0) < best_us) return WgradPlan();

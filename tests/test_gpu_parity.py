@@ -258,12 +258,13 @@ def test_minibatch_gradient_matches_oracle(cfg, batch, dtype):
 # Stride-1 convolutions over equal grids: channel counts around the chunks (a chunk is 16, 32, 48 or 64 channels), output
 # counts around the blocks of 32 columns, and enough pixels for every tile shape to be the cheapest one somewhere; then wide
 # images whose patch takes as many loads as there are window positions to bring it (chunks of 16 channels: one less), and one
-# pixel more.
+# pixel more (most of these wide ones run in the general engine, which is faster there).
 DIRECT_SHAPES = [(8, 8, 3, 5, 7, 3), (16, 40, 5, 6, 9, 2), (48, 136, 3, 8, 8, 4), (72, 200, 3, 6, 5, 9), (120, 96, 3, 9, 9, 4), (136, 24, 5, 7, 11, 3),
                  (24, 128, 3, 33, 31, 64), (24, 128, 3, 31, 31, 50), (24, 96, 3, 31, 31, 80), (24, 96, 3, 31, 31, 53), (24, 192, 3, 31, 31, 26),
                  (24, 192, 3, 31, 31, 40), (32, 96, 5, 13, 13, 64),
                  (48, 64, 3, 3, 223, 1), (48, 48, 3, 4, 224, 1), (80, 64, 3, 2, 479, 1), (80, 64, 3, 2, 480, 1), (128, 64, 3, 3, 111, 1), (128, 64, 3, 3, 112, 1),
-                 (96, 64, 3, 2, 255, 1), (144, 64, 3, 2, 111, 1)]
+                 (96, 64, 3, 2, 255, 1), (144, 64, 3, 2, 111, 1), (40, 72, 3, 2, 194, 1), (16, 104, 3, 46, 46, 12), (24, 72, 3, 65, 65, 13), (24, 72, 3, 7, 7, 449),
+                 (96, 8, 5, 182, 182, 1), (24, 72, 3, 257, 257, 1), (32, 136, 3, 163, 163, 1), (24, 136, 3, 199, 199, 1)]
 
 
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])

@@ -206,3 +206,21 @@ def test_stride1_convolution_plans_copy_every_piece_of_a_patch(dtype):
                             assert not missing, (dtype, k, cin, cout, h, w, p.ks, p.npl, missing)
                             wide += p.npl >= k * k - 1
     assert chunked > 1000 and wide > 10   # the sweep reaches plans at the limit
+
+
+# Layers (channels in, out, window, height, width, images) with the us of the general engine and of the stride-1 kernel in its best
+# tile shape: those that the engine runs faster belong to it, the others do not
+ENGINE_FASTER = [(B.F32, (48, 32, 3, 128, 192, 5), 69, 165), (B.F32, (80, 24, 3, 16, 192, 8), 32, 64), (B.F32, (192, 32, 3, 64, 80, 66), 647, 1070),
+                 (B.F32, (48, 384, 5, 32, 128, 19), 622, 652), (B.BF16, (96, 16, 3, 32, 255, 26), 47, 110), (B.BF16, (64, 128, 3, 64, 480, 6), 44, 102),
+                 (B.BF16, (256, 24, 5, 16, 112, 36), 64, 137), (B.BF16, (96, 384, 3, 128, 224, 1), 33, 52), (B.BF16, (80, 192, 5, 8, 8, 2591), 187, 223),
+                 (B.BF16, (80, 64, 5, 64, 224, 3), 28, 60)]
+DIRECT_FASTER = [(B.F32, (32, 32, 5, 16, 16, 128)), (B.F32, (256, 384, 3, 13, 13, 128)), (B.F32, (96, 256, 5, 27, 27, 16)), (B.F32, (256, 192, 5, 16, 16, 271)),
+                 (B.BF16, (32, 32, 5, 16, 16, 93)), (B.BF16, (96, 256, 5, 27, 27, 128)), (B.BF16, (256, 384, 3, 13, 13, 32)), (B.BF16, (384, 256, 3, 13, 13, 256)),
+                 (B.BF16, (48, 128, 5, 64, 64, 101)), (B.BF16, (192, 192, 3, 13, 13, 77))]
+
+
+def test_stride1_layers_go_to_the_faster_of_the_two_kernels():
+    for dtype, (cin, cout, k, h, w, batch), engine, direct in ENGINE_FASTER:
+        assert engine < direct and _plan_direct(dtype, batch, h, w, cin, cout, k).ks == 0, (dtype, cin, cout, k, h, w, batch)
+    for dtype, (cin, cout, k, h, w, batch) in DIRECT_FASTER:
+        assert _plan_direct(dtype, batch, h, w, cin, cout, k).ks > 0, (dtype, cin, cout, k, h, w, batch)
