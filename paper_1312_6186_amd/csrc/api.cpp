@@ -315,8 +315,14 @@ int plan_net(asgd_net &n)
     // without it: 28 x 28 net (16 k parameters) fp32 8 images 129 / 81 us, 256 images 254 / 235; 32 x 32 net (0.1 M) bf16 93
     // images 234 / 203, 512 images 311 / 303, fp32 512 images 997 / 952; the same with 2.5 M parameters in its first
     // fully-connected layer 283 / 228.  AlexNet-style bf16 with 6.4 M parameters 32 images 589 / 600, 128 images 1155 / 1213; with
-    // its 62 M 16 images 713 / 754, 128 images 1403 / 1450.
-    n.fork_pays = n.param_count >= (size_t)4 << 20;
+    // its 62 M 16 images 713 / 754, 128 images 1403 / 1450.  And it hides the filter gradients of small fully-connected layers over
+    // thousands of images, a few workgroups with a long sum each: 192 -> 8 outputs in fp32 at 16417 images are 1025 us, a pass takes
+    // 2153 with it and 2584 without; with 435 us of such sums (6733 images) 8955 / 9311, with 286 (4435) 916 / 1146; with 187 (2904)
+    // it is 3745 / 3428, the convolutions then share the CUs with each other.
+    double lone = 0;
+    for (const Stage &s : n.stages)
+        if (s.kind == ST_FC) lone += lone_fc_wgrad_us(n.dtype, s.out_f, s.in_f, n.batch);
+    n.fork_pays = n.param_count >= (size_t)4 << 20 || lone >= 200;
 
     int rc = size_net(n, SIZE_MAX, false);
     if (rc != ASGD_OK || n.ws_bytes <= kStaticWsBytes) return rc;

@@ -80,6 +80,9 @@ template <class F> double rounds_us(long workgroups, int per_cu, F t)
     return (double)(workgroups / round) * t(per_cu) + (rest ? t((int)((rest + 255) / 256)) : 0.0);
 }
 
+// us that the filter gradient of a fully-connected layer takes while it leaves more than half of the CUs idle (0 if it does not).
+double lone_fc_wgrad_us(int dtype, long out, long in, long batch);
+
 // Stride-1 convolutions over equal grids (forward, and the data gradient as a convolution with flipped filters): K steps
 // of 16 channels per chunk (0: the convolution does not run this way), chunks, tile shape, patch loads per thread and chunk,
 // and the size of the packed filters.  Packed element (n, pos, c): blocks of 32 output columns, then chunks, window positions and K steps, each K

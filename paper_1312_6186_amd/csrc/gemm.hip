@@ -1149,6 +1149,14 @@ GemmPlan plan_gemm(long M, long N, long K, int dtype, int max_splits)
     return p;
 }
 
+double lone_fc_wgrad_us(int dtype, long out, long in, long batch)
+{
+    const long tiles = ((out + Cfg128::BM - 1) / Cfg128::BM) * ((in + Cfg128::BN - 1) / Cfg128::BN);
+    if (tiles >= 128) return 0.0;
+    // a workgroup alone on its CU: us per K tile of 128 bytes
+    return dtype == kBF16 ? 0.54 * ((batch + 63) / 64) : 2.06 * ((batch + 31) / 32);
+}
+
 template <typename T, class Cfg, class LA, class LB>
 static int run_tile(const LA &la, const LB &lb, int M, int N, int K, const Epilogue &ep, const GemmPlan &plan, float *ws, hipStream_t s)
 {

@@ -224,3 +224,16 @@ def test_stride1_layers_go_to_the_faster_of_the_two_kernels():
         assert engine < direct and _plan_direct(dtype, batch, h, w, cin, cout, k).ks == 0, (dtype, cin, cout, k, h, w, batch)
     for dtype, (cin, cout, k, h, w, batch) in DIRECT_FASTER:
         assert _plan_direct(dtype, batch, h, w, cin, cout, k).ks > 0, (dtype, cin, cout, k, h, w, batch)
+
+
+def test_side_stream_hides_long_sums_of_few_workgroups():
+    """Filter gradients of small fully-connected layers over very many images leave the chip to the side stream's neighbours;
+    those of minibatches and of large layers do not."""
+    f = B.lib()["_ZN4asgd16lone_fc_wgrad_usEilll"]
+    f.argtypes, f.restype = [ctypes.c_int] + [ctypes.c_long] * 3, ctypes.c_double
+    for dtype, out, fin, batch, us in ((B.F32, 8, 64, 16417, 1025), (B.F32, 8, 576, 8792, 552), (B.F32, 8, 256, 10372, 650), (B.F32, 8, 256, 4435, 286)):
+        assert 200 <= f(dtype, out, fin, batch) and abs(f(dtype, out, fin, batch) / us - 1) < 0.1
+    assert abs(f(B.BF16, 8, 512, 11591) / 105 - 1) < 0.1
+    for dtype, out, fin, batch in ((B.F32, 10, 1024, 512), (B.BF16, 10, 1024, 512), (B.F32, 8, 3456, 2904)):
+        assert f(dtype, out, fin, batch) < 200
+    assert f(B.F32, 4096, 4096, 16384) == 0
