@@ -428,6 +428,10 @@ def test_small_cnn_twenty_sgd_steps(dtype):
 FCWIDE = dict(name="fcwide", in_shape=(3, 16, 16), classes=10,
               layers=[("conv", 8, 3, 1, 1), ("relu",), ("fc", 200), ("relu",), ("dropout", 0.5), ("fc", 136), ("relu",), ("fc", 10),
                       ("softmax_ce",)])
+# enough weights for the side stream (5.3 M): a convolution under a pool, a grouped one and one without a pool behind them
+FORKED = dict(name="forked", in_shape=(3, 16, 16), classes=10,
+              layers=[("conv", 16, 3, 1, 1), ("relu",), ("maxpool", 2, 2), ("conv", 32, 5, 1, 2, 2), ("relu",), ("conv", 32, 3, 1, 1), ("relu",),
+                      ("maxpool", 2, 2), ("fc", 2048), ("relu",), ("fc", 2048), ("relu",), ("dropout", 0.5), ("fc", 10), ("softmax_ce",)])
 SENTINEL = 777.0
 
 
@@ -441,7 +445,7 @@ def _fusable_fc_slices(onet, layers):
 
 
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
-@pytest.mark.parametrize("cfg", [wl.SMALL, RAGGED, FCWIDE], ids=["small", "ragged", "fcwide"])
+@pytest.mark.parametrize("cfg", [wl.SMALL, RAGGED, FCWIDE, FORKED], ids=["small", "ragged", "fcwide", "forked"])
 def test_train_step_is_the_three_calls_bit_for_bit_and_matches_the_oracle(cfg, dtype):
     """asgd_train_step pipelines the push by layer, asgd_train_step_fused pushes the fully-connected weights inside their
     gradient kernel; the results of both must be those of fwd_bwd + update + fetch."""
@@ -866,15 +870,20 @@ def test_image_staging_takes_any_width(c, w, dtype):
         g.close()
 
 
-@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
-def test_serial_plan_gives_the_same_bits(dtype):
+# RAGGED runs on the caller's stream alone either way; FORKED has a side stream for its weights, LONGSUM for the 3200 images that a
+# few workgroups sum up in its last layer
+LONGSUM = dict(name="longsum", in_shape=(3, 6, 6), classes=8, layers=[("conv", 8, 3, 1, 1), ("relu",), ("maxpool", 2, 2), ("fc", 8), ("softmax_ce",)])
+
+
+@pytest.mark.parametrize("cfg,batch,dtype", [(RAGGED, 37, B.F32), (RAGGED, 37, B.BF16), (FORKED, 37, B.F32), (FORKED, 37, B.BF16), (LONGSUM, 3200, B.F32)],
+                         ids=lambda v: v["name"] if isinstance(v, dict) else str(v))
+def test_serial_plan_gives_the_same_bits(cfg, batch, dtype):
     """asgd_net_set_serial keeps every kernel on the caller's stream; the results must not change by a bit."""
-    cfg = RAGGED
     params = wl.make_params(cfg["layers"], cfg["in_shape"], 3)
-    images, labels = wl.make_batch(cfg["in_shape"], 37, 10, 4)
+    images, labels = wl.make_batch(cfg["in_shape"], batch, cfg["classes"], 4)
     out = []
     for serial in (False, True):
-        g = GpuNet(cfg["layers"], cfg["in_shape"], 37, dtype)
+        g = GpuNet(cfg["layers"], cfg["in_shape"], batch, dtype)
         try:
             B.asgd_net_set_serial(g.net, serial)
             out.append(g.fwd_bwd(params, images, labels, 11, 2, 1))
