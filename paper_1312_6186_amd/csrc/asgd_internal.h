@@ -152,7 +152,7 @@ struct PackJob {
     const void *w; void *wf; void *wd;
     int cout, cin, k, coutp, cinp, rw, KW;
     int fks, fch, dks, dch;   // K steps per chunk and chunks of wf / wd where they are packed for conv_direct (0: rows)
-    unsigned start, nf;   // filled by launch_pack_conv
+    unsigned start, nf;   // filled by launch_head
 };
 struct PackJobs { PackJob j[12]; int n; unsigned total; };
 // Input staging: images [B][C][H][W] (compute type) -> channel-last [B][H][W][Cp] with zero padding channels (pc = 0), or

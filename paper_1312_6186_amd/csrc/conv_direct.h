@@ -22,7 +22,7 @@
 // us, before -> after, bf16, 128 images (two layers with 5 x 5 windows on 27 x 27, then 3 x 3 on 13 x 13; kernel alone,
 // inside a step): 96 -> 256 channels 129 -> 104, 256 -> 384 44 -> 37, 384 -> 384 58 -> 49, 384 -> 256 53 -> 39; data
 // gradients 256 -> 96 136 -> 92, 384 -> 256 53 -> 42, 384 -> 384 58 -> 54, 256 -> 384 41 -> 41.  32 images: 42 -> 36,
-// 28 -> 19, 36 -> 25, 31 -> 21; 58 -> 50, 32 -> 22, 35 -> 26, 26 -> 20.
+// 28 -> 19, 36 -> 25, 31 -> 21; 58 -> 50, 32 -> 22, 35 -> 26, 26 -> 20 (256 -> 96 alone 44, and 41 since it runs in 128 x 128).
 #pragma once
 #include "asgd_internal.h"
 #include "mfma_common.h"

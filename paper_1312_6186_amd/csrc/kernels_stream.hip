@@ -1142,8 +1142,8 @@ int launch_unflatten(int dtype, const void *dflat, const void *x, int relu, void
 // ---------------------------------------------------------------- bias gradient (column sums)
 // Stage 1: a block owns a band of rows and up to 256 column chunks of 16 bytes;
 // thread (c, r) adds rows r, r+RL, ... of chunk c, the RL row lanes are then
-// added in lane order.  Stage 2 adds the bands in order.  No atomics, so the
-// result does not depend on scheduling.
+// added in lane order.  Stage 2 adds the bands in a fixed tree.  No atomics, so
+// the result does not depend on scheduling.
 // Stage 1 for several tensors in one launch: a block finds its job and its (column group, band) in it.
 template <typename T>
 __global__ __launch_bounds__(256) void colsum_stage1(ColsumS1Jobs jobs)
