@@ -45,20 +45,19 @@ GROUPED = dict(name="grouped", in_shape=(3, 23, 21), classes=10,
                        ("fc", 10), ("softmax_ce",)])
 
 
-# stride-1 convolutions with equal input and output grids over enough channels take the patch form: 120 channels
+# stride-1 convolutions with equal input and output grids, in chunks of channels over a patch of pixels in LDS: 120 channels
 # (a partial last chunk of channels in both element types), 3x3 and 5x5 windows, 120 output columns (a ragged
-# column tile), rows that are no multiple of the tile, K ranges of a split that begin in the middle of a chunk
+# column tile), rows that are no multiple of the tile
 PATCHNET = dict(name="patch", in_shape=(3, 15, 13), classes=10,
                 layers=[("conv", 120, 3, 1, 1), ("relu",), ("conv", 120, 3, 1, 1), ("relu",), ("conv", 16, 5, 1, 2), ("relu",),
                         ("maxpool", 3, 2), ("fc", 10), ("softmax_ce",)])
-# the same on rows of 27 pixels with a 5x5 window: the longer run of pixels per tile (240), 72 output columns (narrow tiles)
+# the same on rows of 27 pixels with a 5x5 window: a longer run of pixels per tile, 72 output columns
 PATCHWIDE = dict(name="patchwide", in_shape=(3, 8, 27), classes=10,
                  layers=[("conv", 64, 3, 1, 1), ("relu",), ("conv", 72, 5, 1, 2), ("relu",), ("conv", 8, 5, 1, 2), ("relu",),
                          ("maxpool", 2, 2), ("fc", 10), ("softmax_ce",)])
 
-# channel counts of 1.5 K tiles (48 channels in 32-bit data, 96 in 16-bit data): chunks of half a K tile with two
-# window positions per K tile, 3x3 and 5x5 windows (an odd number of positions: the last tile of a chunk is half empty),
-# forward and, for the 96 channels that the 48-channel layer feeds, the data gradient
+# channel counts whose chunks are not of 64 channels (48 and 40: one of 48 in 16-bit data, three of 16 in 32-bit data; 96: of 32),
+# 3x3 and 5x5 windows, forward and data gradient
 HALFCHUNK = dict(name="halfchunk", in_shape=(3, 14, 13), classes=10,
                  layers=[("conv", 48, 3, 1, 1), ("relu",), ("conv", 96, 3, 1, 1), ("relu",), ("conv", 40, 5, 1, 2), ("relu",),
                          ("maxpool", 2, 2), ("fc", 10), ("softmax_ce",)])
