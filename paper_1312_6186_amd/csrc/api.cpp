@@ -107,6 +107,7 @@ struct asgd_net {
     float *row_loss = nullptr;
     int *version_counter = nullptr;  // device-side count of applied updates (A-SGD replay)
     size_t scratch_floats = 0, scratch_side_floats = 0;
+    size_t shared_off = 0, apart_bytes = 0;   // where the part of the workspace starts that partial sums and forward filters share; its size if they did not
     // key of the last forward pass (for the dropout mask export)
     uint64_t last_seed = 0, last_step = 0;
     uint32_t last_worker = 0;
@@ -151,7 +152,6 @@ size_t carve(asgd_net &n, char *base)
         s.dout = at(oe * es + 256);
         if (s.kind == ST_POOL) s.argmax = static_cast<uint8_t *>(at(oe));
         if (s.kind == ST_CONV) {
-            s.wf = at(s.wf_elems * s.groups * es);
             s.wd = i > 0 ? at(s.wd_elems * s.groups * es) : nullptr;
         }
         if (s.has_params()) s.colsum_ws = static_cast<float *>(at(s.colsum_floats * 4));
@@ -163,8 +163,16 @@ size_t carve(asgd_net &n, char *base)
     n.row_loss = static_cast<float *>(at(B * 4));
     n.version_counter = static_cast<int *>(at(256));
     n.scratch = static_cast<float *>(at(n.scratch_floats * 4));
+    // The filters of the forward pass are dead when the first partial sum of a parameter gradient is written, and all that counts
+    // of them is written anew at the head of the next pass: both in one place.
+    const size_t shared = n.shared_off = c.off;
     n.scratch_side = static_cast<float *>(at(n.scratch_side_floats * 4));
-    return c.off;
+    const size_t end = c.off;
+    c.off = shared;
+    for (Stage &s : n.stages)
+        if (s.kind == ST_CONV) s.wf = at(s.wf_elems * s.groups * es);
+    n.apart_bytes = end + (c.off - shared);
+    return std::max(c.off, end);
 }
 
 Gather conv_gather(const Stage &s, const void *x, int B, int dt, int group = 0);
@@ -174,9 +182,8 @@ Gather dgrad_gather(const Stage &s, const void *dy, int B, int dt, int group);
 constexpr size_t kStaticWsBytes = (size_t)64 << 20;
 
 // Chooses the kernels of every stage and sizes the workspace.  partials: floats that the partial sums of a filter gradient may
-// take in conv_wgrad; lean: none of the kernels whose filters are padded to their chunks (conv_direct) or whose partial sums
-// are not the general engine's (conv_wgrad).
-int size_net(asgd_net &n, size_t partials, bool lean);
+// take in conv_wgrad; plain: no filters padded to their chunks (conv_direct).
+int size_net(asgd_net &n, size_t partials, bool plain);
 
 int plan_net(asgd_net &n)
 {
@@ -326,20 +333,26 @@ int plan_net(asgd_net &n)
 
     int rc = size_net(n, SIZE_MAX, false);
     if (rc != ASGD_OK || n.ws_bytes <= kStaticWsBytes) return rc;
-    // Beyond the static workspace with the kernels chosen for speed: a plan that fits it with fewer partial sums, or else without
-    // the padded filters, is made to (what asgd_fwd_bwd_static accepts does not depend on how the fast kernels are split).
+    // Beyond the static workspace with the kernels chosen for speed.  If the general engine's kernels would fit it, the plan is made
+    // to, with fewer partial sums or (few need that) without padded filters: what asgd_fwd_bwd_static accepts does not depend on how
+    // the fast kernels are split.
     const std::vector<Stage> fast = n.stages;
-    const size_t bytes = n.ws_bytes, scratch = n.scratch_floats, scratch_side = n.scratch_side_floats, rest = bytes - scratch_side * 4;
-    if (rest + 512 < kStaticWsBytes) rc = size_net(n, (kStaticWsBytes - rest - 512) / 4, false);
-    if (rc == ASGD_OK && n.ws_bytes > kStaticWsBytes) rc = size_net(n, 0, true);
-    if (rc == ASGD_OK && n.ws_bytes > kStaticWsBytes) {
-        n.stages = fast;
-        n.ws_bytes = bytes; n.scratch_floats = scratch; n.scratch_side_floats = scratch_side;
+    const size_t bytes = n.ws_bytes, scratch_side = n.scratch_side_floats;
+    auto room = [&](size_t off) { return off + 1024 < kStaticWsBytes ? (kStaticWsBytes - off - 1024) / 4 : 0; };
+    const size_t fast_room = room(n.shared_off);
+    rc = size_net(n, 0, true);
+    if (rc == ASGD_OK && n.apart_bytes <= kStaticWsBytes) {
+        const size_t plain_room = room(n.shared_off);
+        rc = size_net(n, fast_room, false);
+        if (rc == ASGD_OK && n.ws_bytes > kStaticWsBytes) rc = size_net(n, plain_room, true);
+        return rc;
     }
+    n.stages = fast;
+    n.ws_bytes = bytes; n.scratch_side_floats = scratch_side;
     return rc;
 }
 
-int size_net(asgd_net &n, size_t partials, bool lean)
+int size_net(asgd_net &n, size_t partials, bool plain)
 {
     const long B = n.batch;
     size_t scratch = 0, scratch_side = 0;
@@ -363,11 +376,11 @@ int size_net(asgd_net &n, size_t partials, bool lean)
                 if (s.rw) s.p_wgrad.ws_floats = std::max(s.p_wgrad.ws_floats, rows_wgrad_ws_floats(n.dtype, s.outCp, conv_gather(s, nullptr, (int)B, n.dtype)));
             }
             const int Ng = s.groups > 1 ? s.outC / s.groups : s.outCp, Cg = s.groups > 1 ? s.inC / s.groups : s.inCp;
-            s.d_wgrad = lean ? WgradPlan() : plan_wgrad(n.dtype, Ng, s.groups, conv_gather(s, nullptr, (int)B, n.dtype), partials);
-            s.d_fwd = lean ? DirectPlan() : plan_direct(n.dtype, conv_gather(s, nullptr, (int)B, n.dtype), Ng);
+            s.d_wgrad = plan_wgrad(n.dtype, Ng, s.groups, conv_gather(s, nullptr, (int)B, n.dtype), partials);
+            s.d_fwd = plain ? DirectPlan() : plan_direct(n.dtype, conv_gather(s, nullptr, (int)B, n.dtype), Ng);
             s.wf_elems = s.d_fwd.ks ? s.d_fwd.pack_elems : (size_t)Ng * s.k * (s.rw ? s.rwKW : s.k * Cg);
             if (si > 0) {
-                s.d_dgrad = lean ? DirectPlan() : plan_direct(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg);
+                s.d_dgrad = plain ? DirectPlan() : plan_direct(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg);
                 s.wd_elems = s.d_dgrad.ks ? s.d_dgrad.pack_elems : (size_t)Cg * s.k * s.k * Ng;
             }
             scratch_side = std::max(scratch_side, s.d_wgrad.tile >= 0 ? s.d_wgrad.ws_floats : s.p_wgrad.ws_floats);

@@ -152,6 +152,7 @@ struct PackJob {
     const void *w; void *wf; void *wd;
     int cout, cin, k, coutp, cinp, rw, KW;
     int fks, fch, dks, dch;   // K steps per chunk and chunks of wf / wd where they are packed for conv_direct (0: rows)
+    int cinw;             // filled by launch_head: input channels of wf with the padding of its last chunk
     unsigned start, nf;   // filled by launch_head
 };
 struct PackJobs { PackJob j[12]; int n; unsigned total; };

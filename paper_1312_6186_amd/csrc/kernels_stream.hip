@@ -473,8 +473,8 @@ template <typename T> __global__ __launch_bounds__(256) void pack_conv_kernel(Pa
             out[e] = (co < J.cout && ci < J.cin && kx < k) ? w[((long)co * J.cin + ci) * kk + ky * k + kx] : (T)0.f;
         }
         dst = static_cast<T *>(J.wf) + li;
-    } else if (li < J.nf) {  // wf[co][ky][kx][ci]
-        const int ci0 = (int)(li % (unsigned)J.cinp); unsigned t = li / (unsigned)J.cinp;
+    } else if (li < J.nf) {  // wf[co][ky][kx][ci], with zeros up to the end of the last chunk
+        const int ci0 = (int)(li % (unsigned)J.cinw); unsigned t = li / (unsigned)J.cinw;
         const int kx = (int)(t % (unsigned)k); t /= (unsigned)k;
         const int ky = (int)(t % (unsigned)k), co = (int)(t / (unsigned)k);
         const T *src = w + ((long)co * J.cin + ci0) * kk + ky * k + kx;
@@ -537,8 +537,8 @@ template <typename T> __device__ __forceinline__ void pack_lds_block(const PackJ
         }
         return;
     }
-    if (J.wf) {  // wf[co][ky][kx][ci]
-        const int cv = J.cinp / V, n = V * kk * cv;
+    if (J.wf) {  // wf[co][ky][kx][ci], with zeros up to the end of the last chunk
+        const int cv = J.cinw / V, n = V * kk * cv;
         for (int i = tid; i < n; i += NT) {
             const int cg = i % cv, t = i / cv, pp = t % kk, c = t / kk;
 #pragma unroll
@@ -609,6 +609,7 @@ int launch_head(int dtype, PackJobs &jobs, const StageJob &st, hipStream_t s)
     PackJobs none;
     none.n = 0; none.total = 0;
     if (jobs.n == 0) return head(none);
+    for (int q = 0; q < jobs.n; ++q) { PackJob &J = jobs.j[q]; J.cinw = J.fks ? J.fch * J.fks * 16 : J.cinp; }
     // the LDS form, if every layer qualifies
     {
         const size_t es = dtype_size(dtype), V = 16 / es;
@@ -633,9 +634,9 @@ int launch_head(int dtype, PackJobs &jobs, const StageJob &st, hipStream_t s)
     for (int q = 0; q < jobs.n; ++q) {
         PackJob &J = jobs.j[q];
         const size_t full = J.rw ? (size_t)J.coutp * J.k * J.KW : (size_t)J.coutp * J.k * J.k * J.cinp;
-        const size_t nf = J.wf ? full : 0;
+        const size_t nf = !J.wf ? 0 : J.rw ? full : full / J.cinp * J.cinw;
         const size_t nd = (!J.rw && J.wd) ? full : 0;
-        if (nf + nd > 0xffffffffull || (nf & 7)) return -1;   // cinp, coutp and KW are multiples of 8
+        if (nf + nd > 0xffffffffull || (nf & 7)) return -1;   // cinp, cinw, coutp and KW are multiples of 8
         J.start = (unsigned)total; J.nf = (unsigned)nf;
         total += (nf + nd) / 8;                                 // in groups of 8 elements
     }

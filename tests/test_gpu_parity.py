@@ -842,6 +842,37 @@ def test_out_of_range_label_gives_nan_loss_and_no_fault():
 
 # Bias gradients: bands of rows below and above four rows per lane (a layer without a pool), and of a layer under a pool from
 # fewer bands than the lanes of a workgroup to more than eight times as many.
+# Channel counts that fill their last chunk in part (40 and 56 of 48 and 64): its zeros lie where the partial sums of the filter
+# gradients are written later in a pass.
+PARTCHUNK = dict(name="partchunk", in_shape=(3, 19, 17), classes=10,
+                 layers=[("conv", 40, 3, 1, 1), ("relu",), ("conv", 56, 3, 1, 1), ("relu",), ("conv", 24, 5, 1, 2), ("relu",), ("maxpool", 2, 2),
+                         ("conv", 104, 3, 1, 1), ("relu",), ("conv", 40, 5, 1, 2), ("relu",), ("fc", 8), ("softmax_ce",)])
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("cfg", [PARTCHUNK, FORKED], ids=["partchunk", "forked"])
+def test_nothing_of_a_pass_reaches_the_next(cfg, dtype):
+    """A pass over an image with infinities leaves NaN in every partial sum; the pass after it must give the bits of a new plan."""
+    batch = 13
+    params = wl.make_params(cfg["layers"], cfg["in_shape"], 3)
+    images, labels = wl.make_batch(cfg["in_shape"], batch, 8, 4)
+    broken = images.copy()
+    broken[:, :, ::2] = np.inf
+    out = []
+    for first in (None, broken, images):
+        g = GpuNet(cfg["layers"], cfg["in_shape"], batch, dtype)
+        try:
+            if first is not None:
+                _, grads = g.fwd_bwd(params, first, labels, 11, 2, 1)
+                assert np.isfinite(grads).all() == (first is images)
+            out.append(g.fwd_bwd(params, images, labels, 11, 2, 1))
+        finally:
+            g.close()
+    assert np.isfinite(out[0][1]).all()
+    for loss, grads in out[1:]:
+        assert loss == out[0][0] and grads.tobytes() == out[0][1].tobytes()
+
+
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
 @pytest.mark.parametrize("c,h,w,batch", [(8, 5, 7, 1), (40, 9, 11, 3), (200, 13, 13, 7), (40, 31, 33, 40), (136, 41, 43, 60)])
 def test_bias_gradient_shapes(c, h, w, batch, dtype):

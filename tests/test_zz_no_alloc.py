@@ -34,6 +34,7 @@ STATIC_NETS = {
     "grouped": (_conv(200, 1) + _conv(448, 1) + _conv(192, 5, 2) + [("maxpool", 2, 2), ("fc", 160), ("softmax_ce",)], (1, 45, 55), 4, B.BF16),
     "partials": (_conv(360, 3) + _conv(504, 5) + [("maxpool", 2, 2)] + _conv(320, 3) + [("fc", 40), ("softmax_ce",)], (3, 30, 31), 2, B.BF16),
     "padded_f32": (_conv(80, 1) + _conv(360, 3) + [("maxpool", 2, 2), ("fc", 8), ("softmax_ce",)], (3, 15, 12), 39, B.F32),
+    "wide_f32": (_conv(424, 3) + [("maxpool", 2, 2)] + _conv(392, 3) + _conv(424, 3) + _conv(400, 5) + [("fc", 16), ("softmax_ce",)], (3, 12, 35), 2, B.F32),
     "padded_bf16": (_conv(40, 5) + _conv(480, 3) + [("maxpool", 2, 2), ("fc", 8), ("softmax_ce",)], (8, 11, 25), 45, B.BF16),
 }
 
@@ -97,9 +98,9 @@ def test_static_entry_point_matches_fwd_bwd_on_two_calls_in_a_row():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("name", ["alexnet", "grouped", "padded_f32", "padded_bf16"])
+@pytest.mark.parametrize("name", ["alexnet", "grouped", "wide_f32", "padded_f32", "padded_bf16"])
 def test_static_entry_point_takes_plans_near_the_size_of_its_workspace(name):
-    """Plans that fit with fewer partial sums, or with the general engine's kernels only: two calls in a row, bit for bit."""
+    """Plans that fit as they are, with fewer partial sums, or with the general engine's kernels only: two calls in a row, bit for bit."""
     layers, in_shape, batch, dtype = STATIC_NETS[name]
     classes = [l for l in layers if l[0] == "fc"][-1][1]
     _, _, copy, images, labels = _case({"layers": layers, "in_shape": in_shape, "classes": classes}, batch, dtype, 21)
