@@ -55,7 +55,9 @@ struct Stage {
     // window-row form (first stage, <= 4 input channels): bordered input [B][rwHp][rwWp][rwC], K = k * rwKW
     int rw = 0, rwC = 0, rwKW = 0, rwHp = 0, rwWp = 0;
     int relu = 0, drop = 0, drop_layer = -1;
+    bool nonneg = false;         // the output holds no negative values (CONV + RELU, and LRN and POOL on top of it)
     float lrn_alpha = 0.f, lrn_beta = 0.f, lrn_bias = 0.f;   // ST_LRN (window size in k)
+    bool with_pool = false;    // ST_LRN: one kernel does it together with the pool that follows (out is written for export only)
     bool has_params() const { return kind == ST_CONV || kind == ST_FC; }
     float drop_p = 0.f, drop_scale = 1.f;
     uint32_t drop_thr = 0;
@@ -66,8 +68,8 @@ struct Stage {
     void *wf = nullptr, *wd = nullptr;
     void *flat_in = nullptr, *dflat_in = nullptr;
     float *colsum_ws = nullptr; size_t colsum_floats = 0;   // band sums of the bias gradient
-    long pool_bands = 0;       // CONV directly under a pool whose backward kernel leaves those band sums: their number
-    bool bands_ready = false;  // ... and whether the pool's backward pass of this call has left them
+    long pool_bands = 0;       // CONV whose output gradient a kernel writes that leaves those band sums (a pool's, a normalisation's): their number
+    bool bands_ready = false;  // ... and whether the backward pass of this call has left them
     GemmPlan p_fwd, p_dgrad, p_wgrad;
     WgradPlan d_wgrad;           // CONV: set where the filter gradient (of all groups) runs as conv_wgrad
     DirectPlan d_fwd, d_dgrad;   // CONV: set where the forward pass / the data gradient (of one group) runs as conv_direct
@@ -149,7 +151,7 @@ size_t carve(asgd_net &n, char *base)
         Stage &s = n.stages[i];
         const size_t oe = B * s.out_elems();
         s.out = at(oe * (s.last ? 4 : es) + 256);
-        s.dout = at(oe * es + 256);
+        if (!s.with_pool) s.dout = at(oe * es + 256);
         if (s.kind == ST_POOL) s.argmax = static_cast<uint8_t *>(at(oe));
         if (s.kind == ST_CONV) {
             s.wd = i > 0 ? at(s.wd_elems * s.groups * es) : nullptr;
@@ -237,7 +239,7 @@ int plan_net(asgd_net &n)
             C = l.out; H = s.outH; W = s.outW;
             n.layer_shape[3 * i] = C; n.layer_shape[3 * i + 1] = H; n.layer_shape[3 * i + 2] = W;
             if (i + 1 < L && n.layers[i + 1].kind == ASGD_LAYER_RELU) {
-                s.relu = 1; ++i;
+                s.relu = 1; s.nonneg = true; ++i;
                 n.layer_shape[3 * i] = C; n.layer_shape[3 * i + 1] = H; n.layer_shape[3 * i + 2] = W;
             }
         } else if (l.kind == ASGD_LAYER_MAXPOOL) {
@@ -245,7 +247,7 @@ int plan_net(asgd_net &n)
             if (l.k <= 0 || l.k > 15 || l.stride <= 0 || H < l.k || W < l.k) return fail(ASGD_ESHAPE, "layer %d: bad MAXPOOL window", i);
             s.kind = ST_POOL;
             s.inC = s.outC = C; s.inCp = s.outCp = round_up(C, 8); s.inH = H; s.inW = W;
-            s.k = l.k; s.stride = l.stride;
+            s.k = l.k; s.stride = l.stride; s.nonneg = !n.stages.empty() && n.stages.back().nonneg;
             s.outH = (H - l.k) / l.stride + 1; s.outW = (W - l.k) / l.stride + 1;
             H = s.outH; W = s.outW;
             n.layer_shape[3 * i] = C; n.layer_shape[3 * i + 1] = H; n.layer_shape[3 * i + 2] = W;
@@ -256,7 +258,7 @@ int plan_net(asgd_net &n)
             if (!(l.bias > 0.f) || !(l.p >= 0.f) || !(l.scale >= 0.f)) return fail(ASGD_ESHAPE, "layer %d: LRN needs bias > 0, alpha >= 0, beta >= 0", i);
             s.kind = ST_LRN;
             s.inC = s.outC = C; s.inCp = s.outCp = round_up(C, 8); s.inH = s.outH = H; s.inW = s.outW = W;
-            s.k = l.k; s.lrn_alpha = l.p; s.lrn_beta = l.scale; s.lrn_bias = l.bias;
+            s.k = l.k; s.nonneg = true; s.lrn_alpha = l.p; s.lrn_beta = l.scale; s.lrn_bias = l.bias;
             n.layer_shape[3 * i] = C; n.layer_shape[3 * i + 1] = H; n.layer_shape[3 * i + 2] = W;
         } else if (l.kind == ASGD_LAYER_FC) {
             if (l.out <= 0) return fail(ASGD_ESHAPE, "layer %d: bad FC size", i);
@@ -388,6 +390,11 @@ int size_net(asgd_net &n, size_t partials, bool plain)
             if (si + 1 < n.stages.size() && n.stages[si + 1].kind == ST_POOL) {
                 const Stage &pl = n.stages[si + 1];
                 s.pool_bands = pool_bwd_bands(n.dtype, B, s.outH, s.outW, s.outCp, pl.k, pl.stride);
+                s.colsum_floats = std::max(s.colsum_floats, (size_t)s.pool_bands * s.outCp);
+            } else if (si + 2 < n.stages.size() && n.stages[si + 1].kind == ST_LRN && n.stages[si + 2].kind == ST_POOL) {
+                const Stage &pl = n.stages[si + 2];
+                s.pool_bands = lrn_pool_bands(n.dtype, (int)B, s.outH, s.outW, s.outCp, pl.k, pl.stride);
+                n.stages[si + 1].with_pool = s.pool_bands > 0;
                 s.colsum_floats = std::max(s.colsum_floats, (size_t)s.pool_bands * s.outCp);
             }
         } else if (s.kind == ST_FC) {
@@ -602,12 +609,19 @@ int forward(asgd_net *n, const void *params, const void *images, const int32_t *
                 if (s.d_fwd.ks) CHECK_LAUNCH(conv_direct(dt, g, wf, Og, ep, s.d_fwd, st), "conv forward");
                 else CHECK_LAUNCH(gemm_gather_plain(dt, g, wf, (long)g.kh * g.kw * g.C, Og, ep, s.p_fwd, n->scratch, st), "conv forward");
             }
+        } else if (s.kind == ST_LRN && s.with_pool) {
+            continue;   // cur stays the convolution's output: the pool's stage normalises it
+        } else if (s.kind == ST_POOL && si > 0 && n->stages[si - 1].with_pool) {
+            const Stage &l = n->stages[si - 1];
+            ProfScope ps(n, st, ASGD_K_LRN, 0, Bd * s.outC * ((double)s.inH * s.inW * es + (double)s.outH * s.outW * (es + 1)));
+            CHECK_LAUNCH(launch_lrn_pool_fwd(dt, cur, s.out, s.argmax, B, s.inH, s.inW, s.inCp, l.k, l.lrn_alpha, l.lrn_beta, l.lrn_bias, s.k, st),
+                         "lrn and pool forward");
         } else if (s.kind == ST_LRN) {
             ProfScope ps(n, st, ASGD_K_LRN, 0, 2 * Bd * s.outC * s.outH * s.outW * es);
             CHECK_LAUNCH(launch_lrn_fwd(dt, cur, s.out, (size_t)B * s.outH * s.outW, s.outCp, s.k, s.lrn_alpha, s.lrn_beta, s.lrn_bias, st), "lrn forward");
         } else if (s.kind == ST_POOL) {
             ProfScope ps(n, st, ASGD_K_POOL_FWD, 0, Bd * s.outC * ((double)s.inH * s.inW * es + (double)s.outH * s.outW * (es + 1)));
-            CHECK_LAUNCH(launch_pool_fwd(dt, cur, s.out, s.argmax, B, s.inH, s.inW, s.inCp, s.k, s.stride, st), "pool forward");
+            CHECK_LAUNCH(launch_pool_fwd(dt, cur, s.nonneg, s.out, s.argmax, B, s.inH, s.inW, s.inCp, s.k, s.stride, st), "pool forward");
         } else {
             const void *x = cur;
             long ldx = si > 0 && n->stages[si - 1].kind == ST_FC ? n->stages[si - 1].out_ld : s.in_f;
@@ -771,6 +785,15 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                 if (frc == ASGD_OK) frc = data_grad();
             }
             if (frc != ASGD_OK) return frc;
+        } else if (s.kind == ST_LRN && s.with_pool) {
+            continue;   // done with the pool's stage above
+        } else if (s.kind == ST_POOL && prev && prev->with_pool) {
+            Stage &conv = n->stages[si - 2];   // the CONV + RELU under both
+            ProfScope ps(n, st, ASGD_K_LRN, 0, Bd * s.outC * (2.0 * s.inH * s.inW * es + (double)s.outH * s.outW * (es + 1)));
+            CHECK_LAUNCH(launch_lrn_pool_bwd(dt, conv.out, s.dout, s.argmax, conv.dout, B, s.inH, s.inW, s.inCp, prev->k, prev->lrn_alpha, prev->lrn_beta,
+                                             prev->lrn_bias, s.k, conv.colsum_ws, st),
+                         "lrn and pool backward");
+            conv.bands_ready = true;
         } else if (s.kind == ST_LRN) {
             // prev is the CONV + RELU it normalises: the ReLU mask of that convolution is applied here
             ProfScope ps(n, st, ASGD_K_LRN, 0, 3 * Bd * s.outC * s.outH * s.outW * es);
@@ -1149,6 +1172,10 @@ int asgd_debug_get(asgd_net_t *net, int what, int layer, void *dst, size_t cap_b
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int B = net->batch;
     if (what == ASGD_DEBUG_OUTPUT) {
+        if (s.with_pool) {   // the pass keeps the normalised tensor in LDS: formed from the convolution's output, by the kernel of the pass's arithmetic
+            CHECK_LAUNCH(launch_lrn_fwd(net->dtype, net->stages[net->layer_stage[layer] - 1].out, s.out, (size_t)B * s.outH * s.outW, s.outCp, s.k,
+                                        s.lrn_alpha, s.lrn_beta, s.lrn_bias, st), "lrn forward");
+        }
         if (layer != s.last_layer) return fail(ASGD_EINVAL, "asgd_debug_get: layer %d is fused into the group ending at layer %d", layer, s.last_layer);
         if (s.kind == ST_FC) {
             if (cap_bytes < (size_t)B * s.out_f * 4) return fail(ASGD_EINVAL, "asgd_debug_get: destination too small");

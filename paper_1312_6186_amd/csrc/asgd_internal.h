@@ -165,7 +165,8 @@ struct StageJob {
 };
 // the head of a forward pass: the filters of up to 12 layers packed and the images staged, in one launch where it can be
 int launch_head(int dtype, PackJobs &jobs, const StageJob &st, hipStream_t s);
-int launch_pool_fwd(int dtype, const void *x, void *y, uint8_t *arg, int B, int H, int W, int Cp, int k, int stride,
+// nonneg: x holds no negative values (below is a ReLU); a matter of speed only
+int launch_pool_fwd(int dtype, const void *x, int nonneg, void *y, uint8_t *arg, int B, int H, int W, int Cp, int k, int stride,
                     hipStream_t s);
 // dx[pixel] = sum of dy over the windows whose recorded maximum is this pixel; times [x > 0] if relu
 int launch_pool_bwd(int dtype, const void *dy, const uint8_t *arg, const void *x, int relu, void *dx, int B, int H,
@@ -178,6 +179,14 @@ long pool_bwd_bands(int dtype, int B, int H, int W, int Cp, int k, int stride);
 int launch_lrn_fwd(int dtype, const void *a, void *y, size_t pixels, int Cp, int size, float alpha, float beta, float bias, hipStream_t s);
 int launch_lrn_bwd(int dtype, const void *a, const void *dy, int relu, void *da, size_t pixels, int Cp, int size, float alpha, float beta,
                    float bias, hipStream_t s);
+// Normalisation and a pool of window k, stride 2, on top of it in one pass each: forward a -> pooled y and positions; backward
+// writes da, times [a > 0], from the gradient dy at the pool's output, and leaves the column sums of da in
+// bands[Cp][lrn_pool_bands(...)].  lrn_pool_bands is 0 where the pair does not run this way.
+long lrn_pool_bands(int dtype, int B, int H, int W, int Cp, int k, int stride);
+int launch_lrn_pool_fwd(int dtype, const void *a, void *y, uint8_t *arg, int B, int H, int W, int Cp, int size, float alpha, float beta, float bias, int k,
+                        hipStream_t s);
+int launch_lrn_pool_bwd(int dtype, const void *a, const void *dy, const uint8_t *arg, void *da, int B, int H, int W, int Cp, int size, float alpha,
+                        float beta, float bias, int k, float *bands, hipStream_t s);
 // channel-last [B][H][W][Cp] -> [B][C*H*W] in (c,h,w) order, and back (zero padding channels; optional ReLU mask)
 int launch_flatten(int dtype, const void *x, void *flat, int B, int H, int W, int C, int Cp, hipStream_t s);
 int launch_unflatten(int dtype, const void *dflat, const void *x_for_mask, int relu, void *dx, int B, int H, int W,

@@ -8,10 +8,9 @@
 #include <hip/hip_runtime.h>
 
 #include "asgd_internal.h"
+#include "mfma_common.h"
 
 namespace asgd {
-
-typedef __bf16 bf16_t;
 
 __device__ inline float ldf(const float *p) { return *p; }
 __device__ inline float ldf(const bf16_t *p) { return (float)*p; }
@@ -20,14 +19,6 @@ __device__ inline void stf(bf16_t *p, float v) { *p = (bf16_t)v; }
 
 static inline unsigned blocks_for(size_t n, unsigned per_block) { return (unsigned)((n + per_block - 1) / per_block); }
 static inline int launch_ok() { return hipGetLastError() == hipSuccess ? 0 : -1; }
-
-__host__ __device__ inline uint64_t mix64(uint64_t z)
-{
-    z ^= z >> 30; z *= 0xBF58476D1CE4E5B9ull;
-    z ^= z >> 27; z *= 0x94D049BB133111EBull;
-    z ^= z >> 31;
-    return z;
-}
 
 uint64_t dropout_key(uint64_t seed, uint64_t step, uint32_t worker, uint32_t layer)
 {
@@ -674,8 +665,57 @@ template <typename T> struct Vec16 {
     union { uint4 u; T e[16 / sizeof(T)]; };
 };
 
+// The first maximum of P values per channel in their order (a NaN counts only where it is the first value), and its index, one byte
+// per channel.  KEYS: 16-bit data that is not negative, as after a ReLU, sorts as unsigned integers; value and 15 - index in one
+// word make one v_max3 out of six compares and selects (96 channels 55 x 55, 128 images, windows of 3: 22.8 -> 16.2 us, 256 channels
+// 27 x 27 14.6 -> 10.5).  Keys above infinity's (a NaN, a negative value after all, -0) take the compares.
+template <typename T, int P, bool KEYS> __device__ __forceinline__ void first_max(const Vec16<T> (&v)[P], Vec16<T> &o, uint64_t &pos)
+{
+    constexpr int V = Vec16<T>::N;
+    if constexpr (KEYS) {
+        static_assert(sizeof(T) == 2 && P <= 15, "a key is 16 bits of value over 15 - index");
+        uint32_t m[V], worst = 0;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            uint32_t k[P];
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                const uint32_t w = e / 2 == 0 ? v[j].u.x : e / 2 == 1 ? v[j].u.y : e / 2 == 2 ? v[j].u.z : v[j].u.w;
+                k[j] = (e & 1 ? w & 0xFFFF0000u : w << 16) | (uint32_t)(15 - j);
+            }
+            m[e] = k[0];
+#pragma unroll
+            for (int j = 1; j + 1 < P; j += 2) m[e] = max(max(m[e], k[j]), k[j + 1]);
+            if (P % 2 == 0) m[e] = max(m[e], k[P - 1]);
+            worst = max(worst, m[e]);
+        }
+        if (worst <= 0x7F80FFFFu) {
+            // v_perm_b32: selector bytes 0-3 take the second operand's, 4-7 the first one's
+            o.u = make_uint4(__builtin_amdgcn_perm(m[1], m[0], 0x07060302u), __builtin_amdgcn_perm(m[3], m[2], 0x07060302u),
+                             __builtin_amdgcn_perm(m[5], m[4], 0x07060302u), __builtin_amdgcn_perm(m[7], m[6], 0x07060302u));
+            const uint32_t lo = __builtin_amdgcn_perm(__builtin_amdgcn_perm(m[3], m[2], 0x0C0C0400u), __builtin_amdgcn_perm(m[1], m[0], 0x0C0C0400u), 0x05040100u);
+            const uint32_t hi = __builtin_amdgcn_perm(__builtin_amdgcn_perm(m[7], m[6], 0x0C0C0400u), __builtin_amdgcn_perm(m[5], m[4], 0x0C0C0400u), 0x05040100u);
+            pos = (lo ^ 0x0F0F0F0Fu) | (uint64_t)(hi ^ 0x0F0F0F0Fu) << 32;
+            return;
+        }
+    }
+    float best[V];
+    uint32_t a[V];
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            const float f = ldf(&v[j].e[e]);
+            if (j == 0 || f > best[e]) { best[e] = f; a[e] = (uint32_t)j; }
+        }
+    }
+    pos = 0;
+#pragma unroll
+    for (int e = 0; e < V; ++e) { stf(&o.e[e], best[e]); pos |= (uint64_t)a[e] << (8 * e); }
+}
+
 // KC > 0: window size known at compile time, so the k*k loads of a thread are all issued before the first compare.
-template <typename T, int KC>
+template <typename T, int KC, bool KEYS>
 __global__ __launch_bounds__(256) void pool_fwd_kernel(const T *__restrict__ x, T *__restrict__ y, uint8_t *__restrict__ arg, int B, int H, int W,
                                                      int Cp, int k_rt, int stride, int Ho, int Wo, PoolIndex pi)
 {
@@ -687,21 +727,16 @@ __global__ __launch_bounds__(256) void pool_fwd_kernel(const T *__restrict__ x, 
     pool_decode(i, pi, cg, px, py, n);
     const int c0 = cg * V;
     const T *win = x + (((long)n * H + py * stride) * W + px * stride) * Cp + c0;
-    float best[V];
-    uint8_t a[V];
+    Vec16<T> o;
+    uint64_t packed = 0;
     if constexpr (KC > 0) {
         Vec16<T> v[KC * KC];
 #pragma unroll
         for (int p = 0; p < KC * KC; ++p) v[p].u = *reinterpret_cast<const uint4 *>(win + ((long)(p / KC) * W + (p % KC)) * Cp);
-#pragma unroll
-        for (int p = 0; p < KC * KC; ++p) {
-#pragma unroll
-            for (int e = 0; e < V; ++e) {
-                const float f = ldf(&v[p].e[e]);
-                if (p == 0 || f > best[e]) { best[e] = f; a[e] = (uint8_t)p; }
-            }
-        }
+        first_max<T, KC * KC, KEYS>(v, o, packed);
     } else {
+        float best[V];
+        uint8_t a[V];
         for (int ky = 0; ky < k; ++ky)
             for (int kx = 0; kx < k; ++kx) {
                 Vec16<T> v;
@@ -713,37 +748,34 @@ __global__ __launch_bounds__(256) void pool_fwd_kernel(const T *__restrict__ x, 
                     if (pos == 0 || f > best[e]) { best[e] = f; a[e] = (uint8_t)pos; }
                 }
             }
-    }
-    Vec16<T> o;
 #pragma unroll
-    for (int e = 0; e < V; ++e) stf(&o.e[e], best[e]);
+        for (int e = 0; e < V; ++e) { stf(&o.e[e], best[e]); packed |= (uint64_t)a[e] << (8 * e); }
+    }
     const long off = (((long)n * Ho + py) * Wo + px) * Cp + c0;
     *reinterpret_cast<uint4 *>(y + off) = o.u;
-    uint64_t packed = 0;
-#pragma unroll
-    for (int e = 0; e < V; ++e) packed |= (uint64_t)a[e] << (8 * e);
     if (V == 8) *reinterpret_cast<uint64_t *>(arg + off) = packed;
     else *reinterpret_cast<uint32_t *>(arg + off) = (uint32_t)packed;
 }
 
-template <typename T>
+template <typename T, bool KEYS>
 static void launch_pool_fwd_t(const void *x, void *y, uint8_t *arg, int B, int H, int W, int Cp, int k, int stride, int Ho, int Wo, unsigned blocks,
                               hipStream_t s)
 {
     const T *xx = static_cast<const T *>(x); T *yy = static_cast<T *>(y);
     const PoolIndex pi = make_pool_index(Cp / (16 / (int)sizeof(T)), Wo, Ho);
-    if (k == 3) hipLaunchKernelGGL((pool_fwd_kernel<T, 3>), dim3(blocks), dim3(256), 0, s, xx, yy, arg, B, H, W, Cp, k, stride, Ho, Wo, pi);
-    else if (k == 2) hipLaunchKernelGGL((pool_fwd_kernel<T, 2>), dim3(blocks), dim3(256), 0, s, xx, yy, arg, B, H, W, Cp, k, stride, Ho, Wo, pi);
-    else hipLaunchKernelGGL((pool_fwd_kernel<T, 0>), dim3(blocks), dim3(256), 0, s, xx, yy, arg, B, H, W, Cp, k, stride, Ho, Wo, pi);
+    if (k == 3) hipLaunchKernelGGL((pool_fwd_kernel<T, 3, KEYS>), dim3(blocks), dim3(256), 0, s, xx, yy, arg, B, H, W, Cp, k, stride, Ho, Wo, pi);
+    else if (k == 2) hipLaunchKernelGGL((pool_fwd_kernel<T, 2, KEYS>), dim3(blocks), dim3(256), 0, s, xx, yy, arg, B, H, W, Cp, k, stride, Ho, Wo, pi);
+    else hipLaunchKernelGGL((pool_fwd_kernel<T, 0, false>), dim3(blocks), dim3(256), 0, s, xx, yy, arg, B, H, W, Cp, k, stride, Ho, Wo, pi);
 }
-int launch_pool_fwd(int dtype, const void *x, void *y, uint8_t *arg, int B, int H, int W, int Cp, int k, int stride, hipStream_t s)
+int launch_pool_fwd(int dtype, const void *x, int nonneg, void *y, uint8_t *arg, int B, int H, int W, int Cp, int k, int stride, hipStream_t s)
 {
     const int Ho = (H - k) / stride + 1, Wo = (W - k) / stride + 1;
     const int V = dtype == kBF16 ? 8 : 4;
     if ((size_t)B * Ho * Wo * (Cp / V) > 0x7fffffffu) return -1;
     const unsigned blocks = blocks_for((size_t)B * Ho * Wo * (Cp / V), 256);
-    if (dtype == kBF16) launch_pool_fwd_t<bf16_t>(x, y, arg, B, H, W, Cp, k, stride, Ho, Wo, blocks, s);
-    else launch_pool_fwd_t<float>(x, y, arg, B, H, W, Cp, k, stride, Ho, Wo, blocks, s);
+    if (dtype == kBF16 && nonneg) launch_pool_fwd_t<bf16_t, true>(x, y, arg, B, H, W, Cp, k, stride, Ho, Wo, blocks, s);
+    else if (dtype == kBF16) launch_pool_fwd_t<bf16_t, false>(x, y, arg, B, H, W, Cp, k, stride, Ho, Wo, blocks, s);
+    else launch_pool_fwd_t<float, false>(x, y, arg, B, H, W, Cp, k, stride, Ho, Wo, blocks, s);
     return launch_ok();
 }
 
@@ -822,6 +854,66 @@ __global__ __launch_bounds__(256) void pool_bwd_kernel(const T *__restrict__ dy,
     *reinterpret_cast<uint4 *>(dx + off) = o.u;
 }
 
+// What the 2 x 2 blocks of input pixels of a pool with stride 2 and windows of 2 or 3 need of the pool's side: gradients and
+// positions of the four windows (jy-1, jx-1), (jy-1, jx), (jy, jx-1), (jy, jx), by range-checked loads without a branch: a window
+// outside the grid reads as a gradient of zero (at position 0).  at: element offset of window (jy-1, jx-1) from the start of
+// the ranges, which hold less than 2 GiB.
+template <typename T> struct PoolWindows {
+    Vec16<T> g[4];
+    uint2 a8[4];
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t dy, __amdgpu_buffer_rsrc_t arg, unsigned at, int jy, int jx, int Ho, int Wo, int Cp)
+    {
+        const bool up = jy > 0 && jy <= Ho, down = (unsigned)jy < (unsigned)Ho, left = jx > 0 && jx <= Wo, right = (unsigned)jx < (unsigned)Wo;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool ok = (q < 2 ? up : down) && (q & 1 ? right : left);
+            const unsigned o = at + (unsigned)((q >> 1) * Wo * Cp + (q & 1) * Cp);
+            g[q].u = buf_ld16(dy, ok ? o * (unsigned)sizeof(T) : kInv);
+            if constexpr (sizeof(T) == 2) {
+                typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(arg, (int)(ok ? o : kInv), 0, 0);
+                a8[q] = make_uint2(v.x, v.y);
+            } else {
+                a8[q] = make_uint2(__builtin_amdgcn_raw_buffer_load_b32(arg, (int)(ok ? o : kInv), 0, 0), 0u);
+            }
+        }
+    }
+    // the gradients of the block's pixels (0, 0), (0, 1), (1, 0), (1, 1), added in window order
+    template <int K> __device__ __forceinline__ void sums(float (&acc)[4][Vec16<T>::N]) const
+    {
+        constexpr int V = Vec16<T>::N;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            float ge[4];
+            unsigned pos[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                ge[q] = ldf(&g[q].e[e]);
+                pos[q] = ((e < 4 ? a8[q].x : a8[q].y) >> (8 * (e & 3))) & 0xffu;
+            }
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {   // pixel (by, bx) sits at (by + 2*(1 - wy), bx + 2*(1 - wx)) in window q = (wy, wx); the last one covers all four
+                float t = 0.f;
+                bool any = false;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int ry = (b >> 1) + 2 * (1 - (q >> 1)), rx = (b & 1) + 2 * (1 - (q & 1));
+                    if (ry < K && rx < K) {
+                        const float v = pos[q] == (unsigned)(ry * K + rx) ? ge[q] : 0.f;
+                        t = any ? t + v : v;
+                        any = true;
+                    }
+                }
+                acc[b][e] = t;
+            }
+        }
+    }
+};
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t byte_range(const void *p, size_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)(unsigned)(bytes < 0x7fffffffu ? bytes : 0x7fffffffu), 0x00020000);
+}
+
 // Stride 2, windows of 2 or 3: a thread owns a 2 x 2 block of input pixels (rows 2*jy, 2*jy+1, columns 2*jx,
 // 2*jx+1).  Exactly the four windows (jy-1 .. jy) x (jx-1 .. jx) can cover it: window (jy, jx) covers all four
 // pixels, the two neighbours above / to the left cover the pixels of the block's first row / column (3 x 3
@@ -846,48 +938,22 @@ __global__ __launch_bounds__(256) void pool_bwd_s2_kernel(const T *__restrict__ 
     pool_decode(live ? i : 0u, pi, cg, jx, jy, n);
     if (!live) { jy = -4; jx = -4; }   // no window, no pixel: contributes zeros to the band sums
     const int c0 = cg * V;
-    Vec16<T> g[4];
-    uint64_t a8[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {   // windows (jy-1, jx-1), (jy-1, jx), (jy, jx-1), (jy, jx)
-        const int py = jy - 1 + (q >> 1), px = jx - 1 + (q & 1);
-        g[q].u = make_uint4(0u, 0u, 0u, 0u);
-        a8[q] = ~0ull;   // no position matches
-        if (py >= 0 && py < Ho && px >= 0 && px < Wo) {
-            const long off = (((long)n * Ho + py) * Wo + px) * Cp + c0;
-            g[q].u = *reinterpret_cast<const uint4 *>(dy + off);
-            if (V == 8) a8[q] = *reinterpret_cast<const uint64_t *>(arg + off);
-            else a8[q] = *reinterpret_cast<const uint32_t *>(arg + off) | 0xffffffff00000000ull;
-        }
-    }
+    // ranges that start with the image of the block's first thread
+    const int n0 = (int)fdiv32(fdiv32(fdiv32(blk * 256u, pi.dcv), pi.dw), pi.dh);
+    const size_t before = (size_t)n0 * Ho * Wo * Cp, behind = (size_t)(B - n0) * Ho * Wo * Cp;
+    PoolWindows<T> win;
+    win.load(byte_range(dy + before, behind * sizeof(T)), byte_range(arg + before, behind),
+             (unsigned)((((n - n0) * Ho + jy - 1) * Wo + jx - 1) * Cp + c0), jy, jx, Ho, Wo, Cp);
     float acc[4][V];
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-        for (int e = 0; e < V; ++e) acc[b][e] = 0.f;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-#pragma unroll
-        for (int e = 0; e < V; ++e) {
-            const int pos = (int)((a8[q] >> (8 * e)) & 0xff);
-            const float ge = ldf(&g[q].e[e]);
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {   // pixel (by, bx) of the block sits at (by + 2*(1 - wy), bx + 2*(1 - wx)) in window q
-                constexpr int dummy = 0; (void)dummy;
-                const int wy = q >> 1, wx = q & 1, by = b >> 1, bx = b & 1;
-                const int ry = by + 2 * (1 - wy), rx = bx + 2 * (1 - wx);
-                if (ry < K && rx < K) acc[b][e] += pos == ry * K + rx ? ge : 0.f;
-            }
-        }
-    }
+    win.template sums<K>(acc);
     float colsum[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) colsum[e] = 0.f;
+    const long at = (((long)n * H + 2 * jy) * W + 2 * jx) * Cp + c0;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        const int iy = 2 * jy + (b >> 1), ix = 2 * jx + (b & 1);
-        if (iy >= 0 && iy < H && ix >= 0 && ix < W) {
-            const long off = (((long)n * H + iy) * W + ix) * Cp + c0;
+        if ((unsigned)(2 * jy + (b >> 1)) < (unsigned)H && (unsigned)(2 * jx + (b & 1)) < (unsigned)W) {
+            const long off = at + (long)((b >> 1) * W + (b & 1)) * Cp;
             Vec16<T> o;
             if (relu) {
                 Vec16<T> xv;
@@ -918,12 +984,17 @@ __global__ __launch_bounds__(256) void pool_bwd_s2_kernel(const T *__restrict__ 
     }
 }
 
+// Where pool_bwd_s2_kernel runs: a block's 256 threads see two images, or several small ones, in one range of 2 GiB.
+static bool pool_bwd_blocks(int H, int W, int Cp, int es, int k, int stride)
+{
+    return stride == 2 && (k == 2 || k == 3) && (size_t)H * W * Cp * es < ((size_t)1 << 30);
+}
 template <typename T>
 static void launch_pool_bwd_t(const void *dy, const uint8_t *arg, const void *x, int relu, void *dx, int B, int H, int W, int Cp, int k, int stride,
                               int Ho, int Wo, unsigned blocks, float *bands, hipStream_t s)
 {
     const T *d = static_cast<const T *>(dy), *xx = static_cast<const T *>(x); T *o = static_cast<T *>(dx);
-    if (stride == 2 && (k == 2 || k == 3)) {
+    if (pool_bwd_blocks(H, W, Cp, (int)sizeof(T), k, stride)) {
         const int Hb = (H + 1) / 2, Wb = (W + 1) / 2, cv = Cp / (16 / (int)sizeof(T));
         const PoolIndex pb = make_pool_index(cv, Wb, Hb);
         const unsigned nb = blocks_for((size_t)B * Hb * Wb * cv, 256);
@@ -939,7 +1010,7 @@ static void launch_pool_bwd_t(const void *dy, const uint8_t *arg, const void *x,
 // Number of column-sum bands the pooling backward pass can leave behind (0: this shape runs a kernel that cannot).
 long pool_bwd_bands(int dtype, int B, int H, int W, int Cp, int k, int stride)
 {
-    if (!(stride == 2 && (k == 2 || k == 3))) return 0;
+    if (!pool_bwd_blocks(H, W, Cp, (int)dtype_size(dtype), k, stride)) return 0;
     const int V = dtype == kBF16 ? 8 : 4;
     return (long)blocks_for((size_t)B * ((H + 1) / 2) * ((W + 1) / 2) * (Cp / V), 256);
 }
@@ -1087,6 +1158,288 @@ int launch_lrn_bwd(int dtype, const void *a, const void *dy, int relu, void *da,
 {
     return dtype == kBF16 ? launch_lrn_any<bf16_t>(a, dy, relu, da, pixels, Cp, size, alpha, beta, bias, true, s)
                           : launch_lrn_any<float>(a, dy, relu, da, pixels, Cp, size, alpha, beta, bias, true, s);
+}
+
+// ---------------------------------------------------------------- response normalisation and the pool on top of it, in one pass
+// The normalised tensor is as large as the convolution's output and nothing but the pool reads it; the gradient at the pool's
+// input nothing but the normalisation's backward pass.  Both stay in LDS here, rounded to the element type where the separate
+// kernels store them.  Bound by the vector units (two or three transcendentals and about 25 other instructions per
+// element) a little above HBM's time.  bf16, 128 images, separate kernels / here: 96 channels 55 x 55 forward 52 / 33 us, backward with
+// the first stage of the bias gradient 110 / 59; 256 channels 27 x 27 forward 37 / 21, backward 75 / 45.
+// Channels c0 - S .. c0 + V + S - 1 of a pixel around the V channels of a thread; channels outside the tensor count as zeros.
+template <typename T, int S> struct LrnNear {
+    static constexpr int V = 16 / sizeof(T);
+    float f[V + 2 * S];   // f[S + e] is channel c0 + e
+    struct alignas(4 * sizeof(T)) Four { T e[4]; };
+    __device__ __forceinline__ void load(const T *pix, int c0, int Cp)
+    {
+        Vec16<T> v;
+        v.u = *reinterpret_cast<const uint4 *>(pix + c0);
+        Four l[S / 4], r[S / 4];
+#pragma unroll
+        for (int q = 0; q < S / 4; ++q) {
+            l[q] = Four{}; r[q] = Four{};
+            if (c0 - S + 4 * q >= 0) l[q] = *reinterpret_cast<const Four *>(pix + c0 - S + 4 * q);
+            if (c0 + V + 4 * q < Cp) r[q] = *reinterpret_cast<const Four *>(pix + c0 + V + 4 * q);
+        }
+#pragma unroll
+        for (int e = 0; e < V; ++e) f[S + e] = ldf(&v.e[e]);
+#pragma unroll
+        for (int e = 0; e < S; ++e) { f[e] = ldf(&l[e / 4].e[e % 4]); f[S + V + e] = ldf(&r[e / 4].e[e % 4]); }
+    }
+};
+
+// Forward.  A block makes R pooled rows of one image for `groups` channel groups of 16 bytes: it normalises the rows its windows
+// touch once into LDS (2R + K - 2 of them; the one that two blocks share is done twice), then pools out of LDS.
+struct LrnPool {
+    int H, W, Cp, Ho, Wo, cv;              // cv: channel groups of a pixel
+    int groups, R, tiles, chunks, cols;    // forward: groups per block, pooled rows per block, blocks per image (rows, groups), input columns used
+    int lanes, wlanes, Hb, Wb;             // backward: pixels side by side in a block and in a wavefront, 2 x 2 blocks of input pixels
+    FastDiv dgroups, dtiles, dchunks, dcols, dWo, dcv, dHb;
+    float alpha, beta, bias;
+};
+constexpr int kLrnPoolLds = 40 << 10;      // forward: four blocks a CU
+template <typename T, int HALF, int K>
+__global__ __launch_bounds__(256) void lrn_pool_fwd_kernel(const T *__restrict__ a, T *__restrict__ y, uint8_t *__restrict__ arg, LrnPool p)
+{
+    constexpr int V = Vec16<T>::N, S = 4;
+    extern __shared__ uint4 tile[];
+    uint32_t t = xcd_block();
+    uint32_t q = fdiv32(t, p.dchunks);
+    const int g0 = (int)(t - q * p.chunks) * p.groups;
+    t = q; q = fdiv32(t, p.dtiles);
+    const int py0 = (int)(t - q * p.tiles) * p.R, n = (int)q;
+    const int rows_out = min(p.R, p.Ho - py0), rows_in = 2 * (rows_out - 1) + K;
+    const T *src = a + ((long)n * p.H + 2 * py0) * p.W * p.Cp;
+    const int pieces = rows_in * p.cols * p.groups;
+    // two pieces of a thread in flight
+    for (int i = threadIdx.x; i < pieces; i += 512) {
+        LrnNear<T, S> w[2];
+        bool ok[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int j = i + u * 256;
+            const uint32_t pix = fdiv32((uint32_t)j, p.dgroups), row = fdiv32(pix, p.dcols);
+            const int c0 = (g0 + j - (int)pix * p.groups) * V;
+            ok[u] = j < pieces && c0 < p.Cp;
+            if (ok[u]) w[u].load(src + ((long)row * p.W + (pix - row * p.cols)) * p.Cp, c0, p.Cp);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (!ok[u]) continue;
+            Vec16<T> o;
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                float sum = 0.f;
+#pragma unroll
+                for (int j = -HALF; j <= HALF; ++j) sum += w[u].f[S + e + j] * w[u].f[S + e + j];
+                stf(&o.e[e], w[u].f[S + e] * pow_neg(p.bias + p.alpha * sum, p.beta));
+            }
+            tile[i + u * 256] = o.u;
+        }
+    }
+    __syncthreads();
+    const int outs = rows_out * p.Wo * p.groups;
+    for (int i = threadIdx.x; i < outs; i += 256) {
+        const uint32_t pix = fdiv32((uint32_t)i, p.dgroups), row = fdiv32(pix, p.dWo);
+        const int g = i - (int)pix * p.groups, px = (int)(pix - row * p.Wo), c0 = (g0 + g) * V;
+        if (c0 >= p.Cp) continue;
+        Vec16<T> v[K * K];
+#pragma unroll
+        for (int j = 0; j < K * K; ++j) v[j].u = tile[((2 * (int)row + j / K) * p.cols + 2 * px + j % K) * p.groups + g];
+        Vec16<T> o;
+        uint64_t packed;
+        first_max<T, K * K, sizeof(T) == 2>(v, o, packed);
+        const long off = (((long)n * p.Ho + py0 + row) * p.Wo + px) * p.Cp + c0;
+        *reinterpret_cast<uint4 *>(y + off) = o.u;
+        if (V == 8) *reinterpret_cast<uint64_t *>(arg + off) = packed;
+        else *reinterpret_cast<uint32_t *>(arg + off) = (uint32_t)packed;
+    }
+}
+
+// the value of the lane before / after this one in the wavefront (anything at its ends)
+__device__ __forceinline__ float lane_before(float v) { return __uint_as_float((unsigned)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), 0x138, 0xF, 0xF, true)); }
+__device__ __forceinline__ float lane_after(float v) { return __uint_as_float((unsigned)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), 0x130, 0xF, 0xF, true)); }
+
+// Backward.  A block makes two rows of the convolution's output gradient, all channels: the pool's gradient at them into LDS (as
+// pool_bwd_s2_kernel forms it, a 2 x 2 block of pixels per thread), then the normalisation's, times [a > 0].  A wavefront
+// holds whole pixels, 64 / cv of them, so that what a thread needs of its neighbours' channels comes from the lanes beside it,
+// each power worked out once.  A thread keeps its channel group, so that it can also add up the columns of what it stores
+// (bands[column][block], the first stage of that convolution's bias gradient).
+template <typename T, int HALF, int K>
+__global__ __launch_bounds__(256, 6) void lrn_pool_bwd_kernel(const T *__restrict__ a, const T *__restrict__ dy, const uint8_t *__restrict__ arg,
+                                                         T *__restrict__ da, LrnPool p, float *__restrict__ bands)
+{
+    constexpr int V = Vec16<T>::N;
+    extern __shared__ uint4 tile[];
+    const uint32_t blk = xcd_block();
+    const int n = (int)fdiv32(blk, p.dHb), jy = (int)blk - n * p.Hb;
+    const int lane = threadIdx.x & 63, wl = (int)fdiv32((uint32_t)lane, p.dcv);   // pixel within the wavefront
+    const int cg = lane - wl * p.cv, c0 = cg * V, pl = (int)(threadIdx.x >> 6) * p.wlanes + wl;
+    const bool live = wl < p.wlanes;
+    const int rows = min(2, p.H - 2 * jy);
+    const size_t pooled = (size_t)p.Ho * p.Wo * p.Cp;   // of one image
+    const __amdgpu_buffer_rsrc_t rdy = byte_range(dy + n * pooled, pooled * sizeof(T)), rarg = byte_range(arg + n * pooled, pooled);
+    for (int jx = pl; live && jx < p.Wb; jx += p.lanes) {
+        PoolWindows<T> win;
+        win.load(rdy, rarg, (unsigned)(((jy - 1) * p.Wo + jx - 1) * p.Cp + c0), jy, jx, p.Ho, p.Wo, p.Cp);
+        float acc[4][V];
+        win.template sums<K>(acc);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int by = b >> 1, ix = 2 * jx + (b & 1);
+            if (by < rows && ix < p.W) {
+                Vec16<T> o;
+#pragma unroll
+                for (int e = 0; e < V; ++e) stf(&o.e[e], acc[b][e]);
+                tile[(by * p.W + ix) * p.cv + cg] = o.u;
+            }
+        }
+    }
+    __syncthreads();
+    float colsum[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) colsum[e] = 0.f;
+    const long base = ((long)n * p.H + 2 * jy) * p.W * p.Cp + c0;
+    const int npix = rows * p.W;
+    const bool first = cg == 0, last = cg == p.cv - 1;
+    // channels up to HALF away sit in the next lane, or (four channels a lane, HALF never more than 4) there too
+    static_assert(HALF <= V, "a window reaches no further than the neighbouring lanes");
+    for (int i = pl; live && i < npix; i += p.lanes) {
+        Vec16<T> av, dv;
+        av.u = *reinterpret_cast<const uint4 *>(a + base + (long)i * p.Cp);
+        dv.u = tile[i * p.cv + cg];
+        float f[V + 2 * HALF], t[V + 2 * HALF], pown[V];   // [HALF + e] is channel c0 + e; t: dy * a * s^(-beta-1); pown: s^(-beta)
+#pragma unroll
+        for (int e = 0; e < V; ++e) f[HALF + e] = ldf(&av.e[e]);
+#pragma unroll
+        for (int e = 0; e < HALF; ++e) {
+            const float l = lane_before(f[V + e]), r = lane_after(f[HALF + e]);
+            f[e] = first ? 0.f : l;
+            f[HALF + V + e] = last ? 0.f : r;
+        }
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            float sum = 0.f;
+#pragma unroll
+            for (int r = 0; r <= 2 * HALF; ++r) sum += f[e + r] * f[e + r];
+            const float s = p.bias + p.alpha * sum;
+            pown[e] = pow_neg(s, p.beta);
+            t[HALF + e] = ldf(&dv.e[e]) * f[HALF + e] * (pown[e] * __builtin_amdgcn_rcpf(s));
+        }
+#pragma unroll
+        for (int e = 0; e < HALF; ++e) {
+            const float l = lane_before(t[V + e]), r = lane_after(t[HALF + e]);
+            t[e] = first ? 0.f : l;
+            t[HALF + V + e] = last ? 0.f : r;
+        }
+        Vec16<T> o;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            float acc = 0.f;
+#pragma unroll
+            for (int r = 0; r <= 2 * HALF; ++r) acc += t[e + r];
+            float v = ldf(&dv.e[e]) * pown[e] - 2.f * p.alpha * p.beta * f[HALF + e] * acc;
+            if (!(f[HALF + e] > 0.f)) v = 0.f;
+            stf(&o.e[e], v);
+            colsum[e] += ldf(&o.e[e]);
+        }
+        *reinterpret_cast<uint4 *>(da + base + (long)i * p.Cp) = o.u;
+    }
+    __syncthreads();
+    float *part = reinterpret_cast<float *>(tile);   // [lane][channel]
+    if (live) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) part[pl * p.Cp + c0 + e] = colsum[e];
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < p.Cp; c += 256) {
+        float s = 0.f;
+        for (int j = 0; j < p.lanes; ++j) s += part[j * p.Cp + c];
+        bands[(long)c * gridDim.x + blk] = s;
+    }
+}
+
+// Where the pair runs as one kernel: pools of 2 or 3 with stride 2, rows that fit LDS, pixels that fit a wavefront.
+static bool lrn_pool_plan(int dtype, int H, int W, int Cp, int k, int stride, LrnPool &p, size_t &lds_fwd, size_t &lds_bwd)
+{
+    const int V = dtype == kBF16 ? 8 : 4;
+    if (!pool_bwd_blocks(H, W, Cp, (int)dtype_size(dtype), k, stride) || H < k || W < k) return false;
+    p.H = H; p.W = W; p.Cp = Cp; p.Ho = (H - k) / 2 + 1; p.Wo = (W - k) / 2 + 1; p.cv = Cp / V;
+    if (p.cv > 64) return false;
+    p.cols = 2 * (p.Wo - 1) + k;
+    // 64 bytes of a pixel per block: fewer re-read the row that two blocks share less often, more leave room for fewer rows
+    p.groups = p.cv < 4 ? p.cv : 4;
+    p.chunks = (p.cv + p.groups - 1) / p.groups;
+    const long row = (long)p.cols * p.groups * 16;
+    const long fit = (kLrnPoolLds / row - k) / 2 + 1;   // pooled rows whose input rows fit
+    if (kLrnPoolLds / row < k) return false;
+    p.tiles = (int)((p.Ho + fit - 1) / fit);
+    p.R = (p.Ho + p.tiles - 1) / p.tiles;
+    p.tiles = (p.Ho + p.R - 1) / p.R;
+    lds_fwd = (size_t)(2 * (p.R - 1) + k) * (size_t)row;
+    p.wlanes = 64 / p.cv; p.lanes = 4 * p.wlanes; p.Hb = (H + 1) / 2; p.Wb = (W + 1) / 2;
+    const long tile = 2l * W * p.cv * 16, sums = (long)p.lanes * Cp * 4;
+    if (tile > (64 << 10)) return false;
+    lds_bwd = (size_t)(tile > sums ? tile : sums);
+    p.dgroups = make_fastdiv(p.groups); p.dtiles = make_fastdiv(p.tiles); p.dchunks = make_fastdiv(p.chunks); p.dcols = make_fastdiv(p.cols);
+    p.dWo = make_fastdiv(p.Wo); p.dcv = make_fastdiv(p.cv); p.dHb = make_fastdiv(p.Hb);
+    return true;
+}
+long lrn_pool_bands(int dtype, int B, int H, int W, int Cp, int k, int stride)
+{
+    LrnPool p;
+    size_t f, b;
+    if (!lrn_pool_plan(dtype, H, W, Cp, k, stride, p, f, b)) return 0;
+    if ((long)B * p.tiles * p.chunks > 0x7fffffffL || (long)B * p.Hb > 0x7fffffffL) return 0;
+    return (long)B * p.Hb;
+}
+template <typename T, int HALF>
+static void launch_lrn_pool_t(const LrnPool &p, int B, int k, size_t lds, const void *a, void *y, const void *dy, uint8_t *arg, void *da, float *bands,
+                              hipStream_t s)
+{
+    const T *aa = static_cast<const T *>(a);
+    if (da) {
+        const dim3 grid((unsigned)(B * p.Hb));
+        if (k == 3) hipLaunchKernelGGL((lrn_pool_bwd_kernel<T, HALF, 3>), grid, dim3(256), lds, s, aa, static_cast<const T *>(dy), arg, static_cast<T *>(da), p, bands);
+        else hipLaunchKernelGGL((lrn_pool_bwd_kernel<T, HALF, 2>), grid, dim3(256), lds, s, aa, static_cast<const T *>(dy), arg, static_cast<T *>(da), p, bands);
+    } else {
+        const dim3 grid((unsigned)(B * p.tiles * p.chunks));
+        if (k == 3) hipLaunchKernelGGL((lrn_pool_fwd_kernel<T, HALF, 3>), grid, dim3(256), lds, s, aa, static_cast<T *>(y), arg, p);
+        else hipLaunchKernelGGL((lrn_pool_fwd_kernel<T, HALF, 2>), grid, dim3(256), lds, s, aa, static_cast<T *>(y), arg, p);
+    }
+}
+template <typename T>
+static int launch_lrn_pool(int dtype, int B, int H, int W, int Cp, int size, float alpha, float beta, float bias, int k, const void *a, void *y,
+                           const void *dy, const uint8_t *arg, void *da, float *bands, hipStream_t s)
+{
+    LrnPool p;
+    size_t lf, lb;
+    if (size < 1 || size > 9 || !(size & 1) || !(bias > 0.f)) return -1;
+    if (lrn_pool_bands(dtype, B, H, W, Cp, k, 2) == 0 || !lrn_pool_plan(dtype, H, W, Cp, k, 2, p, lf, lb)) return -1;
+    p.alpha = alpha; p.beta = beta; p.bias = bias;
+    const size_t lds = da ? lb : lf;
+    uint8_t *ar = const_cast<uint8_t *>(arg);
+    switch (size / 2) {
+    case 0: launch_lrn_pool_t<T, 0>(p, B, k, lds, a, y, dy, ar, da, bands, s); break;
+    case 1: launch_lrn_pool_t<T, 1>(p, B, k, lds, a, y, dy, ar, da, bands, s); break;
+    case 2: launch_lrn_pool_t<T, 2>(p, B, k, lds, a, y, dy, ar, da, bands, s); break;
+    case 3: launch_lrn_pool_t<T, 3>(p, B, k, lds, a, y, dy, ar, da, bands, s); break;
+    default: launch_lrn_pool_t<T, 4>(p, B, k, lds, a, y, dy, ar, da, bands, s); break;
+    }
+    return launch_ok();
+}
+int launch_lrn_pool_fwd(int dtype, const void *a, void *y, uint8_t *arg, int B, int H, int W, int Cp, int size, float alpha, float beta, float bias, int k,
+                        hipStream_t s)
+{
+    return dtype == kBF16 ? launch_lrn_pool<bf16_t>(dtype, B, H, W, Cp, size, alpha, beta, bias, k, a, y, nullptr, arg, nullptr, nullptr, s)
+                          : launch_lrn_pool<float>(dtype, B, H, W, Cp, size, alpha, beta, bias, k, a, y, nullptr, arg, nullptr, nullptr, s);
+}
+int launch_lrn_pool_bwd(int dtype, const void *a, const void *dy, const uint8_t *arg, void *da, int B, int H, int W, int Cp, int size, float alpha,
+                        float beta, float bias, int k, float *bands, hipStream_t s)
+{
+    return dtype == kBF16 ? launch_lrn_pool<bf16_t>(dtype, B, H, W, Cp, size, alpha, beta, bias, k, a, nullptr, dy, arg, da, bands, s)
+                          : launch_lrn_pool<float>(dtype, B, H, W, Cp, size, alpha, beta, bias, k, a, nullptr, dy, arg, da, bands, s);
 }
 
 // ---------------------------------------------------------------- flatten / unflatten

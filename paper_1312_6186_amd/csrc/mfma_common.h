@@ -167,7 +167,7 @@ __device__ __forceinline__ void mma(f32x16 &acc, const Frag<float> &first, const
 }
 
 // ------------------------------------------------------------------ epilogue
-__device__ __forceinline__ uint64_t mix64(uint64_t z)
+__host__ __device__ __forceinline__ uint64_t mix64(uint64_t z)
 {
     z ^= z >> 30; z *= 0xBF58476D1CE4E5B9ull;
     z ^= z >> 27; z *= 0x94D049BB133111EBull;

@@ -300,6 +300,59 @@ def test_stride1_filter_gradient_shapes(shape):
         g.close()
 
 
+# Response normalisation with a pool of stride 2 on top, one kernel each way: channels around a wavefront's 64 groups of 16 bytes
+# (512 channels in bf16, 256 in fp32; more run separate kernels) and with padding channels, rows around the width that fits
+# the forward kernel's LDS (213 pixels for windows of 3), one pooled row, an odd last row and column, every window size.
+LRNPOOL_SHAPES = [(8, 3, 4, 3, 1, 3), (12, 9, 10, 2, 5, 3), (96, 23, 21, 3, 5, 3), (40, 13, 14, 2, 9, 2), (256, 9, 6, 2, 3, 3), (264, 5, 6, 1, 7, 2), (512, 6, 5, 1, 5, 3),
+                  (520, 5, 5, 1, 5, 3), (8, 7, 213, 1, 5, 3), (8, 7, 216, 1, 5, 3), (16, 4, 320, 1, 5, 2)]
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("shape", LRNPOOL_SHAPES, ids=lambda s: "%d_%dx%dx%d_n%d_k%d" % s)
+def test_normalised_pool_shapes(shape, dtype):
+    c, h, w, batch, size, k = shape
+    layers = [("conv", c, 3, 1, 1), ("relu",), ("lrn", size, 0.05, 0.75, 2.0), ("maxpool", k, 2), ("fc", 10), ("softmax_ce",)]
+    g, onet, (loss, grads), (ref_loss, ref_grads, _), _ = _net_case({"name": "lrnpool", "in_shape": (3, h, w), "classes": 10, "layers": layers}, batch, dtype, plain=False)
+    try:
+        assert abs(loss - ref_loss) <= TOL[dtype] * abs(ref_loss)
+        compare_grads(onet, grads, ref_grads, TOL[dtype], "lrnpool")
+    finally:
+        g.close()
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("relu,lrn", [(True, False), (True, True), (False, False)])
+def test_pooling_of_infinities_and_nans(relu, lrn, dtype):
+    """A window's result is its first maximum in row-major order; a NaN is one only where it comes first (no later value
+    compares greater).  Infinite pixels make NaNs in the channels beside them and in their normalisation."""
+    C, H, W, batch, k = 16, 13, 11, 3, 3
+    layers = [("conv", C, 1, 1, 0)] + [("relu",)] * relu + [("lrn", 5, 1e-4, 0.75, 2.0)] * lrn + [("maxpool", k, 2), ("fc", 10), ("softmax_ce",)]
+    rng = np.random.default_rng(11)
+    onet = oracle.OracleNet(layers, (C, H, W))
+    params = np.zeros(onet.param_count, dtype=np.float32)
+    params[:C * C] = np.eye(C, dtype=np.float32).reshape(-1)
+    images = (rng.integers(-3, 4, size=(batch, C, H, W)) * 0.25).astype(np.float32)
+    images[rng.random(images.shape) < 0.01] = np.inf
+    images[rng.random(images.shape) < 0.003] = -np.inf
+    g = GpuNet(layers, (C, H, W), batch, dtype)
+    try:
+        g.fwd_bwd(params, images, rng.integers(0, 10, batch).astype(np.int32))
+        below, at = 1 + relu + lrn - 1, 1 + relu + lrn
+        x = g.debug(B.DEBUG_OUTPUT, below)
+        y, idx = g.debug(B.DEBUG_OUTPUT, at), g.debug(B.DEBUG_ARGMAX, at)
+        best, pos = x[:, :, 0:H - 2:2, 0:W - 2:2].copy(), np.zeros(y.shape, np.uint8)
+        for p in range(1, k * k):
+            v = x[:, :, p // k:H - 2 + p // k:2, p % k:W - 2 + p % k:2]
+            up = v > best
+            best[up], pos[up] = v[up], p
+        np.testing.assert_array_equal(y, best)
+        np.testing.assert_array_equal(idx, pos)
+        assert np.isinf(x).any() or lrn
+        assert np.isnan(x).any() or (relu and not lrn)
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
 @pytest.mark.parametrize("k,stride", [(2, 2), (3, 2), (3, 1)])
 def test_pooling_positions_are_bit_exact(k, stride, dtype):
