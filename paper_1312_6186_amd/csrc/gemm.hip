@@ -565,6 +565,70 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::MINB) void gemm_kernel(LA la, LB lb, 
     output_tile<T, Cfg, (int)sizeof(smem), Cfg::NT, LA::kTrans && LB::kTrans>(smem, acc, ep, tm, tn, split, M, N, ws, bias8, tid, wm, wn);
 }
 
+// Weight gradients of fully-connected layers, C[out][in] = sum over the minibatch: a short reduction, and C in fp32 is far more
+// bytes than its operands, so what counts is that stores leave the CUs without a pause.  One LDS stage of K, an output
+// phase in which every wave moves its own blocks through 4 KB of LDS without a barrier, and three workgroups a CU: the stores of one run under
+// the loads of the others.  A wave's 32 columns of a row are one line of memory and leave in one instruction: non-temporal
+// stores of whole lines.  (Plain stores straight from the accumulators, 32 bytes of a row at a time, take the same time
+// alone, but the dirty lines they leave in L2 cost the data gradients beside them 4 % of a step.)
+// 4096 x 9216 in bf16, 32 images: 54 -> 30 us (5.0 TB/s; a fill runs at 6.6), 77 images 47 -> 30; 4096 x 4096 24 -> 14; fp32, 128 images
+// (two thirds of the matrix rate) 112 -> 105.
+template <typename T>
+__global__ __launch_bounds__(512, sizeof(T) == 2 ? 6 : 4) void outer_kernel(PlainT<T> la, PlainT<T> lb, float *out, long ld, int M, int N, int K, int tiles_n)
+{
+    constexpr int BK = Geo<T>::BK, KS = Geo<T>::KSTEPS, BYTES = TransTile<T, 128>::BYTES;
+    __shared__ uint4 smem[2 * BYTES / 16];
+    uint4 *sA = smem, *sB = smem + BYTES / 16;
+    const int tid = threadIdx.x;
+    int bid;
+    {
+        const int nb = gridDim.x, q = nb >> 3, r = nb & 7, x = blockIdx.x & 7;
+        bid = x * q + (x < r ? x : r) + (blockIdx.x >> 3);
+    }
+    const int tm = bid / tiles_n, tn = bid - tm * tiles_n;
+    Stage<T, PlainT<T>, 128, 512, 1> stA, stB;
+    stA.init(la, tm * 128, 0, tid, 0);
+    stB.init(lb, tn * 128, 0, tid, 0);
+    f32x16 acc[2];
+    acc[0] = f32x16{}; acc[1] = f32x16{};
+    const int lane = tid & 63, wave = tid >> 6, wm = (wave & 1) * 64, wn = (wave >> 1) * 32;
+    FragOff<T, true, 128> foA, foB;
+    foA.init(wm, lane);
+    foB.init(wn, lane);
+    const bool busy = __builtin_amdgcn_readfirstlane((tm * 128 + wm < M && tn * 128 + wn < N) ? 1 : 0) != 0;
+    stA.template load<0>(la); stB.template load<0>(lb);
+    for (int k = 0; k < K; k += BK) {
+        if (k) __syncthreads();
+        stA.template store<0>(sA, tid); stB.template store<0>(sB, tid);
+        __syncthreads();
+        if (k + BK < K) { stA.template load<0>(la); stB.template load<0>(lb); }
+        if (!busy) continue;
+        static_for<0, KS>([&](auto ks) ASGD_INLINE {
+            if (k + ks * 16 < K) {
+                Frag<T> fa[2], fb;
+                fb.template read<ks, 0>(reinterpret_cast<const char *>(sB), foB);
+                static_for<0, 2>([&](auto i) ASGD_INLINE { fa[i].template read<ks, i>(reinterpret_cast<const char *>(sA), foA); });
+                static_for<0, 2>([&](auto i) ASGD_INLINE { mma(acc[i], fb, fa[i]); });
+            }
+        });
+    }
+    // through LDS, each wave on its own: 32 columns of a row are one line of memory, a store instruction writes eight of them
+    const int lrow = lane & 31, half = lane >> 5;
+    __syncthreads();
+    f32x4 *stg = reinterpret_cast<f32x4 *>(smem) + wave * 256;
+    static_for<0, 2>([&](auto mb) ASGD_INLINE {
+        static_for<0, 4>([&](auto g) ASGD_INLINE {
+            stg[lrow * 8 + ((2 * g + half) ^ (lrow & 7))] = f32x4{acc[mb][4 * g], acc[mb][4 * g + 1], acc[mb][4 * g + 2], acc[mb][4 * g + 3]};
+        });
+        const int piece = lane & 7, n = tn * 128 + wn + piece * 4;
+        static_for<0, 4>([&](auto r) ASGD_INLINE {
+            const int row = r * 8 + (lane >> 3), m = tm * 128 + wm + mb * 32 + row;
+            const f32x4 v = stg[row * 8 + (piece ^ (row & 7))];
+            if (m < M && n < N) __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(__builtin_assume_aligned(out + (long)m * ld + n, 16)));
+        });
+    });
+}
+
 // gemm_kernel with the waves of a workgroup in two roles: Cfg::NT / 64 waves read
 // fragments and multiply (wave tiles of 64 x 64), four more fetch both operands and move them into LDS.  Step t of
 // a fetching wave: after the barrier, tile t+1 (fetched two steps ago) goes from its register set into the LDS stage
@@ -1309,6 +1373,25 @@ int gemm_plain_trans(int dtype, const void *a, long lda, int M, const void *bt, 
     return run<float>(make_plain_k<float>(a, lda, M, K), make_plain_t<float>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);
 }
 
+// Where outer_kernel runs: plain fp32 sums (no push), stores of 16 bytes, and either a tile for every CU or hardly a loop: with few
+// tiles the K loop is what takes the time, and gemm_kernel fetches two K tiles ahead.  Serial pass of three layers of 4096, 4096 and
+// 1000 outputs, gemm_kernel / here: bf16 128 images 204 / 168 us, 256 images 261 / 228, 512 images 366 / 346; fp32 460 / 417, 760 / 720,
+// 1337 / 1299.  Of 64 and 10 outputs over 576 inputs: bf16 128 images 56.0 / 54.7, 2048 images 96 / 102; fp32 512 images 104 / 109.
+template <typename T> static bool outer_applies(int M, int N, int K, const Epilogue &ep, const GemmPlan &plan)
+{
+    if (ep.upd_w || plan.splits != 1 || ep.mode != 0 || !ep.out_f32 || ep.bias || ep.relu || ep.drop || ep.mask_src) return false;
+    const long tiles = ((M + 127) / 128) * (long)((N + 127) / 128);
+    if (!(K <= 2 * (int)Geo<T>::BK || (tiles >= 256 && K <= 512))) return false;
+    return M > 0 && N > 0 && K > 0 && N % 8 == 0 && ep.ld % 4 == 0 && ((uintptr_t)ep.out & 15) == 0;
+}
+template <typename T> static int run_outer(const PlainT<T> &la, const PlainT<T> &lb, int M, int N, int K, const Epilogue &ep, hipStream_t s)
+{
+    if (la.op.bytes == 0 || lb.op.bytes == 0) return -1;
+    const long tiles_n = (N + 127) / 128, blocks = (long)((M + 127) / 128) * tiles_n;
+    if (blocks > 0x7fffffffL) return -1;
+    hipLaunchKernelGGL((outer_kernel<T>), dim3((unsigned)blocks), dim3(512), 0, s, la, lb, static_cast<float *>(ep.out), ep.ld, M, N, K, (int)tiles_n);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
 int gemm_trans_trans(int dtype, const void *at, long lda, int M, const void *bt, long ldb, int N, int K, const Epilogue &ep,
                      const GemmPlan &plan, float *ws, hipStream_t s)
 {
@@ -1318,8 +1401,10 @@ int gemm_trans_trans(int dtype, const void *at, long lda, int M, const void *bt,
         if (plan.splits != 1 || ep.mode != 0 || !ep.upd_v || !ep.upd_copy || (al & 15) || (ep.ld & 7)) return -1;
     }
     if (dtype == kBF16)
-        return run<bf16_t>(make_plain_t<bf16_t>(at, lda, M, K), make_plain_t<bf16_t>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);
-    return run<float>(make_plain_t<float>(at, lda, M, K), make_plain_t<float>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);
+        return outer_applies<bf16_t>(M, N, K, ep, plan) ? run_outer(make_plain_t<bf16_t>(at, lda, M, K), make_plain_t<bf16_t>(bt, ldb, N, K), M, N, K, ep, s)
+                                                        : run<bf16_t>(make_plain_t<bf16_t>(at, lda, M, K), make_plain_t<bf16_t>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);
+    return outer_applies<float>(M, N, K, ep, plan) ? run_outer(make_plain_t<float>(at, lda, M, K), make_plain_t<float>(bt, ldb, N, K), M, N, K, ep, s)
+                                                   : run<float>(make_plain_t<float>(at, lda, M, K), make_plain_t<float>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);
 }
 
 // The filter gradient of a first convolution in window-row form (16-bit data, up to 96 output channels, up to 448 K

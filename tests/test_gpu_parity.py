@@ -300,6 +300,21 @@ def test_stride1_filter_gradient_shapes(shape):
         g.close()
 
 
+# Weight gradients of fully-connected layers: tiles of 128 x 128 with ragged edges on both sides, batches around the K tiles (64 in
+# bf16, 32 in fp32) and around the limits of the kernel for short sums (two K tiles; 512 with 256 tiles and more).
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("out,batch", [(136, 1), (200, 31), (128, 64), (72, 65), (264, 128), (40, 129), (2040, 33), (2056, 512), (2048, 513)])
+def test_fc_weight_gradient_shapes(out, batch, dtype):
+    shape = (8, 8, 8) if out < 1000 else (32, 8, 8)
+    layers = [("fc", out), ("relu",), ("fc", 10), ("softmax_ce",)]
+    g, onet, (loss, grads), (ref_loss, ref_grads, _), _ = _net_case({"name": "fc", "in_shape": shape, "classes": 10, "layers": layers}, batch, dtype, plain=False)
+    try:
+        assert abs(loss - ref_loss) <= TOL[dtype] * abs(ref_loss)
+        compare_grads(onet, grads, ref_grads, TOL[dtype], "fc")
+    finally:
+        g.close()
+
+
 # Response normalisation with a pool of stride 2 on top, one kernel each way: channels around a wavefront's 64 groups of 16 bytes
 # (512 channels in bf16, 256 in fp32; more run separate kernels) and with padding channels, rows around the width that fits
 # the forward kernel's LDS (213 pixels for windows of 3), one pooled row, an odd last row and column, every window size.
