@@ -664,10 +664,96 @@ int forward(asgd_net *n, const void *params, const void *images, const int32_t *
 // and its data gradient, the last reader of the old values, has been issued.
 struct ServerArgs {
     float *master, *momentum;
-    void *copy;          // the replica's parameters (== params of the step), compute dtype
     float lr, mu, wd;
-    bool fuse;           // fully-connected weights: the push happens inside the weight-gradient kernel, which stores no gradient
+    bool fuse;           // fully-connected weights: the push happens inside the weight-gradient kernel
+    void *copy[kPushCopies] = {};   // replicas' parameters that the push refreshes, compute dtype (copy[0]: those of the step, where a step pushes)
+    int copies = 0;
+    // with fuse
+    bool keep = false;       // ... which stores the gradient too
+    bool later = false;      // the gradient kernels leave the push to push_gradient
+    float *acc = nullptr;    // the gradient is added up here (written if acc_first)
+    bool acc_first = false;
+    int *counter = nullptr;  // advanced once the push is done, and logged for every fetch it does
+    int32_t *log[kPushCopies] = {};
+    int log_update[kPushCopies] = {}, log_worker[kPushCopies] = {}, logs = 0;
 };
+
+// Whether a fully-connected layer's weights can be pushed by its weight-gradient kernel: whole sums (no split-K) and
+// 16-byte rows in the parameter-shaped buffers.
+bool fused_fc(const Stage &s) { return s.kind == ST_FC && s.p_wgrad.splits == 1 && s.in_f % 8 == 0 && s.w_off % 8 == 0; }
+
+// The weight gradient of fully-connected layer si, stored, or pushed if srv is given.
+int fc_weight_grad(asgd_net *n, int si, float *grads, const ServerArgs *srv, hipStream_t st)
+{
+    const Stage &s = n->stages[si];
+    const void *x = s.in_is_spatial ? s.flat_in : n->stages[si - 1].out;
+    const long ldx = s.in_is_spatial ? s.in_f : n->stages[si - 1].out_ld;
+    const double es = (double)dtype_size(n->dtype), Bd = n->batch;
+    Epilogue ew;
+    ew.out = grads + s.w_off; ew.ld = s.in_f; ew.out_f32 = 1;
+    if (srv) {
+        if (!srv->keep) ew.out = nullptr;
+        ew.upd_w = srv->master + s.w_off; ew.upd_v = srv->momentum + s.w_off;
+        for (int c = 0; c < srv->copies; ++c) ew.upd_copy[c] = static_cast<char *>(srv->copy[c]) + s.w_off * dtype_size(n->dtype);
+        ew.upd_copies = srv->copies;
+        if (srv->acc) { ew.upd_acc = srv->acc + s.w_off; ew.upd_acc_first = srv->acc_first; }
+        ew.upd_lr = srv->lr; ew.upd_mu = srv->mu; ew.upd_wd = srv->wd;
+    }
+    ProfScope ps(n, st, ASGD_K_FC_WGRAD, 2 * Bd * s.in_f * s.out_f,
+                 Bd * (s.in_f + s.out_f) * es + (double)s.w_cnt * (srv ? 16.0 + es * srv->copies + (srv->keep ? 4.0 : 0.0) + (srv->acc ? srv->acc_first ? 4.0 : 8.0 : 0.0) : 4.0));
+    CHECK_LAUNCH(gemm_trans_trans(n->dtype, s.dout, s.out_ld, s.out_f, x, ldx, s.in_f, n->batch, ew, s.p_wgrad, n->scratch_side, st), "fc weight gradient");
+    return ASGD_OK;
+}
+
+// Pushes everything that the gradient kernels do not push themselves: maximal runs of adjacent slices, up to eight runs per
+// launch (for an AlexNet-style net: all convolution layers in one run, then one run per fully-connected bias).
+int push_rest(asgd_net *n, const float *grads, const ServerArgs &srv, hipStream_t st)
+{
+    PushRanges p = {};
+    p.w = srv.master; p.v = srv.momentum; p.g = grads; p.acc = srv.acc; p.acc_first = srv.acc_first; p.lr = srv.lr; p.mu = srv.mu; p.wd = srv.wd;
+    for (int c = 0; c < srv.copies; ++c) { p.copy[c] = srv.copy[c]; p.f32mask |= n->dtype == kF32 ? 1u << c : 0u; }
+    p.ncopies = srv.copies;
+    const double es = (double)dtype_size(n->dtype);
+    auto flush = [&](bool last) -> int {
+        if (last) {
+            p.counter = srv.counter; p.nlogs = srv.logs;
+            for (int c = 0; c < srv.logs; ++c) { p.log[c] = srv.log[c]; p.log_update[c] = srv.log_update[c]; p.log_worker[c] = srv.log_worker[c]; }
+        }
+        double total = 0;
+        for (int q = 0; q < p.n; ++q) total += (double)p.cnt[q];
+        ProfScope ps(n, st, ASGD_K_UPDATE, 0, total * (20.0 + es * srv.copies));
+        if (launch_push_ranges(p, st) != 0) return hip_fail(hipGetLastError(), "update kernel");
+        p.n = 0;
+        return ASGD_OK;
+    };
+    auto add = [&](size_t off, size_t cnt) -> int {
+        if (cnt == 0) return ASGD_OK;
+        if (p.n && p.off[p.n - 1] + p.cnt[p.n - 1] == off) { p.cnt[p.n - 1] += cnt; return ASGD_OK; }
+        if (p.n == 8) { const int rc = flush(false); if (rc != ASGD_OK) return rc; }
+        p.off[p.n] = off; p.cnt[p.n] = cnt; ++p.n;
+        return ASGD_OK;
+    };
+    for (const Stage &s : n->stages) {
+        if (!s.has_params()) continue;
+        int rc = ASGD_OK;
+        if (!fused_fc(s)) rc = add(s.w_off, s.w_cnt);
+        if (rc == ASGD_OK) rc = add(s.b_off, s.b_cnt);
+        if (rc != ASGD_OK) return rc;
+    }
+    return flush(true);
+}
+
+// The push of a gradient whose kernels left it (ServerArgs::later) on another stream, behind the backward pass that
+// left the layers' inputs and output gradients in the plan's workspace.
+int push_gradient(asgd_net *n, float *grads, const ServerArgs &srv, hipStream_t st)
+{
+    for (int si = (int)n->stages.size() - 1; si >= 0; --si)
+        if (fused_fc(n->stages[si])) {
+            const int rc = fc_weight_grad(n, si, grads, &srv, st);
+            if (rc != ASGD_OK) return rc;
+        }
+    return push_rest(n, grads, srv, st);
+}
 
 int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStream_t st, const ServerArgs *srv)
 {
@@ -681,11 +767,6 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
     double bias_s1_bytes = 0;
     int first_param = -1;
     for (int q = 0; q < (int)n->stages.size() && first_param < 0; ++q) if (n->stages[q].has_params()) first_param = q;
-    // Whether a fully-connected layer's weights are pushed by its weight-gradient kernel: whole sums (no split-K) and
-    // 16-byte rows in the three parameter-shaped buffers.
-    auto fused_fc = [&](const Stage &s) -> bool {
-        return srv && srv->fuse && s.kind == ST_FC && s.p_wgrad.splits == 1 && s.in_f % 8 == 0 && s.w_off % 8 == 0;
-    };
     // Push by layer (asgd_train_step), or, with fused fully-connected weights, everything else in one pass per
     // contiguous range behind the backward pass.
     const bool by_layer = srv && !srv->fuse;
@@ -725,7 +806,7 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
         const size_t off = s.w_off, cnt = s.w_cnt + s.b_cnt;   // weights and bias of a layer are adjacent
         ProfScope ps(n, sd, ASGD_K_UPDATE, 0, (double)cnt * (20.0 + es));
         if (launch_update_snapshot(srv->master + off, srv->momentum + off, grads + off, cnt, srv->lr, srv->mu, srv->wd,
-                                   static_cast<char *>(srv->copy) + off * dtype_size(dt), dt, sd) != 0)
+                                   static_cast<char *>(srv->copy[0]) + off * dtype_size(dt), dt, sd) != 0)
             return hip_fail(hipGetLastError(), "update kernel");
         return ASGD_OK;
     };
@@ -738,22 +819,10 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
             CHECK_HIP(hipStreamWaitEvent(sd, n->ev_dy[si], 0), "hipStreamWaitEvent");
         }
         if (s.kind == ST_FC) {
-            const void *x = s.in_is_spatial ? s.flat_in : xin;
-            const long ldx = s.in_is_spatial ? s.in_f : prev->out_ld;
-            const bool fused = fused_fc(s);
+            const bool fused = srv && srv->fuse && fused_fc(s);
             auto param_grads = [&]() -> int {
-                Epilogue ew;
-                ew.out = grads + s.w_off; ew.ld = s.in_f; ew.out_f32 = 1;
-                if (fused) {
-                    ew.upd_w = srv->master + s.w_off; ew.upd_v = srv->momentum + s.w_off;
-                    ew.upd_copy = static_cast<char *>(srv->copy) + s.w_off * dtype_size(dt);
-                    ew.upd_lr = srv->lr; ew.upd_mu = srv->mu; ew.upd_wd = srv->wd;
-                }
-                {
-                    ProfScope ps(n, sd, ASGD_K_FC_WGRAD, 2 * Bd * s.in_f * s.out_f,
-                                 Bd * (s.in_f + s.out_f) * es + (double)s.w_cnt * (fused ? 16.0 + es : 4.0));
-                    CHECK_LAUNCH(gemm_trans_trans(dt, s.dout, s.out_ld, s.out_f, x, ldx, s.in_f, B, ew, s.p_wgrad, n->scratch_side, sd), "fc weight gradient");
-                }
+                const int rc = fused && srv->later ? ASGD_OK : fc_weight_grad(n, si, grads, fused ? srv : nullptr, sd);
+                if (rc != ASGD_OK) return rc;
                 return bias_sums(s.dout, s.out_ld, B, s.out_f, grads + s.b_off, s.colsum_ws, Bd * s.out_f * es + s.out_f * 4.0, "fc bias gradient");
             };
             auto data_grad = [&]() -> int {
@@ -917,39 +986,7 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
         CHECK_HIP(hipEventRecord(n->ev_join, sd), "hipEventRecord");
         CHECK_HIP(hipStreamWaitEvent(st, n->ev_join, 0), "hipStreamWaitEvent");
     }
-    if (srv && srv->fuse) {
-        // everything the gradient kernels have not pushed themselves: maximal runs of adjacent slices, up to eight runs
-        // per launch (for an AlexNet-style net: all convolution layers in one run, then one run per fully-connected bias)
-        size_t offs[8], cnts[8];
-        int nr = 0;
-        auto flush = [&]() -> int {
-            if (nr == 0) return ASGD_OK;
-            double total = 0;
-            for (int q = 0; q < nr; ++q) total += (double)cnts[q];
-            ProfScope ps(n, st, ASGD_K_UPDATE, 0, total * (20.0 + es));
-            if (launch_update_snapshot_ranges(srv->master, srv->momentum, grads, offs, cnts, nr, srv->lr, srv->mu, srv->wd, srv->copy, dt, st) != 0)
-                return hip_fail(hipGetLastError(), "update kernel");
-            nr = 0;
-            return ASGD_OK;
-        };
-        auto add = [&](size_t off, size_t cnt) -> int {
-            if (cnt == 0) return ASGD_OK;
-            if (nr && offs[nr - 1] + cnts[nr - 1] == off) { cnts[nr - 1] += cnt; return ASGD_OK; }
-            if (nr == 8) { const int rc = flush(); if (rc != ASGD_OK) return rc; }
-            offs[nr] = off; cnts[nr] = cnt; ++nr;
-            return ASGD_OK;
-        };
-        for (const Stage &s : n->stages) {
-            if (!s.has_params()) continue;
-            int rc = ASGD_OK;
-            if (!fused_fc(s)) rc = add(s.w_off, s.w_cnt);
-            if (rc == ASGD_OK) rc = add(s.b_off, s.b_cnt);
-            if (rc != ASGD_OK) return rc;
-        }
-        const int rc = flush();
-        if (rc != ASGD_OK) return rc;
-    }
-    return ASGD_OK;
+    return srv && srv->fuse && !srv->later ? push_rest(n, grads, *srv, st) : ASGD_OK;
 }
 
 }  // namespace
@@ -1025,8 +1062,10 @@ int asgd_layer_shape(const asgd_net_t *net, int layer, int32_t chw[3])
 
 size_t asgd_workspace_bytes(const asgd_net_t *net) { return net ? net->ws_bytes : 0; }
 
-int asgd_fwd_bwd(asgd_net_t *net, const void *params, const void *images, const int32_t *labels, uint64_t dropout_seed, uint64_t step,
-                 uint32_t worker, float *loss, float *grads, void *stream)
+}  // extern "C"
+
+static int fwd_bwd(asgd_net_t *net, const void *params, const void *images, const int32_t *labels, uint64_t dropout_seed, uint64_t step, uint32_t worker,
+                   float *loss, float *grads, void *stream, const ServerArgs *srv)
 {
     if (!net || !params || !images || !labels || !loss || !grads) return fail(ASGD_EINVAL, "asgd_fwd_bwd: null argument");
     if (((uintptr_t)params | (uintptr_t)grads | (uintptr_t)images) & 15) return fail(ASGD_EALIGN, "asgd_fwd_bwd: params, images and grads must be 16-byte aligned");
@@ -1037,7 +1076,15 @@ int asgd_fwd_bwd(asgd_net_t *net, const void *params, const void *images, const 
     rc = forward(net, params, images, labels, dropout_seed, step, worker, st);
     if (rc != ASGD_OK) return rc;
     net->last_seed = dropout_seed; net->last_step = step; net->last_worker = worker; net->ran = true;
-    return backward(net, params, loss, grads, st, nullptr);
+    return backward(net, params, loss, grads, st, srv);
+}
+
+extern "C" {
+
+int asgd_fwd_bwd(asgd_net_t *net, const void *params, const void *images, const int32_t *labels, uint64_t dropout_seed, uint64_t step,
+                 uint32_t worker, float *loss, float *grads, void *stream)
+{
+    return fwd_bwd(net, params, images, labels, dropout_seed, step, worker, loss, grads, stream, nullptr);
 }
 
 // ---- the entry point that allocates nothing
@@ -1117,7 +1164,8 @@ int train_step_impl(const char *name, bool fuse, asgd_net_t *net, float *master,
     rc = forward(net, worker_copy, images, labels, dropout_seed, step, worker, st);
     if (rc != ASGD_OK) return rc;
     net->last_seed = dropout_seed; net->last_step = step; net->last_worker = worker; net->ran = true;
-    const ServerArgs srv{master, momentum, worker_copy, lr, mu, wd, fuse};
+    ServerArgs srv{master, momentum, lr, mu, wd, fuse};
+    srv.copy[0] = worker_copy; srv.copies = 1;
     return backward(net, worker_copy, loss, grads, st, &srv);
 }
 }  // namespace
@@ -1344,6 +1392,18 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
     for (int w = 0; w < n_workers; ++w) RP(hipStreamWaitEvent(ws[w], ev_start, 0));
     if (rc == ASGD_OK && launch_fill_zero(counter, 4, server) != 0) rc = hip_fail(hipGetLastError(), "fill kernel");
     RP(hipEventRecord(ev_reset, server));
+    // The push of the fully-connected weights happens inside their weight-gradient kernel, on the server's stream (in the n_sync
+    // regime that of a local step, on the replica's), and update v writes the copies of the replicas that fetch version
+    // v + 1 in the same pass: 18 bytes a weight and update instead of 30, 26 a local step instead of 38.  Only the last
+    // gradient of a replica is stored as well, so that worker_grads hold what separate calls would leave.  Buffers
+    // that are not 16-byte aligned go through the separate kernels.
+    uintptr_t align = (uintptr_t)params | (uintptr_t)momentum;
+    for (int w = 0; w < n_workers; ++w) {
+        align |= (uintptr_t)worker_copy[w] | (uintptr_t)worker_grads[w];
+        if (loc) align |= (uintptr_t)loc->params[w] | (uintptr_t)loc->momentum[w] | (uintptr_t)loc->accum[w];
+    }
+    const bool fused = (align & 15) == 0;
+    std::vector<char> fetched(T, 0);   // the fetch of update a was done by update read_version[a] - 1
     // Iteration v enqueues every snapshot that must see exactly v applied updates
     // (and the gradient computed on it), then update v, which waits for them.
     for (int v = 0; v < T && rc == ASGD_OK; ++v) {
@@ -1351,17 +1411,27 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
             if (read_version[a] != v) continue;
             const int w = worker[a];
             RP(hipStreamWaitEvent(ws[w], v > 0 ? ev_upd[v - 1] : ev_reset, 0));
+            if (!fetched[a]) {
             if (launch_snapshot(params, worker_copy[w], P, n0->dtype, counter, log + 3 * (size_t)a, a, w, ws[w]) != 0 && rc == ASGD_OK)
                 rc = hip_fail(hipGetLastError(), "snapshot kernel");
             if (loc && launch_snapshot(params, loc->params[w], P, kF32, nullptr, nullptr, 0, 0, ws[w]) != 0 && rc == ASGD_OK)
                 rc = hip_fail(hipGetLastError(), "snapshot kernel");   // the replica's own fp32 parameters
             RP(hipEventRecord(ev_snap[a], ws[w]));
+            }
             for (int i = 0; i < n_sync && rc == ASGD_OK; ++i) {
                 const size_t b = (size_t)a * n_sync + i;   // minibatch and dropout step of local step i of cycle a
-                rc = asgd_fwd_bwd(nets[w], worker_copy[w], static_cast<const char *>(images) + b * img_bytes, labels + b * n0->batch,
-                                  dropout_seed, (uint64_t)b, (uint32_t)w, losses + b, worker_grads[w], ws[w]);
-                if (loc && rc == ASGD_OK) {
-                    // the push is the sum of the cycle's gradients; the replica keeps training on its own parameters
+                ServerArgs step{params, momentum, lr, mu, wd, true};
+                if (loc) {   // the push is the sum of the cycle's gradients; the replica keeps training on its own parameters
+                    step.master = loc->params[w]; step.momentum = loc->momentum[w];
+                    step.copy[0] = worker_copy[w]; step.copies = 1;
+                    step.acc = loc->accum[w]; step.acc_first = i == 0;
+                    step.keep = i == n_sync - 1 && last_push[w] == a;
+                } else {
+                    step.later = true;
+                }
+                rc = fwd_bwd(nets[w], worker_copy[w], static_cast<const char *>(images) + b * img_bytes, labels + b * n0->batch,
+                             dropout_seed, (uint64_t)b, (uint32_t)w, losses + b, worker_grads[w], ws[w], fused ? &step : nullptr);
+                if (loc && !fused && rc == ASGD_OK) {
                     if (launch_accumulate(loc->accum[w], worker_grads[w], P, i == 0, ws[w]) != 0) rc = hip_fail(hipGetLastError(), "accumulate kernel");
                     else if (launch_update_snapshot(loc->params[w], loc->momentum[w], worker_grads[w], P, lr, mu, wd, worker_copy[w], n0->dtype,
                                                     ws[w]) != 0)
@@ -1371,9 +1441,35 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
             RP(hipEventRecord(ev_grad[a], ws[w]));
         }
         for (int a = v; a < T && rc == ASGD_OK; ++a)
-            if (read_version[a] == v) RP(hipStreamWaitEvent(server, ev_snap[a], 0));
+            if (read_version[a] == v && !fetched[a]) RP(hipStreamWaitEvent(server, ev_snap[a], 0));
         RP(hipStreamWaitEvent(server, ev_grad[v], 0));
-        if (rc == ASGD_OK && launch_update(params, momentum, loc ? loc->accum[worker[v]] : worker_grads[worker[v]], P, lr, mu, wd, counter, server) != 0)
+        if (fused && rc == ASGD_OK) {
+            // a replica that fetches version v + 1 has pushed its last gradient by update v at the latest: its copy is free
+            ServerArgs push{params, momentum, lr, mu, wd, true};
+            int reader[kPushCopies];
+            for (int a = v + 1; a < T && push.copies < kPushCopies; ++a) {
+                if (read_version[a] != v + 1) continue;
+                const int c = push.copies++;
+                reader[c] = worker[a]; push.copy[c] = worker_copy[worker[a]]; push.log[c] = log + 3 * (size_t)a; push.log_update[c] = a; push.log_worker[c] = worker[a];
+                fetched[a] = 1;
+            }
+            push.logs = push.copies; push.counter = counter;
+            if (!loc) {
+                push.keep = last_push[worker[v]] == v;
+                rc = push_gradient(nets[worker[v]], worker_grads[worker[v]], push, server);
+            } else {
+                PushRanges p = {};
+                p.w = params; p.v = momentum; p.g = loc->accum[worker[v]]; p.lr = lr; p.mu = mu; p.wd = wd;
+                p.n = 1; p.off[0] = 0; p.cnt[0] = P;
+                for (int c = 0; c < push.copies; ++c) {   // a fetch fills the compute copy and the replica's own parameters
+                    p.copy[p.ncopies] = push.copy[c]; p.f32mask |= n0->dtype == kF32 ? 1u << p.ncopies : 0u; ++p.ncopies;
+                    p.copy[p.ncopies] = loc->params[reader[c]]; p.f32mask |= 1u << p.ncopies; ++p.ncopies;
+                    p.log[c] = push.log[c]; p.log_update[c] = push.log_update[c]; p.log_worker[c] = push.log_worker[c];
+                }
+                p.nlogs = push.copies; p.counter = counter;
+                if (launch_push_ranges(p, server) != 0) rc = hip_fail(hipGetLastError(), "update kernel");
+            }
+        } else if (rc == ASGD_OK && launch_update(params, momentum, loc ? loc->accum[worker[v]] : worker_grads[worker[v]], P, lr, mu, wd, counter, server) != 0)
             rc = hip_fail(hipGetLastError(), "update kernel");
         RP(hipEventRecord(ev_upd[v], server));
     }

@@ -20,6 +20,8 @@ struct FastDiv {
 };
 FastDiv make_fastdiv(uint32_t d);
 
+constexpr int kPushCopies = 4;   // replicas' copies that one push can write besides the parameters
+
 // What happens to one accumulator element C[m][n] on its way to memory.
 // The same routine serves the GEMM kernels and the split-K reduction.
 struct Epilogue {
@@ -41,11 +43,13 @@ struct Epilogue {
                            // 2: columns are (ky, kx*cw_rwc+ci) over window rows of cw_cinp elements -> the same
     int cw_cout = 0, cw_cin = 0, cw_cinp = 0, cw_kh = 0, cw_kw = 0;
     int cw_rwc = 4;        // mode 2: channels per stored pixel (column j of a window row is kx * cw_rwc + ci)
-    // Push inside the gradient kernel (mode 0, no split-K): C[m][n] is the gradient of parameter upd_w[m*ld + n] and is
-    // not stored; the kernel applies t = g + wd*w, v = mu*v - lr*t, w += v to upd_w / upd_v and writes the new
-    // parameters to upd_copy in the compute type (all [M][ld], rows and column groups of 8 aligned to 16 bytes).
-    float *upd_w = nullptr, *upd_v = nullptr;
-    void *upd_copy = nullptr;
+    // Push inside the gradient kernel (mode 0, no split-K): C[m][n] is the gradient g of parameter upd_w[m*ld + n]; the kernel
+    // applies t = g + wd*w, v = mu*v - lr*t, w += v to upd_w / upd_v and writes the new parameters to upd_copies copies in the
+    // compute type.  out (if any) receives g, upd_acc (if any) upd_acc + g, or g if upd_acc_first.  All [M][ld], rows and column
+    // groups of 8 aligned to 16 bytes.
+    float *upd_w = nullptr, *upd_v = nullptr, *upd_acc = nullptr;
+    void *upd_copy[kPushCopies] = {};
+    int upd_copies = 0, upd_acc_first = 0;
     float upd_lr = 0.f, upd_mu = 0.f, upd_wd = 0.f;
 };
 
@@ -134,9 +138,20 @@ int launch_update(float *w, float *v, const float *g, size_t n, float lr, float 
 // the update, and the updated parameters written to `copy` (fp32 or bf16) in the same pass
 int launch_update_snapshot(float *w, float *v, const float *g, size_t n, float lr, float mu, float wd, void *copy,
                            int dst_dtype, hipStream_t s);
-// the same over up to 8 ranges [off, off + cnt) of the parameter vector in one launch (w, v, g, copy: 16-byte aligned bases)
-int launch_update_snapshot_ranges(float *w, float *v, const float *g, const size_t *off, const size_t *cnt, int n_ranges, float lr, float mu, float wd,
-                                  void *copy, int dst_dtype, hipStream_t s);
+// The update of up to 8 ranges [off, off + cnt) of the parameter vector in one launch, with what a replay does beside it in the same
+// pass: the gradient added to acc (or written there if acc_first), the new parameters written to copies in fp32 or
+// bf16, the version counter advanced and a log record (update, worker, counter) per fetch.  All bases 16-byte aligned.
+struct PushRanges {
+    float *w, *v; const float *g; float *acc;
+    float lr, mu, wd;
+    int acc_first, n, ncopies, nlogs;
+    void *copy[2 * kPushCopies];
+    unsigned f32mask;                       // bit c: copy c is fp32
+    int *counter;
+    int32_t *log[kPushCopies]; int log_update[kPushCopies], log_worker[kPushCopies];
+    size_t off[8], cnt[8]; unsigned blk[9]; // blk filled by the launch
+};
+int launch_push_ranges(PushRanges &p, hipStream_t s);
 // Adagrad / Adadelta server updates (one pass, in place)
 int launch_adagrad(float *w, float *h, const float *g, size_t n, float lr, float eps, float wd, hipStream_t s);
 int launch_adadelta(float *w, float *a, float *b, const float *g, size_t n, float rho, float eps, float wd, hipStream_t s);

@@ -416,11 +416,13 @@ __device__ __forceinline__ void update_tile(const uint4 *smem, const Epilogue &e
     constexpr int BM = Cfg::BM, BN = Cfg::BN, CPR = BN / 4, RPR = NTALL / CPR, R = BM / RPR;
     const float4 *stg = reinterpret_cast<const float4 *>(smem);
     const int chunk = tid % CPR, n0 = tn * BN + chunk * 4;
-    f32x4 w[R], mo[R];
+    f32x4 w[R], mo[R], acc[R];
+    const bool add = ep.upd_acc && !ep.upd_acc_first;
     static_for<0, R>([&](auto r) ASGD_INLINE {
         const int m = tm * BM + r * RPR + tid / CPR;
         if (m < M && n0 < N) {
             const long p = (long)m * ep.ld + n0;
+            if (add) acc[r] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(__builtin_assume_aligned(ep.upd_acc + p, 16)));
             w[r] = *reinterpret_cast<const f32x4 *>(__builtin_assume_aligned(ep.upd_w + p, 16));
             mo[r] = *reinterpret_cast<const f32x4 *>(__builtin_assume_aligned(ep.upd_v + p, 16));
         }
@@ -442,14 +444,20 @@ __device__ __forceinline__ void update_tile(const uint4 *smem, const Epilogue &e
             const long p = (long)m * ep.ld + n0;
             __builtin_nontemporal_store(w[r], reinterpret_cast<f32x4 *>(__builtin_assume_aligned(ep.upd_w + p, 16)));
             __builtin_nontemporal_store(mo[r], reinterpret_cast<f32x4 *>(__builtin_assume_aligned(ep.upd_v + p, 16)));
+            if (ep.out) __builtin_nontemporal_store(f32x4{g[0], g[1], g[2], g[3]}, reinterpret_cast<f32x4 *>(__builtin_assume_aligned(static_cast<float *>(ep.out) + p, 16)));
+            if (ep.upd_acc) {
+                f32x4 a = f32x4{g[0], g[1], g[2], g[3]};
+                if (add) a = acc[r] + a;
+                __builtin_nontemporal_store(a, reinterpret_cast<f32x4 *>(__builtin_assume_aligned(ep.upd_acc + p, 16)));
+            }
             if constexpr (sizeof(T) == 4) {
-                *reinterpret_cast<f32x4 *>(__builtin_assume_aligned(static_cast<float *>(ep.upd_copy) + p, 16)) = w[r];
+                for (int c = 0; c < ep.upd_copies; ++c) *reinterpret_cast<f32x4 *>(__builtin_assume_aligned(static_cast<float *>(ep.upd_copy[c]) + p, 16)) = w[r];
             } else {
                 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
                 u32x2 o;
                 o.x = bf16_bits_rne(__float_as_uint(w[r][0])) | (bf16_bits_rne(__float_as_uint(w[r][1])) << 16);
                 o.y = bf16_bits_rne(__float_as_uint(w[r][2])) | (bf16_bits_rne(__float_as_uint(w[r][3])) << 16);
-                *reinterpret_cast<u32x2 *>(__builtin_assume_aligned(static_cast<bf16_t *>(ep.upd_copy) + p, 8)) = o;
+                for (int c = 0; c < ep.upd_copies; ++c) *reinterpret_cast<u32x2 *>(__builtin_assume_aligned(static_cast<bf16_t *>(ep.upd_copy[c]) + p, 8)) = o;
             }
         }
     });
@@ -1397,8 +1405,10 @@ int gemm_trans_trans(int dtype, const void *at, long lda, int M, const void *bt,
 {
     if (ep.upd_w) {   // push inside the kernel (gemm_kernel over two transposed plain operands carries that path):
                       // whole sums only, 16-byte rows and column groups in all three buffers
-        const uintptr_t al = (uintptr_t)ep.upd_w | (uintptr_t)ep.upd_v | (uintptr_t)ep.upd_copy;
-        if (plan.splits != 1 || ep.mode != 0 || !ep.upd_v || !ep.upd_copy || (al & 15) || (ep.ld & 7)) return -1;
+        uintptr_t al = (uintptr_t)ep.upd_w | (uintptr_t)ep.upd_v | (uintptr_t)ep.upd_acc | (uintptr_t)ep.out;
+        if (ep.upd_copies < 0 || ep.upd_copies > kPushCopies) return -1;
+        for (int c = 0; c < ep.upd_copies; ++c) { if (!ep.upd_copy[c]) return -1; al |= (uintptr_t)ep.upd_copy[c]; }
+        if (plan.splits != 1 || ep.mode != 0 || !ep.upd_v || (al & 15) || (ep.ld & 7)) return -1;
     }
     if (dtype == kBF16)
         return outer_applies<bf16_t>(M, N, K, ep, plan) ? run_outer(make_plain_t<bf16_t>(at, lda, M, K), make_plain_t<bf16_t>(bt, ldb, N, K), M, N, K, ep, s)

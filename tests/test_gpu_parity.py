@@ -638,6 +638,50 @@ def test_accumulate_matches_numpy(n, offset):
 
 
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("n_sync", [0, 1, 3])
+def test_replay_with_fused_pushes_is_the_separate_kernels_bit_for_bit(n_sync, dtype):
+    """Parameters at a 4-byte offset go through the separate update, snapshot and accumulate kernels: everything that the
+    replay leaves, the replicas' gradients among it, must be the same.  Six replicas fetch one version (a push writes
+    four copies at most), and the last replica's only gradient is of an early version."""
+    layers, shape, batch, W = RAGGED["layers"], RAGGED["in_shape"], 8, 6   # minibatches of a multiple of 16 bytes
+    worker = np.array([0, 1, 2, 3, 4, 5, 0, 1, 2, 3, 4, 0, 1], np.int32)
+    rv = np.array([0, 0, 1, 1, 4, 0, 6, 6, 6, 6, 6, 7, 12], np.int32)
+    T, k, tdt = len(worker), max(n_sync, 1), torch.bfloat16 if dtype == B.BF16 else torch.float32
+    nets = [B.asgd_net_create(layers, batch, shape, dtype) for _ in range(W)]
+    P = B.asgd_param_count(nets[0])
+    rng = np.random.default_rng(21)
+    params0 = wl.make_params(layers, shape, 2001)
+    images = torch.from_numpy(rng.standard_normal((T * k, batch) + shape).astype(np.float32)).to(DEV).to(tdt)
+    labels = torch.from_numpy(rng.integers(0, 10, (T * k, batch)).astype(np.int32)).to(DEV)
+    try:
+        results = []
+        for offset in (0, 1):
+            def vec(value=0.0):
+                return torch.full((P + offset,), value, dtype=torch.float32, device=DEV)[offset:]
+            params, mom = vec(), vec()
+            params.copy_(torch.from_numpy(params0))
+            wp, wm, wa = ([vec() for _ in range(W)] for _ in range(3))
+            copies = [torch.full((P,), float("nan"), dtype=tdt, device=DEV) for _ in range(W)]
+            grads = [torch.full((P,), float("nan"), dtype=torch.float32, device=DEV) for _ in range(W)]
+            losses = torch.zeros(T * k, dtype=torch.float32, device=DEV)
+            log = torch.full((T, 3), -7, dtype=torch.int32, device=DEV)
+            for _ in range(2):
+                if n_sync:
+                    B.asgd_replay_nsync_run(nets, n_sync, params, mom, wp, wm, wa, copies, grads, images, labels, worker, rv, 0.001, 0.9, 5e-4, 9, losses, log)
+                else:
+                    B.asgd_replay_run(nets, params, mom, copies, grads, images, labels, worker, rv, 0.001, 0.9, 5e-4, 9, losses, log)
+            torch.cuda.synchronize()
+            results.append([t.cpu().contiguous().view(torch.uint8).numpy() for t in [params.clone(), mom.clone(), losses, log] + copies + grads + (wp + wm + wa if n_sync else [])])
+        np.testing.assert_array_equal(log.cpu().numpy(), np.stack([np.arange(T), worker, rv], 1))
+        assert all(np.isfinite(g.cpu().numpy()).all() for g in grads)
+        for a, b in zip(*results):
+            np.testing.assert_array_equal(a, b)
+    finally:
+        for n in nets:
+            B.asgd_net_destroy(n)
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
 @pytest.mark.parametrize("n_sync", [1, 3])
 def test_nsync_replay_matches_oracle_and_logs_the_schedule(n_sync, dtype):
     cfg = wl.TINY
