@@ -375,11 +375,11 @@ int size_net(asgd_net &n, size_t partials, bool plain)
                 const long Cg = s.inC / s.groups, Og = s.outC / s.groups, Kg = (long)s.k * s.k * Cg;
                 s.p_fwd = plan_gemm(M, Og, Kg, n.dtype, 1);
                 s.p_dgrad = plan_gemm(Min, Cg, (long)s.k * s.k * Og, n.dtype, 1);
-                s.p_wgrad = plan_gemm(Og, Kg, M, n.dtype, 128);
+                s.p_wgrad = plan_filter_grad(Og, Kg, M, n.dtype, plain);
             } else {
                 s.p_fwd = plan_gemm(M, s.outCp, K, n.dtype, 1);
                 s.p_dgrad = plan_gemm(Min, s.inCp, (long)s.k * s.k * s.outCp, n.dtype, 1);
-                s.p_wgrad = plan_gemm(s.outCp, K, M, n.dtype, 128);
+                s.p_wgrad = plan_filter_grad(s.outCp, K, M, n.dtype, plain);
                 // the first layer's filter gradient as one persistent kernel wants a partial result per workgroup
                 if (s.rw) s.p_wgrad.ws_floats = std::max(s.p_wgrad.ws_floats, rows_wgrad_ws_floats(n.dtype, s.outCp, conv_gather(s, nullptr, (int)B, n.dtype)));
             }

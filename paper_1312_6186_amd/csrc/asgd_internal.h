@@ -74,6 +74,7 @@ struct Gather {
 
 struct GemmPlan {
     int splits = 1;          // split-K factor
+    int bm = 128;            // rows of a tile (filter gradients: 32, 64 or 128)
     size_t ws_floats = 0;    // fp32 scratch needed when splits > 1
 };
 
@@ -113,6 +114,7 @@ int splitk_reduce(int dtype, const float *ws, int splits, const Epilogue &ep, in
 // Every operand must fit in 1 GiB.
 // C[M][N] = A[M][K] * B[N][K]^T; A gathered (direct), B plain K-contiguous.
 GemmPlan plan_gemm(long M, long N, long K, int dtype, int max_splits);
+GemmPlan plan_filter_grad(long M, long N, long K, int dtype, bool lean);
 int gemm_gather_plain(int dtype, const Gather &a, const void *b, long ldb, int N, const Epilogue &ep,
                       const GemmPlan &plan, float *ws, hipStream_t s);
 // A plain [M][lda], B plain [b_rows][ldb], both K-contiguous; columns n >= b_rows of C are computed as zeros.

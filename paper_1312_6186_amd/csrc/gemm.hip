@@ -43,10 +43,14 @@ template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, int DEPTH_, int MINB_> s
     static constexpr int BM = BM_, BN = BN_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, DEPTH = DEPTH_, MINB = MINB_;
     static constexpr int NT = 64 * WAVES_M_ * WAVES_N_;
     static constexpr int MB = BM_ / WAVES_M_ / 32, NB = BN_ / WAVES_N_ / 32;   // MFMA 32x32 blocks per wave
-    static_assert((BM_ / WAVES_M_) % 64 == 0 && (BN_ / WAVES_N_) % 32 == 0, "wave tiles: rows in 64s, columns in 32s");
+    static_assert((BM_ / WAVES_M_) % 32 == 0 && (BN_ / WAVES_N_) % 32 == 0, "wave tiles in blocks of 32");
 };
 using Cfg128 = TileCfg<128, 128, 2, 2, 2, 2>;   // 256 threads (wave tile 64x64), two workgroups per CU: two waves per SIMD
 using Cfg128w8 = TileCfg<128, 128, 2, 4, 2, 2>; // 512 threads (wave tile 64x32), two workgroups per CU: four waves per SIMD
+
+// filter gradients of few output channels: in fp32 three workgroups a CU of 32 rows, otherwise two
+template <typename T> using Cfg32 = TileCfg<32, 128, 1, 4, 2, sizeof(T) == 4 ? 6 : 4>;
+using Cfg64 = TileCfg<64, 128, 2, 2, 2, 4>;
 
 FastDiv make_fastdiv(uint32_t d)
 {
@@ -643,7 +647,7 @@ __global__ __launch_bounds__(512, sizeof(T) == 2 ? 6 : 4) void outer_kernel(Plai
 // that was multiplied in step t-1, and the set is refilled with tile t+3.
 constexpr int kFetchThreads = 256;
 template <typename T, class Cfg, class LA, class LB>
-__global__ __launch_bounds__(Cfg::NT + kFetchThreads, 2) void gemm_ws_kernel(LA la, LB lb, Epilogue ep, int M, int N, int nkt, int kt_per_split,
+__global__ __launch_bounds__(Cfg::NT + kFetchThreads, Cfg::MINB) void gemm_ws_kernel(LA la, LB lb, Epilogue ep, int M, int N, int nkt, int kt_per_split,
                                                                            int tiles_m, int tiles_n, float *ws)
 {
     constexpr int BK = Geo<T>::BK, BM = Cfg::BM, BN = Cfg::BN, NT = Cfg::NT, MB = Cfg::MB, NB = Cfg::NB, NP = kFetchThreads;
@@ -1221,6 +1225,33 @@ GemmPlan plan_gemm(long M, long N, long K, int dtype, int max_splits)
     return p;
 }
 
+// Filter gradient over K pixels: M output channels, N window columns.  Up to 64 channels in tiles of 32 or 64 rows (a tile of 128
+// leaves the matrix cores of waves beyond the channels idle: 32 channels, 5 x 5 over 32, fp32, 28800 pixels 51 us there, 24 here; 3 channels, 131072 pixels 73 and 15), and in
+// the number of pixel ranges with the smallest modelled time, partial sums included; in fp32 a K tile is 16 or 32 MFMAs of 64
+// cycles a SIMD, in bf16 it is its latency.  lean: no more partial sums than the tile of 128 would leave.
+GemmPlan plan_filter_grad(long M, long N, long K, int dtype, bool lean)
+{
+    const GemmPlan wide = plan_gemm(M, N, K, dtype, 128);
+    if (M > 64) return wide;
+    GemmPlan p;
+    p.bm = M <= 32 ? 32 : 64;
+    const int BK = dtype == kBF16 ? (int)Geo<bf16_t>::BK : (int)Geo<float>::BK, per_cu = p.bm == 32 && dtype == kF32 ? 3 : 2;
+    const double mfma = dtype == kBF16 ? 0.0 : p.bm == 32 ? 0.43 : 0.86, alone = dtype == kBF16 ? 0.35 : 0.6;
+    const long tiles = (N + 127) / 128, nkt = (K + BK - 1) / BK;
+    const long most = std::max(1L, std::min(std::min(nkt / 2, 512L), lean ? (long)wide.splits : 256 * per_cu / tiles));
+    double best = 0;
+    for (long splits = 1, per = nkt; splits <= most;) {
+        const double us = rounds_us(tiles * splits, per_cu, [&](int r) { return std::max(alone * (0.75 + 0.25 * r), mfma * r) * per; }) +
+                          (splits > 1 ? 2.0 + 1.5e-6 * splits * M * N : 0.0);
+        if (best == 0 || us < best) { p.splits = (int)splits; best = us; }
+        if (per == 1) break;
+        splits = (nkt + per - 2) / (per - 1);                    // the fewest with fewer tiles each, none of them empty
+        per = (nkt + splits - 1) / splits;
+    }
+    p.ws_floats = p.splits > 1 ? (size_t)p.splits * (size_t)M * (size_t)N : 0;
+    return p;
+}
+
 double lone_fc_wgrad_us(int dtype, long out, long in, long batch)
 {
     const long tiles = ((out + Cfg128::BM - 1) / Cfg128::BM) * ((in + Cfg128::BN - 1) / Cfg128::BN);
@@ -1245,7 +1276,7 @@ static int run_tile(const LA &la, const LB &lb, int M, int N, int K, const Epilo
     // fp32 for the class); the im2col forward gather of the first layer is 12 % slower that way (seven K tiles: the
     // head of a workgroup weighs more than its loop) and stays as it is.
     if constexpr (std::is_same<LB, GatherT<T>>::value)
-        hipLaunchKernelGGL((gemm_ws_kernel<T, Cfg128, LA, LB>), dim3((unsigned)blocks), dim3(Cfg128::NT + kFetchThreads), 0, s, la, lb, ep, M, N, nkt,
+        hipLaunchKernelGGL((gemm_ws_kernel<T, Cfg, LA, LB>), dim3((unsigned)blocks), dim3(Cfg::NT + kFetchThreads), 0, s, la, lb, ep, M, N, nkt,
                            per, tiles_m, tiles_n, splits > 1 ? ws : nullptr);
     else
         hipLaunchKernelGGL((gemm_kernel<T, Cfg, LA, LB>), dim3((unsigned)blocks), dim3(Cfg::NT), 0, s, la, lb, ep, M, N, nkt, per, tiles_m,
@@ -1260,11 +1291,14 @@ static int run(const LA &la, const LB &lb, int M, int N, int K, const Epilogue &
     if (M <= 0 || N <= 0 || K <= 0 || (N & 7)) return -1;
     if (la.op.bytes == 0 || lb.op.bytes == 0) return -1;   // an operand beyond the 1 GiB the 32-bit offsets cover
     // Measured on the AlexNet-style shapes: the 8-wave form (four waves per SIMD hide more latency) wins everywhere
-    // except the fp32 convolution filter gradient, whose two transposing operands cost eight 4-byte LDS reads per
-    // fragment: the wider wave tile of the 4-wave form needs a third fewer of them.  (In bf16 the 4-wave form was
-    // ahead there too until the multiplying waves got their raised priority.)
-    if constexpr (std::is_same<LB, GatherT<T>>::value && sizeof(T) == 4) return run_tile<T, Cfg128>(la, lb, M, N, K, ep, plan, ws, s);
-    else return run_tile<T, Cfg128w8>(la, lb, M, N, K, ep, plan, ws, s);
+    // except the convolution filter gradient, whose two transposing operands want wider wave tiles (gemm_ws_kernel).
+    if constexpr (std::is_same<LB, GatherT<T>>::value) {
+        if (plan.bm == 32) return run_tile<T, Cfg32<T>>(la, lb, M, N, K, ep, plan, ws, s);
+        if (plan.bm == 64) return run_tile<T, Cfg64>(la, lb, M, N, K, ep, plan, ws, s);
+        return run_tile<T, Cfg128>(la, lb, M, N, K, ep, plan, ws, s);
+    } else {
+        return run_tile<T, Cfg128w8>(la, lb, M, N, K, ep, plan, ws, s);
+    }
 }
 
 static Operand operand(const void *p, size_t bytes) { return Operand{p, bytes <= kMaxOperandBytes ? (unsigned)bytes : 0u}; }

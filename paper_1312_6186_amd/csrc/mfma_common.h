@@ -59,7 +59,7 @@ __device__ __forceinline__ uint4 buf_ld16(__amdgpu_buffer_rsrc_t rs, unsigned of
 // LDS tile of a row-contiguous operand: BK lines of ROWS elements.  A transposing read makes half a wave touch
 // 4 K lines x 64 bytes; with lines 64 bytes (mod 256) apart those eight 32-byte groups cover all banks once.
 template <typename T, int ROWS> struct TransTile {
-    static constexpr int LINE = ROWS * (int)sizeof(T) + (sizeof(T) == 2 ? 64 : 32);   // bytes
+    static constexpr int LINE = ROWS * (int)sizeof(T) + (sizeof(T) == 4 ? 32 : ROWS == 32 ? 128 : 64);   // bytes
     static constexpr int BYTES = Geo<T>::BK * LINE;
 };
 

@@ -300,6 +300,26 @@ def test_stride1_filter_gradient_shapes(shape):
         g.close()
 
 
+# Filter gradients of few output channels in tiles of 32 and 64 rows: output channels around the tiles, window columns around 128, strided and
+# unstrided, first layers in window-row form, few and many pixels (one range, many ranges), grouped.
+FEW_CHANNEL_SHAPES = [(1, 8, 5, 1, 9, 7, 1, 1), (3, 32, 5, 1, 32, 32, 40, 1), (3, 40, 3, 2, 21, 19, 3, 1), (16, 24, 3, 1, 12, 13, 2, 1), (8, 64, 4, 2, 18, 14, 5, 1),
+                      (40, 56, 3, 1, 6, 5, 4, 1), (32, 72, 5, 1, 7, 7, 3, 1), (64, 64, 3, 2, 11, 11, 6, 2), (24, 32, 5, 1, 16, 15, 33, 1)]
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("shape", FEW_CHANNEL_SHAPES, ids=lambda s: "%dto%d_k%d_s%d_%dx%dx%d_g%d" % s)
+def test_few_channel_filter_gradient_shapes(shape, dtype):
+    cin, cout, k, stride, h, w, batch, groups = shape
+    conv = ("conv", cout, k, stride, k // 2) + ((groups,) if groups > 1 else ())
+    layers = ([] if cin <= 3 else [("conv", cin, 1, 1, 0), ("relu",)]) + [conv, ("relu",), ("maxpool", 2, 2), ("fc", 16), ("relu",), ("fc", 10), ("softmax_ce",)]
+    g, onet, (loss, grads), (ref_loss, ref_grads, _), _ = _net_case({"name": "few", "in_shape": (min(cin, 3), h, w), "classes": 10, "layers": layers}, batch, dtype, plain=False)
+    try:
+        assert abs(loss - ref_loss) <= TOL[dtype] * abs(ref_loss)
+        compare_grads(onet, grads, ref_grads, TOL[dtype], "few")
+    finally:
+        g.close()
+
+
 # Weight gradients of fully-connected layers: tiles of 128 x 128 with ragged edges on both sides, batches around the K tiles (64 in
 # bf16, 32 in fp32) and around the limits of the kernel for short sums (two K tiles; 512 with 256 tiles and more).
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
