@@ -57,6 +57,7 @@ struct Stage {
     int relu = 0, drop = 0, drop_layer = -1;
     bool nonneg = false;         // the output holds no negative values (CONV + RELU, and LRN and POOL on top of it)
     float lrn_alpha = 0.f, lrn_beta = 0.f, lrn_bias = 0.f;   // ST_LRN (window size in k)
+    bool to_flat = false;      // ST_POOL: writes the flattened input of the fully-connected layer above (and has no tensors of its own)
     bool with_pool = false;    // ST_LRN: one kernel does it together with the pool that follows (out is written for export only)
     bool has_params() const { return kind == ST_CONV || kind == ST_FC; }
     float drop_p = 0.f, drop_scale = 1.f;
@@ -156,8 +157,8 @@ size_t carve(asgd_net &n, char *base)
     for (size_t i = 0; i < n.stages.size(); ++i) {
         Stage &s = n.stages[i];
         const size_t oe = B * s.out_elems();
-        s.out = at(oe * (s.last ? 4 : es) + 256);
-        if (!s.with_pool) s.dout = at(oe * es + 256);
+        if (!s.to_flat) s.out = at(oe * (s.last ? 4 : es) + 256);
+        if (!s.with_pool && !s.to_flat) s.dout = at(oe * es + 256);
         if (s.kind == ST_POOL) s.argmax = static_cast<uint8_t *>(at(oe));
         if (s.kind == ST_CONV) {
             s.wd = i > 0 ? at(s.wd_elems * s.groups * es) : nullptr;
@@ -394,8 +395,13 @@ int size_net(asgd_net &n, size_t partials, bool plain)
             scratch_side = std::max(scratch_side, s.d_wgrad.tile >= 0 ? s.d_wgrad.ws_floats : s.p_wgrad.ws_floats);
             s.colsum_floats = colsum_ws_floats(n.dtype, M, s.outCp);
             if (si + 1 < n.stages.size() && n.stages[si + 1].kind == ST_POOL) {
-                const Stage &pl = n.stages[si + 1];
+                Stage &pl = n.stages[si + 1];
                 s.pool_bands = pool_bwd_bands(n.dtype, B, s.outH, s.outW, s.outCp, pl.k, pl.stride);
+                if (si + 2 < n.stages.size() && n.stages[si + 2].kind == ST_FC) {
+                    const long flat = pool_flat_bands(n.dtype, (int)B, s.outH, s.outW, s.outC, s.outCp, pl.k, pl.stride);
+                    pl.to_flat = flat > 0;
+                    if (flat > 0) s.pool_bands = flat;
+                }
                 s.colsum_floats = std::max(s.colsum_floats, (size_t)s.pool_bands * s.outCp);
             } else if (si + 2 < n.stages.size() && n.stages[si + 1].kind == ST_LRN && n.stages[si + 2].kind == ST_POOL) {
                 const Stage &pl = n.stages[si + 2];
@@ -619,6 +625,9 @@ int forward(asgd_net *n, const void *params, const void *images, const int32_t *
             }
         } else if (s.kind == ST_LRN && s.with_pool) {
             continue;   // cur stays the convolution's output: the pool's stage normalises it
+        } else if (s.kind == ST_POOL && s.to_flat) {
+            ProfScope ps(n, st, ASGD_K_POOL_FWD, 0, Bd * s.outC * ((double)s.inH * s.inW * es + (double)s.outH * s.outW * (es + 1)));
+            CHECK_LAUNCH(launch_pool_flat_fwd(dt, cur, s.nonneg, n->stages[si + 1].flat_in, s.argmax, B, s.inH, s.inW, s.inC, s.inCp, s.k, st), "pool forward");
         } else if (s.kind == ST_POOL && si > 0 && n->stages[si - 1].with_pool) {
             const Stage &l = n->stages[si - 1];
             ProfScope ps(n, st, ASGD_K_LRN, 0, Bd * s.outC * ((double)s.inH * s.inW * es + (double)s.outH * s.outW * (es + 1)));
@@ -633,7 +642,10 @@ int forward(asgd_net *n, const void *params, const void *images, const int32_t *
         } else {
             const void *x = cur;
             long ldx = si > 0 && n->stages[si - 1].kind == ST_FC ? n->stages[si - 1].out_ld : s.in_f;
-            if (s.in_is_spatial) {
+            if (s.in_is_spatial && si > 0 && n->stages[si - 1].to_flat) {
+                x = s.flat_in;
+                ldx = s.in_f;
+            } else if (s.in_is_spatial) {
                 ProfScope ps(n, st, ASGD_K_LAYOUT, 0, 2 * Bd * s.in_f * es);
                 CHECK_LAUNCH(launch_flatten(dt, cur, s.flat_in, B, s.inH, s.inW, s.inC, s.inCp, st), "flatten");
                 x = s.flat_in;
@@ -840,9 +852,9 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                                                   n->scratch, st),
                                  "fc data gradient");
                 }
-                ProfScope ps(n, st, ASGD_K_LAYOUT, 0, s.in_is_spatial ? 3 * Bd * s.in_f * es : 0);
-                if (s.in_is_spatial)
-                    CHECK_LAUNCH(launch_unflatten(dt, s.dflat_in, prev->out, (prev->kind == ST_CONV && prev->relu) || relu_under_pool(n->stages, si - 1),
+                if (!s.in_is_spatial || prev->to_flat) return ASGD_OK;
+                ProfScope ps(n, st, ASGD_K_LAYOUT, 0, 3 * Bd * s.in_f * es);
+                CHECK_LAUNCH(launch_unflatten(dt, s.dflat_in, prev->out, (prev->kind == ST_CONV && prev->relu) || relu_under_pool(n->stages, si - 1),
                                                   prev->dout, B, s.inH, s.inW, s.inC, s.inCp, st),
                                  "unflatten");
                 return ASGD_OK;
@@ -864,6 +876,12 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
             if (frc != ASGD_OK) return frc;
         } else if (s.kind == ST_LRN && s.with_pool) {
             continue;   // done with the pool's stage above
+        } else if (s.kind == ST_POOL && s.to_flat) {
+            const Stage &fc = n->stages[si + 1];
+            ProfScope ps(n, st, ASGD_K_POOL_BWD, 0, Bd * s.outC * ((double)s.outH * s.outW * (2 * es + 1) + (double)s.inH * s.inW * es));
+            CHECK_LAUNCH(launch_pool_flat_bwd(dt, fc.dflat_in, fc.flat_in, prev->relu, s.argmax, prev->dout, B, s.inH, s.inW, s.inC, s.inCp, s.k, prev->colsum_ws, st),
+                         "pool backward");
+            prev->bands_ready = true;
         } else if (s.kind == ST_POOL && prev && prev->with_pool) {
             Stage &conv = n->stages[si - 2];   // the CONV + RELU under both
             ProfScope ps(n, st, ASGD_K_LRN, 0, Bd * s.outC * (2.0 * s.inH * s.inW * es + (double)s.outH * s.outW * (es + 1)));
@@ -909,7 +927,7 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                     CHECK_LAUNCH(launch_colsum_finish(bias_jobs, sd), "conv bias gradient");
                 }
                 ColsumJob &J = bias_jobs.j[bias_jobs.n++];
-                J.ws = s.colsum_ws; J.nblk = (int)s.pool_bands; J.ld = s.outCp; J.N = s.outC; J.db = grads + s.b_off; J.start_block = 0; J.colmajor = 1; J.div = 1.f;
+                J.ws = s.colsum_ws; J.nblk = (int)s.pool_bands; J.ld = s.outCp; J.N = s.outC; J.db = grads + s.b_off; J.start_block = 0; J.colmajor = 1; J.bf16 = 0; J.div = 1.f;
                 if (by_layer) CHECK_LAUNCH(launch_colsum_finish(bias_jobs, sd), "conv bias gradient");
                 return ASGD_OK;
             };
@@ -1233,7 +1251,11 @@ int asgd_debug_get(asgd_net_t *net, int what, int layer, void *dst, size_t cap_b
                                         s.lrn_alpha, s.lrn_beta, s.lrn_bias, st), "lrn forward");
         }
         if (layer != s.last_layer) return fail(ASGD_EINVAL, "asgd_debug_get: layer %d is fused into the group ending at layer %d", layer, s.last_layer);
-        if (s.kind == ST_FC) {
+        if (s.to_flat) {   // canonical order already
+            const size_t F = (size_t)s.outC * s.outH * s.outW;
+            if (cap_bytes < (size_t)B * F * 4) return fail(ASGD_EINVAL, "asgd_debug_get: destination too small");
+            CHECK_LAUNCH(launch_export_rows(net->dtype, 0, net->stages[net->layer_stage[layer] + 1].flat_in, (long)F, static_cast<float *>(dst), B, (int)F, st), "export");
+        } else if (s.kind == ST_FC) {
             if (cap_bytes < (size_t)B * s.out_f * 4) return fail(ASGD_EINVAL, "asgd_debug_get: destination too small");
             CHECK_LAUNCH(launch_export_rows(net->dtype, s.last ? 1 : 0, s.out, s.out_ld, static_cast<float *>(dst), B, s.out_f, st), "export");
         } else {

@@ -204,6 +204,13 @@ int launch_lrn_pool_fwd(int dtype, const void *a, void *y, uint8_t *arg, int B, 
                         hipStream_t s);
 int launch_lrn_pool_bwd(int dtype, const void *a, const void *dy, const uint8_t *arg, void *da, int B, int H, int W, int Cp, int size, float alpha,
                         float beta, float bias, int k, float *bands, hipStream_t s);
+// A pool of window k, stride 2, under a fully-connected layer: forward straight into flat [B][C*Ho*Wo] in (c,h,w) order (and the
+// positions, channel-last); backward from dflat, masked where relu by flat > 0, into dx, with the column sums of dx in
+// bands[Cp][pool_flat_bands(...)].  pool_flat_bands is 0 where the pair does not run this way.
+long pool_flat_bands(int dtype, int B, int H, int W, int C, int Cp, int k, int stride);
+int launch_pool_flat_fwd(int dtype, const void *x, int nonneg, void *flat, uint8_t *arg, int B, int H, int W, int C, int Cp, int k, hipStream_t s);
+int launch_pool_flat_bwd(int dtype, const void *dflat, const void *flat, int relu, const uint8_t *arg, void *dx, int B, int H, int W, int C, int Cp, int k,
+                         float *bands, hipStream_t s);
 // channel-last [B][H][W][Cp] -> [B][C*H*W] in (c,h,w) order, and back (zero padding channels; optional ReLU mask)
 int launch_flatten(int dtype, const void *x, void *flat, int B, int H, int W, int C, int Cp, hipStream_t s);
 int launch_unflatten(int dtype, const void *dflat, const void *x_for_mask, int relu, void *dx, int B, int H, int W,
@@ -211,7 +218,7 @@ int launch_unflatten(int dtype, const void *dflat, const void *x_for_mask, int r
 // db[n] = sum_m dy[m][n], n < N, fp32, fixed summation order, in two stages: launch_colsum_partial sums bands of
 // rows into ws (colsum_ws_floats floats, not shared with another pending job) and appends a job;
 // launch_colsum_finish adds the bands of all pending jobs (up to 12) in one launch.
-struct ColsumJob { const float *ws; float *db; long ld; int nblk, N; unsigned start_block; int colmajor; float div; };   // ws[band][ld], or ws[column][nblk] if colmajor; sums are divided by div
+struct ColsumJob { const float *ws; float *db; long ld; int nblk, N; unsigned start_block; int colmajor, bf16; float div; };   // ws[band][ld] (bf16: in that type), or ws[column][nblk] if colmajor; sums are divided by div
 struct ColsumJobs { ColsumJob j[12]; int n; };
 int launch_colsum_partial(int dtype, const void *dy, long ld, long M, int N, float *db, float *ws, ColsumJobs &jobs, hipStream_t s);
 // the same with the first stage put off: colsum_partial_defer appends the tensor to s1 (and its second stage to jobs),

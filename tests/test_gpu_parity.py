@@ -335,6 +335,28 @@ def test_fc_weight_gradient_shapes(out, batch, dtype):
         g.close()
 
 
+# A pool under the first fully-connected layer, flattened by the pool's own kernels: channels with padding and one group of 16 bytes to
+# many, pooled grids of one pixel, around the 256 threads of a block and past its LDS (2048 pixels; the separate kernels), odd last rows
+# and columns, with and without the ReLU.
+FLAT_SHAPES = [(8, 2, 3, 2, 3, True), (12, 9, 10, 3, 2, True), (72, 13, 13, 3, 3, True), (72, 13, 12, 3, 2, False), (40, 33, 32, 2, 2, True), (24, 35, 33, 3, 1, True),
+               (8, 92, 92, 2, 1, True), (264, 5, 4, 2, 5, False)]
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("shape", FLAT_SHAPES, ids=lambda s: "%d_%dx%d_k%dx%d_%d" % s)
+def test_pool_under_fc_shapes(shape, dtype):
+    c, h, w, k, batch, relu = shape
+    layers = [("conv", c, 3, 1, 1)] + [("relu",)] * relu + [("maxpool", k, 2), ("fc", 24), ("relu",), ("fc", 10), ("softmax_ce",)]
+    g, onet, (loss, grads), (ref_loss, ref_grads, trace), _ = _net_case({"name": "flat", "in_shape": (3, h, w), "classes": 10, "layers": layers}, batch, dtype, plain=False)
+    try:
+        assert abs(loss - ref_loss) <= TOL[dtype] * abs(ref_loss)
+        compare_grads(onet, grads, ref_grads, TOL[dtype], "flat")
+        pool = 1 + relu
+        assert rel_l2(g.debug(B.DEBUG_OUTPUT, pool), trace[pool]["out"]) < TOL[dtype]
+    finally:
+        g.close()
+
+
 # Response normalisation with a pool of stride 2 on top, one kernel each way: channels around a wavefront's 64 groups of 16 bytes
 # (512 channels in bf16, 256 in fp32; more run separate kernels) and with padding channels, rows around the width that fits
 # the forward kernel's LDS (213 pixels for windows of 3), one pooled row, an odd last row and column, every window size.
