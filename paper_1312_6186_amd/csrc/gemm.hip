@@ -1185,12 +1185,13 @@ template <typename T> __global__ __launch_bounds__(256) void splitk_reduce_kerne
 }
 
 // The same for few outputs and many partial sums (the first layer's filter gradient: 5280 groups of 8 outputs, up
-// to 256 partials each): L = 8 or 32 neighbouring lanes share a group, lane l adds partials l, l+L, ... in that order, and
-// the L sums are combined in a fixed butterfly, so the result does not depend on anything but the inputs.
+// to 256 partials each): L = 8 or 32 neighbouring lanes, or with L = 256 a workgroup, share a group, lane l adds partials l, l+L,
+// ... in that order, and the L sums are combined in a fixed butterfly (and the four wavefronts' in their order), so the
+// result does not depend on anything but the inputs.
 template <typename T, int L> __global__ __launch_bounds__(256) void splitk_reduce_wide_kernel(const float *ws, int splits, Epilogue ep, int M, int N)
 {
-    static_assert(L == 8 || L == 32, "lanes per group of outputs");
-    constexpr int SH = L == 8 ? 3 : 5;
+    static_assert(L == 8 || L == 32 || L == 256, "lanes per group of outputs");
+    constexpr int SH = L == 8 ? 3 : L == 32 ? 5 : 8;
     const long g = ((long)blockIdx.x * 256 + threadIdx.x) >> SH;
     const int l = threadIdx.x & (L - 1);
     const int n8 = N / 8;
@@ -1221,9 +1222,19 @@ template <typename T, int L> __global__ __launch_bounds__(256) void splitk_reduc
         v[4] += b.x; v[5] += b.y; v[6] += b.z; v[7] += b.w;
     }
 #pragma unroll
-    for (int d = 1; d < L; d <<= 1) {
+    for (int d = 1; d < L && d < 64; d <<= 1) {
 #pragma unroll
-        for (int r = 0; r < 8; ++r) v[r] += __shfl_xor(v[r], d, L);
+        for (int r = 0; r < 8; ++r) v[r] += __shfl_xor(v[r], d, L < 64 ? L : 64);
+    }
+    if constexpr (L == 256) {
+        __shared__ float part[4][8];
+        if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) part[threadIdx.x >> 6][r] = v[r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 8; ++r) v[r] = (part[0][r] + part[1][r]) + (part[2][r] + part[3][r]);
     }
     if (!live || l != 0) return;
     float b8[8];
@@ -1273,7 +1284,12 @@ __global__ __launch_bounds__(256) void splitk_reduce_filters_kernel(const float 
 template <typename T> static void launch_splitk_reduce(const float *ws, int splits, const Epilogue &ep, int M, int N, hipStream_t s)
 {
     const long groups = (long)M * (N / 8);
-    if (splits >= 192 && groups < 8192)      // one partial per CU (the first-layer filter gradient): 32 lanes share a group, two rounds of reads each
+    // Lanes that share a group: a chip full of blocks, and hardly more lanes than partials.  (us: 320 groups of 512 partials 10.8 with
+    // 32 lanes, 8.6 with 256; 40 of 98 7.0 with 8, 3.3 with 256; 800 of 248 6.4 with 32, 7.5 with 256; 3200 of 70 6.8 with 8, 6.4
+    // with 32; 5280 of 256, the AlexNet-style first layer, 14 with 32.)
+    if (splits >= 64 && groups < 512)
+        hipLaunchKernelGGL((splitk_reduce_wide_kernel<T, 256>), dim3((unsigned)groups), dim3(256), 0, s, ws, splits, ep, M, N);
+    else if ((splits >= 192 && groups < 8192) || (splits >= 16 && groups < 1024) || (splits >= 64 && groups < 4096))
         hipLaunchKernelGGL((splitk_reduce_wide_kernel<T, 32>), dim3((unsigned)((groups * 32 + 255) / 256)), dim3(256), 0, s, ws, splits, ep, M, N);
     else if (splits >= 16 && groups < 32768)
         hipLaunchKernelGGL((splitk_reduce_wide_kernel<T, 8>), dim3((unsigned)((groups * 8 + 255) / 256)), dim3(256), 0, s, ws, splits, ep, M, N);
