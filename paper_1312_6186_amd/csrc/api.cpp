@@ -369,29 +369,32 @@ int size_net(asgd_net &n, size_t partials, bool plain)
         Stage &s = n.stages[si];
         if (s.kind == ST_CONV) {
             const long M = B * s.outH * s.outW, Min = B * s.inH * s.inW;
+            // partial sums of a data gradient go where those of the filter gradients go: on one stream, behind the forward pass
+            const bool whole = plain || n.fork_pays;
             const long K = s.rw ? (long)s.k * s.rwKW : (long)s.k * s.k * s.inCp;
             if (s.rw && (long)B * s.rwHp * s.rwWp * s.rwC * 4 > 0x7fffffffL) return fail(ASGD_ESHAPE, "layer %d: tensor too large", s.first_layer);
             if (M > 0x7fffffffL / 2 || Min > 0x7fffffffL / 2 || M * s.outCp * 4 > 0x7fffffffL || Min * s.inCp * 4 > 0x7fffffffL) return fail(ASGD_ESHAPE, "layer %d: tensor too large", s.first_layer);
             if (s.groups > 1) {   // one GEMM per group, on that group's channel slices
                 const long Cg = s.inC / s.groups, Og = s.outC / s.groups, Kg = (long)s.k * s.k * Cg;
-                s.p_fwd = plan_gemm(M, Og, Kg, n.dtype, 1);
-                s.p_dgrad = plan_gemm(Min, Cg, (long)s.k * s.k * Og, n.dtype, 1);
+                s.p_fwd = plan_conv(M, Og, Kg, n.dtype, true, nullptr);
+                s.p_dgrad = plan_conv(Min, Cg, (long)s.k * s.k * Og, n.dtype, whole, nullptr);
                 s.p_wgrad = plan_filter_grad(Og, Kg, M, n.dtype, plain);
             } else {
-                s.p_fwd = plan_gemm(M, s.outCp, K, n.dtype, 1);
-                s.p_dgrad = plan_gemm(Min, s.inCp, (long)s.k * s.k * s.outCp, n.dtype, 1);
+                s.p_fwd = plan_conv(M, s.outCp, K, n.dtype, true, nullptr);
+                s.p_dgrad = plan_conv(Min, s.inCp, (long)s.k * s.k * s.outCp, n.dtype, whole, nullptr);
                 s.p_wgrad = plan_filter_grad(s.outCp, K, M, n.dtype, plain);
                 // the first layer's filter gradient as one persistent kernel wants a partial result per workgroup
                 if (s.rw) s.p_wgrad.ws_floats = std::max(s.p_wgrad.ws_floats, rows_wgrad_ws_floats(n.dtype, s.outCp, conv_gather(s, nullptr, (int)B, n.dtype)));
             }
             const int Ng = s.groups > 1 ? s.outC / s.groups : s.outCp, Cg = s.groups > 1 ? s.inC / s.groups : s.inCp;
             s.d_wgrad = plan_wgrad(n.dtype, Ng, s.groups, conv_gather(s, nullptr, (int)B, n.dtype), partials);
-            s.d_fwd = plain ? DirectPlan() : plan_direct(n.dtype, conv_gather(s, nullptr, (int)B, n.dtype), Ng);
+            s.d_fwd = plain ? DirectPlan() : plan_direct(n.dtype, conv_gather(s, nullptr, (int)B, n.dtype), Ng, true);
             s.wf_elems = s.d_fwd.ks ? s.d_fwd.pack_elems : (size_t)Ng * s.k * (s.rw ? s.rwKW : s.k * Cg);
             if (si > 0) {
-                s.d_dgrad = plain ? DirectPlan() : plan_direct(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg);
+                s.d_dgrad = plain ? DirectPlan() : plan_direct(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg, whole);
                 s.wd_elems = s.d_dgrad.ks ? s.d_dgrad.pack_elems : (size_t)Cg * s.k * s.k * Ng;
             }
+            if (si > 0 && !s.d_dgrad.ks) scratch_side = std::max(scratch_side, s.p_dgrad.ws_floats);
             scratch_side = std::max(scratch_side, s.d_wgrad.tile >= 0 ? s.d_wgrad.ws_floats : s.p_wgrad.ws_floats);
             s.colsum_floats = colsum_ws_floats(n.dtype, M, s.outCp);
             if (si + 1 < n.stages.size() && n.stages[si + 1].kind == ST_POOL) {
@@ -987,7 +990,7 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                     if (masked) { ed.mask_src = static_cast<const char *>(prev->out) + (size_t)gi * Cg * esz; ed.mask_ld = s.inCp; ed.mask_scale = 1.f; }
                     const void *wd = static_cast<const char *>(s.wd) + gi * s.wd_elems * esz;
                     if (s.d_dgrad.ks) CHECK_LAUNCH(conv_direct(dt, d, wd, Cgp, ed, s.d_dgrad, st), "conv data gradient");
-                    else CHECK_LAUNCH(gemm_gather_plain(dt, d, wd, (long)s.k * s.k * Ogp, Cgp, ed, s.p_dgrad, n->scratch, st), "conv data gradient");
+                    else CHECK_LAUNCH(gemm_gather_plain(dt, d, wd, (long)s.k * s.k * Ogp, Cgp, ed, s.p_dgrad, n->scratch_side, st), "conv data gradient");
                 }
             }
         }

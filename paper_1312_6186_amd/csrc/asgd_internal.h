@@ -74,7 +74,7 @@ struct Gather {
 
 struct GemmPlan {
     int splits = 1;          // split-K factor
-    int bm = 128;            // rows of a tile (filter gradients: 32, 64 or 128)
+    int bm = 128, bn = 128;  // rows of a tile (filter gradients: 32, 64 or 128), columns (convolutions: 32 or 128)
     size_t ws_floats = 0;    // fp32 scratch needed when splits > 1
 };
 
@@ -96,7 +96,8 @@ struct DirectPlan {
     int ks = 0, nchunks = 0, tile = 0, npl = 0;
     size_t nblk_elems = 0, pack_elems = 0;
 };
-DirectPlan plan_direct(int dtype, const Gather &a, int N);
+// whole: no K splits in the general engine, which keeps the layers that it runs faster
+DirectPlan plan_direct(int dtype, const Gather &a, int N, bool whole);
 int conv_direct(int dtype, const Gather &a, const void *wpack, int N, const Epilogue &ep, const DirectPlan &plan, hipStream_t s);
 
 // Filter gradients of stride-1 convolutions over equal grids in 16-bit data (conv_wgrad.hip): tile shape (-1: does not run
@@ -114,6 +115,7 @@ int splitk_reduce(int dtype, const float *ws, int splits, const Epilogue &ep, in
 // Every operand must fit in 1 GiB.
 // C[M][N] = A[M][K] * B[N][K]^T; A gathered (direct), B plain K-contiguous.
 GemmPlan plan_gemm(long M, long N, long K, int dtype, int max_splits);
+GemmPlan plan_conv(long M, long N, long K, int dtype, bool lean, double *us);
 GemmPlan plan_filter_grad(long M, long N, long K, int dtype, bool lean);
 int gemm_gather_plain(int dtype, const Gather &a, const void *b, long ldb, int N, const Epilogue &ep,
                       const GemmPlan &plan, float *ws, hipStream_t s);

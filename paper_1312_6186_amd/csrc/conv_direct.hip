@@ -67,7 +67,7 @@ double engine_us(int es, const Gather &a, int N)
 
 }  // namespace
 
-DirectPlan plan_direct(int dtype, const Gather &a, int N)
+DirectPlan plan_direct(int dtype, const Gather &a, int N, bool whole)
 {
     DirectPlan d;
     const int es = (int)dtype_size(dtype), npos = a.kh * a.kw;
@@ -115,6 +115,9 @@ DirectPlan plan_direct(int dtype, const Gather &a, int N)
     // 96 -> 16 on 32 x 255, 26 images 47 / 110, 64 -> 128 on 64 x 480, 6 images 44 / 102).
     const int tile = cost_us > 1.1 * best_us ? by_time : by_cost;
     if (tile < 0 || engine_us(es, a, N) < (tile == by_time ? best_us : cost_us)) return DirectPlan();
+    // Few columns over few pixels: the general engine in K splits, where it is modelled a quarter faster.
+    double split_us = 0;
+    if (!whole && plan_conv(M, N, (long)npos * a.C, dtype, false, &split_us).splits > 1 && split_us < 0.75 * (tile == by_time ? best_us : cost_us)) return DirectPlan();
     d.tile = tile;
     d.npl = fit(es, d.ks, d.nchunks, kTiles[tile], a).npl;
     d.nblk_elems = (size_t)d.nchunks * npos * d.ks * 512;

@@ -51,6 +51,7 @@ using Cfg128w8 = TileCfg<128, 128, 2, 4, 2, 2>; // 512 threads (wave tile 64x32)
 // filter gradients of few output channels: in fp32 three workgroups a CU of 32 rows, otherwise two
 template <typename T> using Cfg32 = TileCfg<32, 128, 1, 4, 2, sizeof(T) == 4 ? 6 : 4>;
 using Cfg64 = TileCfg<64, 128, 2, 2, 2, 4>;
+using CfgN32 = TileCfg<128, 32, 4, 1, 2, 4>;    // convolutions of up to 32 output columns: 256 threads (wave tile 32x32), four workgroups per CU
 
 FastDiv make_fastdiv(uint32_t d)
 {
@@ -1335,6 +1336,32 @@ GemmPlan plan_gemm(long M, long N, long K, int dtype, int max_splits)
     return p;
 }
 
+// Convolution over M pixels with N output columns.  Up to 32 columns in tiles of 128 x 32 (a tile of 128 columns leaves three of four
+// waves without a column: 3 -> 32 channels 5 x 5 on 32 x 32 in fp32, 128 images 28 -> 18 us), and where those tiles are fewer than half the CUs
+// and K is long, in K splits: the launch that adds them up costs 5 us, a K tile alone on a CU 0.6 (64 -> 32 channels 5 x 5 on 7 x 7 in
+// fp32, 128 images, 31 us in 49 tiles of conv_direct, 16 + 4 in 10 splits).  us: the modelled time; lean: no partial sums.
+GemmPlan plan_conv(long M, long N, long K, int dtype, bool lean, double *us)
+{
+    GemmPlan p = plan_gemm(M, N, K, dtype, 1);
+    if (N > 32) return p;
+    p.bn = 32;
+    const int BK = dtype == kBF16 ? (int)Geo<bf16_t>::BK : (int)Geo<float>::BK;
+    const double mfma = dtype == kBF16 ? 0.1 : 0.43;
+    const long tiles = (M + 127) / 128, nkt = (K + BK - 1) / BK;
+    const long most = lean || tiles >= 128 ? 1 : std::max(1L, std::min(std::min(nkt / 4, 32L), 512 / tiles));
+    double best = 0;
+    for (long splits = 1, per = nkt; splits <= most;) {
+        const double t = 8.0 + rounds_us(tiles * splits, 4, [&](int r) { return std::max(0.6, mfma * r) * per; }) + (splits > 1 ? 5.0 + 1.5e-6 * splits * M * N : 0.0);
+        if (best == 0 || t < best) { p.splits = (int)splits; best = t; }
+        if (per == 1) break;
+        splits = (nkt + per - 2) / (per - 1);
+        per = (nkt + splits - 1) / splits;
+    }
+    p.ws_floats = p.splits > 1 ? (size_t)p.splits * (size_t)M * (size_t)N : 0;
+    if (us) *us = best;
+    return p;
+}
+
 // Filter gradient over K pixels: M output channels, N window columns.  Up to 64 channels in tiles of 32 or 64 rows (a tile of 128
 // leaves the matrix cores of waves beyond the channels idle: 32 channels, 5 x 5 over 32, fp32, 28800 pixels 51 us there, 24 here; 3 channels, 131072 pixels 73 and 15), and in
 // the number of pixel ranges with the smallest modelled time, partial sums included; in fp32 a K tile is 16 or 32 MFMAs of 64
@@ -1362,12 +1389,17 @@ GemmPlan plan_filter_grad(long M, long N, long K, int dtype, bool lean)
     return p;
 }
 
-// Where lone_kernel runs: hardly any work, which every tile may fetch anew.
-static bool lone_applies(long M, long N, long K) { return M * N * K <= 32L << 20 && ((M + 15) / 16) * ((N + 15) / 16) <= 1024; }
+// Where lone_kernel runs: hardly any work, which every tile may fetch anew, and a K that eight waves are not long over unless the
+// tiles of 128 could not split it either (10 outputs over 125 000 inputs, 2 images: 222 us here, 95 in 32 K splits; both take about 10
+// us at 4096).
+static bool lone_applies(long M, long N, long K, int splits)
+{
+    return M * N * K <= 32L << 20 && ((M + 15) / 16) * ((N + 15) / 16) <= 1024 && (K <= 4096 || splits == 1);
+}
 
 double lone_fc_wgrad_us(int dtype, long out, long in, long batch)
 {
-    if (lone_applies(out, in, batch)) return 0.0;
+    if (lone_applies(out, in, batch, 1)) return 0.0;
     const long tiles = ((out + Cfg128::BM - 1) / Cfg128::BM) * ((in + Cfg128::BN - 1) / Cfg128::BN);
     if (tiles >= 128) return 0.0;
     // a workgroup alone on its CU: us per K tile of 128 bytes
@@ -1408,7 +1440,7 @@ static int run(const LA &la, const LB &lb, int M, int N, int K, const Epilogue &
     // except the convolution filter gradient, whose two transposing operands want wider wave tiles (gemm_ws_kernel).
     constexpr bool plain = (std::is_same<LA, PlainK<T>>::value || std::is_same<LA, PlainT<T>>::value) && (std::is_same<LB, PlainK<T>>::value || std::is_same<LB, PlainT<T>>::value);
     if constexpr (plain) {
-        if (lone_applies(M, N, K)) {
+        if (lone_applies(M, N, K, plan.splits)) {
             const int tiles_n = (N + 15) / 16, waves = std::min(kLoneWaves, (K + 31) / 32);
             hipLaunchKernelGGL((lone_kernel<T, LA, LB>), dim3((unsigned)((M + 15) / 16 * tiles_n)), dim3((unsigned)(64 * waves)), 0, s, la, lb, ep, M, N, K, tiles_n);
             return hipGetLastError() == hipSuccess ? 0 : -1;
@@ -1419,6 +1451,8 @@ static int run(const LA &la, const LB &lb, int M, int N, int K, const Epilogue &
         if (plan.bm == 64) return run_tile<T, Cfg64>(la, lb, M, N, K, ep, plan, ws, s);
         return run_tile<T, Cfg128>(la, lb, M, N, K, ep, plan, ws, s);
     } else {
+        if constexpr (!plain)
+            if (plan.bn == 32) return run_tile<T, CfgN32>(la, lb, M, N, K, ep, plan, ws, s);
         return run_tile<T, Cfg128w8>(la, lb, M, N, K, ep, plan, ws, s);
     }
 }
@@ -1545,7 +1579,7 @@ template <typename T> static bool outer_applies(int M, int N, int K, const Epilo
 {
     if (ep.upd_w || plan.splits != 1 || ep.mode != 0 || !ep.out_f32 || ep.bias || ep.relu || ep.drop || ep.mask_src) return false;
     const long tiles = ((M + 127) / 128) * (long)((N + 127) / 128);
-    if (lone_applies(M, N, K) || !(K <= 2 * (int)Geo<T>::BK || (tiles >= 256 && K <= 512))) return false;
+    if (lone_applies(M, N, K, plan.splits) || !(K <= 2 * (int)Geo<T>::BK || (tiles >= 256 && K <= 512))) return false;
     return M > 0 && N > 0 && K > 0 && N % 8 == 0 && ep.ld % 4 == 0 && ((uintptr_t)ep.out & 15) == 0;
 }
 template <typename T> static int run_outer(const PlainT<T> &la, const PlainT<T> &lb, int M, int N, int K, const Epilogue &ep, hipStream_t s)

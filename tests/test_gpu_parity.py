@@ -320,6 +320,25 @@ def test_few_channel_filter_gradient_shapes(shape, dtype):
         g.close()
 
 
+# Convolutions of up to 32 output columns in tiles of 128 x 32, forward and data gradient, and data gradients over few pixels in K
+# splits (nets that stay on one stream): columns around the tile, pixels around one tile and half the CUs, strided and unstrided.
+NARROW_SHAPES = [(32, 64, 5, 1, 7, 7, 60), (24, 96, 3, 1, 5, 5, 5), (8, 136, 3, 1, 11, 12, 1), (40, 32, 3, 2, 13, 12, 7), (32, 40, 5, 1, 16, 16, 63), (32, 40, 5, 1, 16, 16, 65),
+                 (16, 8, 7, 2, 20, 18, 9)]
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("shape", NARROW_SHAPES, ids=lambda s: "%dto%d_k%d_s%d_%dx%dx%d" % s)
+def test_narrow_convolution_shapes(shape, dtype):
+    cin, cout, k, stride, h, w, batch = shape
+    layers = [("conv", cin, 3, 1, 1), ("relu",), ("conv", cout, k, stride, k // 2), ("relu",), ("maxpool", 2, 2), ("fc", 16), ("relu",), ("fc", 10), ("softmax_ce",)]
+    g, onet, (loss, grads), (ref_loss, ref_grads, _), _ = _net_case({"name": "narrow", "in_shape": (3, h, w), "classes": 10, "layers": layers}, batch, dtype, plain=False)
+    try:
+        assert abs(loss - ref_loss) <= TOL[dtype] * abs(ref_loss)
+        compare_grads(onet, grads, ref_grads, TOL[dtype], "narrow")
+    finally:
+        g.close()
+
+
 # Weight gradients of fully-connected layers: tiles of 128 x 128 with ragged edges on both sides, batches around the K tiles (64 in
 # bf16, 32 in fp32) and around the limits of the kernel for short sums (two K tiles; 512 with 256 tiles and more).
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
