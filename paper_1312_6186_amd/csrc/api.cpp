@@ -327,7 +327,7 @@ int plan_net(asgd_net &n)
     if (n.classes == 0 || n.stages.empty() || !n.stages.back().last) return fail(ASGD_ESHAPE, "the layer list must end with FC, SOFTMAX_CE");
     n.param_count = off;
     // What the side stream hides are the parameter side's partial sums and updates, which grow with the number of weights; what
-    // it costs is a pair of events per layer with parameters and a join, 35 to 60 us a step whatever the batch.  One step with /
+    // it costs is a pair of events per layer with parameters and a join, 35 to 60 us a step whatever the batch (all times here with a fence on every event, see kInnerEvent).  One step with /
     // without it: 28 x 28 net (16 k parameters) fp32 8 images 129 / 81 us, 256 images 254 / 235; 32 x 32 net (0.1 M) bf16 93
     // images 234 / 203, 512 images 311 / 303, fp32 512 images 997 / 952; the same with 2.5 M parameters in its first
     // fully-connected layer 283 / 228.  AlexNet-style bf16 with 6.4 M parameters 32 images 589 / 600, 128 images 1155 / 1213; with
@@ -388,10 +388,11 @@ int size_net(asgd_net &n, size_t partials, bool plain)
             }
             const int Ng = s.groups > 1 ? s.outC / s.groups : s.outCp, Cg = s.groups > 1 ? s.inC / s.groups : s.inCp;
             s.d_wgrad = plan_wgrad(n.dtype, Ng, s.groups, conv_gather(s, nullptr, (int)B, n.dtype), partials);
-            s.d_fwd = plain ? DirectPlan() : plan_direct(n.dtype, conv_gather(s, nullptr, (int)B, n.dtype), Ng, true);
+            s.d_fwd = plain ? DirectPlan() : plan_direct(n.dtype, conv_gather(s, nullptr, (int)B, n.dtype), Ng);
             s.wf_elems = s.d_fwd.ks ? s.d_fwd.pack_elems : (size_t)Ng * s.k * (s.rw ? s.rwKW : s.k * Cg);
             if (si > 0) {
-                s.d_dgrad = plain ? DirectPlan() : plan_direct(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg, whole);
+                s.d_dgrad = plain ? DirectPlan() : plan_direct(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg);
+                if (!whole && split_is_faster(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg, s.d_dgrad)) s.d_dgrad = DirectPlan();
                 s.wd_elems = s.d_dgrad.ks ? s.d_dgrad.pack_elems : (size_t)Cg * s.k * s.k * Ng;
             }
             if (si > 0 && !s.d_dgrad.ks) scratch_side = std::max(scratch_side, s.p_dgrad.ws_floats);

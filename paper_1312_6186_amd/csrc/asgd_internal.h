@@ -96,8 +96,8 @@ struct DirectPlan {
     int ks = 0, nchunks = 0, tile = 0, npl = 0;
     size_t nblk_elems = 0, pack_elems = 0;
 };
-// whole: no K splits in the general engine, which keeps the layers that it runs faster
-DirectPlan plan_direct(int dtype, const Gather &a, int N, bool whole);
+DirectPlan plan_direct(int dtype, const Gather &a, int N);   // none where the general engine is the faster one
+bool split_is_faster(int dtype, const Gather &a, int N, const DirectPlan &d);   // than plan d: the general engine in K splits (plan_conv)
 int conv_direct(int dtype, const Gather &a, const void *wpack, int N, const Epilogue &ep, const DirectPlan &plan, hipStream_t s);
 
 // Filter gradients of stride-1 convolutions over equal grids in 16-bit data (conv_wgrad.hip): tile shape (-1: does not run

@@ -67,7 +67,7 @@ double engine_us(int es, const Gather &a, int N)
 
 }  // namespace
 
-DirectPlan plan_direct(int dtype, const Gather &a, int N, bool whole)
+DirectPlan plan_direct(int dtype, const Gather &a, int N)
 {
     DirectPlan d;
     const int es = (int)dtype_size(dtype), npos = a.kh * a.kw;
@@ -115,15 +115,20 @@ DirectPlan plan_direct(int dtype, const Gather &a, int N, bool whole)
     // 96 -> 16 on 32 x 255, 26 images 47 / 110, 64 -> 128 on 64 x 480, 6 images 44 / 102).
     const int tile = cost_us > 1.1 * best_us ? by_time : by_cost;
     if (tile < 0 || engine_us(es, a, N) < (tile == by_time ? best_us : cost_us)) return DirectPlan();
-    // Few columns over few pixels: the general engine in K splits, where it is modelled a quarter faster.
-    double split_us = 0;
-    if (!whole && plan_conv(M, N, (long)npos * a.C, dtype, false, &split_us).splits > 1 && split_us < 0.75 * (tile == by_time ? best_us : cost_us)) return DirectPlan();
     d.tile = tile;
     d.npl = fit(es, d.ks, d.nchunks, kTiles[tile], a).npl;
     d.nblk_elems = (size_t)d.nchunks * npos * d.ks * 512;
     d.pack_elems = (size_t)((N + 31) / 32) * d.nblk_elems;
     if (d.pack_elems * es > kMaxOperandBytes) return DirectPlan();
     return d;
+}
+
+// Few columns over few pixels: the general engine in K splits, where it is modelled a quarter faster.
+bool split_is_faster(int dtype, const Gather &a, int N, const DirectPlan &d)
+{
+    double us = 0;
+    return d.ks && plan_conv((long)a.N * a.H * a.W, N, (long)a.kh * a.kw * a.C, dtype, false, &us).splits > 1 &&
+           us < 0.75 * direct_us((int)dtype_size(dtype), d.ks, d.nchunks, kTiles[d.tile], a, N);
 }
 
 int conv_direct(int dtype, const Gather &a, const void *wpack, int N, const Epilogue &ep, const DirectPlan &d, hipStream_t s)

@@ -25,7 +25,10 @@
 // lies outside C does not multiply at all.
 //
 // Stride-1 convolutions whose output grid equals their input grid run
-// conv_direct_kernel (conv_direct.h) instead.
+// conv_direct_kernel (conv_direct.h) instead.  Small fully-connected products run
+// lone_kernel, weight gradients over a minibatch outer_kernel (both below); few
+// output channels or columns take narrower tiles of the same engine (Cfg32, Cfg64,
+// CfgN32).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1389,17 +1392,13 @@ GemmPlan plan_filter_grad(long M, long N, long K, int dtype, bool lean)
     return p;
 }
 
-// Where lone_kernel runs: hardly any work, which every tile may fetch anew, and a K that eight waves are not long over unless the
-// tiles of 128 could not split it either (10 outputs over 125 000 inputs, 2 images: 222 us here, 95 in 32 K splits; both take about 10
-// us at 4096).
-static bool lone_applies(long M, long N, long K, int splits)
-{
-    return M * N * K <= 32L << 20 && ((M + 15) / 16) * ((N + 15) / 16) <= 1024 && (K <= 4096 || splits == 1);
-}
+// Where lone_kernel runs: hardly any work, which every tile may fetch anew, and a K that eight waves are not long over (10 outputs
+// over 125 000 inputs, 2 images: 222 us here, 95 in 32 K splits of the tiles of 128; both take about 10 us at 4096).
+static bool lone_applies(long M, long N, long K) { return M * N * K <= 32L << 20 && ((M + 15) / 16) * ((N + 15) / 16) <= 1024 && K <= 4096; }
 
 double lone_fc_wgrad_us(int dtype, long out, long in, long batch)
 {
-    if (lone_applies(out, in, batch, 1)) return 0.0;
+    if (lone_applies(out, in, batch)) return 0.0;
     const long tiles = ((out + Cfg128::BM - 1) / Cfg128::BM) * ((in + Cfg128::BN - 1) / Cfg128::BN);
     if (tiles >= 128) return 0.0;
     // a workgroup alone on its CU: us per K tile of 128 bytes
@@ -1440,7 +1439,7 @@ static int run(const LA &la, const LB &lb, int M, int N, int K, const Epilogue &
     // except the convolution filter gradient, whose two transposing operands want wider wave tiles (gemm_ws_kernel).
     constexpr bool plain = (std::is_same<LA, PlainK<T>>::value || std::is_same<LA, PlainT<T>>::value) && (std::is_same<LB, PlainK<T>>::value || std::is_same<LB, PlainT<T>>::value);
     if constexpr (plain) {
-        if (lone_applies(M, N, K, plan.splits)) {
+        if (lone_applies(M, N, K)) {
             const int tiles_n = (N + 15) / 16, waves = std::min(kLoneWaves, (K + 31) / 32);
             hipLaunchKernelGGL((lone_kernel<T, LA, LB>), dim3((unsigned)((M + 15) / 16 * tiles_n)), dim3((unsigned)(64 * waves)), 0, s, la, lb, ep, M, N, K, tiles_n);
             return hipGetLastError() == hipSuccess ? 0 : -1;
@@ -1579,7 +1578,7 @@ template <typename T> static bool outer_applies(int M, int N, int K, const Epilo
 {
     if (ep.upd_w || plan.splits != 1 || ep.mode != 0 || !ep.out_f32 || ep.bias || ep.relu || ep.drop || ep.mask_src) return false;
     const long tiles = ((M + 127) / 128) * (long)((N + 127) / 128);
-    if (lone_applies(M, N, K, plan.splits) || !(K <= 2 * (int)Geo<T>::BK || (tiles >= 256 && K <= 512))) return false;
+    if (lone_applies(M, N, K) || !(K <= 2 * (int)Geo<T>::BK || (tiles >= 256 && K <= 512))) return false;
     return M > 0 && N > 0 && K > 0 && N % 8 == 0 && ep.ld % 4 == 0 && ((uintptr_t)ep.out & 15) == 0;
 }
 template <typename T> static int run_outer(const PlainT<T> &la, const PlainT<T> &lb, int M, int N, int K, const Epilogue &ep, hipStream_t s)

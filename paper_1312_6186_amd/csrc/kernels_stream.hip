@@ -105,7 +105,8 @@ __global__ __launch_bounds__(256) void update_kernel(f32x4 *__restrict__ w, f32x
 
 // The same over up to eight separate ranges of one parameter vector in one launch, with a replay's accumulator, copies and log in
 // the same pass (PushRanges): a block finds its range.  A range whose start is not a multiple of 4 elements runs element by
-// element.  Bound by memory.  62.4 M parameters, update and a separate snapshot in bf16 284 us, here 222.
+// element.  Bound by memory.  62.4 M parameters: 204 us without a copy (the update 209, each fetch by a snapshot of its own 75 more); 2
+// bytes more a parameter and copy in bf16.
 __device__ __forceinline__ uint2 bf16x4(const f32x4 &v)
 {
     return make_uint2(f32_to_bf16_bits(__float_as_uint(v.x)) | (f32_to_bf16_bits(__float_as_uint(v.y)) << 16),
