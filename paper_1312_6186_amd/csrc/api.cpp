@@ -189,10 +189,15 @@ Gather dgrad_gather(const Stage &s, const void *dy, int B, int dt, int group);
 
 // Bytes of the static workspace of asgd_fwd_bwd_static.
 constexpr size_t kStaticWsBytes = (size_t)64 << 20;
+constexpr size_t kScratchSpare = 64;   // floats behind the largest partial sums
 
-// Chooses the kernels of every stage and sizes the workspace.  partials: floats that the partial sums of a filter gradient may
-// take in conv_wgrad; plain: no filters padded to their chunks (conv_direct).
-int size_net(asgd_net &n, size_t partials, bool plain);
+// Floats that the partial sums of one kernel may take.
+struct Budget {
+    size_t wgrad;    // filter gradients in conv_wgrad
+    size_t narrow;   // the general engine's filter gradients of up to 64 channels, beyond what its tiles of 128 rows would leave, and split data gradients
+};
+// Chooses the kernels of every stage and sizes the workspace.  plain: no filters padded to their chunks (conv_direct).
+int size_net(asgd_net &n, const Budget &partials, bool plain);
 
 int plan_net(asgd_net &n)
 {
@@ -340,20 +345,27 @@ int plan_net(asgd_net &n)
         if (s.kind == ST_FC) lone += lone_fc_wgrad_us(n.dtype, s.out_f, s.in_f, n.batch);
     n.fork_pays = n.param_count >= (size_t)4 << 20 || lone >= 200;
 
-    int rc = size_net(n, SIZE_MAX, false);
+    int rc = size_net(n, {SIZE_MAX, SIZE_MAX}, false);
     if (rc != ASGD_OK || n.ws_bytes <= kStaticWsBytes) return rc;
-    // Beyond the static workspace with the kernels chosen for speed.  If the general engine's kernels would fit it, the plan is made
-    // to, with fewer partial sums or (few need that) without padded filters: what asgd_fwd_bwd_static accepts does not depend on how
-    // the fast kernels are split.
+    // Beyond the static workspace with the kernels chosen for speed.  If it would fit with no more partial sums than tiles of 128 rows
+    // leave, or with the general engine's kernels, the plan is made to, with fewer partial sums or (few need that) without padded
+    // filters: what asgd_fwd_bwd_static accepts does not depend on how the fast kernels are split.
     const std::vector<Stage> fast = n.stages;
     const size_t bytes = n.ws_bytes, scratch_side = n.scratch_side_floats;
-    auto room = [&](size_t off) { return off + 1024 < kStaticWsBytes ? (kStaticWsBytes - off - 1024) / 4 : 0; };
-    const size_t fast_room = room(n.shared_off);
-    rc = size_net(n, 0, true);
-    if (rc == ASGD_OK && n.apart_bytes <= kStaticWsBytes) {
-        const size_t plain_room = room(n.shared_off);
-        rc = size_net(n, fast_room, false);
-        if (rc == ASGD_OK && n.ws_bytes > kStaticWsBytes) rc = size_net(n, plain_room, true);
+    auto room = [&]() { return n.shared_off + 1024 < kStaticWsBytes ? (kStaticWsBytes - n.shared_off - 1024) / 4 : 0; };
+    rc = size_net(n, {SIZE_MAX, 0}, false);   // no split data gradient: all of their filters padded, so the room is the least there is
+    size_t fast_room = room(), plain_room = 0;
+    bool fits = n.ws_bytes <= kStaticWsBytes;
+    if (fits) {
+        fast_room = std::max(fast_room, n.scratch_side_floats - kScratchSpare);
+    } else {
+        rc = size_net(n, {0, 0}, true);
+        plain_room = room();
+        fits = n.apart_bytes <= kStaticWsBytes;
+    }
+    if (rc == ASGD_OK && fits) {
+        rc = size_net(n, {fast_room, fast_room}, false);
+        if (rc == ASGD_OK && n.ws_bytes > kStaticWsBytes) rc = size_net(n, {plain_room, plain_room}, true);
         return rc;
     }
     n.stages = fast;
@@ -361,7 +373,7 @@ int plan_net(asgd_net &n)
     return rc;
 }
 
-int size_net(asgd_net &n, size_t partials, bool plain)
+int size_net(asgd_net &n, const Budget &partials, bool plain)
 {
     const long B = n.batch;
     size_t scratch = 0, scratch_side = 0;
@@ -370,29 +382,29 @@ int size_net(asgd_net &n, size_t partials, bool plain)
         if (s.kind == ST_CONV) {
             const long M = B * s.outH * s.outW, Min = B * s.inH * s.inW;
             // partial sums of a data gradient go where those of the filter gradients go: on one stream, behind the forward pass
-            const bool whole = plain || n.fork_pays;
+            const size_t side = n.fork_pays ? 0 : partials.narrow;
             const long K = s.rw ? (long)s.k * s.rwKW : (long)s.k * s.k * s.inCp;
             if (s.rw && (long)B * s.rwHp * s.rwWp * s.rwC * 4 > 0x7fffffffL) return fail(ASGD_ESHAPE, "layer %d: tensor too large", s.first_layer);
             if (M > 0x7fffffffL / 2 || Min > 0x7fffffffL / 2 || M * s.outCp * 4 > 0x7fffffffL || Min * s.inCp * 4 > 0x7fffffffL) return fail(ASGD_ESHAPE, "layer %d: tensor too large", s.first_layer);
             if (s.groups > 1) {   // one GEMM per group, on that group's channel slices
                 const long Cg = s.inC / s.groups, Og = s.outC / s.groups, Kg = (long)s.k * s.k * Cg;
-                s.p_fwd = plan_conv(M, Og, Kg, n.dtype, true, nullptr);
-                s.p_dgrad = plan_conv(Min, Cg, (long)s.k * s.k * Og, n.dtype, whole, nullptr);
-                s.p_wgrad = plan_filter_grad(Og, Kg, M, n.dtype, plain);
+                s.p_fwd = plan_conv(M, Og, Kg, n.dtype, 0, nullptr);
+                s.p_dgrad = plan_conv(Min, Cg, (long)s.k * s.k * Og, n.dtype, side, nullptr);
+                s.p_wgrad = plan_filter_grad(Og, Kg, M, n.dtype, partials.narrow);
             } else {
-                s.p_fwd = plan_conv(M, s.outCp, K, n.dtype, true, nullptr);
-                s.p_dgrad = plan_conv(Min, s.inCp, (long)s.k * s.k * s.outCp, n.dtype, whole, nullptr);
-                s.p_wgrad = plan_filter_grad(s.outCp, K, M, n.dtype, plain);
+                s.p_fwd = plan_conv(M, s.outCp, K, n.dtype, 0, nullptr);
+                s.p_dgrad = plan_conv(Min, s.inCp, (long)s.k * s.k * s.outCp, n.dtype, side, nullptr);
+                s.p_wgrad = plan_filter_grad(s.outCp, K, M, n.dtype, partials.narrow);
                 // the first layer's filter gradient as one persistent kernel wants a partial result per workgroup
                 if (s.rw) s.p_wgrad.ws_floats = std::max(s.p_wgrad.ws_floats, rows_wgrad_ws_floats(n.dtype, s.outCp, conv_gather(s, nullptr, (int)B, n.dtype)));
             }
             const int Ng = s.groups > 1 ? s.outC / s.groups : s.outCp, Cg = s.groups > 1 ? s.inC / s.groups : s.inCp;
-            s.d_wgrad = plan_wgrad(n.dtype, Ng, s.groups, conv_gather(s, nullptr, (int)B, n.dtype), partials);
+            s.d_wgrad = plan_wgrad(n.dtype, Ng, s.groups, conv_gather(s, nullptr, (int)B, n.dtype), partials.wgrad);
             s.d_fwd = plain ? DirectPlan() : plan_direct(n.dtype, conv_gather(s, nullptr, (int)B, n.dtype), Ng);
             s.wf_elems = s.d_fwd.ks ? s.d_fwd.pack_elems : (size_t)Ng * s.k * (s.rw ? s.rwKW : s.k * Cg);
             if (si > 0) {
                 s.d_dgrad = plain ? DirectPlan() : plan_direct(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg);
-                if (!whole && split_is_faster(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg, s.d_dgrad)) s.d_dgrad = DirectPlan();
+                if (split_is_faster(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg, s.d_dgrad, side)) s.d_dgrad = DirectPlan();
                 s.wd_elems = s.d_dgrad.ks ? s.d_dgrad.pack_elems : (size_t)Cg * s.k * s.k * Ng;
             }
             if (si > 0 && !s.d_dgrad.ks) scratch_side = std::max(scratch_side, s.p_dgrad.ws_floats);
@@ -421,8 +433,8 @@ int size_net(asgd_net &n, size_t partials, bool plain)
             s.colsum_floats = colsum_ws_floats(n.dtype, B, s.out_ld);
         }
     }
-    n.scratch_floats = scratch + 64;
-    n.scratch_side_floats = scratch_side + 64;
+    n.scratch_floats = scratch + kScratchSpare;
+    n.scratch_side_floats = scratch_side + kScratchSpare;
     n.ws_bytes = carve(n, nullptr);
     return ASGD_OK;
 }

@@ -97,7 +97,8 @@ struct DirectPlan {
     size_t nblk_elems = 0, pack_elems = 0;
 };
 DirectPlan plan_direct(int dtype, const Gather &a, int N);   // none where the general engine is the faster one
-bool split_is_faster(int dtype, const Gather &a, int N, const DirectPlan &d);   // than plan d: the general engine in K splits (plan_conv)
+// whether the general engine in K splits (plan_conv) is faster than plan d
+bool split_is_faster(int dtype, const Gather &a, int N, const DirectPlan &d, size_t partials);
 int conv_direct(int dtype, const Gather &a, const void *wpack, int N, const Epilogue &ep, const DirectPlan &plan, hipStream_t s);
 
 // Filter gradients of stride-1 convolutions over equal grids in 16-bit data (conv_wgrad.hip): tile shape (-1: does not run
@@ -115,8 +116,9 @@ int splitk_reduce(int dtype, const float *ws, int splits, const Epilogue &ep, in
 // Every operand must fit in 1 GiB.
 // C[M][N] = A[M][K] * B[N][K]^T; A gathered (direct), B plain K-contiguous.
 GemmPlan plan_gemm(long M, long N, long K, int dtype, int max_splits);
-GemmPlan plan_conv(long M, long N, long K, int dtype, bool lean, double *us);
-GemmPlan plan_filter_grad(long M, long N, long K, int dtype, bool lean);
+// partials: floats that partial sums may take
+GemmPlan plan_conv(long M, long N, long K, int dtype, size_t partials, double *us);
+GemmPlan plan_filter_grad(long M, long N, long K, int dtype, size_t partials);
 int gemm_gather_plain(int dtype, const Gather &a, const void *b, long ldb, int N, const Epilogue &ep,
                       const GemmPlan &plan, float *ws, hipStream_t s);
 // A plain [M][lda], B plain [b_rows][ldb], both K-contiguous; columns n >= b_rows of C are computed as zeros.

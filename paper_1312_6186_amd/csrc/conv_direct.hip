@@ -124,10 +124,10 @@ DirectPlan plan_direct(int dtype, const Gather &a, int N)
 }
 
 // Few columns over few pixels: the general engine in K splits, where it is modelled a quarter faster.
-bool split_is_faster(int dtype, const Gather &a, int N, const DirectPlan &d)
+bool split_is_faster(int dtype, const Gather &a, int N, const DirectPlan &d, size_t partials)
 {
     double us = 0;
-    return d.ks && plan_conv((long)a.N * a.H * a.W, N, (long)a.kh * a.kw * a.C, dtype, false, &us).splits > 1 &&
+    return d.ks && plan_conv((long)a.N * a.H * a.W, N, (long)a.kh * a.kw * a.C, dtype, partials, &us).splits > 1 &&
            us < 0.75 * direct_us((int)dtype_size(dtype), d.ks, d.nchunks, kTiles[d.tile], a, N);
 }
 

@@ -1342,8 +1342,8 @@ GemmPlan plan_gemm(long M, long N, long K, int dtype, int max_splits)
 // Convolution over M pixels with N output columns.  Up to 32 columns in tiles of 128 x 32 (a tile of 128 columns leaves three of four
 // waves without a column: 3 -> 32 channels 5 x 5 on 32 x 32 in fp32, 128 images 28 -> 18 us), and where those tiles are fewer than half the CUs
 // and K is long, in K splits: the launch that adds them up costs 5 us, a K tile alone on a CU 0.6 (64 -> 32 channels 5 x 5 on 7 x 7 in
-// fp32, 128 images, 31 us in 49 tiles of conv_direct, 16 + 4 in 10 splits).  us: the modelled time; lean: no partial sums.
-GemmPlan plan_conv(long M, long N, long K, int dtype, bool lean, double *us)
+// fp32, 128 images, 31 us in 49 tiles of conv_direct, 16 + 4 in 10 splits), as far as the partial sums fit.  us: the modelled time.
+GemmPlan plan_conv(long M, long N, long K, int dtype, size_t partials, double *us)
 {
     GemmPlan p = plan_gemm(M, N, K, dtype, 1);
     if (N > 32) return p;
@@ -1351,7 +1351,8 @@ GemmPlan plan_conv(long M, long N, long K, int dtype, bool lean, double *us)
     const int BK = dtype == kBF16 ? (int)Geo<bf16_t>::BK : (int)Geo<float>::BK;
     const double mfma = dtype == kBF16 ? 0.1 : 0.43;
     const long tiles = (M + 127) / 128, nkt = (K + BK - 1) / BK;
-    const long most = lean || tiles >= 128 ? 1 : std::max(1L, std::min(std::min(nkt / 4, 32L), 512 / tiles));
+    const long fit = (long)std::min(partials / ((size_t)M * (size_t)N), (size_t)32);
+    const long most = tiles >= 128 ? 1 : std::max(1L, std::min(std::min(nkt / 4, fit), 512 / tiles));
     double best = 0;
     for (long splits = 1, per = nkt; splits <= most;) {
         const double t = 8.0 + rounds_us(tiles * splits, 4, [&](int r) { return std::max(0.6, mfma * r) * per; }) + (splits > 1 ? 5.0 + 1.5e-6 * splits * M * N : 0.0);
@@ -1368,8 +1369,8 @@ GemmPlan plan_conv(long M, long N, long K, int dtype, bool lean, double *us)
 // Filter gradient over K pixels: M output channels, N window columns.  Up to 64 channels in tiles of 32 or 64 rows (a tile of 128
 // leaves the matrix cores of waves beyond the channels idle: 32 channels, 5 x 5 over 32, fp32, 28800 pixels 51 us there, 24 here; 3 channels, 131072 pixels 73 and 15), and in
 // the number of pixel ranges with the smallest modelled time, partial sums included; in fp32 a K tile is 16 or 32 MFMAs of 64
-// cycles a SIMD, in bf16 it is its latency.  lean: no more partial sums than the tile of 128 would leave.
-GemmPlan plan_filter_grad(long M, long N, long K, int dtype, bool lean)
+// cycles a SIMD, in bf16 it is its latency.  As many partial sums as the tile of 128 would leave are always allowed, more as far as they fit.
+GemmPlan plan_filter_grad(long M, long N, long K, int dtype, size_t partials)
 {
     const GemmPlan wide = plan_gemm(M, N, K, dtype, 128);
     if (M > 64) return wide;
@@ -1378,7 +1379,8 @@ GemmPlan plan_filter_grad(long M, long N, long K, int dtype, bool lean)
     const int BK = dtype == kBF16 ? (int)Geo<bf16_t>::BK : (int)Geo<float>::BK, per_cu = p.bm == 32 && dtype == kF32 ? 3 : 2;
     const double mfma = dtype == kBF16 ? 0.0 : p.bm == 32 ? 0.43 : 0.86, alone = dtype == kBF16 ? 0.35 : 0.6;
     const long tiles = (N + 127) / 128, nkt = (K + BK - 1) / BK;
-    const long most = std::max(1L, std::min(std::min(nkt / 2, 512L), lean ? (long)wide.splits : 256 * per_cu / tiles));
+    const long fit = (long)std::min(partials / ((size_t)M * (size_t)N), (size_t)512);
+    const long most = std::max(1L, std::min(nkt / 2, std::min(std::max(fit, (long)wide.splits), 256 * per_cu / tiles)));
     double best = 0;
     for (long splits = 1, per = nkt; splits <= most;) {
         const double us = rounds_us(tiles * splits, per_cu, [&](int r) { return std::max(alone * (0.75 + 0.25 * r), mfma * r) * per; }) +

@@ -36,6 +36,11 @@ STATIC_NETS = {
     "padded_f32": (_conv(80, 1) + _conv(360, 3) + [("maxpool", 2, 2), ("fc", 8), ("softmax_ce",)], (3, 15, 12), 39, B.F32),
     "wide_f32": (_conv(424, 3) + [("maxpool", 2, 2)] + _conv(392, 3) + _conv(424, 3) + _conv(400, 5) + [("fc", 16), ("softmax_ce",)], (3, 12, 35), 2, B.F32),
     "padded_bf16": (_conv(40, 5) + _conv(480, 3) + [("maxpool", 2, 2), ("fc", 8), ("softmax_ce",)], (8, 11, 25), 45, B.BF16),
+    # filter gradients of up to 64 channels, split data gradients: their partial sums are held to what is left of the workspace
+    "few_channels": (_conv(64, 3) + [("fc", 128), ("relu",), ("fc", 10), ("softmax_ce",)], (16, 36, 57), 55, B.BF16),
+    "few_strided": (_conv(256, 3) + [("maxpool", 3, 2), ("conv", 64, 7, 2, 3), ("relu",), ("lrn", 5, 1e-4, 0.75, 2.0), ("maxpool", 2, 2), ("fc", 64), ("relu",),
+                                     ("fc", 10), ("softmax_ce",)], (8, 23, 12), 146, B.BF16),
+    "small": (wl.SMALL["layers"], wl.SMALL["in_shape"], 131, B.F32),
 }
 
 
@@ -98,7 +103,7 @@ def test_static_entry_point_matches_fwd_bwd_on_two_calls_in_a_row():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("name", ["alexnet", "grouped", "wide_f32", "padded_f32", "padded_bf16"])
+@pytest.mark.parametrize("name", ["alexnet", "grouped", "wide_f32", "padded_f32", "padded_bf16", "few_channels", "small"])
 def test_static_entry_point_takes_plans_near_the_size_of_its_workspace(name):
     """Plans that fit as they are, with fewer partial sums, or with the general engine's kernels only: two calls in a row, bit for bit."""
     layers, in_shape, batch, dtype = STATIC_NETS[name]
@@ -119,3 +124,29 @@ def test_static_entry_point_takes_plans_near_the_size_of_its_workspace(name):
     finally:
         torch.cuda.synchronize()
         B.asgd_net_destroy(net)
+
+
+@pytest.mark.gpu
+def test_a_net_near_the_static_workspace_keeps_its_fast_convolutions():
+    """At 118 images this net fits the static workspace with all the partial sums it could use, at 120 with fewer: that must not cost it the
+    convolutions whose padded filters fit.  They sum in another order (chunks of channels, then window positions) than the general engine, so the
+    third convolution's outputs, over two chunks, are the same bits only if both plans run the same kernel."""
+    layers = [("conv", 16, 3, 1, 0), ("relu",), ("conv", 64, 3, 1, 1, 2), ("relu",), ("maxpool", 3, 2), ("conv", 8, 5, 1, 2), ("relu",), ("maxpool", 3, 2), ("fc", 208),
+              ("relu",), ("fc", 7), ("softmax_ce",)]
+    in_shape, outs = (8, 13, 60), []
+    _, _, copy, images, labels = _case({"layers": layers, "in_shape": in_shape, "classes": 7}, 120, B.F32, 31)
+    for batch in (118, 120):
+        net = B.asgd_net_create(layers, batch, in_shape, B.F32)
+        try:
+            assert B.asgd_workspace_bytes(net) <= B.asgd_static_workspace_bytes()
+            grads = torch.empty(B.asgd_param_count(net), device=DEV)
+            B.asgd_fwd_bwd(net, copy, images[:batch].contiguous(), labels[:batch].contiguous(), 77, 5, 2, torch.zeros(1, device=DEV), grads)
+            c, h, w = B.asgd_layer_shape(net, 6)
+            out = torch.full((batch, c, h, w), float("nan"), device=DEV)
+            B.asgd_debug_get(net, B.DEBUG_OUTPUT, 6, out)
+            torch.cuda.synchronize()
+            outs.append(out[:118])
+        finally:
+            torch.cuda.synchronize()
+            B.asgd_net_destroy(net)
+    assert torch.isfinite(outs[0]).all() and torch.equal(outs[0], outs[1])
