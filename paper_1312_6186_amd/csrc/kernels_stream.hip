@@ -1203,7 +1203,14 @@ static bool pool_flat_plan(int dtype, int B, int H, int W, int C, int Cp, int k,
     p.groups = std::max(1, std::min(p.cv, 256 / p.hw));   // one pooled pixel and group a thread
     p.chunks = (p.cv + p.groups - 1) / p.groups;
     p.lanes = 256 / p.groups; p.Hb = (H + 1) / 2; p.Wb = (W + 1) / 2;
-    if ((long)B * p.chunks > 0x7fffffffL) return false;
+    const long blocks = (long)B * p.chunks, reads = (long)p.hw * k * k;
+    if (blocks > 0x7fffffffL) return false;
+    // A block that makes many pooled pixels in turn, one 16-byte group of each, is long: the two launches that the separate kernels
+    // cost (about 8 us) pay for 1800 reads of a group, or for 4500 where a group is the whole pixel; beyond, half the CUs have to
+    // have a block, and more of them the more a block reads (four-byte data and windows of 3 over large grids gain nothing).  A pass
+    // with separate kernels / here, us: bf16, 64 channels, 20 x 20 pools of 2 1 image 53 / 55, 64 images 90 / 79, 45 x 45
+    // 78 / 99 and 221 / 182; 32 x 32 pools of 3 63 / 85 and 142 / 136.
+    if (reads > (p.cv == 1 ? 4500 : 1800) && (blocks < std::max(128L, reads / 36) || (V == 4 && k == 3 && reads > 4600))) return false;
     lds_fwd = (size_t)p.groups * p.hw * 16;
     lds_bwd = std::max(lds_fwd, (size_t)p.lanes * p.groups * V * 4);
     p.dgroups = make_fastdiv(p.groups); p.dchunks = make_fastdiv(p.chunks); p.dWo = make_fastdiv(p.Wo); p.dWb = make_fastdiv(p.Wb);
