@@ -388,12 +388,12 @@ int size_net(asgd_net &n, const Budget &partials, bool plain)
             if (M > 0x7fffffffL / 2 || Min > 0x7fffffffL / 2 || M * s.outCp * 4 > 0x7fffffffL || Min * s.inCp * 4 > 0x7fffffffL) return fail(ASGD_ESHAPE, "layer %d: tensor too large", s.first_layer);
             if (s.groups > 1) {   // one GEMM per group, on that group's channel slices
                 const long Cg = s.inC / s.groups, Og = s.outC / s.groups, Kg = (long)s.k * s.k * Cg;
-                s.p_fwd = plan_conv(M, Og, Kg, n.dtype, 0, nullptr);
-                s.p_dgrad = plan_conv(Min, Cg, (long)s.k * s.k * Og, n.dtype, side, nullptr);
+                s.p_fwd = plan_conv(M, Og, Kg, n.dtype, 1, 0, nullptr);
+                s.p_dgrad = plan_conv(Min, Cg, (long)s.k * s.k * Og, n.dtype, s.stride, side, nullptr);
                 s.p_wgrad = plan_filter_grad(Og, Kg, M, n.dtype, partials.narrow);
             } else {
-                s.p_fwd = plan_conv(M, s.outCp, K, n.dtype, 0, nullptr);
-                s.p_dgrad = plan_conv(Min, s.inCp, (long)s.k * s.k * s.outCp, n.dtype, side, nullptr);
+                s.p_fwd = plan_conv(M, s.outCp, K, n.dtype, 1, 0, nullptr);
+                s.p_dgrad = plan_conv(Min, s.inCp, (long)s.k * s.k * s.outCp, n.dtype, s.stride, side, nullptr);
                 s.p_wgrad = plan_filter_grad(s.outCp, K, M, n.dtype, partials.narrow);
                 // the first layer's filter gradient as one persistent kernel wants a partial result per workgroup
                 if (s.rw) s.p_wgrad.ws_floats = std::max(s.p_wgrad.ws_floats, rows_wgrad_ws_floats(n.dtype, s.outCp, conv_gather(s, nullptr, (int)B, n.dtype)));

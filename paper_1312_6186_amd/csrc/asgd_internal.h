@@ -117,7 +117,7 @@ int splitk_reduce(int dtype, const float *ws, int splits, const Epilogue &ep, in
 // C[M][N] = A[M][K] * B[N][K]^T; A gathered (direct), B plain K-contiguous.
 GemmPlan plan_gemm(long M, long N, long K, int dtype, int max_splits);
 // partials: floats that partial sums may take
-GemmPlan plan_conv(long M, long N, long K, int dtype, size_t partials, double *us);
+GemmPlan plan_conv(long M, long N, long K, int dtype, int zoom, size_t partials, double *us);
 GemmPlan plan_filter_grad(long M, long N, long K, int dtype, size_t partials);
 int gemm_gather_plain(int dtype, const Gather &a, const void *b, long ldb, int N, const Epilogue &ep,
                       const GemmPlan &plan, float *ws, hipStream_t s);

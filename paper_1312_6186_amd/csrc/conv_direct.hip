@@ -127,7 +127,7 @@ DirectPlan plan_direct(int dtype, const Gather &a, int N)
 bool split_is_faster(int dtype, const Gather &a, int N, const DirectPlan &d, size_t partials)
 {
     double us = 0;
-    return d.ks && plan_conv((long)a.N * a.H * a.W, N, (long)a.kh * a.kw * a.C, dtype, partials, &us).splits > 1 &&
+    return d.ks && plan_conv((long)a.N * a.H * a.W, N, (long)a.kh * a.kw * a.C, dtype, 1, partials, &us).splits > 1 &&
            us < 0.75 * direct_us((int)dtype_size(dtype), d.ks, d.nchunks, kTiles[d.tile], a, N);
 }
 

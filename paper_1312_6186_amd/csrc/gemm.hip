@@ -1342,8 +1342,11 @@ GemmPlan plan_gemm(long M, long N, long K, int dtype, int max_splits)
 // Convolution over M pixels with N output columns.  Up to 32 columns in tiles of 128 x 32 (a tile of 128 columns leaves three of four
 // waves without a column: 3 -> 32 channels 5 x 5 on 32 x 32 in fp32, 128 images 28 -> 18 us), and where those tiles are fewer than half the CUs
 // and K is long, in K splits: the launch that adds them up costs 5 us, a K tile alone on a CU 0.6 (64 -> 32 channels 5 x 5 on 7 x 7 in
-// fp32, 128 images, 31 us in 49 tiles of conv_direct, 16 + 4 in 10 splits), as far as the partial sums fit.  us: the modelled time.
-GemmPlan plan_conv(long M, long N, long K, int dtype, size_t partials, double *us)
+// fp32, 128 images, 31 us in 49 tiles of conv_direct, 16 + 4 in 10 splits), as far as the partial sums fit.  Data gradients of strided convolutions (zoom: their stride) in bf16 are bound by the
+// addresses of their gather, which the 512 threads of the tiles of 128 columns work out faster where a CU has one tile, or two and a
+// long K: 25 K tiles (5 x 5, stride 2, over 64 channels) 129 to 252 tiles 27 us in 128 columns, 32 here, 368 and 509 tiles 34.5 in both, 613 tiles
+// 52 and 41; 49 K tiles 44 and 56, 58 and 61, 88 and 73.  us: the modelled time.
+GemmPlan plan_conv(long M, long N, long K, int dtype, int zoom, size_t partials, double *us)
 {
     GemmPlan p = plan_gemm(M, N, K, dtype, 1);
     if (N > 32) return p;
@@ -1361,6 +1364,7 @@ GemmPlan plan_conv(long M, long N, long K, int dtype, size_t partials, double *u
         splits = (nkt + per - 2) / (per - 1);
         per = (nkt + splits - 1) / splits;
     }
+    if (zoom > 1 && dtype == kBF16 && p.splits == 1 && tiles <= 512 && nkt > (tiles <= 256 ? 8 : 32)) p.bn = 128;
     p.ws_floats = p.splits > 1 ? (size_t)p.splits * (size_t)M * (size_t)N : 0;
     if (us) *us = best;
     return p;

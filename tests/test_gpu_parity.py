@@ -321,9 +321,10 @@ def test_few_channel_filter_gradient_shapes(shape, dtype):
 
 
 # Convolutions of up to 32 output columns in tiles of 128 x 32, forward and data gradient, and data gradients over few pixels in K
-# splits (nets that stay on one stream): columns around the tile, pixels around one tile and half the CUs, strided and unstrided.
+# splits (nets that stay on one stream): columns around the tile, pixels around one tile and half the CUs, strided and unstrided; data gradients
+# of strided convolutions in bf16 by tiles of 128 columns, one or two to a CU, and past them.
 NARROW_SHAPES = [(32, 64, 5, 1, 7, 7, 60), (24, 96, 3, 1, 5, 5, 5), (8, 136, 3, 1, 11, 12, 1), (40, 32, 3, 2, 13, 12, 7), (32, 40, 5, 1, 16, 16, 63), (32, 40, 5, 1, 16, 16, 65),
-                 (16, 8, 7, 2, 20, 18, 9)]
+                 (16, 8, 7, 2, 20, 18, 9), (24, 64, 5, 2, 28, 27, 22), (8, 256, 3, 2, 41, 40, 23), (32, 64, 3, 2, 33, 32, 67)]
 
 
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
