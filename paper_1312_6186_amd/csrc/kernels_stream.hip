@@ -1622,8 +1622,14 @@ long lrn_pool_bands(int dtype, int B, int H, int W, int Cp, int k, int stride)
     LrnPool p;
     size_t f, b;
     if (!lrn_pool_plan(dtype, H, W, Cp, k, stride, p, f, b)) return 0;
-    if ((long)B * p.tiles * p.chunks > 0x7fffffffL || (long)B * p.Hb > 0x7fffffffL) return 0;
-    return (long)B * p.Hb;
+    const long blocks = (long)B * p.Hb;
+    if ((long)B * p.tiles * p.chunks > 0x7fffffffL || blocks > 0x7fffffffL) return 0;
+    // A block of the backward kernel takes 2 * W pixels, p.lanes side by side: more than seven rounds of that are longer than the launch
+    // and the tensors they save unless the CUs are full of blocks.  Both kernels with the bias sums, separate / here, us, bf16: 55 x 55
+    // over 256 channels (14 rounds) 1 image 78 / 88, 4 images 85 / 90, 8 images (224 blocks) 94 / 93, 32 images 149 / 135; 16 x 200 over
+    // 64 (12.5 rounds) 8 images 81 / 86, 32 images (256 blocks) 96 / 93; 13 x 13 over 512 (6.5 rounds) 4 images 58 / 48.
+    if (2 * W > 7 * p.lanes && blocks * p.lanes < 32L * W) return 0;
+    return blocks;
 }
 template <typename T, int HALF>
 static void launch_lrn_pool_t(const LrnPool &p, int B, int k, size_t lds, const void *a, void *y, const void *dy, uint8_t *arg, void *da, float *bands,

@@ -381,9 +381,11 @@ def test_pool_under_fc_shapes(shape, dtype):
 
 # Response normalisation with a pool of stride 2 on top, one kernel each way: channels around a wavefront's 64 groups of 16 bytes
 # (512 channels in bf16, 256 in fp32; more run separate kernels) and with padding channels, rows around the width that fits
-# the forward kernel's LDS (213 pixels for windows of 3), one pooled row, an odd last row and column, every window size.
+# the forward kernel's LDS (213 pixels for windows of 3), one pooled row, an odd last row and column, every window size; many pixels in
+# turn for a workgroup, with too few of them (separate kernels) and with enough.
 LRNPOOL_SHAPES = [(8, 3, 4, 3, 1, 3), (12, 9, 10, 2, 5, 3), (96, 23, 21, 3, 5, 3), (40, 13, 14, 2, 9, 2), (256, 9, 6, 2, 3, 3), (264, 5, 6, 1, 7, 2), (512, 6, 5, 1, 5, 3),
-                  (520, 5, 5, 1, 5, 3), (8, 7, 213, 1, 5, 3), (8, 7, 216, 1, 5, 3), (16, 4, 320, 1, 5, 2)]
+                  (520, 5, 5, 1, 5, 3), (8, 7, 213, 1, 5, 3), (8, 7, 216, 1, 5, 3), (16, 4, 320, 1, 5, 2),
+                  (256, 5, 30, 1, 5, 3), (256, 22, 30, 11, 5, 3), (128, 16, 32, 16, 5, 2), (128, 16, 32, 15, 5, 2)]
 
 
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
