@@ -340,12 +340,14 @@ def test_narrow_convolution_shapes(shape, dtype):
         g.close()
 
 
-# Weight gradients of fully-connected layers: tiles of 128 x 128 with ragged edges on both sides, batches around the K tiles (64 in
-# bf16, 32 in fp32) and around the limits of the kernel for short sums (two K tiles; 512 with 256 tiles and more).
+# Weight gradients of fully-connected layers, batches around the K tiles (64 in bf16, 32 in fp32).  From 512 inputs into up to 264: the
+# kernel for small products (up to 1024 tiles of 16 x 16), ragged outputs.  Larger ones in tiles of 128 x 128, ragged on both sides (648 inputs) or with
+# 256 tiles and more (2048 inputs): the kernel for short sums up to its limits (two K tiles; 512 with 256 tiles and more), the general one past them.
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
-@pytest.mark.parametrize("out,batch", [(136, 1), (200, 31), (128, 64), (72, 65), (264, 128), (40, 129), (2040, 33), (2056, 512), (2048, 513)])
+@pytest.mark.parametrize("out,batch", [(136, 1), (200, 31), (128, 64), (72, 65), (264, 128), (40, 129), (536, 1), (528, 31), (520, 32), (552, 33), (520, 64), (552, 65), (536, 128),
+                                       (520, 129), (2040, 33), (2056, 512), (2048, 513)])
 def test_fc_weight_gradient_shapes(out, batch, dtype):
-    shape = (8, 8, 8) if out < 1000 else (32, 8, 8)
+    shape = (8, 8, 8) if out < 500 else (8, 9, 9) if out < 1000 else (32, 8, 8)
     layers = [("fc", out), ("relu",), ("fc", 10), ("softmax_ce",)]
     g, onet, (loss, grads), (ref_loss, ref_grads, _), _ = _net_case({"name": "fc", "in_shape": shape, "classes": 10, "layers": layers}, batch, dtype, plain=False)
     try:
