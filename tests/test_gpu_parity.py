@@ -705,13 +705,19 @@ def test_accumulate_matches_numpy(n, offset):
     assert (acc.cpu().numpy()[:offset] == 7.0).all()
 
 
+# Fully-connected weights of more than 1024 tiles of 16 x 16, ragged on both sides of the tiles of 128 x 128: past the kernel for small products
+WIDE_FC = {"layers": [("conv", 24, 3, 1, 1), ("relu",), ("maxpool", 2, 2), ("fc", 264), ("relu",), ("dropout", 0.5), ("fc", 1032), ("relu",), ("fc", 10), ("softmax_ce",)],
+           "in_shape": (3, 14, 14)}
+
+
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
 @pytest.mark.parametrize("n_sync", [0, 1, 3])
-def test_replay_with_fused_pushes_is_the_separate_kernels_bit_for_bit(n_sync, dtype):
+@pytest.mark.parametrize("cfg", [RAGGED, WIDE_FC], ids=["ragged", "wide_fc"])
+def test_replay_with_fused_pushes_is_the_separate_kernels_bit_for_bit(cfg, n_sync, dtype):
     """Parameters at a 4-byte offset go through the separate update, snapshot and accumulate kernels: everything that the
     replay leaves, the replicas' gradients among it, must be the same.  Six replicas fetch one version (a push writes
     four copies at most), and the last replica's only gradient is of an early version."""
-    layers, shape, batch, W = RAGGED["layers"], RAGGED["in_shape"], 8, 6   # minibatches of a multiple of 16 bytes
+    layers, shape, batch, W = cfg["layers"], cfg["in_shape"], 8, 6   # minibatches of a multiple of 16 bytes
     worker = np.array([0, 1, 2, 3, 4, 5, 0, 1, 2, 3, 4, 0, 1], np.int32)
     rv = np.array([0, 0, 1, 1, 4, 0, 6, 6, 6, 6, 6, 7, 12], np.int32)
     T, k, tdt = len(worker), max(n_sync, 1), torch.bfloat16 if dtype == B.BF16 else torch.float32
