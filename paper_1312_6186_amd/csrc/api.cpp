@@ -1262,10 +1262,6 @@ int asgd_debug_get(asgd_net_t *net, int what, int layer, void *dst, size_t cap_b
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int B = net->batch;
     if (what == ASGD_DEBUG_OUTPUT) {
-        if (s.with_pool) {   // the pass keeps the normalised tensor in LDS: formed from the convolution's output, by the kernel of the pass's arithmetic
-            CHECK_LAUNCH(launch_lrn_fwd(net->dtype, net->stages[net->layer_stage[layer] - 1].out, s.out, (size_t)B * s.outH * s.outW, s.outCp, s.k,
-                                        s.lrn_alpha, s.lrn_beta, s.lrn_bias, st), "lrn forward");
-        }
         if (layer != s.last_layer) return fail(ASGD_EINVAL, "asgd_debug_get: layer %d is fused into the group ending at layer %d", layer, s.last_layer);
         if (s.to_flat) {   // canonical order already
             const size_t F = (size_t)s.outC * s.outH * s.outW;
@@ -1276,6 +1272,9 @@ int asgd_debug_get(asgd_net_t *net, int what, int layer, void *dst, size_t cap_b
             CHECK_LAUNCH(launch_export_rows(net->dtype, s.last ? 1 : 0, s.out, s.out_ld, static_cast<float *>(dst), B, s.out_f, st), "export");
         } else {
             if (cap_bytes < (size_t)B * s.outC * s.outH * s.outW * 4) return fail(ASGD_EINVAL, "asgd_debug_get: destination too small");
+            if (s.with_pool)   // the pass keeps the normalised tensor in LDS: formed from the convolution's output, by the kernel of the pass's arithmetic
+                CHECK_LAUNCH(launch_lrn_fwd(net->dtype, net->stages[net->layer_stage[layer] - 1].out, s.out, (size_t)B * s.outH * s.outW, s.outCp, s.k,
+                                            s.lrn_alpha, s.lrn_beta, s.lrn_bias, st), "lrn forward");
             CHECK_LAUNCH(launch_export_nhwc(net->dtype, s.out, static_cast<float *>(dst), B, s.outH, s.outW, s.outC, s.outCp, st), "export");
         }
         return ASGD_OK;
