@@ -125,9 +125,9 @@ struct asgd_net {
 
 namespace {
 
-// Events between streams of one GPU inside a pass carry no fence towards the host and other devices, which costs the recording
-// stream about 3 us each; those that join an internal stream back into the caller's, and those that start one behind the caller's
-// work, do.  One step / with the fence on every event: alexnet bf16 128 images 1333 / 1360 us, one gradient at 32 images 715 / 733.
+// Events between streams of one GPU inside a pass or a replay carry no fence towards the host and other devices, which costs the
+// recording stream about 3 us each.  The one that joins the side stream back into the caller's (ev_join), and those that start a replay behind
+// the caller's work and end it (replay_start, replay_done), do.  One step / with the fence on every event: alexnet bf16 128 images 1333 / 1360 us, one gradient at 32 images 715 / 733.
 constexpr unsigned kInnerEvent = hipEventDisableTiming | hipEventDisableSystemFence, kOuterEvent = hipEventDisableTiming;
 
 struct Carver {
@@ -194,7 +194,8 @@ constexpr size_t kScratchSpare = 64;   // floats behind the largest partial sums
 // Floats that the partial sums of one kernel may take.
 struct Budget {
     size_t wgrad;    // filter gradients in conv_wgrad
-    size_t narrow;   // the general engine's filter gradients of up to 64 channels, beyond what its tiles of 128 rows would leave, and split data gradients
+    size_t narrow;   // split data gradients, and the general engine's filter gradients of up to 64 channels (which may always
+                     // take what its tiles of 128 rows would leave)
 };
 // Chooses the kernels of every stage and sizes the workspace.  plain: no filters padded to their chunks (conv_direct).
 int size_net(asgd_net &n, const Budget &partials, bool plain);
@@ -331,15 +332,17 @@ int plan_net(asgd_net &n)
     }
     if (n.classes == 0 || n.stages.empty() || !n.stages.back().last) return fail(ASGD_ESHAPE, "the layer list must end with FC, SOFTMAX_CE");
     n.param_count = off;
-    // What the side stream hides are the parameter side's partial sums and updates, which grow with the number of weights; what
-    // it costs is a pair of events per layer with parameters and a join, 35 to 60 us a step whatever the batch (all times here with a fence on every event, see kInnerEvent).  One step with /
-    // without it: 28 x 28 net (16 k parameters) fp32 8 images 129 / 81 us, 256 images 254 / 235; 32 x 32 net (0.1 M) bf16 93
-    // images 234 / 203, 512 images 311 / 303, fp32 512 images 997 / 952; the same with 2.5 M parameters in its first
-    // fully-connected layer 283 / 228.  AlexNet-style bf16 with 6.4 M parameters 32 images 589 / 600, 128 images 1155 / 1213; with
-    // its 62 M 16 images 713 / 754, 128 images 1403 / 1450.  And it hides the filter gradients of small fully-connected layers over
-    // thousands of images, a few workgroups with a long sum each: 192 -> 8 outputs in fp32 at 16417 images are 1025 us, a pass takes
-    // 2153 with it and 2584 without; with 435 us of such sums (6733 images) 8955 / 9311, with 286 (4435) 916 / 1146; with 187 (2904)
-    // it is 3745 / 3428, the convolutions then share the CUs with each other.
+    // What the side stream hides are the parameter side's partial sums and updates, which grow with the number of weights; what it
+    // costs is two events per layer with parameters and a join.  One fused step with it / without it, us: 28 x 28 net (16 k
+    // parameters) fp32 8 images 90 / 51, 256 images 113 / 90; 32 x 32 net (0.1 M) bf16 128 images 221 / 165, 512 images 237 / 233,
+    // fp32 512 images 477 / 488; the same with 2.5 M parameters bf16 128 images 223 / 199, 512 images 279 / 280.  AlexNet-style bf16
+    // with 4.4 M parameters 8 images 376 / 399, 128 images 949 / 1019; with its 62 M 16 images 664 / 728, 128 images 1225 / 1292.
+    // (Against the rule: the latter at 256 images 2094 / 2069, 4.4 M in fp32 at 32 images 2121 / 2058.)
+    //
+    // And it hides the filter gradients of small fully-connected layers over thousands of images, a few workgroups with a long sum
+    // each.  192 -> 8 outputs behind three convolutions (64, 128 and 48 channels on 4 x 4) in fp32: 16417 images, 1060 us of such
+    // sums, 2681 / 3184; 4435 images, 286 us, 831 / 961; 3500 images, which the small products' kernel takes, 580 / 580.  Where
+    // there is little beside them it changes nothing (32 and 48 channels, 4435 images 474 / 476).
     double lone = 0;
     for (const Stage &s : n.stages)
         if (s.kind == ST_FC) lone += lone_fc_wgrad_us(n.dtype, s.out_f, s.in_f, n.batch);
@@ -728,8 +731,10 @@ int fc_weight_grad(asgd_net *n, int si, float *grads, const ServerArgs *srv, hip
         ew.upd_lr = srv->lr; ew.upd_mu = srv->mu; ew.upd_wd = srv->wd;
     }
     ProfScope ps(n, st, ASGD_K_FC_WGRAD, 2 * Bd * s.in_f * s.out_f,
-                 Bd * (s.in_f + s.out_f) * es + (double)s.w_cnt * (srv ? 16.0 + es * srv->copies + (srv->keep ? 4.0 : 0.0) + (srv->acc ? srv->acc_first ? 4.0 : 8.0 : 0.0) : 4.0));
-    CHECK_LAUNCH(gemm_trans_trans(n->dtype, s.dout, s.out_ld, s.out_f, x, ldx, s.in_f, n->batch, ew, s.p_wgrad, n->scratch_side, st), "fc weight gradient");
+                 Bd * (s.in_f + s.out_f) * es +
+                     (double)s.w_cnt * (srv ? 16.0 + es * srv->copies + (srv->keep ? 4.0 : 0.0) + (srv->acc ? srv->acc_first ? 4.0 : 8.0 : 0.0) : 4.0));
+    CHECK_LAUNCH(gemm_trans_trans(n->dtype, s.dout, s.out_ld, s.out_f, x, ldx, s.in_f, n->batch, ew, s.p_wgrad, n->scratch_side, st),
+                 "fc weight gradient");
     return ASGD_OK;
 }
 
@@ -1272,7 +1277,7 @@ int asgd_debug_get(asgd_net_t *net, int what, int layer, void *dst, size_t cap_b
             CHECK_LAUNCH(launch_export_rows(net->dtype, s.last ? 1 : 0, s.out, s.out_ld, static_cast<float *>(dst), B, s.out_f, st), "export");
         } else {
             if (cap_bytes < (size_t)B * s.outC * s.outH * s.outW * 4) return fail(ASGD_EINVAL, "asgd_debug_get: destination too small");
-            if (s.with_pool)   // the pass keeps the normalised tensor in LDS: formed from the convolution's output, by the kernel of the pass's arithmetic
+            if (s.with_pool)   // the pass keeps the normalised tensor in LDS: formed anew, in the pass's arithmetic
                 CHECK_LAUNCH(launch_lrn_fwd(net->dtype, net->stages[net->layer_stage[layer] - 1].out, s.out, (size_t)B * s.outH * s.outW, s.outCp, s.k,
                                             s.lrn_alpha, s.lrn_beta, s.lrn_bias, st), "lrn forward");
             CHECK_LAUNCH(launch_export_nhwc(net->dtype, s.out, static_cast<float *>(dst), B, s.outH, s.outW, s.outC, s.outCp, st), "export");
@@ -1449,11 +1454,11 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
             const int w = worker[a];
             RP(hipStreamWaitEvent(ws[w], v > 0 ? ev_upd[v - 1] : ev_reset, 0));
             if (!fetched[a]) {
-            if (launch_snapshot(params, worker_copy[w], P, n0->dtype, counter, log + 3 * (size_t)a, a, w, ws[w]) != 0 && rc == ASGD_OK)
-                rc = hip_fail(hipGetLastError(), "snapshot kernel");
-            if (loc && launch_snapshot(params, loc->params[w], P, kF32, nullptr, nullptr, 0, 0, ws[w]) != 0 && rc == ASGD_OK)
-                rc = hip_fail(hipGetLastError(), "snapshot kernel");   // the replica's own fp32 parameters
-            RP(hipEventRecord(ev_snap[a], ws[w]));
+                if (launch_snapshot(params, worker_copy[w], P, n0->dtype, counter, log + 3 * (size_t)a, a, w, ws[w]) != 0 && rc == ASGD_OK)
+                    rc = hip_fail(hipGetLastError(), "snapshot kernel");
+                if (loc && launch_snapshot(params, loc->params[w], P, kF32, nullptr, nullptr, 0, 0, ws[w]) != 0 && rc == ASGD_OK)
+                    rc = hip_fail(hipGetLastError(), "snapshot kernel");   // the replica's own fp32 parameters
+                RP(hipEventRecord(ev_snap[a], ws[w]));
             }
             for (int i = 0; i < n_sync && rc == ASGD_OK; ++i) {
                 const size_t b = (size_t)a * n_sync + i;   // minibatch and dropout step of local step i of cycle a
@@ -1487,7 +1492,8 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
             for (int a = v + 1; a < T && push.copies < kPushCopies; ++a) {
                 if (read_version[a] != v + 1) continue;
                 const int c = push.copies++;
-                reader[c] = worker[a]; push.copy[c] = worker_copy[worker[a]]; push.log[c] = log + 3 * (size_t)a; push.log_update[c] = a; push.log_worker[c] = worker[a];
+                reader[c] = worker[a]; push.copy[c] = worker_copy[worker[a]];
+                push.log[c] = log + 3 * (size_t)a; push.log_update[c] = a; push.log_worker[c] = worker[a];
                 fetched[a] = 1;
             }
             push.logs = push.copies; push.counter = counter;
@@ -1506,7 +1512,8 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
                 p.nlogs = push.copies; p.counter = counter;
                 if (launch_push_ranges(p, server) != 0) rc = hip_fail(hipGetLastError(), "update kernel");
             }
-        } else if (rc == ASGD_OK && launch_update(params, momentum, loc ? loc->accum[worker[v]] : worker_grads[worker[v]], P, lr, mu, wd, counter, server) != 0)
+        } else if (rc == ASGD_OK &&
+                   launch_update(params, momentum, loc ? loc->accum[worker[v]] : worker_grads[worker[v]], P, lr, mu, wd, counter, server) != 0)
             rc = hip_fail(hipGetLastError(), "update kernel");
         RP(hipEventRecord(ev_upd[v], server));
     }

@@ -222,7 +222,8 @@ int launch_unflatten(int dtype, const void *dflat, const void *x_for_mask, int r
 // db[n] = sum_m dy[m][n], n < N, fp32, fixed summation order, in two stages: launch_colsum_partial sums bands of
 // rows into ws (colsum_ws_floats floats, not shared with another pending job) and appends a job;
 // launch_colsum_finish adds the bands of all pending jobs (up to 12) in one launch.
-struct ColsumJob { const float *ws; float *db; long ld; int nblk, N; unsigned start_block; int colmajor, bf16; float div; };   // ws[band][ld] (bf16: in that type), or ws[column][nblk] if colmajor; sums are divided by div
+// ws[band][ld] (bf16: in that type), or ws[column][nblk] if colmajor; sums are divided by div
+struct ColsumJob { const float *ws; float *db; long ld; int nblk, N; unsigned start_block; int colmajor, bf16; float div; };
 struct ColsumJobs { ColsumJob j[12]; int n; };
 int launch_colsum_partial(int dtype, const void *dy, long ld, long M, int N, float *db, float *ws, ColsumJobs &jobs, hipStream_t s);
 // the same with the first stage put off: colsum_partial_defer appends the tensor to s1 (and its second stage to jobs),

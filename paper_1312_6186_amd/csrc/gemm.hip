@@ -1342,10 +1342,11 @@ GemmPlan plan_gemm(long M, long N, long K, int dtype, int max_splits)
 // Convolution over M pixels with N output columns.  Up to 32 columns in tiles of 128 x 32 (a tile of 128 columns leaves three of four
 // waves without a column: 3 -> 32 channels 5 x 5 on 32 x 32 in fp32, 128 images 28 -> 18 us), and where those tiles are fewer than half the CUs
 // and K is long, in K splits: the launch that adds them up costs 5 us, a K tile alone on a CU 0.6 (64 -> 32 channels 5 x 5 on 7 x 7 in
-// fp32, 128 images, 31 us in 49 tiles of conv_direct, 16 + 4 in 10 splits), as far as the partial sums fit.  Data gradients of strided convolutions (zoom: their stride) in bf16 are bound by the
-// addresses of their gather, which the 512 threads of the tiles of 128 columns work out faster where a CU has one tile, or two and a
-// long K: 25 K tiles (5 x 5, stride 2, over 64 channels) 129 to 252 tiles 27 us in 128 columns, 32 here, 368 and 509 tiles 34.5 in both, 613 tiles
-// 52 and 41; 49 K tiles 44 and 56, 58 and 61, 88 and 73.  us: the modelled time.
+// fp32, 128 images, 31 us in 49 tiles of conv_direct, 16 + 4 in 10 splits), as far as the partial sums fit.  Data gradients of strided
+// convolutions (zoom: their stride) in bf16 are bound by the addresses of their gather, which the 512 threads of the tiles of 128
+// columns work out faster where a CU has one tile, or two and a long K: 25 K tiles (5 x 5, stride 2, over 64 channels) 129 to 252 tiles
+// 27 us in 128 columns, 32 here, 368 and 509 tiles 34.5 in both, 613 tiles 52 and 41; 49 K tiles 44 and 56, 58 and 61, 88 and 73.  us: the
+// modelled time.
 GemmPlan plan_conv(long M, long N, long K, int dtype, int zoom, size_t partials, double *us)
 {
     GemmPlan p = plan_gemm(M, N, K, dtype, 1);
@@ -1358,7 +1359,8 @@ GemmPlan plan_conv(long M, long N, long K, int dtype, int zoom, size_t partials,
     const long most = tiles >= 128 ? 1 : std::max(1L, std::min(std::min(nkt / 4, fit), 512 / tiles));
     double best = 0;
     for (long splits = 1, per = nkt; splits <= most;) {
-        const double t = 8.0 + rounds_us(tiles * splits, 4, [&](int r) { return std::max(0.6, mfma * r) * per; }) + (splits > 1 ? 5.0 + 1.5e-6 * splits * M * N : 0.0);
+        const double t = 8.0 + rounds_us(tiles * splits, 4, [&](int r) { return std::max(0.6, mfma * r) * per; }) +
+                         (splits > 1 ? 5.0 + 1.5e-6 * splits * M * N : 0.0);
         if (best == 0 || t < best) { p.splits = (int)splits; best = t; }
         if (per == 1) break;
         splits = (nkt + per - 2) / (per - 1);
@@ -1371,9 +1373,10 @@ GemmPlan plan_conv(long M, long N, long K, int dtype, int zoom, size_t partials,
 }
 
 // Filter gradient over K pixels: M output channels, N window columns.  Up to 64 channels in tiles of 32 or 64 rows (a tile of 128
-// leaves the matrix cores of waves beyond the channels idle: 32 channels, 5 x 5 over 32, fp32, 28800 pixels 51 us there, 24 here; 3 channels, 131072 pixels 73 and 15), and in
-// the number of pixel ranges with the smallest modelled time, partial sums included; in fp32 a K tile is 16 or 32 MFMAs of 64
-// cycles a SIMD, in bf16 it is its latency.  As many partial sums as the tile of 128 would leave are always allowed, more as far as they fit.
+// leaves the matrix cores of waves beyond the channels idle: 32 channels, 5 x 5 over 32, fp32, 28800 pixels 51 us there, 24 here; 3
+// channels, 131072 pixels 73 and 15), and in the number of pixel ranges with the smallest modelled time, partial sums included; in
+// fp32 a K tile is 16 or 32 MFMAs of 64 cycles a SIMD, in bf16 it is its latency.  As many partial sums as the tile of 128 would leave
+// are always allowed, more as far as they fit.
 GemmPlan plan_filter_grad(long M, long N, long K, int dtype, size_t partials)
 {
     const GemmPlan wide = plan_gemm(M, N, K, dtype, 128);
@@ -1443,11 +1446,13 @@ static int run(const LA &la, const LB &lb, int M, int N, int K, const Epilogue &
     if (la.op.bytes == 0 || lb.op.bytes == 0) return -1;   // an operand beyond the 1 GiB the 32-bit offsets cover
     // Measured on the AlexNet-style shapes: the 8-wave form (four waves per SIMD hide more latency) wins everywhere
     // except the convolution filter gradient, whose two transposing operands want wider wave tiles (gemm_ws_kernel).
-    constexpr bool plain = (std::is_same<LA, PlainK<T>>::value || std::is_same<LA, PlainT<T>>::value) && (std::is_same<LB, PlainK<T>>::value || std::is_same<LB, PlainT<T>>::value);
+    constexpr bool plain = (std::is_same<LA, PlainK<T>>::value || std::is_same<LA, PlainT<T>>::value) &&
+                           (std::is_same<LB, PlainK<T>>::value || std::is_same<LB, PlainT<T>>::value);
     if constexpr (plain) {
         if (lone_applies(M, N, K)) {
             const int tiles_n = (N + 15) / 16, waves = std::min(kLoneWaves, (K + 31) / 32);
-            hipLaunchKernelGGL((lone_kernel<T, LA, LB>), dim3((unsigned)((M + 15) / 16 * tiles_n)), dim3((unsigned)(64 * waves)), 0, s, la, lb, ep, M, N, K, tiles_n);
+            hipLaunchKernelGGL((lone_kernel<T, LA, LB>), dim3((unsigned)((M + 15) / 16 * tiles_n)), dim3((unsigned)(64 * waves)), 0, s, la, lb, ep, M, N, K,
+                               tiles_n);
             return hipGetLastError() == hipSuccess ? 0 : -1;
         }
     }
@@ -1598,16 +1603,17 @@ template <typename T> static int run_outer(const PlainT<T> &la, const PlainT<T> 
 int gemm_trans_trans(int dtype, const void *at, long lda, int M, const void *bt, long ldb, int N, int K, const Epilogue &ep,
                      const GemmPlan &plan, float *ws, hipStream_t s)
 {
-    if (ep.upd_w) {   // push inside the kernel (gemm_kernel over two transposed plain operands carries that path):
-                      // whole sums only, 16-byte rows and column groups in all three buffers
+    if (ep.upd_w) {   // push inside the kernel (update_tile of gemm_kernel over two transposed plain operands, or lone_kernel):
+                      // whole sums only, 16-byte rows and column groups in all buffers
         uintptr_t al = (uintptr_t)ep.upd_w | (uintptr_t)ep.upd_v | (uintptr_t)ep.upd_acc | (uintptr_t)ep.out;
         if (ep.upd_copies < 0 || ep.upd_copies > kPushCopies) return -1;
         for (int c = 0; c < ep.upd_copies; ++c) { if (!ep.upd_copy[c]) return -1; al |= (uintptr_t)ep.upd_copy[c]; }
         if (plan.splits != 1 || ep.mode != 0 || !ep.upd_v || (al & 15) || (ep.ld & 7)) return -1;
     }
     if (dtype == kBF16)
-        return outer_applies<bf16_t>(M, N, K, ep, plan) ? run_outer(make_plain_t<bf16_t>(at, lda, M, K), make_plain_t<bf16_t>(bt, ldb, N, K), M, N, K, ep, s)
-                                                        : run<bf16_t>(make_plain_t<bf16_t>(at, lda, M, K), make_plain_t<bf16_t>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);
+        return outer_applies<bf16_t>(M, N, K, ep, plan)
+                   ? run_outer(make_plain_t<bf16_t>(at, lda, M, K), make_plain_t<bf16_t>(bt, ldb, N, K), M, N, K, ep, s)
+                   : run<bf16_t>(make_plain_t<bf16_t>(at, lda, M, K), make_plain_t<bf16_t>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);
     return outer_applies<float>(M, N, K, ep, plan) ? run_outer(make_plain_t<float>(at, lda, M, K), make_plain_t<float>(bt, ldb, N, K), M, N, K, ep, s)
                                                    : run<float>(make_plain_t<float>(at, lda, M, K), make_plain_t<float>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);
 }

@@ -948,7 +948,7 @@ template <typename T> struct PoolWindows {
                 pos[q] = ((e < 4 ? a8[q].x : a8[q].y) >> (8 * (e & 3))) & 0xffu;
             }
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {   // pixel (by, bx) sits at (by + 2*(1 - wy), bx + 2*(1 - wx)) in window q = (wy, wx); the last one covers all four
+            for (int b = 0; b < 4; ++b) {   // pixel (by, bx) sits at (by + 2*(1 - wy), bx + 2*(1 - wx)) in window q = (wy, wx)
                 float t = 0.f;
                 bool any = false;
 #pragma unroll
@@ -1638,8 +1638,10 @@ static void launch_lrn_pool_t(const LrnPool &p, int B, int k, size_t lds, const 
     const T *aa = static_cast<const T *>(a);
     if (da) {
         const dim3 grid((unsigned)(B * p.Hb));
-        if (k == 3) hipLaunchKernelGGL((lrn_pool_bwd_kernel<T, HALF, 3>), grid, dim3(256), lds, s, aa, static_cast<const T *>(dy), arg, static_cast<T *>(da), p, bands);
-        else hipLaunchKernelGGL((lrn_pool_bwd_kernel<T, HALF, 2>), grid, dim3(256), lds, s, aa, static_cast<const T *>(dy), arg, static_cast<T *>(da), p, bands);
+        const T *g = static_cast<const T *>(dy);
+        T *o = static_cast<T *>(da);
+        if (k == 3) hipLaunchKernelGGL((lrn_pool_bwd_kernel<T, HALF, 3>), grid, dim3(256), lds, s, aa, g, arg, o, p, bands);
+        else hipLaunchKernelGGL((lrn_pool_bwd_kernel<T, HALF, 2>), grid, dim3(256), lds, s, aa, g, arg, o, p, bands);
     } else {
         const dim3 grid((unsigned)(B * p.tiles * p.chunks));
         if (k == 3) hipLaunchKernelGGL((lrn_pool_fwd_kernel<T, HALF, 3>), grid, dim3(256), lds, s, aa, static_cast<T *>(y), arg, p);
@@ -1790,7 +1792,8 @@ __global__ __launch_bounds__(256) void colsum_stage1(ColsumS1Jobs jobs)
 // Stage 2 for several layers in one launch.
 __global__ __launch_bounds__(256) void colsum_stage2(ColsumJobs jobs)
 {
-    // Band-major jobs (ws[band][ld], from colsum_stage1, or the rows of a short tensor itself, up to 512 bands): 8 columns per block, 32 lanes per column.
+    // Band-major jobs (ws[band][ld], from colsum_stage1, or the rows of a short tensor itself, up to 512 bands): 8 columns per block,
+    // 32 lanes per column.
     // Column-major jobs (ws[column][nblk], from the pooling backward pass, thousands of bands): a block per column.  A
     // lane adds bands lane, lane + L, ... (eight loads in flight); the lanes are then added in a fixed tree, the lanes of
     // a wavefront by shuffles and its four wavefronts in LDS.  Latency bounds it: with a wavefront per column and one lane
@@ -1854,7 +1857,8 @@ int colsum_partial_defer(int dtype, const void *dy, long ld, long M, int N, floa
     if (jobs.n >= 12 || s1.n >= 12 || (ld & 7) || M <= 0) return -1;
     if (M <= kColsumDirect) {
         ColsumJob &J = jobs.j[jobs.n++];
-        J.ws = static_cast<const float *>(dy); J.nblk = (int)M; J.ld = ld; J.N = N; J.db = db; J.start_block = 0; J.colmajor = 0; J.bf16 = dtype == kBF16; J.div = 1.f;
+        J.ws = static_cast<const float *>(dy); J.nblk = (int)M; J.ld = ld; J.N = N; J.db = db;
+        J.start_block = 0; J.colmajor = 0; J.bf16 = dtype == kBF16; J.div = 1.f;
         return 0;
     }
     int chunks, cpb, rl, nblk; long rpb;
