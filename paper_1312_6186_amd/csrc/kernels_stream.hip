@@ -1592,7 +1592,7 @@ __global__ __launch_bounds__(256, 6) void lrn_pool_bwd_kernel(const T *__restric
 }
 
 // Where the pair runs as one kernel: pools of 2 or 3 with stride 2, rows that fit LDS, pixels that fit a wavefront.
-static bool lrn_pool_plan(int dtype, int H, int W, int Cp, int k, int stride, LrnPool &p, size_t &lds_fwd, size_t &lds_bwd)
+static bool lrn_pool_plan(int dtype, int B, int H, int W, int Cp, int k, int stride, LrnPool &p, size_t &lds_fwd, size_t &lds_bwd)
 {
     const int V = dtype == kBF16 ? 8 : 4;
     if (!pool_bwd_blocks(H, W, Cp, (int)dtype_size(dtype), k, stride) || H < k || W < k) return false;
@@ -1605,7 +1605,8 @@ static bool lrn_pool_plan(int dtype, int H, int W, int Cp, int k, int stride, Lr
     const long row = (long)p.cols * p.groups * 16;
     const long fit = (kLrnPoolLds / row - k) / 2 + 1;   // pooled rows whose input rows fit
     if (kLrnPoolLds / row < k) return false;
-    p.tiles = (int)((p.Ho + fit - 1) / fit);
+    // and fewer while CUs are idle (bf16, 55 x 55 over 96 channels, 1 image: a pass 115 us with 6 blocks for the rows, 110 with 27)
+    p.tiles = (int)std::max((p.Ho + fit - 1) / fit, std::min((long)p.Ho, 256 / ((long)B * p.chunks)));
     p.R = (p.Ho + p.tiles - 1) / p.tiles;
     p.tiles = (p.Ho + p.R - 1) / p.R;
     lds_fwd = (size_t)(2 * (p.R - 1) + k) * (size_t)row;
@@ -1621,14 +1622,15 @@ long lrn_pool_bands(int dtype, int B, int H, int W, int Cp, int k, int stride)
 {
     LrnPool p;
     size_t f, b;
-    if (!lrn_pool_plan(dtype, H, W, Cp, k, stride, p, f, b)) return 0;
+    if (!lrn_pool_plan(dtype, B, H, W, Cp, k, stride, p, f, b)) return 0;
     const long blocks = (long)B * p.Hb;
     if ((long)B * p.tiles * p.chunks > 0x7fffffffL || blocks > 0x7fffffffL) return 0;
-    // A block of the backward kernel takes 2 * W pixels, p.lanes side by side: more than seven rounds of that are longer than the launch
-    // and the tensors they save unless the CUs are full of blocks.  Both kernels with the bias sums, separate / here, us, bf16: 55 x 55
-    // over 256 channels (14 rounds) 1 image 78 / 88, 4 images 85 / 90, 8 images (224 blocks) 94 / 93, 32 images 149 / 135; 16 x 200 over
-    // 64 (12.5 rounds) 8 images 81 / 86, 32 images (256 blocks) 96 / 93; 13 x 13 over 512 (6.5 rounds) 4 images 58 / 48.
-    if (2 * W > 7 * p.lanes && blocks * p.lanes < 32L * W) return 0;
+    // A block of the backward kernel takes 2 * W pixels, p.lanes side by side: more than five rounds of that on less than a third of
+    // the CUs are longer than the launch and the tensors they save.  A pass of two convolutions, separate / here, us, bf16: 55 x 55 over
+    // 256 channels (14 rounds) 1 image 108 / 118, 2 images (56 blocks) 116 / 120, 4 images (112) 130 / 126; 16 x 200 over 64 (12.5 rounds) 6
+    // images (48 blocks) 112 / 120, 12 images (96) 124 / 123; 55 x 55 over 96 (5.5 rounds) 1 image 107 / 110, 4 images 117 / 117; fewer
+    // rounds, 13 x 13 over 256, 1 image 72 / 71.
+    if (2 * W > 5 * p.lanes && blocks < 80) return 0;
     return blocks;
 }
 template <typename T, int HALF>
@@ -1655,7 +1657,7 @@ static int launch_lrn_pool(int dtype, int B, int H, int W, int Cp, int size, flo
     LrnPool p;
     size_t lf, lb;
     if (size < 1 || size > 9 || !(size & 1) || !(bias > 0.f)) return -1;
-    if (lrn_pool_bands(dtype, B, H, W, Cp, k, 2) == 0 || !lrn_pool_plan(dtype, H, W, Cp, k, 2, p, lf, lb)) return -1;
+    if (lrn_pool_bands(dtype, B, H, W, Cp, k, 2) == 0 || !lrn_pool_plan(dtype, B, H, W, Cp, k, 2, p, lf, lb)) return -1;
     p.alpha = alpha; p.beta = beta; p.bias = bias;
     const size_t lds = da ? lb : lf;
     uint8_t *ar = const_cast<uint8_t *>(arg);
