@@ -191,11 +191,12 @@ Gather dgrad_gather(const Stage &s, const void *dy, int B, int dt, int group);
 constexpr size_t kStaticWsBytes = (size_t)64 << 20;
 constexpr size_t kScratchSpare = 64;   // floats behind the largest partial sums
 
-// Floats that the partial sums of one kernel may take.
+// What the kernels may take of the workspace: floats for the partial sums of one kernel, tensors between two kernels.
 struct Budget {
     size_t wgrad;    // filter gradients in conv_wgrad
     size_t narrow;   // split data gradients, and the general engine's filter gradients of up to 64 channels (which may always
                      // take what its tiles of 128 rows would leave)
+    bool fuse_pools = false;   // pools in one kernel with what is above or below them also where separate ones, and a tensor more, are faster
 };
 // Chooses the kernels of every stage and sizes the workspace.  plain: no filters padded to their chunks (conv_direct).
 int size_net(asgd_net &n, const Budget &partials, bool plain);
@@ -351,25 +352,31 @@ int plan_net(asgd_net &n)
     int rc = size_net(n, {SIZE_MAX, SIZE_MAX}, false);
     if (rc != ASGD_OK || n.ws_bytes <= kStaticWsBytes) return rc;
     // Beyond the static workspace with the kernels chosen for speed.  If it would fit with no more partial sums than tiles of 128 rows
-    // leave, or with the general engine's kernels, the plan is made to, with fewer partial sums or (few need that) without padded
-    // filters: what asgd_fwd_bwd_static accepts does not depend on how the fast kernels are split.
+    // leave, with every pool fused that can be, or with the general engine's kernels, the plan is made to, with fewer partial sums, fused
+    // pools or (few need that) without padded filters: what asgd_fwd_bwd_static accepts does not depend on how the fast kernels are split.
     const std::vector<Stage> fast = n.stages;
     const size_t bytes = n.ws_bytes, scratch_side = n.scratch_side_floats;
     auto room = [&]() { return n.shared_off + 1024 < kStaticWsBytes ? (kStaticWsBytes - n.shared_off - 1024) / 4 : 0; };
-    rc = size_net(n, {SIZE_MAX, 0}, false);   // no split data gradient: all of their filters padded, so the room is the least there is
-    size_t fast_room = room(), plain_room = 0;
-    bool fits = n.ws_bytes <= kStaticWsBytes;
-    if (fits) {
-        fast_room = std::max(fast_room, n.scratch_side_floats - kScratchSpare);
-    } else {
-        rc = size_net(n, {0, 0}, true);
-        plain_room = room();
-        fits = n.apart_bytes <= kStaticWsBytes;
-    }
-    if (rc == ASGD_OK && fits) {
-        rc = size_net(n, {fast_room, fast_room}, false);
-        if (rc == ASGD_OK && n.ws_bytes > kStaticWsBytes) rc = size_net(n, {plain_room, plain_room}, true);
-        return rc;
+    auto within = [&]() { return rc == ASGD_OK && n.ws_bytes <= kStaticWsBytes; };
+    for (const bool fuse : {false, true}) {
+        if (fuse) {
+            rc = size_net(n, {SIZE_MAX, SIZE_MAX, true}, false);
+            if (within()) return rc;
+        }
+        rc = size_net(n, {SIZE_MAX, 0, fuse}, false);   // no split data gradient: all of their filters padded, so the room is the least there is
+        size_t fast_room = room(), plain_room = 0;
+        bool fits = within();
+        if (fits) {
+            fast_room = std::max(fast_room, n.scratch_side_floats - kScratchSpare);
+        } else {
+            rc = size_net(n, {0, 0, fuse}, true);
+            plain_room = room();
+            fits = rc == ASGD_OK && n.apart_bytes <= kStaticWsBytes;
+        }
+        if (!fits) continue;
+        rc = size_net(n, {fast_room, fast_room, fuse}, false);
+        if (within()) return rc;
+        if (fuse) return size_net(n, {plain_room, plain_room, true}, true);
     }
     n.stages = fast;
     n.ws_bytes = bytes; n.scratch_side_floats = scratch_side;
@@ -417,14 +424,14 @@ int size_net(asgd_net &n, const Budget &partials, bool plain)
                 Stage &pl = n.stages[si + 1];
                 s.pool_bands = pool_bwd_bands(n.dtype, B, s.outH, s.outW, s.outCp, pl.k, pl.stride);
                 if (si + 2 < n.stages.size() && n.stages[si + 2].kind == ST_FC) {
-                    const long flat = pool_flat_bands(n.dtype, (int)B, s.outH, s.outW, s.outC, s.outCp, pl.k, pl.stride);
+                    const long flat = pool_flat_bands(n.dtype, (int)B, s.outH, s.outW, s.outC, s.outCp, pl.k, pl.stride, partials.fuse_pools);
                     pl.to_flat = flat > 0;
                     if (flat > 0) s.pool_bands = flat;
                 }
                 s.colsum_floats = std::max(s.colsum_floats, (size_t)s.pool_bands * s.outCp);
             } else if (si + 2 < n.stages.size() && n.stages[si + 1].kind == ST_LRN && n.stages[si + 2].kind == ST_POOL) {
                 const Stage &pl = n.stages[si + 2];
-                s.pool_bands = lrn_pool_bands(n.dtype, (int)B, s.outH, s.outW, s.outCp, pl.k, pl.stride);
+                s.pool_bands = lrn_pool_bands(n.dtype, (int)B, s.outH, s.outW, s.outCp, pl.k, pl.stride, partials.fuse_pools);
                 n.stages[si + 1].with_pool = s.pool_bands > 0;
                 s.colsum_floats = std::max(s.colsum_floats, (size_t)s.pool_bands * s.outCp);
             }

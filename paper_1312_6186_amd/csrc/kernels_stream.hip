@@ -1203,24 +1203,25 @@ static bool pool_flat_plan(int dtype, int B, int H, int W, int C, int Cp, int k,
     p.groups = std::max(1, std::min(p.cv, 256 / p.hw));   // one pooled pixel and group a thread
     p.chunks = (p.cv + p.groups - 1) / p.groups;
     p.lanes = 256 / p.groups; p.Hb = (H + 1) / 2; p.Wb = (W + 1) / 2;
-    const long blocks = (long)B * p.chunks, reads = (long)p.hw * k * k;
-    if (blocks > 0x7fffffffL) return false;
-    // A block that makes many pooled pixels in turn, one 16-byte group of each, is long: the two launches that the separate kernels
-    // cost (about 8 us) pay for 1800 reads of a group, or for 4500 where a group is the whole pixel; beyond, half the CUs have to
-    // have a block, and more of them the more a block reads (four-byte data and windows of 3 over large grids gain nothing).  A pass
-    // with separate kernels / here, us: bf16, 64 channels, 20 x 20 pools of 2 1 image 53 / 55, 64 images 90 / 79, 45 x 45
-    // 78 / 99 and 221 / 182; 32 x 32 pools of 3 63 / 85 and 142 / 136.
-    if (reads > (p.cv == 1 ? 4500 : 1800) && (blocks < std::max(128L, reads / 36) || (V == 4 && k == 3 && reads > 4600))) return false;
+    if ((long)B * p.chunks > 0x7fffffffL) return false;
     lds_fwd = (size_t)p.groups * p.hw * 16;
     lds_bwd = std::max(lds_fwd, (size_t)p.lanes * p.groups * V * 4);
     p.dgroups = make_fastdiv(p.groups); p.dchunks = make_fastdiv(p.chunks); p.dWo = make_fastdiv(p.Wo); p.dWb = make_fastdiv(p.Wb);
     return true;
 }
-long pool_flat_bands(int dtype, int B, int H, int W, int C, int Cp, int k, int stride)
+long pool_flat_bands(int dtype, int B, int H, int W, int C, int Cp, int k, int stride, bool always)
 {
     PoolFlat p;
     size_t f, b;
-    return pool_flat_plan(dtype, B, H, W, C, Cp, k, stride, p, f, b) ? B : 0;
+    if (!pool_flat_plan(dtype, B, H, W, C, Cp, k, stride, p, f, b)) return 0;
+    const long blocks = (long)B * p.chunks, reads = (long)p.hw * k * k, V = dtype == kBF16 ? 8 : 4;
+    // A block that makes many pooled pixels in turn, one 16-byte group of each, is long: the two launches that the separate kernels
+    // cost (about 8 us) pay for 1800 reads of a group, or for 4500 where a group is the whole pixel; beyond, half the CUs have to
+    // have a block, and more of them the more a block reads (four-byte data and windows of 3 over large grids gain nothing).  A pass
+    // with separate kernels / here, us: bf16, 64 channels, 20 x 20 pools of 2 1 image 53 / 55, 64 images 90 / 79, 45 x 45
+    // 78 / 99 and 221 / 182; 32 x 32 pools of 3 63 / 85 and 142 / 136.
+    if (!always && reads > (p.cv == 1 ? 4500 : 1800) && (blocks < std::max(128L, reads / 36) || (V == 4 && k == 3 && reads > 4600))) return 0;
+    return B;
 }
 template <typename T, bool KEYS> static void launch_pool_flat_fwd_t(const void *x, void *flat, uint8_t *arg, int B, int k, const PoolFlat &p, size_t lds, hipStream_t s)
 {
@@ -1618,7 +1619,7 @@ static bool lrn_pool_plan(int dtype, int B, int H, int W, int Cp, int k, int str
     p.dWo = make_fastdiv(p.Wo); p.dcv = make_fastdiv(p.cv); p.dHb = make_fastdiv(p.Hb);
     return true;
 }
-long lrn_pool_bands(int dtype, int B, int H, int W, int Cp, int k, int stride)
+long lrn_pool_bands(int dtype, int B, int H, int W, int Cp, int k, int stride, bool always)
 {
     LrnPool p;
     size_t f, b;
@@ -1630,7 +1631,7 @@ long lrn_pool_bands(int dtype, int B, int H, int W, int Cp, int k, int stride)
     // 256 channels (14 rounds) 1 image 108 / 118, 2 images (56 blocks) 116 / 120, 4 images (112) 130 / 126; 16 x 200 over 64 (12.5 rounds) 6
     // images (48 blocks) 112 / 120, 12 images (96) 124 / 123; 55 x 55 over 96 (5.5 rounds) 1 image 107 / 110, 4 images 117 / 117; fewer
     // rounds, 13 x 13 over 256, 1 image 72 / 71.
-    if (2 * W > 5 * p.lanes && blocks < 80) return 0;
+    if (!always && 2 * W > 5 * p.lanes && blocks < 80) return 0;
     return blocks;
 }
 template <typename T, int HALF>
@@ -1657,7 +1658,7 @@ static int launch_lrn_pool(int dtype, int B, int H, int W, int Cp, int size, flo
     LrnPool p;
     size_t lf, lb;
     if (size < 1 || size > 9 || !(size & 1) || !(bias > 0.f)) return -1;
-    if (lrn_pool_bands(dtype, B, H, W, Cp, k, 2) == 0 || !lrn_pool_plan(dtype, B, H, W, Cp, k, 2, p, lf, lb)) return -1;
+    if (lrn_pool_bands(dtype, B, H, W, Cp, k, 2, true) == 0 || !lrn_pool_plan(dtype, B, H, W, Cp, k, 2, p, lf, lb)) return -1;
     p.alpha = alpha; p.beta = beta; p.bias = bias;
     const size_t lds = da ? lb : lf;
     uint8_t *ar = const_cast<uint8_t *>(arg);

@@ -41,6 +41,9 @@ STATIC_NETS = {
     "few_strided": (_conv(256, 3) + [("maxpool", 3, 2), ("conv", 64, 7, 2, 3), ("relu",), ("lrn", 5, 1e-4, 0.75, 2.0), ("maxpool", 2, 2), ("fc", 64), ("relu",),
                                      ("fc", 10), ("softmax_ce",)], (8, 23, 12), 146, B.BF16),
     "small": (wl.SMALL["layers"], wl.SMALL["in_shape"], 131, B.F32),
+    # pools that separate kernels would be faster for, with tensors that do not fit: in one kernel with what is above or below them
+    "wide_pools": (_conv(32, 5) + [("maxpool", 3, 2), ("fc", 8), ("relu",), ("fc", 10), ("softmax_ce",)], (64, 65, 49), 31, B.F32),
+    "few_normalised": (_conv(576, 1) + _conv(32, 1) + [("lrn", 5, 1e-4, 0.75, 2.0), ("maxpool", 3, 2), ("fc", 10), ("softmax_ce",)], (8, 69, 86), 2, B.F32),
 }
 
 
@@ -103,7 +106,7 @@ def test_static_entry_point_matches_fwd_bwd_on_two_calls_in_a_row():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("name", ["alexnet", "grouped", "wide_f32", "padded_f32", "padded_bf16", "few_channels", "small"])
+@pytest.mark.parametrize("name", ["alexnet", "grouped", "wide_f32", "padded_f32", "padded_bf16", "few_channels", "small", "wide_pools", "few_normalised"])
 def test_static_entry_point_takes_plans_near_the_size_of_its_workspace(name):
     """Plans that fit as they are, with fewer partial sums, or with the general engine's kernels only: two calls in a row, bit for bit."""
     layers, in_shape, batch, dtype = STATIC_NETS[name]
