@@ -351,32 +351,29 @@ int plan_net(asgd_net &n)
 
     int rc = size_net(n, {SIZE_MAX, SIZE_MAX}, false);
     if (rc != ASGD_OK || n.ws_bytes <= kStaticWsBytes) return rc;
-    // Beyond the static workspace with the kernels chosen for speed.  If it would fit with no more partial sums than tiles of 128 rows
-    // leave, with every pool fused that can be, or with the general engine's kernels, the plan is made to, with fewer partial sums, fused
-    // pools or (few need that) without padded filters: what asgd_fwd_bwd_static accepts does not depend on how the fast kernels are split.
+    // Beyond the static workspace with the kernels chosen for speed.  If it would fit with every pool fused that can be (a third more
+    // time at most, where a lack of partial sums may cost a filter gradient several times its own), and then with no more partial sums
+    // than tiles of 128 rows leave, or with the general engine's kernels, the plan is made to, with fewer partial sums or (few need
+    // that) without padded filters: what asgd_fwd_bwd_static accepts does not depend on how the fast kernels are split.
     const std::vector<Stage> fast = n.stages;
     const size_t bytes = n.ws_bytes, scratch_side = n.scratch_side_floats;
     auto room = [&]() { return n.shared_off + 1024 < kStaticWsBytes ? (kStaticWsBytes - n.shared_off - 1024) / 4 : 0; };
-    auto within = [&]() { return rc == ASGD_OK && n.ws_bytes <= kStaticWsBytes; };
-    for (const bool fuse : {false, true}) {
-        if (fuse) {
-            rc = size_net(n, {SIZE_MAX, SIZE_MAX, true}, false);
-            if (within()) return rc;
-        }
-        rc = size_net(n, {SIZE_MAX, 0, fuse}, false);   // no split data gradient: all of their filters padded, so the room is the least there is
-        size_t fast_room = room(), plain_room = 0;
-        bool fits = within();
-        if (fits) {
-            fast_room = std::max(fast_room, n.scratch_side_floats - kScratchSpare);
-        } else {
-            rc = size_net(n, {0, 0, fuse}, true);
-            plain_room = room();
-            fits = rc == ASGD_OK && n.apart_bytes <= kStaticWsBytes;
-        }
-        if (!fits) continue;
-        rc = size_net(n, {fast_room, fast_room, fuse}, false);
-        if (within()) return rc;
-        if (fuse) return size_net(n, {plain_room, plain_room, true}, true);
+    rc = size_net(n, {SIZE_MAX, SIZE_MAX, true}, false);
+    if (rc != ASGD_OK || n.ws_bytes <= kStaticWsBytes) return rc;
+    rc = size_net(n, {SIZE_MAX, 0, true}, false);   // no split data gradient: all of their filters padded, so the room is the least there is
+    size_t fast_room = room(), plain_room = 0;
+    bool fits = n.ws_bytes <= kStaticWsBytes;
+    if (fits) {
+        fast_room = std::max(fast_room, n.scratch_side_floats - kScratchSpare);
+    } else {
+        rc = size_net(n, {0, 0, true}, true);
+        plain_room = room();
+        fits = n.apart_bytes <= kStaticWsBytes;
+    }
+    if (rc == ASGD_OK && fits) {
+        rc = size_net(n, {fast_room, fast_room, true}, false);
+        if (rc == ASGD_OK && n.ws_bytes > kStaticWsBytes) rc = size_net(n, {plain_room, plain_room, true}, true);
+        return rc;
     }
     n.stages = fast;
     n.ws_bytes = bytes; n.scratch_side_floats = scratch_side;
