@@ -1290,7 +1290,9 @@ template <typename T> static void launch_splitk_reduce(const float *ws, int spli
     const long groups = (long)M * (N / 8);
     // Lanes that share a group: a chip full of blocks, and hardly more lanes than partials.  (us: 320 groups of 512 partials 10.8 with
     // 32 lanes, 8.6 with 256; 40 of 98 7.0 with 8, 3.3 with 256; 800 of 248 6.4 with 32, 7.5 with 256; 3200 of 70 6.8 with 8, 6.4
-    // with 32; 5280 of 256, the AlexNet-style first layer, 14 with 32.)
+    // with 32; 5280 of 256, the AlexNet-style first layer, 14 with 32.  Few partials leave some of the 32 lanes without one and are
+    // no longer for it: 300 to 1000 groups of 16 3.7 with 8, 3.5 with 32; of 32 4.2 and 3.6; of 63 6.4 and 4.0; 2500 to 8000 groups of
+    // 16 3.9 and 4.0 to 5.2.)
     if (splits >= 64 && groups < 512)
         hipLaunchKernelGGL((splitk_reduce_wide_kernel<T, 256>), dim3((unsigned)groups), dim3(256), 0, s, ws, splits, ep, M, N);
     else if ((splits >= 192 && groups < 8192) || (splits >= 16 && groups < 1024) || (splits >= 64 && groups < 4096))
@@ -1342,7 +1344,9 @@ GemmPlan plan_gemm(long M, long N, long K, int dtype, int max_splits)
 // Convolution over M pixels with N output columns.  Up to 32 columns in tiles of 128 x 32 (a tile of 128 columns leaves three of four
 // waves without a column: 3 -> 32 channels 5 x 5 on 32 x 32 in fp32, 128 images 28 -> 18 us), and where those tiles are fewer than half the CUs
 // and K is long, in K splits: the launch that adds them up costs 5 us, a K tile alone on a CU 0.6 (64 -> 32 channels 5 x 5 on 7 x 7 in
-// fp32, 128 images, 31 us in 49 tiles of conv_direct, 16 + 4 in 10 splits), as far as the partial sums fit.  Data gradients of strided
+// fp32, 128 images, 31 us in 49 tiles of conv_direct, 16 + 4 in 10 splits), as far as the partial sums fit.  In bf16, too: passes with one
+// such convolution, tiles of 32 / 128 columns, 16 -> 32 channels 3 x 3, 25 tiles 55 / 56 us, 1693 tiles 138 / 153; 256 -> 24 channels 1 x 1,
+// 1875 tiles 268 / 281; at most 1.01 over 460 convolutions and unstrided data gradients of 1 to 1875 tiles.  Data gradients of strided
 // convolutions (zoom: their stride) in bf16 are bound by the addresses of their gather, which the 512 threads of the tiles of 128
 // columns work out faster where a CU has one tile, or two and a long K: 25 K tiles (5 x 5, stride 2, over 64 channels) 129 to 252 tiles
 // 27 us in 128 columns, 32 here, 368 and 509 tiles 34.5 in both, 613 tiles 52 and 41; 49 K tiles 44 and 56, 58 and 61, 88 and 73.  us: the
