@@ -57,6 +57,27 @@ def test_static_workspace_holds_what_fits_it_without_the_fast_convolutions(name)
         B.asgd_net_destroy(net)
 
 
+# Plans close to 64 MiB, whose partial sums are cut to what is left: they keep their fast kernels, and with them need more bytes than
+# with one image less.  (With the general engine's kernels it would be 1.2 to 3.2 MB fewer.)
+NEAR_LIMIT = {
+    "few_channels": (_conv(48, 3) + [("fc", 8), ("softmax_ce",)], (1, 57, 67), 40, B.BF16),
+    "few_strided": (_conv(384, 3) + [("conv", 32, 3, 2, 1), ("relu",), ("fc", 8), ("relu",), ("fc", 10), ("softmax_ce",)], (1, 74, 9), 27, B.F32),
+    "few_normalised": (_conv(384, 1) + [("lrn", 5, 1e-4, 0.75, 2.0), ("maxpool", 3, 2)] + _conv(32, 7) + [("maxpool", 3, 2), ("fc", 128), ("relu",), ("fc", 8), ("softmax_ce",)],
+                       (24, 14, 67), 18, B.BF16),
+}
+
+
+@pytest.mark.parametrize("name", list(NEAR_LIMIT))
+def test_plans_at_the_static_workspace_keep_their_fast_kernels(name):
+    layers, shape, batch, dtype = NEAR_LIMIT[name]
+    sizes = []
+    for b in (batch - 1, batch):
+        net = B.asgd_net_create(layers, b, shape, dtype)
+        sizes.append(B.asgd_workspace_bytes(net))
+        B.asgd_net_destroy(net)
+    assert sizes[0] < sizes[1] <= B.asgd_static_workspace_bytes()
+
+
 def _case(cfg, batch, dtype, seed):
     layers, in_shape = cfg["layers"], cfg["in_shape"]
     tdt = torch.bfloat16 if dtype == B.BF16 else torch.float32
