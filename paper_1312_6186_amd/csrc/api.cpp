@@ -126,8 +126,9 @@ struct asgd_net {
 namespace {
 
 // Events between streams of one GPU inside a pass or a replay carry no fence towards the host and other devices, which costs the
-// recording stream about 3 us each.  The one that joins the side stream back into the caller's (ev_join), and those that start a replay behind
-// the caller's work and end it (replay_start, replay_done), do.  One step / with the fence on every event: alexnet bf16 128 images 1333 / 1360 us, one gradient at 32 images 715 / 733.
+// recording stream about 3 us each.  The one that joins the side stream back into the caller's (ev_join), and those that start a
+// replay behind the caller's work and end it (replay_start, replay_done), do.  One step / with the fence on every event: alexnet
+// bf16 128 images 1333 / 1360 us, one gradient at 32 images 715 / 733.
 constexpr unsigned kInnerEvent = hipEventDisableTiming | hipEventDisableSystemFence, kOuterEvent = hipEventDisableTiming;
 
 struct Carver {
@@ -952,7 +953,8 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                     CHECK_LAUNCH(launch_colsum_finish(bias_jobs, sd), "conv bias gradient");
                 }
                 ColsumJob &J = bias_jobs.j[bias_jobs.n++];
-                J.ws = s.colsum_ws; J.nblk = (int)s.pool_bands; J.ld = s.outCp; J.N = s.outC; J.db = grads + s.b_off; J.start_block = 0; J.colmajor = 1; J.bf16 = 0; J.div = 1.f;
+                J.ws = s.colsum_ws; J.nblk = (int)s.pool_bands; J.ld = s.outCp; J.N = s.outC; J.db = grads + s.b_off;
+                J.start_block = 0; J.colmajor = 1; J.bf16 = 0; J.div = 1.f;
                 if (by_layer) CHECK_LAUNCH(launch_colsum_finish(bias_jobs, sd), "conv bias gradient");
                 return ASGD_OK;
             };
