@@ -422,7 +422,8 @@ int size_net(asgd_net &n, const Budget &partials, bool plain)
                 Stage &pl = n.stages[si + 1];
                 s.pool_bands = pool_bwd_bands(n.dtype, B, s.outH, s.outW, s.outCp, pl.k, pl.stride);
                 if (si + 2 < n.stages.size() && n.stages[si + 2].kind == ST_FC) {
-                    const long flat = pool_flat_bands(n.dtype, (int)B, s.outH, s.outW, s.outC, s.outCp, pl.k, pl.stride, partials.fuse_pools);
+                    const long flat = pool_flat_bands(n.dtype, (int)B, s.outH, s.outW, s.outC, s.outCp, pl.k, pl.stride, n.fork_pays,
+                                                      partials.fuse_pools);
                     pl.to_flat = flat > 0;
                     if (flat > 0) s.pool_bands = flat;
                 }

@@ -1209,19 +1209,24 @@ static bool pool_flat_plan(int dtype, int B, int H, int W, int C, int Cp, int k,
     p.dgroups = make_fastdiv(p.groups); p.dchunks = make_fastdiv(p.chunks); p.dWo = make_fastdiv(p.Wo); p.dWb = make_fastdiv(p.Wb);
     return true;
 }
-long pool_flat_bands(int dtype, int B, int H, int W, int C, int Cp, int k, int stride, bool always)
+long pool_flat_bands(int dtype, int B, int H, int W, int C, int Cp, int k, int stride, bool forked, bool always)
 {
     PoolFlat p;
     size_t f, b;
     if (!pool_flat_plan(dtype, B, H, W, C, Cp, k, stride, p, f, b)) return 0;
     const long blocks = (long)B * p.chunks, reads = (long)p.hw * k * k, V = dtype == kBF16 ? 8 : 4;
     // A block that makes many pooled pixels in turn, one 16-byte group of each, is long: the two launches that the separate kernels
-    // cost (about 8 us) pay for 1800 reads of a group, or for 4500 where a group is the whole pixel; beyond, half the CUs have to
-    // have a block, and more of them the more a block reads (four-byte data and windows of 3 over large grids gain nothing).  A pass
-    // with separate kernels / here, us: bf16, 64 channels, 20 x 20 pools of 2 1 image 53 / 55, 64 images 90 / 79, 45 x 45
-    // 78 / 99 and 221 / 182; 32 x 32 pools of 3 63 / 85 and 142 / 136.
-    if (!always && reads > (p.cv == 1 ? 4500 : 1800) && (blocks < std::max(128L, reads / 36) || (V == 4 && k == 3 && reads > 4600))) return 0;
-    return B;
+    // cost (about 8 us) pay for 2200 reads of a group, for 3400 where a pixel is two or three groups and for 4500 where it is one;
+    // beyond, half the CUs have to have a block, and more of them the more a block reads (four-byte data and windows of 3 over large
+    // grids gain nothing).  Beside a weight gradient on the side stream a long block costs less and a launch more: up to 6500 reads, or
+    // four groups a pixel, one kernel.  A pass with separate kernels / here, us, bf16, 64 channels: pools of 2, 20 x 20 1 image
+    // 53 / 55, 64 images 90 / 79, 45 x 45 78 / 99 and 221 / 182; pools of 3, 32 x 32 63 / 85 and 142 / 136; with the side stream 27 x 25
+    // pools of 2 4 images 137 / 125, 28 x 20 pools of 3 2 images 149 / 139, 44 x 40 146 / 163.  Over 320 passes without and 150 with the side
+    // stream the choice is at most 1.05 of the better one.
+    const long few = p.cv == 1 ? 4500 : p.cv <= 3 ? 3400 : 2200;
+    const bool apart = forked ? reads > 6500 && p.cv > 4 && blocks < std::max(128L, reads / 72)
+                              : reads > few && (blocks < std::max(128L, reads / 36) || (V == 4 && k == 3 && reads > 4600));
+    return apart && !always ? 0 : B;
 }
 template <typename T, bool KEYS> static void launch_pool_flat_fwd_t(const void *x, void *flat, uint8_t *arg, int B, int k, const PoolFlat &p, size_t lds, hipStream_t s)
 {

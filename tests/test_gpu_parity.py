@@ -361,7 +361,7 @@ def test_fc_weight_gradient_shapes(out, batch, dtype):
 # many, pooled grids of one pixel, around the 256 threads of a block, of several rounds of them (whole pixels of 8 channels, or where many
 # blocks share the work) and past its LDS (2048 pixels) or its share of the work (the separate kernels), odd last rows and columns, with
 # and without the ReLU.
-FLAT_SHAPES = [(8, 67, 66, 2, 1, True), (24, 43, 42, 2, 1, False), (24, 44, 42, 2, 1, True), (136, 90, 91, 2, 14, True), (64, 41, 42, 3, 16, False),
+FLAT_SHAPES = [(64, 34, 33, 3, 2, True), (8, 67, 66, 2, 1, True), (24, 43, 42, 2, 1, False), (24, 44, 42, 2, 1, True), (136, 90, 91, 2, 14, True), (64, 41, 42, 3, 16, False),
                (8, 2, 3, 2, 3, True), (12, 9, 10, 3, 2, True), (72, 13, 13, 3, 3, True), (72, 13, 12, 3, 2, False), (40, 33, 32, 2, 2, True), (24, 35, 33, 3, 1, True),
                (8, 92, 92, 2, 1, True), (264, 5, 4, 2, 5, False)]
 
