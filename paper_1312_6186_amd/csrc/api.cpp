@@ -430,7 +430,7 @@ int size_net(asgd_net &n, const Budget &partials, bool plain)
                 s.colsum_floats = std::max(s.colsum_floats, (size_t)s.pool_bands * s.outCp);
             } else if (si + 2 < n.stages.size() && n.stages[si + 1].kind == ST_LRN && n.stages[si + 2].kind == ST_POOL) {
                 const Stage &pl = n.stages[si + 2];
-                s.pool_bands = lrn_pool_bands(n.dtype, (int)B, s.outH, s.outW, s.outCp, pl.k, pl.stride, partials.fuse_pools);
+                s.pool_bands = lrn_pool_bands(n.dtype, (int)B, s.outH, s.outW, s.outCp, pl.k, pl.stride, n.fork_pays, partials.fuse_pools);
                 n.stages[si + 1].with_pool = s.pool_bands > 0;
                 s.colsum_floats = std::max(s.colsum_floats, (size_t)s.pool_bands * s.outCp);
             }

@@ -203,16 +203,16 @@ int launch_lrn_bwd(int dtype, const void *a, const void *dy, int relu, void *da,
 // Normalisation and a pool of window k, stride 2, on top of it in one pass each: forward a -> pooled y and positions; backward
 // writes da, times [a > 0], from the gradient dy at the pool's output, and leaves the column sums of da in
 // bands[Cp][lrn_pool_bands(...)].  lrn_pool_bands is 0 where the pair does not run this way: where the kernels do not
-// take it, or (not if always) where separate ones are faster.  Separate ones need more workspace.
-long lrn_pool_bands(int dtype, int B, int H, int W, int Cp, int k, int stride, bool always);
+// take it, or (not if always) where separate ones are faster.  Separate ones need more workspace.  forked: the
+// weight gradients run on the side stream.
+long lrn_pool_bands(int dtype, int B, int H, int W, int Cp, int k, int stride, bool forked, bool always);
 int launch_lrn_pool_fwd(int dtype, const void *a, void *y, uint8_t *arg, int B, int H, int W, int Cp, int size, float alpha, float beta, float bias, int k,
                         hipStream_t s);
 int launch_lrn_pool_bwd(int dtype, const void *a, const void *dy, const uint8_t *arg, void *da, int B, int H, int W, int Cp, int size, float alpha,
                         float beta, float bias, int k, float *bands, hipStream_t s);
 // A pool of window k, stride 2, under a fully-connected layer: forward straight into flat [B][C*Ho*Wo] in (c,h,w) order (and the
 // positions, channel-last); backward from dflat, masked where relu by flat > 0, into dx, with the column sums of dx in
-// bands[Cp][pool_flat_bands(...)].  pool_flat_bands is 0 as lrn_pool_bands is.  forked: the
-// weight gradients run on the side stream.
+// bands[Cp][pool_flat_bands(...)].  pool_flat_bands is 0 as lrn_pool_bands is.
 long pool_flat_bands(int dtype, int B, int H, int W, int C, int Cp, int k, int stride, bool forked, bool always);
 int launch_pool_flat_fwd(int dtype, const void *x, int nonneg, void *flat, uint8_t *arg, int B, int H, int W, int C, int Cp, int k, hipStream_t s);
 int launch_pool_flat_bwd(int dtype, const void *dflat, const void *flat, int relu, const uint8_t *arg, void *dx, int B, int H, int W, int C, int Cp, int k,

@@ -1624,19 +1624,21 @@ static bool lrn_pool_plan(int dtype, int B, int H, int W, int Cp, int k, int str
     p.dWo = make_fastdiv(p.Wo); p.dcv = make_fastdiv(p.cv); p.dHb = make_fastdiv(p.Hb);
     return true;
 }
-long lrn_pool_bands(int dtype, int B, int H, int W, int Cp, int k, int stride, bool always)
+long lrn_pool_bands(int dtype, int B, int H, int W, int Cp, int k, int stride, bool forked, bool always)
 {
     LrnPool p;
     size_t f, b;
     if (!lrn_pool_plan(dtype, B, H, W, Cp, k, stride, p, f, b)) return 0;
     const long blocks = (long)B * p.Hb;
     if ((long)B * p.tiles * p.chunks > 0x7fffffffL || blocks > 0x7fffffffL) return 0;
-    // A block of the backward kernel takes 2 * W pixels, p.lanes side by side: more than five rounds of that on less than a third of
-    // the CUs are longer than the launch and the tensors they save.  A pass of two convolutions, separate / here, us, bf16: 55 x 55 over
-    // 256 channels (14 rounds) 1 image 108 / 118, 2 images (56 blocks) 116 / 120, 4 images (112) 130 / 126; 16 x 200 over 64 (12.5 rounds) 6
-    // images (48 blocks) 112 / 120, 12 images (96) 124 / 123; 55 x 55 over 96 (5.5 rounds) 1 image 107 / 110, 4 images 117 / 117; fewer
-    // rounds, 13 x 13 over 256, 1 image 72 / 71.
-    if (!always && 2 * W > 5 * p.lanes && blocks < 80) return 0;
+    // A block of the backward kernel takes 2 * W pixels, p.lanes side by side, in up to 18 rounds: in bf16 more than nine of them on
+    // less than a quarter of the CUs are longer than the launches and the tensors they save, unless there is hardly anything to do.  A
+    // pass of two convolutions, separate / here, us: 55 x 55 over 256 channels (14 rounds) 1 image 108 / 118, 2 images (56 blocks)
+    // 116 / 120, 4 images (112) 130 / 126; 17 x 84 over 128 (10.5 rounds) 3 images (27 blocks) 107 / 112; 16 x 85 over 128 1 image (8
+    // blocks) 101 / 95; 19 x 23 over 256 (6 rounds) 3 images 98 / 88; fp32 25 x 88 over 64 (11 rounds) 1 image 103 / 105, 36 x 22 over
+    // 256 (11 rounds) 114 / 108.  With the side stream the separate kernels are never ahead: AlexNet-style net with two normalised
+    // layers, 1 image, 424 / 417.  Over 58 passes without and 82 with it the choice is at most 1.02 of the better one.
+    if (!always && !forked && dtype == kBF16 && 2 * W > 9 * p.lanes && blocks >= 20 && blocks < 60) return 0;
     return blocks;
 }
 template <typename T, int HALF>
@@ -1663,7 +1665,7 @@ static int launch_lrn_pool(int dtype, int B, int H, int W, int Cp, int size, flo
     LrnPool p;
     size_t lf, lb;
     if (size < 1 || size > 9 || !(size & 1) || !(bias > 0.f)) return -1;
-    if (lrn_pool_bands(dtype, B, H, W, Cp, k, 2, true) == 0 || !lrn_pool_plan(dtype, B, H, W, Cp, k, 2, p, lf, lb)) return -1;
+    if (lrn_pool_bands(dtype, B, H, W, Cp, k, 2, false, true) == 0 || !lrn_pool_plan(dtype, B, H, W, Cp, k, 2, p, lf, lb)) return -1;
     p.alpha = alpha; p.beta = beta; p.bias = bias;
     const size_t lds = da ? lb : lf;
     uint8_t *ar = const_cast<uint8_t *>(arg);

@@ -387,7 +387,7 @@ def test_pool_under_fc_shapes(shape, dtype):
 # turn for a workgroup, with too few of them (separate kernels) and with enough.
 LRNPOOL_SHAPES = [(8, 3, 4, 3, 1, 3), (12, 9, 10, 2, 5, 3), (96, 23, 21, 3, 5, 3), (40, 13, 14, 2, 9, 2), (256, 9, 6, 2, 3, 3), (264, 5, 6, 1, 7, 2), (512, 6, 5, 1, 5, 3),
                   (520, 5, 5, 1, 5, 3), (8, 7, 213, 1, 5, 3), (8, 7, 216, 1, 5, 3), (16, 4, 320, 1, 5, 2),
-                  (256, 5, 30, 1, 5, 3), (256, 22, 30, 8, 5, 3), (128, 16, 32, 10, 5, 2), (128, 16, 32, 9, 5, 2)]
+                  (256, 5, 30, 1, 5, 3), (256, 22, 30, 8, 5, 3), (128, 16, 32, 10, 5, 2), (128, 16, 32, 9, 5, 2), (256, 14, 37, 3, 5, 3), (256, 14, 36, 3, 5, 3)]
 
 
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
