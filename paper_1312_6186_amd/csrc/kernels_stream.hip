@@ -1611,8 +1611,10 @@ static bool lrn_pool_plan(int dtype, int B, int H, int W, int Cp, int k, int str
     const long row = (long)p.cols * p.groups * 16;
     const long fit = (kLrnPoolLds / row - k) / 2 + 1;   // pooled rows whose input rows fit
     if (kLrnPoolLds / row < k) return false;
-    // and fewer while CUs are idle (bf16, 55 x 55 over 96 channels, 1 image: a pass 115 us with 6 blocks for the rows, 110 with 27)
-    p.tiles = (int)std::max((p.Ho + fit - 1) / fit, std::min((long)p.Ho, 256 / ((long)B * p.chunks)));
+    // and fewer while CUs are idle and a block would take more than one round of its threads (bf16, 55 x 55 over 96 channels, 1 image: a
+    // pass 115 us with 6 blocks for the rows, 110 with 27; fp32, 8 x 11 over 64, 3 images, one round: 92.9 in 1, 94.3 in 3)
+    const long round = std::max(1L, (512 / ((long)p.cols * p.groups) - k) / 2 + 1);
+    p.tiles = (int)std::max((p.Ho + fit - 1) / fit, std::min((p.Ho + round - 1) / round, 256 / ((long)B * p.chunks)));
     p.R = (p.Ho + p.tiles - 1) / p.tiles;
     p.tiles = (p.Ho + p.R - 1) / p.R;
     lds_fwd = (size_t)(2 * (p.R - 1) + k) * (size_t)row;
