@@ -73,7 +73,7 @@ struct Stage {
     bool bands_ready = false;  // ... and whether the backward pass of this call has left them
     GemmPlan p_fwd, p_dgrad, p_wgrad;
     WgradPlan d_wgrad;           // CONV: set where the filter gradient (of all groups) runs as conv_wgrad
-    DirectPlan d_fwd, d_dgrad;   // CONV: set where the forward pass / the data gradient (of one group) runs as conv_direct
+    DirectPlan d_fwd, d_dgrad;   // CONV: set where the forward pass / the data gradient (of all groups) runs as conv_direct
     size_t wf_elems = 0, wd_elems = 0;   // packed filters of one group
     size_t out_elems() const { return kind == ST_FC ? (size_t)out_ld : (size_t)outH * outW * outCp; }
 };
@@ -408,11 +408,11 @@ int size_net(asgd_net &n, const Budget &partials, bool plain)
             }
             const int Ng = s.groups > 1 ? s.outC / s.groups : s.outCp, Cg = s.groups > 1 ? s.inC / s.groups : s.inCp;
             s.d_wgrad = plan_wgrad(n.dtype, Ng, s.groups, conv_gather(s, nullptr, (int)B, n.dtype), partials.wgrad);
-            s.d_fwd = plain ? DirectPlan() : plan_direct(n.dtype, conv_gather(s, nullptr, (int)B, n.dtype), Ng);
+            s.d_fwd = plain ? DirectPlan() : plan_direct(n.dtype, conv_gather(s, nullptr, (int)B, n.dtype), Ng, s.groups);
             s.wf_elems = s.d_fwd.ks ? s.d_fwd.pack_elems : (size_t)Ng * s.k * (s.rw ? s.rwKW : s.k * Cg);
             if (si > 0) {
-                s.d_dgrad = plain ? DirectPlan() : plan_direct(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg);
-                if (split_is_faster(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg, s.d_dgrad, side)) s.d_dgrad = DirectPlan();
+                s.d_dgrad = plain ? DirectPlan() : plan_direct(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg, s.groups);
+                if (split_is_faster(n.dtype, dgrad_gather(s, nullptr, (int)B, n.dtype, 0), Cg, s.groups, s.d_dgrad, side)) s.d_dgrad = DirectPlan();
                 s.wd_elems = s.d_dgrad.ks ? s.d_dgrad.pack_elems : (size_t)Cg * s.k * s.k * Ng;
             }
             if (si > 0 && !s.d_dgrad.ks) scratch_side = std::max(scratch_side, s.p_dgrad.ws_floats);
@@ -639,13 +639,14 @@ int forward(asgd_net *n, const void *params, const void *images, const int32_t *
             ProfScope ps(n, st, ASGD_K_CONV_FWD, 2 * Mo * s.outC * (s.inC / s.groups) * s.k * s.k,
                          (Bd * s.inH * s.inW * s.inC + (double)s.w_cnt + Mo * s.outC) * es);
             const int Og = s.groups > 1 ? s.outC / s.groups : s.outCp;   // columns of one group
-            for (int gi = 0; gi < s.groups; ++gi) {
+            const int launches = s.d_fwd.ks ? 1 : s.groups;   // conv_direct takes all groups at once
+            for (int gi = 0; gi < launches; ++gi) {
                 const Gather g = conv_gather(s, cur, B, dt, gi);
                 const void *wf = static_cast<const char *>(s.wf) + gi * s.wf_elems * dtype_size(dt);
                 Epilogue ep;
                 ep.out = static_cast<char *>(s.out) + (size_t)gi * Og * dtype_size(dt); ep.ld = s.outCp;
                 ep.bias = param_ptr(n, params, s.b_off + (size_t)gi * Og); ep.bias_n = s.outC / s.groups; ep.relu = s.relu;
-                if (s.d_fwd.ks) CHECK_LAUNCH(conv_direct(dt, g, wf, Og, ep, s.d_fwd, st), "conv forward");
+                if (s.d_fwd.ks) CHECK_LAUNCH(conv_direct(dt, g, wf, Og, s.groups, ep, s.d_fwd, st), "conv forward");
                 else CHECK_LAUNCH(gemm_gather_plain(dt, g, wf, (long)g.kh * g.kw * g.C, Og, ep, s.p_fwd, n->scratch, st), "conv forward");
             }
         } else if (s.kind == ST_LRN && s.with_pool) {
@@ -1006,7 +1007,8 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                 const bool masked = (prev->kind == ST_CONV && prev->relu) || relu_under_pool(n->stages, si - 1);
                 ProfScope ps(n, st, ASGD_K_CONV_DGRAD, conv_flops,
                              (Mo * s.outC + (double)s.w_cnt + Bd * s.inH * s.inW * s.inC * (masked ? 2 : 1)) * es);
-                for (int gi = 0; gi < s.groups; ++gi) {
+                const int launches = s.d_dgrad.ks ? 1 : s.groups;
+                for (int gi = 0; gi < launches; ++gi) {
                     // the group's slice of the output gradient, gathered with the flipped filters of that group
                     const int Ogp = s.groups > 1 ? Og : s.outCp, Cgp = s.groups > 1 ? Cg : s.inCp;
                     const Gather d = dgrad_gather(s, s.dout, B, dt, gi);
@@ -1014,7 +1016,7 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                     ed.out = static_cast<char *>(prev->dout) + (size_t)gi * Cg * esz; ed.ld = s.inCp;
                     if (masked) { ed.mask_src = static_cast<const char *>(prev->out) + (size_t)gi * Cg * esz; ed.mask_ld = s.inCp; ed.mask_scale = 1.f; }
                     const void *wd = static_cast<const char *>(s.wd) + gi * s.wd_elems * esz;
-                    if (s.d_dgrad.ks) CHECK_LAUNCH(conv_direct(dt, d, wd, Cgp, ed, s.d_dgrad, st), "conv data gradient");
+                    if (s.d_dgrad.ks) CHECK_LAUNCH(conv_direct(dt, d, wd, Cgp, s.groups, ed, s.d_dgrad, st), "conv data gradient");
                     else CHECK_LAUNCH(gemm_gather_plain(dt, d, wd, (long)s.k * s.k * Ogp, Cgp, ed, s.p_dgrad, n->scratch_side, st), "conv data gradient");
                 }
             }

@@ -90,16 +90,17 @@ double lone_fc_wgrad_us(int dtype, long out, long in, long batch);
 
 // Stride-1 convolutions over equal grids (forward, and the data gradient as a convolution with flipped filters): K steps
 // of 16 channels per chunk (0: the convolution does not run this way), chunks, tile shape, patch loads per thread and chunk,
-// and the size of the packed filters.  Packed element (n, pos, c): blocks of 32 output columns, then chunks, window positions and K steps, each K
+// and the size of a group's packed filters.  Packed element (n, pos, c): blocks of 32 output columns, then chunks, window positions and K steps, each K
 // step 64 lanes x 8 channels in the order the matrix cores take them (see direct_index).
 struct DirectPlan {
     int ks = 0, nchunks = 0, tile = 0, npl = 0;
     size_t nblk_elems = 0, pack_elems = 0;
 };
-DirectPlan plan_direct(int dtype, const Gather &a, int N);   // none where the general engine is the faster one
+// All groups of a layer run in one launch: a and ep of the first group (N columns each), the groups' packed filters one after the other.
+DirectPlan plan_direct(int dtype, const Gather &a, int N, int groups);   // none where the general engine is the faster one
 // whether the general engine in K splits (plan_conv) is faster than plan d
-bool split_is_faster(int dtype, const Gather &a, int N, const DirectPlan &d, size_t partials);
-int conv_direct(int dtype, const Gather &a, const void *wpack, int N, const Epilogue &ep, const DirectPlan &plan, hipStream_t s);
+bool split_is_faster(int dtype, const Gather &a, int N, int groups, const DirectPlan &d, size_t partials);
+int conv_direct(int dtype, const Gather &a, const void *wpack, int N, int groups, const Epilogue &ep, const DirectPlan &plan, hipStream_t s);
 
 // Filter gradients of stride-1 convolutions over equal grids in 16-bit data (conv_wgrad.hip): tile shape (-1: does not run
 // this way), pixel ranges.  All groups of a layer run in one launch: dy [pixels][ldy]

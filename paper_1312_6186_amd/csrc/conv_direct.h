@@ -23,6 +23,10 @@
 // inside a step): 96 -> 256 channels 129 -> 104, 256 -> 384 44 -> 37, 384 -> 384 58 -> 49, 384 -> 256 53 -> 39; data
 // gradients 256 -> 96 136 -> 92, 384 -> 256 53 -> 42, 384 -> 384 58 -> 54, 256 -> 384 41 -> 41.  32 images: 42 -> 36,
 // 28 -> 19, 36 -> 25, 31 -> 21; 58 -> 50, 32 -> 22, 35 -> 26, 26 -> 20 (256 -> 96 alone 44, and 41 since it runs in 128 x 128).
+//
+// The groups of a grouped layer are column tiles of one launch (a group has other input channels and filters, the pixels are the
+// same): a launch each leaves the CUs idle twice at its start and end.  One step of the two-column net, bf16, 128 images
+// (2 x 48 -> 128, 192 -> 192 and 192 -> 128 channels): 1235 -> 1201 us.
 #pragma once
 #include "asgd_internal.h"
 #include "mfma_common.h"
@@ -35,7 +39,8 @@ struct DirectConv {
     int nchunks, npl;                      // channel chunks; patch loads per thread and chunk
     unsigned patch_bytes, patch_off2;      // one patch buffer; offset of the second one (0 if there is one chunk)
     Operand w; unsigned nblk_bytes; int nblks;   // packed filters: bytes of a block of 32 output columns, and their number
-    int tiles_n;
+    int tiles_n, groups;                   // column tiles of a group; groups, whose channels (C in, N out) and filters follow each other
+    unsigned xg_bytes, wg_bytes;           // from one group's channels of a pixel to the next group's, and of the packed filters
     FastDiv dW, dHW;
 };
 
@@ -84,7 +89,7 @@ __global__ __launch_bounds__(64 * WM * WN, (MB * NB > 8 ? 1 : 2)) void conv_dire
         const int nb = gridDim.x, q = nb >> 3, r = nb & 7, x = blockIdx.x & 7;
         bid = x * q + (x < r ? x : r) + (blockIdx.x >> 3);
     }
-    const int tm = bid / p.tiles_n, tn = bid - tm * p.tiles_n;
+    const int tiles_row = p.tiles_n * p.groups, tm = bid / tiles_row, col = bid - tm * tiles_row, grp = col / p.tiles_n, tn = col - grp * p.tiles_n;
     const int wm = (wave % WM) * (32 * MB), wn = (wave / WM) * (32 * NB);
     const int total = p.nchunks * p.npos;
     const unsigned zero_base = sm + p.patch_off2 + p.patch_bytes;   // a multiple of 256
@@ -94,7 +99,7 @@ __global__ __launch_bounds__(64 * WM * WN, (MB * NB > 8 ? 1 : 2)) void conv_dire
     unsigned wvo[NB];
     static_for<0, NB>([&](auto nb) ASGD_INLINE {
         const int blk = min(tn * (BN / 32) + wn / 32 + nb, p.nblks - 1);   // columns past N: any block (never stored)
-        wvo[nb] = (unsigned)blk * p.nblk_bytes + (unsigned)lane * (16u * VPF);
+        wvo[nb] = (unsigned)grp * p.wg_bytes + (unsigned)blk * p.nblk_bytes + (unsigned)lane * (16u * VPF);
     });
     Frag<T> b[LOOK * KS][NB];   // LOOK window positions ahead; set r holds positions r, r + LOOK, ... (npos % LOOK == 0)
     auto load_b = [&](auto set, auto ks, auto nb, int step) ASGD_INLINE {
@@ -116,7 +121,7 @@ __global__ __launch_bounds__(64 * WM * WN, (MB * NB > 8 ? 1 : 2)) void conv_dire
     const bool act = slot < G::PIECES;
     // offset of load j (pixel gp = gp0 + j * PPL); cok: the slot's channels exist and load j belongs to the patch
     auto patch_off = [&](int gp, unsigned off, bool cok) ASGD_INLINE -> unsigned { return (((unsigned)gp < (unsigned)p.M) & cok) ? off : kInv; };
-    const unsigned pvo0 = (unsigned)gp0 * p.pix + (unsigned)slot * 16u, pvo_step = (unsigned)PPL * p.pix;
+    const unsigned pvo0 = (unsigned)gp0 * p.pix + (unsigned)grp * p.xg_bytes + (unsigned)slot * 16u, pvo_step = (unsigned)PPL * p.pix;
     const unsigned pst = sm + (unsigned)(prow * PITCH + slot * 16);
     static_for<0, LOOK>([&](auto r) ASGD_INLINE { static_for<0, KS>([&](auto ks) ASGD_INLINE { static_for<0, NB>([&](auto nb) ASGD_INLINE { load_b(r, ks, nb, r); }); }); });
     for (int j0 = 0; j0 < p.npl; j0 += 6) {
@@ -138,7 +143,7 @@ __global__ __launch_bounds__(64 * WM * WN, (MB * NB > 8 ? 1 : 2)) void conv_dire
         });
     }
     float bias_v = 0.f;
-    if (ep.bias && tid < BN && tn * BN + tid < ep.bias_n) bias_v = to_f32(static_cast<const T *>(ep.bias)[tn * BN + tid]);
+    if (ep.bias && tid < BN && tn * BN + tid < ep.bias_n) bias_v = to_f32(static_cast<const T *>(ep.bias)[grp * p.N + tn * BN + tid]);
 
     // ---- this lane's rows: patch address at window position (0, 0), and the window positions inside the image
     unsigned abase[MB], amask[MB];
@@ -269,8 +274,8 @@ __global__ __launch_bounds__(64 * WM * WN, (MB * NB > 8 ? 1 : 2)) void conv_dire
     char *st = smp + wave * (NB * 4096);
     constexpr int ITEMS = 2 * NB;
     const bool linear = !ep.relu;
-    T *out = static_cast<T *>(ep.out);
-    const T *mask = static_cast<const T *>(ep.mask_src);
+    T *out = static_cast<T *>(ep.out) + grp * p.N;
+    const T *mask = static_cast<const T *>(ep.mask_src) + grp * p.N;
     static_for<0, MB>([&](auto mb) ASGD_INLINE {
         const int m0 = tm * BM + wm + mb * 32;
         Vec8<T> ms[MASKED ? ITEMS : 1];

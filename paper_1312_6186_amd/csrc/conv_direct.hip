@@ -42,7 +42,7 @@ struct DirectRates {
 constexpr DirectRates kRatesF32 = {4.7, 0.16, 0.5, 0.215, 0, 1, 0, 0, 0.06, 1.2}, kRatesBf16 = {3.3, 0, 1.0, 0.0113, 0.0195, 0.85, 0.155, 0.083, 0.6, 1.8};
 constexpr double kPatchUs = 35e-6;   // a byte of patch: 28 GB/s for each CU while all of them fetch
 
-double direct_us(int es, int ks, int nchunks, const Tile &t, const Gather &a, int N)
+double direct_us(int es, int ks, int nchunks, const Tile &t, const Gather &a, int N, int groups)
 {
     const DirectRates &q = es == 2 ? kRatesBf16 : kRatesF32;
     const Fit f = fit(es, ks, nchunks, t, a);
@@ -51,7 +51,7 @@ double direct_us(int es, int ks, int nchunks, const Tile &t, const Gather &a, in
     const double position = ks * t.nb * std::max(q.mma * t.mb * (blocks >= 8 ? q.large : 1.0), q.filters) * (ks == 1 ? q.single : 1.0);
     const double least = es == 2 && blocks <= 4 && ks >= 2 && npos % 3 == 0 ? q.pos3 : q.pos1;
     const double alone = (double)nchunks * npos * std::max(position, least) + q.load * f.npl + q.store * blocks;
-    const long M = (long)a.N * a.H * a.W, tiles = ((M + 32 * t.mb * t.wm - 1) / (32 * t.mb * t.wm)) * ((N + 32 * t.nb * t.wn - 1) / (32 * t.nb * t.wn));
+    const long M = (long)a.N * a.H * a.W, tiles = ((M + 32 * t.mb * t.wm - 1) / (32 * t.mb * t.wm)) * ((N + 32 * t.nb * t.wn - 1) / (32 * t.nb * t.wn)) * groups;
     return q.launch + rounds_us(tiles, per_cu, [&](int r) {
         return std::max(alone, r * nchunks * (npos * position + kPatchUs * f.patch_bytes) + q.apart * alone);
     });
@@ -67,7 +67,7 @@ double engine_us(int es, const Gather &a, int N)
 
 }  // namespace
 
-DirectPlan plan_direct(int dtype, const Gather &a, int N)
+DirectPlan plan_direct(int dtype, const Gather &a, int N, int groups)
 {
     DirectPlan d;
     const int es = (int)dtype_size(dtype), npos = a.kh * a.kw;
@@ -102,8 +102,8 @@ DirectPlan plan_direct(int dtype, const Gather &a, int N)
         // 77 images 38 and 26 in 204 of 128 x 128).  fp32 MFMAs take eight times as long: every shape keeps them busy.
         const double eff_bf16 = t.mb * t.nb >= 6 ? 0.61 : t.mb * t.nb >= 4 ? 0.57 : t.mb * t.nb == 3 ? 0.45 : t.mb == 2 ? 0.47 : t.nb == 2 ? 0.37 : 0.3;
         const double eff = es == 2 ? eff_bf16 : 0.8;
-        const long tiles = ((M + 32 * t.mb * t.wm - 1) / (32 * t.mb * t.wm)) * ((N + 32 * t.nb * t.wn - 1) / (32 * t.nb * t.wn));
-        const double cost = (double)((tiles + 255) / 256) * (t.mb * t.nb) * (t.wm * t.wn / 4.0) / eff, us = direct_us(es, d.ks, d.nchunks, t, a, N);
+        const long tiles = ((M + 32 * t.mb * t.wm - 1) / (32 * t.mb * t.wm)) * ((N + 32 * t.nb * t.wn - 1) / (32 * t.nb * t.wn)) * groups;
+        const double cost = (double)((tiles + 255) / 256) * (t.mb * t.nb) * (t.wm * t.wn / 4.0) / eff, us = direct_us(es, d.ks, d.nchunks, t, a, N, groups);
         if (by_cost < 0 || cost < best_cost) { by_cost = v; best_cost = cost; cost_us = us; }
         if (by_time < 0 || us < best_us) { by_time = v; best_us = us; }
     }
@@ -114,24 +114,24 @@ DirectPlan plan_direct(int dtype, const Gather &a, int N)
     // would share the CU and is late (us, engine / here: fp32 48 -> 32 channels 3 x 3 on 128 x 192, 5 images 69 / 165; bf16
     // 96 -> 16 on 32 x 255, 26 images 47 / 110, 64 -> 128 on 64 x 480, 6 images 44 / 102).
     const int tile = cost_us > 1.1 * best_us ? by_time : by_cost;
-    if (tile < 0 || engine_us(es, a, N) < (tile == by_time ? best_us : cost_us)) return DirectPlan();
+    if (tile < 0 || groups * engine_us(es, a, N) < (tile == by_time ? best_us : cost_us)) return DirectPlan();
     d.tile = tile;
     d.npl = fit(es, d.ks, d.nchunks, kTiles[tile], a).npl;
     d.nblk_elems = (size_t)d.nchunks * npos * d.ks * 512;
     d.pack_elems = (size_t)((N + 31) / 32) * d.nblk_elems;
-    if (d.pack_elems * es > kMaxOperandBytes) return DirectPlan();
+    if (d.pack_elems * groups * es > kMaxOperandBytes) return DirectPlan();
     return d;
 }
 
 // Few columns over few pixels: the general engine in K splits, where it is modelled a quarter faster.
-bool split_is_faster(int dtype, const Gather &a, int N, const DirectPlan &d, size_t partials)
+bool split_is_faster(int dtype, const Gather &a, int N, int groups, const DirectPlan &d, size_t partials)
 {
     double us = 0;
     return d.ks && plan_conv((long)a.N * a.H * a.W, N, (long)a.kh * a.kw * a.C, dtype, 1, partials, &us).splits > 1 &&
-           us < 0.75 * direct_us((int)dtype_size(dtype), d.ks, d.nchunks, kTiles[d.tile], a, N);
+           groups * us < 0.75 * direct_us((int)dtype_size(dtype), d.ks, d.nchunks, kTiles[d.tile], a, N, groups);
 }
 
-int conv_direct(int dtype, const Gather &a, const void *wpack, int N, const Epilogue &ep, const DirectPlan &d, hipStream_t s)
+int conv_direct(int dtype, const Gather &a, const void *wpack, int N, int groups, const Epilogue &ep, const DirectPlan &d, hipStream_t s)
 {
     const int es = (int)dtype_size(dtype);
     if (d.ks == 0 || ((uintptr_t)a.x & 15) || ((uintptr_t)wpack & 15) || ((uintptr_t)ep.out & 15) || (ep.ld & 7) || ep.mode || ep.drop || ep.out_f32) return -1;
@@ -145,11 +145,12 @@ int conv_direct(int dtype, const Gather &a, const void *wpack, int N, const Epil
     p.M = a.N * a.H * a.W; p.N = N;
     p.nchunks = d.nchunks; p.npl = f.npl;
     p.patch_bytes = f.patch_bytes; p.patch_off2 = d.nchunks > 1 ? f.patch_bytes : 0;
-    p.w = Operand{wpack, (unsigned)(d.pack_elems * es)};
+    p.w = Operand{wpack, (unsigned)(d.pack_elems * groups * es)};
+    p.groups = groups; p.xg_bytes = (unsigned)(a.C * es); p.wg_bytes = (unsigned)(d.pack_elems * es);
     p.nblk_bytes = (unsigned)(d.nblk_elems * es); p.nblks = (N + 31) / 32;
     p.tiles_n = (N + 32 * t.nb * t.wn - 1) / (32 * t.nb * t.wn);
     p.dW = make_fastdiv((uint32_t)a.W); p.dHW = make_fastdiv((uint32_t)(a.H * a.W));
-    const long grid = (long)((p.M + 32 * t.mb * t.wm - 1) / (32 * t.mb * t.wm)) * p.tiles_n;
+    const long grid = (long)((p.M + 32 * t.mb * t.wm - 1) / (32 * t.mb * t.wm)) * p.tiles_n * groups;
     if (grid <= 0 || grid > 0x7fffffffL) return -1;
     const auto launch = dtype == kBF16 ? (ep.mask_src ? launch_direct_bf16_bwd : launch_direct_bf16_fwd) : (ep.mask_src ? launch_direct_f32_bwd : launch_direct_f32_fwd);
     return launch(d.tile, d.ks, p, ep, (unsigned)grid, f.lds, s);

@@ -279,6 +279,24 @@ def test_stride1_convolution_shapes(shape, dtype):
         g.close()
 
 
+# Grouped ones, all groups in one launch: channels per group around the chunks, outputs per group around the blocks of 32 columns (data gradients:
+# the other way round), two to four groups, fewer pixels than a tile and many tiles.
+GROUPED_SHAPES = [(16, 16, 3, 5, 7, 1, 2), (72, 120, 3, 9, 11, 3, 3), (96, 256, 5, 27, 27, 2, 2), (64, 64, 5, 12, 9, 5, 4), (144, 400, 3, 13, 13, 4, 2), (384, 384, 3, 13, 13, 40, 2)]
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("shape", GROUPED_SHAPES, ids=lambda s: "%dto%d_k%d_%dx%dx%d_g%d" % s)
+def test_grouped_stride1_convolution_shapes(shape, dtype):
+    cin, cout, k, h, w, batch, groups = shape
+    layers = [("conv", cin, 1, 1, 0), ("relu",), ("conv", cout, k, 1, k // 2, groups), ("relu",), ("maxpool", 2, 2), ("fc", 10), ("softmax_ce",)]
+    g, onet, (loss, grads), (ref_loss, ref_grads, _), _ = _net_case({"name": "grouped", "in_shape": (3, h, w), "classes": 10, "layers": layers}, batch, dtype, plain=False)
+    try:
+        assert abs(loss - ref_loss) <= TOL[dtype] * abs(ref_loss)
+        compare_grads(onet, grads, ref_grads, TOL[dtype], "grouped")
+    finally:
+        g.close()
+
+
 # Filter gradients of such layers in bf16: output channels around the tiles of 128, 192 and 256, input channels around the
 # chunks of 32 and 64, two groups, images narrower and wider than a tile of 64 pixels, pixel counts below one tile and around
 # an odd and an even number of tiles, and the largest count of splits.
