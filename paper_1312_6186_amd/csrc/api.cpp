@@ -708,7 +708,8 @@ struct ServerArgs {
     int copies = 0;
     // with fuse
     bool keep = false;       // ... which stores the gradient too
-    bool later = false;      // the gradient kernels leave the push to push_gradient
+    bool later = false;      // the gradient kernels leave the push to push_weights and push_rest
+    hipEvent_t ready = nullptr;   // ... and this event says that what push_weights reads and replaces is done with
     float *acc = nullptr;    // the gradient is added up here (written if acc_first)
     bool acc_first = false;
     int *counter = nullptr;  // advanced once the push is done, and logged for every fetch it does
@@ -783,16 +784,16 @@ int push_rest(asgd_net *n, const float *grads, const ServerArgs &srv, hipStream_
     return flush(true);
 }
 
-// The push of a gradient whose kernels left it (ServerArgs::later) on another stream, behind the backward pass that
-// left the layers' inputs and output gradients in the plan's workspace.
-int push_gradient(asgd_net *n, float *grads, const ServerArgs &srv, hipStream_t st)
+// The push of the fully-connected weights whose gradient kernels left it (ServerArgs::later) on another stream, behind the part of
+// the backward pass that left the layers' inputs and output gradients in the plan's workspace.
+int push_weights(asgd_net *n, float *grads, const ServerArgs &srv, hipStream_t st)
 {
     for (int si = (int)n->stages.size() - 1; si >= 0; --si)
         if (fused_fc(n->stages[si])) {
             const int rc = fc_weight_grad(n, si, grads, &srv, st);
             if (rc != ASGD_OK) return rc;
         }
-    return push_rest(n, grads, srv, st);
+    return ASGD_OK;
 }
 
 int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStream_t st, const ServerArgs *srv)
@@ -902,6 +903,7 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                 if (frc == ASGD_OK) frc = data_grad();
             }
             if (frc != ASGD_OK) return frc;
+            if (srv && srv->ready && s.in_is_spatial) CHECK_HIP(hipEventRecord(srv->ready, st), "hipEventRecord");
         } else if (s.kind == ST_LRN && s.with_pool) {
             continue;   // done with the pool's stage above
         } else if (s.kind == ST_POOL && s.to_flat) {
@@ -1425,7 +1427,7 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
     }
     if (rc == ASGD_OK && !keeper->replay_start) RP(hipEventCreateWithFlags(&keeper->replay_start, kOuterEvent));
     if (rc == ASGD_OK && !keeper->replay_done) RP(hipEventCreateWithFlags(&keeper->replay_done, kOuterEvent));
-    const size_t n_events = 3 * (size_t)T + 1;
+    const size_t n_events = 4 * (size_t)T + 1;
     while (keeper->replay_events.size() < n_events && rc == ASGD_OK) {
         hipEvent_t e = nullptr;
         RP(hipEventCreateWithFlags(&e, kInnerEvent));
@@ -1434,8 +1436,8 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
     if (rc != ASGD_OK) { for (int w = 0; w < n_workers; ++w) nets[w]->in_replay = false; return rc; }
     hipStream_t *ws = keeper->replay_streams.data();
     hipStream_t server = keeper->replay_streams[n_workers];
-    hipEvent_t *ev_upd = keeper->replay_events.data(), *ev_snap = ev_upd + T, *ev_grad = ev_snap + T;
-    hipEvent_t ev_start = keeper->replay_start, ev_reset = keeper->replay_events[3 * (size_t)T];
+    hipEvent_t *ev_upd = keeper->replay_events.data(), *ev_snap = ev_upd + T, *ev_grad = ev_snap + T, *ev_fc = ev_grad + T;
+    hipEvent_t ev_start = keeper->replay_start, ev_reset = keeper->replay_events[4 * (size_t)T];
     // Everything below waits, directly or through the server stream, for the work already on the caller's stream; the
     // internal streams of a previous replay on these plans were joined into the caller's stream of that replay.
     RP(hipEventRecord(ev_start, caller));
@@ -1479,6 +1481,7 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
                     step.keep = i == n_sync - 1 && last_push[w] == a;
                 } else {
                     step.later = true;
+                    step.ready = ev_fc[a];
                 }
                 rc = fwd_bwd(nets[w], worker_copy[w], static_cast<const char *>(images) + b * img_bytes, labels + b * n0->batch,
                              dropout_seed, (uint64_t)b, (uint32_t)w, losses + b, worker_grads[w], ws[w], fused ? &step : nullptr);
@@ -1493,7 +1496,8 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
         }
         for (int a = v; a < T && rc == ASGD_OK; ++a)
             if (read_version[a] == v && !fetched[a]) RP(hipStreamWaitEvent(server, ev_snap[a], 0));
-        RP(hipStreamWaitEvent(server, ev_grad[v], 0));
+        const bool early = fused && !loc;   // the fully-connected weights are pushed beside the rest of their backward pass
+        RP(hipStreamWaitEvent(server, early ? ev_fc[v] : ev_grad[v], 0));
         if (fused && rc == ASGD_OK) {
             // a replica that fetches version v + 1 has pushed its last gradient by update v at the latest: its copy is free
             ServerArgs push{params, momentum, lr, mu, wd, true};
@@ -1508,7 +1512,9 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
             push.logs = push.copies; push.counter = counter;
             if (!loc) {
                 push.keep = last_push[worker[v]] == v;
-                rc = push_gradient(nets[worker[v]], worker_grads[worker[v]], push, server);
+                rc = push_weights(nets[worker[v]], worker_grads[worker[v]], push, server);
+                RP(hipStreamWaitEvent(server, ev_grad[v], 0));
+                if (rc == ASGD_OK) rc = push_rest(nets[worker[v]], worker_grads[worker[v]], push, server);
             } else {
                 PushRanges p = {};
                 p.w = params; p.v = momentum; p.g = loc->accum[worker[v]]; p.lr = lr; p.mu = mu; p.wd = wd;

@@ -131,6 +131,9 @@ int gemm_plain_trans(int dtype, const void *a, long lda, int M, const void *bt, 
 // A stored [K][lda] (rows m contiguous), B stored [K][ldb].
 int gemm_trans_trans(int dtype, const void *at, long lda, int M, const void *bt, long ldb, int N, int K,
                      const Epilogue &ep, const GemmPlan &plan, float *ws, hipStream_t s);
+// The push of a fully-connected layer's weights in their gradient kernel (fc_push.hip): operands as in gemm_trans_trans
+bool fc_push_applies(int dtype, int M, int N, int K, const Epilogue &ep);
+int fc_push(const void *at, long lda, int M, const void *bt, long ldb, int N, int K, const Epilogue &ep, hipStream_t s);
 // Filter gradient: A stored [K = B*Ho*Wo][lda] (rows = cout), B gathered with the
 // reduction index enumerating (n, oy, ox) and rows enumerating (ky, kx, c).
 int gemm_trans_gather(int dtype, const void *at, long lda, int M, const Gather &b, const Epilogue &ep,

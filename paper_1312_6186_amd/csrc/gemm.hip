@@ -1607,12 +1607,13 @@ template <typename T> static int run_outer(const PlainT<T> &la, const PlainT<T> 
 int gemm_trans_trans(int dtype, const void *at, long lda, int M, const void *bt, long ldb, int N, int K, const Epilogue &ep,
                      const GemmPlan &plan, float *ws, hipStream_t s)
 {
-    if (ep.upd_w) {   // push inside the kernel (update_tile of gemm_kernel over two transposed plain operands, or lone_kernel):
+    if (ep.upd_w) {   // push inside the kernel (fc_push, update_tile of gemm_kernel over two transposed plain operands, or lone_kernel):
                       // whole sums only, 16-byte rows and column groups in all buffers
         uintptr_t al = (uintptr_t)ep.upd_w | (uintptr_t)ep.upd_v | (uintptr_t)ep.upd_acc | (uintptr_t)ep.out;
         if (ep.upd_copies < 0 || ep.upd_copies > kPushCopies) return -1;
         for (int c = 0; c < ep.upd_copies; ++c) { if (!ep.upd_copy[c]) return -1; al |= (uintptr_t)ep.upd_copy[c]; }
         if (plan.splits != 1 || ep.mode != 0 || !ep.upd_v || (al & 15) || (ep.ld & 7)) return -1;
+        if (fc_push_applies(dtype, M, N, K, ep)) return fc_push(at, lda, M, bt, ldb, N, K, ep, s);
     }
     if (dtype == kBF16)
         return outer_applies<bf16_t>(M, N, K, ep, plan)

@@ -660,6 +660,64 @@ def test_train_step_is_the_three_calls_bit_for_bit_and_matches_the_oracle(cfg, d
 
 
 # ---------------------------------------------------------------- A-SGD replay
+# The push of fully-connected weights in its own kernel: 2048 and 2056 inputs (strips of 128, the last one whole and ragged) into outputs around the tiles
+# of 64 rows, enough tiles for it and one too few; batches around what a set of fragments holds (32, 64, 128, 256 images) and past it.
+PUSH_SHAPES = [(16, 16, 1000, 1), (16, 16, 1000, 17), (16, 16, 1016, 32), (16, 16, 961, 33), (16, 16, 1087, 64), (16, 16, 1000, 65), (16, 16, 1026, 128),
+               (16, 16, 1000, 129), (16, 16, 1000, 256), (16, 16, 1000, 257), (16, 16, 960, 20), (1, 257, 1000, 8), (1, 257, 968, 72), (1, 257, 2048, 136)]
+
+
+@pytest.mark.parametrize("shape", PUSH_SHAPES, ids=lambda s: "%dx%d_%d_%d" % s)
+def test_pushed_weights_are_the_calls_bit_for_bit(shape):
+    """One fused step against the separate calls, and a replay of local steps, whose gradients are summed up too, against the separate kernels that
+    parameters at a 4-byte offset take."""
+    h, w_, out, batch = shape
+    layers, tdt = [("conv", 8, 1, 1, 0), ("relu",), ("fc", out), ("softmax_ce",)], torch.bfloat16
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(5)
+    nets = [B.asgd_net_create(layers, batch, (3, h, w_), B.BF16) for _ in range(2)]
+    P = B.asgd_param_count(nets[0])
+    params0 = torch.randn(P, generator=gen, device=DEV) * 0.05
+    mom0 = torch.randn(P, generator=gen, device=DEV) * 0.01
+    images = torch.randn((4, batch, 3, h, w_), generator=gen, device=DEV).to(tdt)
+    labels = torch.randint(0, 10, (4, batch), generator=gen, device=DEV, dtype=torch.int32)
+
+    def bits(tensors):
+        torch.cuda.synchronize()
+        return [t.cpu().contiguous().view(torch.uint8).numpy() for t in tensors]
+
+    try:
+        steps = []
+        for fused in (True, False):
+            w, v, copy, grads, loss = params0.clone(), mom0.clone(), torch.empty(P, dtype=tdt, device=DEV), torch.zeros(P, device=DEV), torch.zeros(1, device=DEV)
+            B.asgd_snapshot(w, copy, B.BF16)
+            if fused:
+                B.asgd_train_step_fused(nets[0], w, v, copy, images[0], labels[0], 3, 0, 0, loss, grads, 0.01, 0.9, 5e-4)
+            else:
+                B.asgd_fwd_bwd(nets[0], copy, images[0], labels[0], 3, 0, 0, loss, grads)
+                B.asgd_apply_update_snapshot(w, v, grads, 0.01, 0.9, 5e-4, copy, B.BF16)
+            steps.append(bits([w, v, copy, loss]))
+        for a, b in zip(*steps):
+            np.testing.assert_array_equal(a, b)
+        if (images[0].numel() * 2) % 16:
+            return   # the second minibatch would not be aligned
+        replays = []
+        for offset in (0, 1):
+            def vec():
+                return torch.zeros(P + offset, device=DEV)[offset:]
+            params, mom, local = vec(), vec(), [[vec() for _ in range(2)] for _ in range(3)]
+            params.copy_(params0)
+            copies, grads = [torch.zeros(P, dtype=tdt, device=DEV) for _ in range(2)], [torch.zeros(P, device=DEV) for _ in range(2)]
+            losses, log = torch.zeros(4, device=DEV), torch.zeros((2, 3), dtype=torch.int32, device=DEV)
+            B.asgd_replay_nsync_run(nets, 2, params, mom, local[0], local[1], local[2], copies, grads, images, labels, np.array([0, 1], np.int32), np.array([0, 1], np.int32),
+                                    0.01, 0.9, 5e-4, 9, losses, log)
+            replays.append(bits([params.clone(), mom.clone(), losses, log] + copies + grads + [t.clone() for l in local for t in l]))
+        for a, b in zip(*replays):
+            np.testing.assert_array_equal(a, b)
+    finally:
+        for n in nets:
+            B.asgd_net_destroy(n)
+
+
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
 def test_asgd_replay_matches_oracle_and_logs_the_schedule(dtype):
     cfg = wl.TINY
