@@ -684,6 +684,11 @@ int forward(asgd_net *n, const void *params, const void *images, const int32_t *
                 ep.drop = 1; ep.drop_key = dropout_key(seed, step, worker, (uint32_t)s.drop_layer);
                 ep.drop_thr = s.drop_thr; ep.drop_F = s.out_f; ep.drop_scale = s.drop_scale;
             }
+            if (s.last && !n->prof_on && fc_softmax_applies(B, s.out_ld, s.in_f)) {
+                CHECK_LAUNCH(fc_softmax(dt, x, ldx, B, param_ptr(n, params, s.w_off), s.in_f, s.out_ld, s.out_f, s.in_f, ep, labels, s.dout, n->row_loss, st),
+                             "fc forward and softmax cross-entropy");
+                return ASGD_OK;
+            }
             ProfScope ps(n, st, ASGD_K_FC_FWD, 2 * Bd * s.in_f * s.out_f, (Bd * s.in_f + (double)s.w_cnt) * es + Bd * s.out_f * (s.last ? 4 : es));
             CHECK_LAUNCH(gemm_plain_plain(dt, x, ldx, B, param_ptr(n, params, s.w_off), s.in_f, s.out_ld, s.out_f, s.in_f, ep, s.p_fwd, n->scratch, st),
                          "fc forward");
@@ -721,13 +726,21 @@ struct ServerArgs {
 // 16-byte rows in the parameter-shaped buffers.
 bool fused_fc(const Stage &s) { return s.kind == ST_FC && s.p_wgrad.splits == 1 && s.in_f % 8 == 0 && s.w_off % 8 == 0; }
 
-// The weight gradient of fully-connected layer si, stored, or pushed if srv is given.
-int fc_weight_grad(asgd_net *n, int si, float *grads, const ServerArgs *srv, hipStream_t st)
+// Operands of a fully-connected layer's gradients.
+FcGrads fc_grads(const asgd_net *n, int si, const void *params)
 {
     const Stage &s = n->stages[si];
-    const void *x = s.in_is_spatial ? s.flat_in : n->stages[si - 1].out;
-    const long ldx = s.in_is_spatial ? s.in_f : n->stages[si - 1].out_ld;
-    const double es = (double)dtype_size(n->dtype), Bd = n->batch;
+    FcGrads g;
+    g.dy = s.dout; g.ld_dy = s.out_ld; g.batch = n->batch; g.in = s.in_f; g.out = s.out_f;
+    g.x = s.in_is_spatial ? s.flat_in : n->stages[si - 1].out;
+    g.ld_x = s.in_is_spatial ? s.in_f : n->stages[si - 1].out_ld;
+    g.w = params ? param_ptr(n, params, s.w_off) : nullptr;
+    return g;
+}
+// What becomes of the weight gradient of layer si: stored, or pushed if srv is given.
+Epilogue fc_weight_epilogue(const asgd_net *n, int si, float *grads, const ServerArgs *srv)
+{
+    const Stage &s = n->stages[si];
     Epilogue ew;
     ew.out = grads + s.w_off; ew.ld = s.in_f; ew.out_f32 = 1;
     if (srv) {
@@ -738,10 +751,18 @@ int fc_weight_grad(asgd_net *n, int si, float *grads, const ServerArgs *srv, hip
         if (srv->acc) { ew.upd_acc = srv->acc + s.w_off; ew.upd_acc_first = srv->acc_first; }
         ew.upd_lr = srv->lr; ew.upd_mu = srv->mu; ew.upd_wd = srv->wd;
     }
+    return ew;
+}
+int fc_weight_grad(asgd_net *n, int si, float *grads, const ServerArgs *srv, hipStream_t st)
+{
+    const Stage &s = n->stages[si];
+    const FcGrads g = fc_grads(n, si, nullptr);
+    const double es = (double)dtype_size(n->dtype), Bd = n->batch;
     ProfScope ps(n, st, ASGD_K_FC_WGRAD, 2 * Bd * s.in_f * s.out_f,
                  Bd * (s.in_f + s.out_f) * es +
                      (double)s.w_cnt * (srv ? 16.0 + es * srv->copies + (srv->keep ? 4.0 : 0.0) + (srv->acc ? srv->acc_first ? 4.0 : 8.0 : 0.0) : 4.0));
-    CHECK_LAUNCH(gemm_trans_trans(n->dtype, s.dout, s.out_ld, s.out_f, x, ldx, s.in_f, n->batch, ew, s.p_wgrad, n->scratch_side, st),
+    CHECK_LAUNCH(gemm_trans_trans(n->dtype, g.dy, g.ld_dy, s.out_f, g.x, g.ld_x, s.in_f, n->batch, fc_weight_epilogue(n, si, grads, srv), s.p_wgrad,
+                                  n->scratch_side, st),
                  "fc weight gradient");
     return ASGD_OK;
 }
@@ -817,13 +838,13 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
         if (by_layer) {
             ProfScope ps(n, sd, ASGD_K_BIAS_GRAD, 0, bytes);
             CHECK_LAUNCH(launch_colsum_partial(dt, dy, ld, M, N, db, ws, bias_jobs, sd), what);
-            CHECK_LAUNCH(launch_colsum_finish(bias_jobs, sd), what);
+            CHECK_LAUNCH(launch_colsum_finish(dt, bias_jobs, nullptr, sd), what);
             return ASGD_OK;
         }
         if (bias_s1.n == 12 || bias_jobs.n == 12) {
             ProfScope ps(n, sd, ASGD_K_BIAS_GRAD, 0, bias_s1_bytes);
             CHECK_LAUNCH(launch_colsum_stage1(dt, bias_s1, sd), what);
-            CHECK_LAUNCH(launch_colsum_finish(bias_jobs, sd), what);
+            CHECK_LAUNCH(launch_colsum_finish(dt, bias_jobs, nullptr, sd), what);
             bias_s1_bytes = 0;
         }
         if (colsum_partial_defer(dt, dy, ld, M, N, db, ws, bias_s1, bias_jobs) != 0) return fail(ASGD_EINVAL, "%s: bad shape", what);
@@ -851,6 +872,18 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
             return hip_fail(hipGetLastError(), "update kernel");
         return ASGD_OK;
     };
+    // On one stream the partial sums of a filter gradient are added up in the launch of the next pool below or of the bias gradients, if
+    // nothing else takes their place before.
+    const bool join = !fork && !n->prof_on && !by_layer;
+    Reduction partial;
+    auto add_partial = [&]() -> int {
+        if (partial.blocks == 0) return ASGD_OK;
+        const Reduction r = partial;
+        partial.blocks = 0;
+        CHECK_LAUNCH(launch_reduction(dt, r, st), "conv filter gradient");
+        return ASGD_OK;
+    };
+    int waiting = -1;   // fully-connected layer whose weights are pushed with the data gradient of the layer below
     for (int si = (int)n->stages.size() - 1; si >= 0; --si) {
         Stage &s = n->stages[si];
         Stage *prev = si > 0 ? &n->stages[si - 1] : nullptr;
@@ -861,46 +894,57 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
         }
         if (s.kind == ST_FC) {
             const bool fused = srv && srv->fuse && fused_fc(s);
-            auto param_grads = [&]() -> int {
-                const int rc = fused && srv->later ? ASGD_OK : fc_weight_grad(n, si, grads, fused ? srv : nullptr, sd);
-                if (rc != ASGD_OK) return rc;
-                return bias_sums(s.dout, s.out_ld, B, s.out_f, grads + s.b_off, s.colsum_ws, Bd * s.out_f * es + s.out_f * 4.0, "fc bias gradient");
+            Epilogue ed;
+            if (s.in_is_spatial) {
+                ed.out = s.dflat_in; ed.ld = s.in_f;
+            } else if (prev) {
+                ed.out = prev->dout; ed.ld = prev->out_ld;
+                if (prev->relu) { ed.mask_src = prev->out; ed.mask_ld = prev->out_ld; ed.mask_scale = prev->drop ? prev->drop_scale : 1.f; }
+            }
+            auto weight_grad = [&](int layer) -> int { return fc_weight_grad(n, layer, grads, fused ? srv : nullptr, sd); };
+            // Small layers: the weight gradient of layer w with the data gradient of this one
+            auto pair = [&](int w, bool &done) -> int {
+                done = w >= 0 && prev && !fork && !n->prof_on && fc_pair_applies(fc_grads(n, w, params), fc_grads(n, si, params));
+                if (!done) return ASGD_OK;
+                CHECK_LAUNCH(fc_pair(dt, fc_grads(n, w, params), fc_grads(n, si, params), fc_weight_epilogue(n, w, grads, fused ? srv : nullptr), ed, st), "fc gradients");
+                return ASGD_OK;
             };
             auto data_grad = [&]() -> int {
                 if (!prev) return ASGD_OK;
-                Epilogue ed;
-                if (s.in_is_spatial) {
-                    ed.out = s.dflat_in; ed.ld = s.in_f;
-                } else {
-                    ed.out = prev->dout; ed.ld = prev->out_ld;
-                    if (prev->relu) { ed.mask_src = prev->out; ed.mask_ld = prev->out_ld; ed.mask_scale = prev->drop ? prev->drop_scale : 1.f; }
-                }
-                {
-                    ProfScope ps(n, st, ASGD_K_FC_DGRAD, 2 * Bd * s.in_f * s.out_f, (Bd * s.out_f + (double)s.w_cnt + Bd * s.in_f * (ed.mask_src ? 2 : 1)) * es);
-                    CHECK_LAUNCH(gemm_plain_trans(dt, s.dout, s.out_ld, B, param_ptr(n, params, s.w_off), s.in_f, s.in_f, s.out_f, ed, s.p_dgrad,
-                                                  n->scratch, st),
-                                 "fc data gradient");
-                }
-                if (!s.in_is_spatial || prev->to_flat) return ASGD_OK;
-                ProfScope ps(n, st, ASGD_K_LAYOUT, 0, 3 * Bd * s.in_f * es);
-                CHECK_LAUNCH(launch_unflatten(dt, s.dflat_in, prev->out, (prev->kind == ST_CONV && prev->relu) || relu_under_pool(n->stages, si - 1),
-                                                  prev->dout, B, s.inH, s.inW, s.inC, s.inCp, st),
-                                 "unflatten");
+                ProfScope ps(n, st, ASGD_K_FC_DGRAD, 2 * Bd * s.in_f * s.out_f, (Bd * s.out_f + (double)s.w_cnt + Bd * s.in_f * (ed.mask_src ? 2 : 1)) * es);
+                CHECK_LAUNCH(gemm_plain_trans(dt, s.dout, s.out_ld, B, param_ptr(n, params, s.w_off), s.in_f, s.in_f, s.out_f, ed, s.p_dgrad, n->scratch, st),
+                             "fc data gradient");
                 return ASGD_OK;
             };
-            // A fused layer's weight-gradient kernel rewrites the replica's weights, which the data gradient reads: the
-            // data gradient goes first and the other stream waits for it.
             int frc = ASGD_OK;
-            if (fused) {
+            bool paired = false;
+            if (fused && srv->later) {
                 frc = data_grad();
+            } else if (fused) {
+                // A fused layer's weight-gradient kernel rewrites the replica's weights, which the data gradient reads: the
+                // data gradient goes first and the other stream waits for it, or the kernel joins the next layer's data gradient.
+                frc = pair(waiting, paired);
+                if (frc == ASGD_OK && !paired && waiting >= 0) frc = weight_grad(waiting);
+                if (frc == ASGD_OK && !paired) frc = data_grad();
+                waiting = -1;
                 if (frc == ASGD_OK && fork) {
                     CHECK_HIP(hipEventRecord(n->ev_dg[si], st), "hipEventRecord");
                     CHECK_HIP(hipStreamWaitEvent(sd, n->ev_dg[si], 0), "hipStreamWaitEvent");
                 }
-                if (frc == ASGD_OK) frc = param_grads();
+                if (fork || s.in_is_spatial || !prev) { if (frc == ASGD_OK) frc = weight_grad(si); }
+                else waiting = si;
             } else {
-                frc = param_grads();
-                if (frc == ASGD_OK) frc = data_grad();
+                if (waiting >= 0) { frc = fc_weight_grad(n, waiting, grads, srv, sd); waiting = -1; }   // the layer above was fused
+                if (frc == ASGD_OK) frc = pair(si, paired);
+                if (frc == ASGD_OK && !paired) frc = weight_grad(si);
+                if (frc == ASGD_OK && !paired) frc = data_grad();
+            }
+            if (frc == ASGD_OK) frc = bias_sums(s.dout, s.out_ld, B, s.out_f, grads + s.b_off, s.colsum_ws, Bd * s.out_f * es + s.out_f * 4.0, "fc bias gradient");
+            if (frc == ASGD_OK && s.in_is_spatial && prev && !prev->to_flat) {
+                ProfScope ps(n, st, ASGD_K_LAYOUT, 0, 3 * Bd * s.in_f * es);
+                CHECK_LAUNCH(launch_unflatten(dt, s.dflat_in, prev->out, (prev->kind == ST_CONV && prev->relu) || relu_under_pool(n->stages, si - 1),
+                                              prev->dout, B, s.inH, s.inW, s.inC, s.inCp, st),
+                             "unflatten");
             }
             if (frc != ASGD_OK) return frc;
             if (srv && srv->ready && s.in_is_spatial) CHECK_HIP(hipEventRecord(srv->ready, st), "hipEventRecord");
@@ -938,8 +982,11 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                 // first stage of that layer's bias gradient behind, which saves reading the tensor again
                 float *bands = nullptr;
                 if (prev->kind == ST_CONV && prev->pool_bands > 0) { bands = prev->colsum_ws; prev->bands_ready = true; }
-                CHECK_LAUNCH(launch_pool_bwd(dt, s.dout, s.argmax, prev->out, relu_here, prev->dout, B, s.inH, s.inW, s.inCp, s.k, s.stride, bands, st),
+                const bool beside = partial.blocks && pool_bwd_bands(dt, B, s.inH, s.inW, s.inCp, s.k, s.stride) > 0;
+                CHECK_LAUNCH(launch_pool_bwd(dt, s.dout, s.argmax, prev->out, relu_here, prev->dout, B, s.inH, s.inW, s.inCp, s.k, s.stride, bands,
+                                             beside ? &partial : nullptr, st),
                              "pool backward");
+                if (beside) partial.blocks = 0;
             }
         } else {
             const long M = (long)B * s.outH * s.outW;
@@ -954,12 +1001,12 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                 ProfScope ps(n, sd, ASGD_K_BIAS_GRAD, 0, s.outC * 4.0);
                 if (bias_jobs.n == 12) {
                     CHECK_LAUNCH(launch_colsum_stage1(dt, bias_s1, sd), "conv bias gradient");
-                    CHECK_LAUNCH(launch_colsum_finish(bias_jobs, sd), "conv bias gradient");
+                    CHECK_LAUNCH(launch_colsum_finish(dt, bias_jobs, nullptr, sd), "conv bias gradient");
                 }
                 ColsumJob &J = bias_jobs.j[bias_jobs.n++];
                 J.ws = s.colsum_ws; J.nblk = (int)s.pool_bands; J.ld = s.outCp; J.N = s.outC; J.db = grads + s.b_off;
                 J.start_block = 0; J.colmajor = 1; J.bf16 = 0; J.div = 1.f;
-                if (by_layer) CHECK_LAUNCH(launch_colsum_finish(bias_jobs, sd), "conv bias gradient");
+                if (by_layer) CHECK_LAUNCH(launch_colsum_finish(dt, bias_jobs, nullptr, sd), "conv bias gradient");
                 return ASGD_OK;
             };
             // The last layer of the backward pass: its filter gradient is the tail of the side stream, which ends after
@@ -972,16 +1019,16 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                 if (brc != ASGD_OK) return brc;
                 CHECK_HIP(hipEventRecord(n->ev_bias, sd), "hipEventRecord");
                 CHECK_HIP(hipStreamWaitEvent(st, n->ev_bias, 0), "hipStreamWaitEvent");
-                CHECK_LAUNCH(launch_colsum_finish(bias_jobs, st), "bias gradients");
+                CHECK_LAUNCH(launch_colsum_finish(dt, bias_jobs, nullptr, st), "bias gradients");
             }
-            {
+            auto filter_grad = [&]() -> int {
                 ProfScope ps(n, sd, ASGD_K_CONV_WGRAD, conv_flops, (Mo * s.outC + Bd * s.inH * s.inW * s.inC) * es + (double)s.w_cnt * 4);
                 if (s.d_wgrad.tile >= 0) {
                     const int Ogp = s.groups > 1 ? Og : s.outCp;
                     Epilogue ew;   // the groups' filters follow each other: one matrix of groups * Og rows
                     ew.out = grads + s.w_off; ew.mode = 1; ew.out_f32 = 1;
                     ew.cw_cout = s.outC; ew.cw_cin = Cg; ew.cw_cinp = s.groups > 1 ? Cg : s.inCp; ew.cw_kh = s.k; ew.cw_kw = s.k;
-                    CHECK_LAUNCH(conv_wgrad(s.dout, s.outCp, Ogp, s.groups, conv_gather(s, xin, B, dt), ew, s.d_wgrad, n->scratch_side, sd),
+                    CHECK_LAUNCH(conv_wgrad(s.dout, s.outCp, Ogp, s.groups, conv_gather(s, xin, B, dt), ew, s.d_wgrad, n->scratch_side, join ? &partial : nullptr, sd),
                                  "conv filter gradient");
                 } else if (s.groups > 1) {
                     for (int gi = 0; gi < s.groups; ++gi) {
@@ -990,7 +1037,7 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                         ew.out = grads + s.w_off + (size_t)gi * Og * Cg * s.k * s.k; ew.mode = 1; ew.out_f32 = 1;
                         ew.cw_cout = Og; ew.cw_cin = Cg; ew.cw_cinp = Cg; ew.cw_kh = s.k; ew.cw_kw = s.k;
                         CHECK_LAUNCH(gemm_trans_gather(dt, static_cast<const char *>(s.dout) + (size_t)gi * Og * esz, s.outCp, Og, g, ew, s.p_wgrad,
-                                                       n->scratch_side, sd),
+                                                       n->scratch_side, nullptr, sd),
                                      "conv filter gradient");
                     }
                 } else {
@@ -998,14 +1045,12 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                     Epilogue ew;
                     ew.out = grads + s.w_off; ew.mode = s.rw ? 2 : 1; ew.out_f32 = 1;
                     ew.cw_cout = s.outC; ew.cw_cin = s.inC; ew.cw_cinp = s.rw ? s.rwKW : s.inCp; ew.cw_kh = s.k; ew.cw_kw = s.k; ew.cw_rwc = s.rw ? s.rwC : 4;
-                    CHECK_LAUNCH(gemm_trans_gather(dt, s.dout, s.outCp, s.outCp, g, ew, s.p_wgrad, n->scratch_side, sd), "conv filter gradient");
+                    CHECK_LAUNCH(gemm_trans_gather(dt, s.dout, s.outCp, s.outCp, g, ew, s.p_wgrad, n->scratch_side, join ? &partial : nullptr, sd), "conv filter gradient");
                 }
-            }
-            if (!bias_first) {
-                const int brc = bias_part();
-                if (brc != ASGD_OK) return brc;
-            }
-            if (prev) {
+                return ASGD_OK;
+            };
+            auto data_grad = [&]() -> int {
+                if (!prev) return ASGD_OK;
                 const bool masked = (prev->kind == ST_CONV && prev->relu) || relu_under_pool(n->stages, si - 1);
                 ProfScope ps(n, st, ASGD_K_CONV_DGRAD, conv_flops,
                              (Mo * s.outC + (double)s.w_cnt + Bd * s.inH * s.inW * s.inC * (masked ? 2 : 1)) * es);
@@ -1021,7 +1066,16 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                     if (s.d_dgrad.ks) CHECK_LAUNCH(conv_direct(dt, d, wd, Cgp, s.groups, ed, s.d_dgrad, st), "conv data gradient");
                     else CHECK_LAUNCH(gemm_gather_plain(dt, d, wd, (long)s.k * s.k * Ogp, Cgp, ed, s.p_dgrad, n->scratch_side, st), "conv data gradient");
                 }
-            }
+                return ASGD_OK;
+            };
+            // On one stream the data gradient goes first: its partial sums, if it has any, have the same place as the filter gradient's, which
+            // wait there for a later launch.
+            int crc = add_partial();
+            if (crc == ASGD_OK && !fork) crc = data_grad();
+            if (crc == ASGD_OK) crc = filter_grad();
+            if (crc == ASGD_OK && !bias_first) crc = bias_part();
+            if (crc == ASGD_OK && fork) crc = data_grad();
+            if (crc != ASGD_OK) return crc;
         }
         const int prc = push(si);
         if (prc != ASGD_OK) return prc;
@@ -1030,7 +1084,7 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
         const int brc = bias_first_stages();
         if (brc != ASGD_OK) return brc;
         ProfScope ps(n, sd, ASGD_K_BIAS_GRAD, 0, 0);
-        CHECK_LAUNCH(launch_colsum_finish(bias_jobs, sd), "bias gradients");
+        CHECK_LAUNCH(launch_colsum_finish(dt, bias_jobs, partial.blocks ? &partial : nullptr, sd), "bias gradients");
     }
     if (fork) {
         CHECK_HIP(hipEventRecord(n->ev_join, sd), "hipEventRecord");

@@ -78,6 +78,17 @@ struct GemmPlan {
     size_t ws_floats = 0;    // fp32 scratch needed when splits > 1
 };
 
+// The partial sums of a split GEMM, to be added up by `blocks` workgroups of 256 threads: in a launch of their own, or beside something
+// else that neither waits for them nor writes their place.  later (where a routine has it): filled instead of launching the reduction
+// (blocks stays 0 where the sums were whole).  On one stream a reduction of its own is 4 to 8 us in a chain of small kernels.
+struct Reduction {
+    const float *ws = nullptr; Epilogue ep;
+    int splits = 0, M = 0, N = 0;
+    int lanes = 1;                          // that share eight outputs (1, 8, 32, 256); 0: filters by runs of the canonical layout, with
+    int npos = 0, cb = 0, chunks = 0;       // window positions, channels of a workgroup, and workgroups per output channel
+    unsigned blocks = 0;
+};
+
 // us that the workgroups of a launch keep the 256 CUs busy, where per_cu of them fit a CU and r on one CU take t(r) us.
 template <class F> double rounds_us(long workgroups, int per_cu, F t)
 {
@@ -110,9 +121,10 @@ struct WgradPlan {
     size_t ws_floats = 0;    // fp32 scratch
 };
 WgradPlan plan_wgrad(int dtype, int M, int groups, const Gather &x, size_t max_ws_floats);
-int conv_wgrad(const void *dy, long ldy, int M, int groups, const Gather &x, const Epilogue &ep, const WgradPlan &plan, float *ws, hipStream_t s);
-// C = ep(sum over splits of ws[split][M][N]), added in a fixed order
-int splitk_reduce(int dtype, const float *ws, int splits, const Epilogue &ep, int M, int N, hipStream_t s);
+int conv_wgrad(const void *dy, long ldy, int M, int groups, const Gather &x, const Epilogue &ep, const WgradPlan &plan, float *ws, Reduction *later, hipStream_t s);
+// C = ep(sum over splits of ws[split][M][N]), added in a fixed order: launched, or left to the caller in *later
+int splitk_reduce(int dtype, const float *ws, int splits, const Epilogue &ep, int M, int N, Reduction *later, hipStream_t s);
+int launch_reduction(int dtype, const Reduction &r, hipStream_t s);
 
 // Every operand must fit in 1 GiB.
 // C[M][N] = A[M][K] * B[N][K]^T; A gathered (direct), B plain K-contiguous.
@@ -131,13 +143,22 @@ int gemm_plain_trans(int dtype, const void *a, long lda, int M, const void *bt, 
 // A stored [K][lda] (rows m contiguous), B stored [K][ldb].
 int gemm_trans_trans(int dtype, const void *at, long lda, int M, const void *bt, long ldb, int N, int K,
                      const Epilogue &ep, const GemmPlan &plan, float *ws, hipStream_t s);
+// Small fully-connected products (the kernel for them takes both): the weight gradient of layer w (stored or pushed as we says) and the
+// data gradient of layer d in one launch.  They may be one layer's; not where the push rewrites the weights that d reads.
+struct FcGrads { const void *dy, *x, *w; long ld_dy, ld_x; int batch, in, out; };   // output gradients, inputs, weights [out][in]
+bool fc_pair_applies(const FcGrads &w, const FcGrads &d);
+int fc_pair(int dtype, const FcGrads &w, const FcGrads &d, const Epilogue &we, const Epilogue &de, hipStream_t s);
+// Logits (as gemm_plain_plain) and softmax cross-entropy (as launch_softmax_ce; dz [M][ep.ld]) in one launch: up to 16 classes
+bool fc_softmax_applies(long M, long N, long K);
+int fc_softmax(int dtype, const void *a, long lda, int M, const void *b, long ldb, int N, int classes, int K, const Epilogue &ep, const int32_t *labels, void *dz,
+               float *row_loss, hipStream_t s);
 // The push of a fully-connected layer's weights in their gradient kernel (fc_push.hip): operands as in gemm_trans_trans
 bool fc_push_applies(int dtype, int M, int N, int K, const Epilogue &ep);
 int fc_push(const void *at, long lda, int M, const void *bt, long ldb, int N, int K, const Epilogue &ep, hipStream_t s);
 // Filter gradient: A stored [K = B*Ho*Wo][lda] (rows = cout), B gathered with the
 // reduction index enumerating (n, oy, ox) and rows enumerating (ky, kx, c).
 int gemm_trans_gather(int dtype, const void *at, long lda, int M, const Gather &b, const Epilogue &ep,
-                      const GemmPlan &plan, float *ws, hipStream_t s);
+                      const GemmPlan &plan, float *ws, Reduction *later, hipStream_t s);
 // fp32 scratch (in floats) the filter gradient of a first convolution in window-row form wants in plan.ws_floats to
 // run as one persistent kernel with a partial result per workgroup; 0 where that kernel does not apply
 size_t rows_wgrad_ws_floats(int dtype, int M, const Gather &b);
@@ -195,9 +216,9 @@ int launch_pool_fwd(int dtype, const void *x, int nonneg, void *y, uint8_t *arg,
                     hipStream_t s);
 // dx[pixel] = sum of dy over the windows whose recorded maximum is this pixel; times [x > 0] if relu
 int launch_pool_bwd(int dtype, const void *dy, const uint8_t *arg, const void *x, int relu, void *dx, int B, int H,
-                    int W, int Cp, int k, int stride, float *bands, hipStream_t s);
+                    int W, int Cp, int k, int stride, float *bands, const Reduction *beside, hipStream_t s);
 // bands != nullptr: the kernel also leaves the column sums of dx in bands[Cp][pool_bwd_bands(...)] (stage 1 of a
-// bias gradient); only for shapes where pool_bwd_bands is not 0
+// bias gradient); only for shapes where pool_bwd_bands is not 0.  beside != nullptr, for the same shapes: partial sums added up in the same launch
 long pool_bwd_bands(int dtype, int B, int H, int W, int Cp, int k, int stride);
 // cross-channel response normalisation on channel-last tensors: y = a * (bias + alpha * window sum of a^2)^(-beta);
 // backward writes da (times [a > 0], the ReLU of the convolution below, if relu) from a and dy; size odd, <= 9
@@ -238,7 +259,8 @@ struct ColsumS1Job { const void *dy; float *ws; long ld, M, rows_per_block; int 
 struct ColsumS1Jobs { ColsumS1Job j[12]; int n; };
 int colsum_partial_defer(int dtype, const void *dy, long ld, long M, int N, float *db, float *ws, ColsumS1Jobs &s1, ColsumJobs &jobs);
 int launch_colsum_stage1(int dtype, ColsumS1Jobs &s1, hipStream_t s);
-int launch_colsum_finish(ColsumJobs &jobs, hipStream_t s);
+// beside != nullptr: partial sums added up in the same launch
+int launch_colsum_finish(int dtype, ColsumJobs &jobs, const Reduction *beside, hipStream_t s);
 size_t colsum_ws_floats(int dtype, long M, long ld);
 // softmax cross-entropy over fp32 logits [B][ld]: the loss of every row, whose mean loss_job appends to the bias sums' second
 // stage, and dz (compute type, [B][ld], zero padding columns)

@@ -273,7 +273,7 @@ WgradPlan plan_wgrad(int dtype, int M, int groups, const Gather &x, size_t max_w
     return best;
 }
 
-int conv_wgrad(const void *dy, long ldy, int M, int groups, const Gather &x, const Epilogue &ep, const WgradPlan &plan, float *ws, hipStream_t s)
+int conv_wgrad(const void *dy, long ldy, int M, int groups, const Gather &x, const Epilogue &ep, const WgradPlan &plan, float *ws, Reduction *later, hipStream_t s)
 {
     if (plan.tile < 0 || plan.tile >= kWgTileCount || kWgTiles[plan.tile].kw != x.kw || ep.mode != 1 || !ep.out_f32 || !ws || ((uintptr_t)ws & 15) || ((uintptr_t)dy & 15) || ((uintptr_t)x.x & 15) || ldy % 8) return -1;
     const WgTile &t = kWgTiles[plan.tile];
@@ -298,7 +298,7 @@ int conv_wgrad(const void *dy, long ldy, int M, int groups, const Gather &x, con
     case 2: hipLaunchKernelGGL((conv_wgrad_kernel<2, 5, 4, 1>), g, b, 0, s, p); break;
     default: hipLaunchKernelGGL((conv_wgrad_kernel<2, 5, 2, 2>), g, b, 0, s, p); break;
     }
-    return splitk_reduce(kBF16, ws, plan.splits, ep, groups * M, p.N, s);
+    return splitk_reduce(kBF16, ws, plan.splits, ep, groups * M, p.N, later, s);
 }
 
 }  // namespace asgd

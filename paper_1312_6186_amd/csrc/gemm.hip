@@ -37,6 +37,7 @@
 
 #include "asgd_internal.h"
 #include "mfma_common.h"
+#include "reduce.h"
 
 namespace asgd {
 
@@ -689,13 +690,20 @@ __device__ __forceinline__ void mma16(f32x4 &acc, const Frag<float> &first, cons
 template <typename T> __device__ __forceinline__ unsigned row_offset(const PlainK<T> &l, int r) { return l.row(r).off; }
 template <typename T> __device__ __forceinline__ unsigned row_offset(const PlainT<T> &l, int r) { return l.col(r).off; }
 constexpr int kLoneWaves = 8;
-template <typename T, class LA, class LB>
-__global__ __launch_bounds__(64 * kLoneWaves) void lone_kernel(LA la, LB lb, Epilogue ep, int M, int N, int K, int tiles_n)
+template <typename T> struct LonePair {
+    PlainT<T> wa, wb; Epilogue w_ep; int w_m, w_n, w_k, w_tiles_n, w_blocks;   // weight gradient: output gradients and inputs, K = images
+    PlainK<T> da; PlainT<T> db; Epilogue d_ep; int d_m, d_n, d_k, d_tiles_n;   // data gradient: output gradients and weights, K = outputs
+};
+struct LoneShared { f32x4 part[kLoneWaves][64]; float sums[16][20]; };
+// softmax cross-entropy over the logits of a tile (all classes in its 16 columns): labels, gradient at the logits [M][ld], loss per row
+struct LoneCe { const int32_t *labels; void *dz; float *row_loss; int classes; };
+template <typename T, bool CE, class LA, class LB>
+__device__ __forceinline__ void lone_tile(LoneShared &sh, const LA &la, const LB &lb, const Epilogue &ep, int M, int N, int K, int tiles_n, int block, const LoneCe &ce)
 {
-    __shared__ f32x4 part[kLoneWaves][64];
-    __shared__ float sums[16][20];
+    auto &part = sh.part;
+    auto &sums = sh.sums;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6;
-    const int tm = (int)blockIdx.x / tiles_n, tn = (int)blockIdx.x - tm * tiles_n;
+    const int tm = block / tiles_n, tn = block - tm * tiles_n;
     const __amdgpu_buffer_rsrc_t ra = la.op.rsrc(), rb = lb.op.rsrc();
     const unsigned oa = row_offset(la, tm * 16 + (lane & 15)), ob = row_offset(lb, tn * 16 + (lane & 15));
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -729,6 +737,29 @@ __global__ __launch_bounds__(64 * kLoneWaves) void lone_kernel(LA la, LB lb, Epi
     }
     *reinterpret_cast<f32x4 *>(&sums[lane & 15][4 * (lane >> 4)]) = v;
     __builtin_amdgcn_wave_barrier();   // one wave: its LDS accesses keep their order
+    if constexpr (CE) {
+        // four rows at a time, a lane per column; sums and comparisons in the order of softmax_ce_kernel
+        const int c = lane & 15;
+        const float bias = c < ep.bias_n ? to_f32(static_cast<const T *>(ep.bias)[c]) : 0.f, inv_b = 1.f / (float)M;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int row = q * 4 + (lane >> 4), m = tm * 16 + row;
+            const float z = sums[row][c] + bias;
+            float mx = c < ce.classes ? z : -INFINITY;
+            for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+            float sum = c < ce.classes ? expf(z - mx) : 0.f;
+            for (int o = 8; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+            const float lse = mx + logf(sum);
+            const int label = m < M ? ce.labels[m] : 0;
+            const bool label_ok = (unsigned)label < (unsigned)ce.classes;   // otherwise the row's loss is NaN and dz the plain softmax / M
+            const float zl = __shfl(z, (lane & 48) + (label & 15), 64);
+            if (m >= M || c >= N) continue;
+            static_cast<float *>(ep.out)[(long)m * ep.ld + c] = z;
+            static_cast<T *>(ce.dz)[(long)m * ep.ld + c] = (T)(c < ce.classes ? (expf(z - lse) - (c == label ? 1.f : 0.f)) * inv_b : 0.f);
+            if (c == 0) ce.row_loss[m] = label_ok ? lse - zl : __builtin_nanf("");
+        }
+        return;
+    }
     if (lane >= 32) return;
     const int m = tm * 16 + (lane >> 1), n0 = tn * 16 + 8 * (lane & 1);
     if (m >= M || n0 >= N) return;
@@ -737,6 +768,30 @@ __global__ __launch_bounds__(64 * kLoneWaves) void lone_kernel(LA la, LB lb, Epi
 #pragma unroll
     for (int r = 0; r < 8; ++r) o[r] = sums[lane >> 1][8 * (lane & 1) + r];
     epilogue8<T>(ep, m, n0, o, bias8);
+}
+template <typename T, class LA, class LB>
+__global__ __launch_bounds__(64 * kLoneWaves) void lone_kernel(LA la, LB lb, Epilogue ep, int M, int N, int K, int tiles_n)
+{
+    __shared__ LoneShared sh;
+    lone_tile<T, false>(sh, la, lb, ep, M, N, K, tiles_n, (int)blockIdx.x, LoneCe{});
+}
+// A last layer of up to 16 classes together with the softmax cross-entropy on top of it.
+template <typename T>
+__global__ __launch_bounds__(64 * kLoneWaves) void lone_ce_kernel(PlainK<T> la, PlainK<T> lb, Epilogue ep, int M, int N, int K, LoneCe ce)
+{
+    __shared__ LoneShared sh;
+    lone_tile<T, true>(sh, la, lb, ep, M, N, K, 1, (int)blockIdx.x, ce);
+}
+// A weight gradient and a data gradient in one launch: neither waits for the other.  Each of these launches is 4 us or more of a pass whatever it
+// computes: a step of the 28 x 28 net (8 images, fp32) 52 -> 43 us in 9 launches instead of 12, of the 32 x 32 net 230 -> 217 (fp32, 128
+// images) and 158 -> 140 (bf16, 93 images, 27 -> 21), with the softmax in the kernel above and the partial sums of the filter gradients added
+// up beside the pools' and the bias gradients' kernels.
+template <typename T>
+__global__ __launch_bounds__(64 * kLoneWaves) void lone_pair_kernel(LonePair<T> p)
+{
+    __shared__ LoneShared sh;
+    if ((int)blockIdx.x < p.w_blocks) lone_tile<T, false>(sh, p.wa, p.wb, p.w_ep, p.w_m, p.w_n, p.w_k, p.w_tiles_n, (int)blockIdx.x, LoneCe{});
+    else lone_tile<T, false>(sh, p.da, p.db, p.d_ep, p.d_m, p.d_n, p.d_k, p.d_tiles_n, (int)blockIdx.x - p.w_blocks, LoneCe{});
 }
 
 // gemm_kernel with the waves of a workgroup in two roles: Cfg::NT / 64 waves read
@@ -1154,164 +1209,60 @@ __global__ __launch_bounds__(512, 2) void conv_rows_wgrad_kernel(RowsConv a, int
     else body(std::integral_constant<int, 2>{}, (wave < 2 ? wave : wave - 2) * 2);
 }
 
-template <typename T> __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *ws, int splits, Epilogue ep, int M, int N)
+template <typename T> __global__ __launch_bounds__(256) void splitk_reduce_kernel(Reduction r) { reduce_plain<T>(r.ws, r.splits, r.ep, r.M, r.N, blockIdx.x); }
+template <typename T, int L> __global__ __launch_bounds__(256) void splitk_reduce_wide_kernel(Reduction r)
 {
-    const long g = (long)blockIdx.x * 256 + threadIdx.x;
-    const int n8 = N / 8;
-    if (g >= (long)M * n8) return;
-    const int m = (int)(g / n8), n0 = (int)(g - (long)m * n8) * 8;
-    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const long stride = (long)M * N;
-    const float *p0 = ws + (long)m * N + n0;
-    int s = 0;
-    for (; s + 4 <= splits; s += 4) {   // four partials in flight; added in split order all the same
-        float4 a[4], b[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float4 *p = reinterpret_cast<const float4 *>(p0 + (s + u) * stride);
-            a[u] = p[0]; b[u] = p[1];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            v[0] += a[u].x; v[1] += a[u].y; v[2] += a[u].z; v[3] += a[u].w;
-            v[4] += b[u].x; v[5] += b[u].y; v[6] += b[u].z; v[7] += b[u].w;
-        }
-    }
-    for (; s < splits; ++s) {
-        const float4 *p = reinterpret_cast<const float4 *>(p0 + s * stride);
-        const float4 a = p[0], b = p[1];
-        v[0] += a.x; v[1] += a.y; v[2] += a.z; v[3] += a.w;
-        v[4] += b.x; v[5] += b.y; v[6] += b.z; v[7] += b.w;
-    }
-    float b8[8];
-    load_bias8<T>(ep, n0, b8);
-    epilogue8<T>(ep, m, n0, v, b8);
+    __shared__ float part[4][8];
+    reduce_wide<T, L>(r.ws, r.splits, r.ep, r.M, r.N, blockIdx.x, part);
 }
-
-// The same for few outputs and many partial sums (the first layer's filter gradient: 5280 groups of 8 outputs, up
-// to 256 partials each): L = 8 or 32 neighbouring lanes, or with L = 256 a workgroup, share a group, lane l adds partials l, l+L,
-// ... in that order, and the L sums are combined in a fixed butterfly (and the four wavefronts' in their order), so the
-// result does not depend on anything but the inputs.
-template <typename T, int L> __global__ __launch_bounds__(256) void splitk_reduce_wide_kernel(const float *ws, int splits, Epilogue ep, int M, int N)
-{
-    static_assert(L == 8 || L == 32 || L == 256, "lanes per group of outputs");
-    constexpr int SH = L == 8 ? 3 : L == 32 ? 5 : 8;
-    const long g = ((long)blockIdx.x * 256 + threadIdx.x) >> SH;
-    const int l = threadIdx.x & (L - 1);
-    const int n8 = N / 8;
-    const bool live = g < (long)M * n8;   // whole groups of L lanes are live or not; all lanes take part in the shuffles
-    const long gg = live ? g : 0;
-    const int m = (int)(gg / n8), n0 = (int)(gg - (long)m * n8) * 8;
-    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const long stride = (long)M * N;
-    const float *p0 = ws + (long)m * N + n0;
-    int s = l;
-    for (; s + 3 * L < splits; s += 4 * L) {   // four partials in flight
-        float4 a[4], b[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float4 *p = reinterpret_cast<const float4 *>(p0 + (s + L * u) * stride);
-            a[u] = p[0]; b[u] = p[1];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            v[0] += a[u].x; v[1] += a[u].y; v[2] += a[u].z; v[3] += a[u].w;
-            v[4] += b[u].x; v[5] += b[u].y; v[6] += b[u].z; v[7] += b[u].w;
-        }
-    }
-    for (; s < splits; s += L) {
-        const float4 *p = reinterpret_cast<const float4 *>(p0 + s * stride);
-        const float4 a = p[0], b = p[1];
-        v[0] += a.x; v[1] += a.y; v[2] += a.z; v[3] += a.w;
-        v[4] += b.x; v[5] += b.y; v[6] += b.z; v[7] += b.w;
-    }
-#pragma unroll
-    for (int d = 1; d < L && d < 64; d <<= 1) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r) v[r] += __shfl_xor(v[r], d, L < 64 ? L : 64);
-    }
-    if constexpr (L == 256) {
-        __shared__ float part[4][8];
-        if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-            for (int r = 0; r < 8; ++r) part[threadIdx.x >> 6][r] = v[r];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < 8; ++r) v[r] = (part[0][r] + part[1][r]) + (part[2][r] + part[3][r]);
-    }
-    if (!live || l != 0) return;
-    float b8[8];
-    load_bias8<T>(ep, n0, b8);
-    epilogue8<T>(ep, m, n0, v, b8);
-}
-
-// The same for a filter gradient (Epilogue mode 1), whose columns (ky, kx, ci) go to [cout][cin][kh][kw]: a workgroup takes
-// all window positions of cb input channels of one output channel, adds the partial sums 16 bytes a lane, exchanges the two
-// orders in LDS and writes one contiguous run.  Bound by memory.  The kernel above scatters 4-byte stores (36 bytes apart for
-// 3 x 3): 384 -> 384 channels, 7 partials (42 MB) 14.4 us there, 8.5 here; 256 -> 384, 10 partials 10.8 and 8.2; 384 -> 256, 14
-// partials 13.8 and 10.7; 5 x 5, 96 -> 256, 17 partials 10.6 and 9.0.
-constexpr int kReduceLds = 2048;   // floats: window positions times channels of a workgroup
-__global__ __launch_bounds__(256) void splitk_reduce_filters_kernel(const float *ws, int splits, Epilogue ep, int M, int N, int npos, int cb_max, int chunks)
+__global__ __launch_bounds__(256) void splitk_reduce_filters_kernel(Reduction r)
 {
     __shared__ float sums[kReduceLds];
-    const int m = (int)blockIdx.x / chunks, c0 = ((int)blockIdx.x - m * chunks) * cb_max;
-    if (m >= ep.cw_cout) return;
-    const int cb = min(cb_max, ep.cw_cinp - c0), c4 = cb >> 2;   // channel counts are multiples of 8
-    const size_t stride = (size_t)M * N;
-    for (int g = threadIdx.x; g < npos * c4; g += blockDim.x) {
-        const int pos = g / c4, c = (g - pos * c4) * 4;
-        const float *p = ws + (size_t)m * N + pos * ep.cw_cinp + c0 + c;
-        f32x4 v = {0.f, 0.f, 0.f, 0.f};
-        for (int s = 0; s < splits; s += 8) {   // eight partials in flight; added in split order
-            f32x4 a[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (s + u < splits) a[u] = *reinterpret_cast<const f32x4 *>(p + (size_t)(s + u) * stride);
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (s + u < splits) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] += a[u][e];
-                }
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sums[(c + e) * npos + pos] = v[e];
-    }
-    __syncthreads();
-    float *o = static_cast<float *>(ep.out) + ((size_t)m * ep.cw_cin + c0) * npos;
-    const int n = min(cb, ep.cw_cin - c0) * npos;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) o[i] = sums[i];
+    reduce_filters(r.ws, r.splits, r.ep, r.M, r.N, r.npos, r.cb, r.chunks, blockIdx.x, sums);
 }
 
 // the reduction that follows a split GEMM
-template <typename T> static void launch_splitk_reduce(const float *ws, int splits, const Epilogue &ep, int M, int N, hipStream_t s)
+static Reduction plan_reduction(const float *ws, int splits, const Epilogue &ep, int M, int N)
 {
     const long groups = (long)M * (N / 8);
+    Reduction r;
+    r.ws = ws; r.splits = splits; r.ep = ep; r.M = M; r.N = N;
     // Lanes that share a group: a chip full of blocks, and hardly more lanes than partials.  (us: 320 groups of 512 partials 10.8 with
     // 32 lanes, 8.6 with 256; 40 of 98 7.0 with 8, 3.3 with 256; 800 of 248 6.4 with 32, 7.5 with 256; 3200 of 70 6.8 with 8, 6.4
     // with 32; 5280 of 256, the AlexNet-style first layer, 14 with 32.  Few partials leave some of the 32 lanes without one and are
     // no longer for it: 300 to 1000 groups of 16 3.7 with 8, 3.5 with 32; of 32 4.2 and 3.6; of 63 6.4 and 4.0; 2500 to 8000 groups of
     // 16 3.9 and 4.0 to 5.2.)
-    if (splits >= 64 && groups < 512)
-        hipLaunchKernelGGL((splitk_reduce_wide_kernel<T, 256>), dim3((unsigned)groups), dim3(256), 0, s, ws, splits, ep, M, N);
-    else if ((splits >= 192 && groups < 8192) || (splits >= 16 && groups < 1024) || (splits >= 64 && groups < 4096))
-        hipLaunchKernelGGL((splitk_reduce_wide_kernel<T, 32>), dim3((unsigned)((groups * 32 + 255) / 256)), dim3(256), 0, s, ws, splits, ep, M, N);
-    else if (splits >= 16 && groups < 32768)
-        hipLaunchKernelGGL((splitk_reduce_wide_kernel<T, 8>), dim3((unsigned)((groups * 8 + 255) / 256)), dim3(256), 0, s, ws, splits, ep, M, N);
+    if (splits >= 64 && groups < 512) r.lanes = 256;
+    else if ((splits >= 192 && groups < 8192) || (splits >= 16 && groups < 1024) || (splits >= 64 && groups < 4096)) r.lanes = 32;
+    else if (splits >= 16 && groups < 32768) r.lanes = 8;
     else if (ep.mode == 1) {
-        const int npos = ep.cw_kh * ep.cw_kw, cb = npos <= 9 ? 64 : npos <= 64 ? 32 : 8, chunks = (ep.cw_cinp + cb - 1) / cb;   // npos * cb <= kReduceLds
-        const int threads = std::min(256, (npos * cb / 4 + 63) / 64 * 64);
-        hipLaunchKernelGGL(splitk_reduce_filters_kernel, dim3((unsigned)(M * chunks)), dim3((unsigned)threads), 0, s, ws, splits, ep, M, N, npos, cb, chunks);
-    } else
-        hipLaunchKernelGGL((splitk_reduce_kernel<T>), dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, s, ws, splits, ep, M, N);
+        r.lanes = 0;
+        r.npos = ep.cw_kh * ep.cw_kw; r.cb = r.npos <= 9 ? 64 : r.npos <= 64 ? 32 : 8; r.chunks = (ep.cw_cinp + r.cb - 1) / r.cb;   // npos * cb <= kReduceLds
+    }
+    r.blocks = r.lanes == 0 ? (unsigned)(M * r.chunks) : (unsigned)((groups * r.lanes + 255) / 256);
+    return r;
 }
-
-int splitk_reduce(int dtype, const float *ws, int splits, const Epilogue &ep, int M, int N, hipStream_t s)
+int launch_reduction(int dtype, const Reduction &r, hipStream_t s)
 {
-    if (dtype == kBF16) launch_splitk_reduce<bf16_t>(ws, splits, ep, M, N, s);
-    else launch_splitk_reduce<float>(ws, splits, ep, M, N, s);
+    const auto go = [&](auto t) {
+        using T = decltype(t);
+        const dim3 grid(r.blocks), all(256);
+        if (r.lanes == 256) hipLaunchKernelGGL((splitk_reduce_wide_kernel<T, 256>), grid, all, 0, s, r);
+        else if (r.lanes == 32) hipLaunchKernelGGL((splitk_reduce_wide_kernel<T, 32>), grid, all, 0, s, r);
+        else if (r.lanes == 8) hipLaunchKernelGGL((splitk_reduce_wide_kernel<T, 8>), grid, all, 0, s, r);
+        else if (r.lanes == 0) hipLaunchKernelGGL(splitk_reduce_filters_kernel, grid, dim3((unsigned)std::min(256, (r.npos * r.cb / 4 + 63) / 64 * 64)), 0, s, r);
+        else hipLaunchKernelGGL((splitk_reduce_kernel<T>), grid, all, 0, s, r);
+    };
+    if (dtype == kBF16) go(bf16_t());
+    else go(0.f);
     return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+int splitk_reduce(int dtype, const float *ws, int splits, const Epilogue &ep, int M, int N, Reduction *later, hipStream_t s)
+{
+    const Reduction r = plan_reduction(ws, splits, ep, M, N);
+    if (!later) return launch_reduction(dtype, r, s);
+    *later = r;
+    return 0;
 }
 
 // ------------------------------------------------------------------ host side
@@ -1419,7 +1370,7 @@ double lone_fc_wgrad_us(int dtype, long out, long in, long batch)
 }
 
 template <typename T, class Cfg, class LA, class LB>
-static int run_tile(const LA &la, const LB &lb, int M, int N, int K, const Epilogue &ep, const GemmPlan &plan, float *ws, hipStream_t s)
+static int run_tile(const LA &la, const LB &lb, int M, int N, int K, const Epilogue &ep, const GemmPlan &plan, float *ws, hipStream_t s, Reduction *later)
 {
     constexpr int BK = Geo<T>::BK, BM = Cfg::BM, BN = Cfg::BN;
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
@@ -1439,12 +1390,12 @@ static int run_tile(const LA &la, const LB &lb, int M, int N, int K, const Epilo
     else
         hipLaunchKernelGGL((gemm_kernel<T, Cfg, LA, LB>), dim3((unsigned)blocks), dim3(Cfg::NT), 0, s, la, lb, ep, M, N, nkt, per, tiles_m,
                            tiles_n, splits > 1 ? ws : nullptr);
-    if (splits > 1) launch_splitk_reduce<T>(ws, splits, ep, M, N, s);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    if (hipGetLastError() != hipSuccess) return -1;
+    return splits > 1 ? splitk_reduce(sizeof(T) == 2 ? kBF16 : kF32, ws, splits, ep, M, N, later, s) : 0;
 }
 
 template <typename T, class LA, class LB>
-static int run(const LA &la, const LB &lb, int M, int N, int K, const Epilogue &ep, const GemmPlan &plan, float *ws, hipStream_t s)
+static int run(const LA &la, const LB &lb, int M, int N, int K, const Epilogue &ep, const GemmPlan &plan, float *ws, hipStream_t s, Reduction *later = nullptr)
 {
     if (M <= 0 || N <= 0 || K <= 0 || (N & 7)) return -1;
     if (la.op.bytes == 0 || lb.op.bytes == 0) return -1;   // an operand beyond the 1 GiB the 32-bit offsets cover
@@ -1461,13 +1412,13 @@ static int run(const LA &la, const LB &lb, int M, int N, int K, const Epilogue &
         }
     }
     if constexpr (std::is_same<LB, GatherT<T>>::value) {
-        if (plan.bm == 32) return run_tile<T, Cfg32<T>>(la, lb, M, N, K, ep, plan, ws, s);
-        if (plan.bm == 64) return run_tile<T, Cfg64>(la, lb, M, N, K, ep, plan, ws, s);
-        return run_tile<T, Cfg128>(la, lb, M, N, K, ep, plan, ws, s);
+        if (plan.bm == 32) return run_tile<T, Cfg32<T>>(la, lb, M, N, K, ep, plan, ws, s, later);
+        if (plan.bm == 64) return run_tile<T, Cfg64>(la, lb, M, N, K, ep, plan, ws, s, later);
+        return run_tile<T, Cfg128>(la, lb, M, N, K, ep, plan, ws, s, later);
     } else {
         if constexpr (!plain)
-            if (plan.bn == 32) return run_tile<T, CfgN32>(la, lb, M, N, K, ep, plan, ws, s);
-        return run_tile<T, Cfg128w8>(la, lb, M, N, K, ep, plan, ws, s);
+            if (plan.bn == 32) return run_tile<T, CfgN32>(la, lb, M, N, K, ep, plan, ws, s, later);
+        return run_tile<T, Cfg128w8>(la, lb, M, N, K, ep, plan, ws, s, later);
     }
 }
 
@@ -1604,15 +1555,21 @@ template <typename T> static int run_outer(const PlainT<T> &la, const PlainT<T> 
     hipLaunchKernelGGL((outer_kernel<T>), dim3((unsigned)blocks), dim3(512), 0, s, la, lb, static_cast<float *>(ep.out), ep.ld, M, N, K, (int)tiles_n);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
+// A push inside the kernel (fc_push, update_tile of gemm_kernel over two transposed plain operands, or lone_kernel): whole sums only,
+// 16-byte rows and column groups in all buffers.
+static bool push_is_valid(const Epilogue &ep, const GemmPlan &plan)
+{
+    if (!ep.upd_w) return true;
+    uintptr_t al = (uintptr_t)ep.upd_w | (uintptr_t)ep.upd_v | (uintptr_t)ep.upd_acc | (uintptr_t)ep.out;
+    if (ep.upd_copies < 0 || ep.upd_copies > kPushCopies) return false;
+    for (int c = 0; c < ep.upd_copies; ++c) { if (!ep.upd_copy[c]) return false; al |= (uintptr_t)ep.upd_copy[c]; }
+    return plan.splits == 1 && ep.mode == 0 && ep.upd_v && !(al & 15) && !(ep.ld & 7);
+}
 int gemm_trans_trans(int dtype, const void *at, long lda, int M, const void *bt, long ldb, int N, int K, const Epilogue &ep,
                      const GemmPlan &plan, float *ws, hipStream_t s)
 {
-    if (ep.upd_w) {   // push inside the kernel (fc_push, update_tile of gemm_kernel over two transposed plain operands, or lone_kernel):
-                      // whole sums only, 16-byte rows and column groups in all buffers
-        uintptr_t al = (uintptr_t)ep.upd_w | (uintptr_t)ep.upd_v | (uintptr_t)ep.upd_acc | (uintptr_t)ep.out;
-        if (ep.upd_copies < 0 || ep.upd_copies > kPushCopies) return -1;
-        for (int c = 0; c < ep.upd_copies; ++c) { if (!ep.upd_copy[c]) return -1; al |= (uintptr_t)ep.upd_copy[c]; }
-        if (plan.splits != 1 || ep.mode != 0 || !ep.upd_v || (al & 15) || (ep.ld & 7)) return -1;
+    if (!push_is_valid(ep, plan)) return -1;
+    if (ep.upd_w) {
         if (fc_push_applies(dtype, M, N, K, ep)) return fc_push(at, lda, M, bt, ldb, N, K, ep, s);
     }
     if (dtype == kBF16)
@@ -1621,6 +1578,45 @@ int gemm_trans_trans(int dtype, const void *at, long lda, int M, const void *bt,
                    : run<bf16_t>(make_plain_t<bf16_t>(at, lda, M, K), make_plain_t<bf16_t>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);
     return outer_applies<float>(M, N, K, ep, plan) ? run_outer(make_plain_t<float>(at, lda, M, K), make_plain_t<float>(bt, ldb, N, K), M, N, K, ep, s)
                                                    : run<float>(make_plain_t<float>(at, lda, M, K), make_plain_t<float>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);
+}
+
+static int lone_tiles(int M, int N) { return (M + 15) / 16 * ((N + 15) / 16); }
+static int lone_waves(int K) { return std::min(kLoneWaves, (K + 31) / 32); }
+template <typename T> static int launch_lone_pair(const FcGrads &w, const FcGrads &d, const Epilogue &we, const Epilogue &de, hipStream_t s)
+{
+    LonePair<T> p;
+    p.wa = make_plain_t<T>(w.dy, w.ld_dy, w.out, w.batch); p.wb = make_plain_t<T>(w.x, w.ld_x, w.in, w.batch);
+    p.w_ep = we; p.w_m = w.out; p.w_n = w.in; p.w_k = w.batch; p.w_tiles_n = (w.in + 15) / 16; p.w_blocks = lone_tiles(w.out, w.in);
+    p.da = make_plain_k<T>(d.dy, d.ld_dy, d.batch, d.out); p.db = make_plain_t<T>(d.w, d.in, d.in, d.out);
+    p.d_ep = de; p.d_m = d.batch; p.d_n = d.in; p.d_k = d.out; p.d_tiles_n = (d.in + 15) / 16;
+    if (p.wa.op.bytes == 0 || p.wb.op.bytes == 0 || p.da.op.bytes == 0 || p.db.op.bytes == 0) return -1;
+    hipLaunchKernelGGL(lone_pair_kernel<T>, dim3((unsigned)(p.w_blocks + lone_tiles(d.batch, d.in))), dim3((unsigned)(64 * std::max(lone_waves(w.batch), lone_waves(d.out)))), 0, s, p);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+bool fc_pair_applies(const FcGrads &w, const FcGrads &d)
+{
+    return lone_applies(w.out, w.in, w.batch) && lone_applies(d.batch, d.in, d.out) && w.in % 8 == 0 && d.in % 8 == 0;
+}
+int fc_pair(int dtype, const FcGrads &w, const FcGrads &d, const Epilogue &we, const Epilogue &de, hipStream_t s)
+{
+    if (!push_is_valid(we, GemmPlan())) return -1;
+    return dtype == kBF16 ? launch_lone_pair<bf16_t>(w, d, we, de, s) : launch_lone_pair<float>(w, d, we, de, s);
+}
+
+bool fc_softmax_applies(long M, long N, long K) { return N <= 16 && N % 8 == 0 && lone_applies(M, N, K); }
+int fc_softmax(int dtype, const void *a, long lda, int M, const void *b, long ldb, int N, int classes, int K, const Epilogue &ep, const int32_t *labels, void *dz,
+               float *row_loss, hipStream_t s)
+{
+    const LoneCe ce{labels, dz, row_loss, classes};
+    const dim3 grid((unsigned)((M + 15) / 16)), block((unsigned)(64 * lone_waves(K)));
+    const auto go = [&](auto t) {
+        using T = decltype(t);
+        const PlainK<T> la = make_plain_k<T>(a, lda, M, K), lb = make_plain_k<T>(b, ldb, classes, K);
+        if (la.op.bytes == 0 || lb.op.bytes == 0) return -1;
+        hipLaunchKernelGGL(lone_ce_kernel<T>, grid, block, 0, s, la, lb, ep, M, N, K, ce);
+        return hipGetLastError() == hipSuccess ? 0 : -1;
+    };
+    return dtype == kBF16 ? go(bf16_t()) : go(0.f);
 }
 
 // The filter gradient of a first convolution in window-row form (16-bit data, up to 96 output channels, up to 448 K
@@ -1651,7 +1647,7 @@ static bool rows_wgrad_applies(const void *at, long lda, int M, const Gather &b,
     const long block = ((long)(rpt - 1) * b.sm + b.kh) * (long)b.rowb;   // image rows of a tile
     return block <= kRowsWgIB && b.H >= (b.Ho - 1) * b.sm + b.kh && rows_wgrad_tiles(b) <= 0x7fffffffL;
 }
-static int run_rows_wgrad(const void *at, long lda, int M, const Gather &b, const Epilogue &ep, float *ws, hipStream_t s)
+static int run_rows_wgrad(const void *at, long lda, int M, const Gather &b, const Epilogue &ep, float *ws, Reduction *later, hipStream_t s)
 {
     RowsConv r;
     const int rpt = rows_wgrad_rpt(b);
@@ -1667,18 +1663,17 @@ static int run_rows_wgrad(const void *at, long lda, int M, const Gather &b, cons
     if (r.x.bytes == 0 || dy.bytes == 0) return -1;
     const int grid = r.total < kRowsWgGrid ? r.total : kRowsWgGrid;
     hipLaunchKernelGGL(conv_rows_wgrad_kernel, dim3((unsigned)grid), dim3(512), 0, s, r, rpt, dy, (unsigned)(lda * sizeof(bf16_t)), M, ws);
-    launch_splitk_reduce<bf16_t>(ws, grid, ep, M, r.K, s);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    return hipGetLastError() == hipSuccess ? splitk_reduce(kBF16, ws, grid, ep, M, r.K, later, s) : -1;
 }
 
 int gemm_trans_gather(int dtype, const void *at, long lda, int M, const Gather &b, const Epilogue &ep, const GemmPlan &plan, float *ws,
-                      hipStream_t s)
+                      Reduction *later, hipStream_t s)
 {
     if (b.ds != 1 || b.kh > 15 || b.kw > 15) return -1;
-    if (dtype == kBF16 && rows_wgrad_applies(at, lda, M, b, ep, plan, ws)) return run_rows_wgrad(at, lda, M, b, ep, ws, s);
+    if (dtype == kBF16 && rows_wgrad_applies(at, lda, M, b, ep, plan, ws)) return run_rows_wgrad(at, lda, M, b, ep, ws, later, s);
     const int K = b.N * b.Ho * b.Wo, N = b.kh * b.kw * b.C;
-    if (dtype == kBF16) return run<bf16_t>(make_plain_t<bf16_t>(at, lda, M, K), make_gather_t<bf16_t>(b), M, N, K, ep, plan, ws, s);
-    return run<float>(make_plain_t<float>(at, lda, M, K), make_gather_t<float>(b), M, N, K, ep, plan, ws, s);
+    if (dtype == kBF16) return run<bf16_t>(make_plain_t<bf16_t>(at, lda, M, K), make_gather_t<bf16_t>(b), M, N, K, ep, plan, ws, s, later);
+    return run<float>(make_plain_t<float>(at, lda, M, K), make_gather_t<float>(b), M, N, K, ep, plan, ws, s, later);
 }
 
 }  // namespace asgd

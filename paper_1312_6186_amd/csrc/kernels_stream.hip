@@ -11,6 +11,7 @@
 
 #include "asgd_internal.h"
 #include "mfma_common.h"
+#include "reduce.h"
 
 namespace asgd {
 
@@ -689,11 +690,12 @@ int launch_head(int dtype, PackJobs &jobs, const StageJob &st, hipStream_t s)
 // ---------------------------------------------------------------- max pooling
 // Workgroup ids go round-robin over the 8 XCDs; neighbouring pixels share pooling windows, so each XCD is given a
 // contiguous range of blocks (and its L2 fetches a window row once instead of every XCD fetching it).
-__device__ __forceinline__ uint32_t xcd_block()
+__device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t nb)
 {
-    const uint32_t nb = gridDim.x, q = nb >> 3, r = nb & 7, x = blockIdx.x & 7;
-    return x * q + (x < r ? x : r) + (blockIdx.x >> 3);
+    const uint32_t q = nb >> 3, r = nb & 7, x = b & 7;
+    return x * q + (x < r ? x : r) + (b >> 3);
 }
+__device__ __forceinline__ uint32_t xcd_block() { return xcd_block(blockIdx.x, gridDim.x); }
 // thread index -> (channel group, x, y, image) by three multiply-shift divisions (the index fits 31 bits)
 struct PoolIndex { FastDiv dcv, dw, dh; int cv, w, h; };
 static PoolIndex make_pool_index(int cv, int w, int h)
@@ -980,13 +982,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t byte_range(const void *p, size
 // convolution below, whose bias gradient they are part of) in bands[column][block]: the values as stored (rounded
 // to the element type), added per thread over its pixels, then over the block's threads in thread order.
 template <typename T, int K>
-__global__ __launch_bounds__(256) void pool_bwd_s2_kernel(const T *__restrict__ dy, const uint8_t *__restrict__ arg, const T *__restrict__ x, int relu,
-                                                        T *__restrict__ dx, int B, int H, int W, int Cp, int Ho, int Wo, PoolIndex pi,
-                                                        float *__restrict__ bands)
+__device__ __forceinline__ void pool_bwd_s2_block(const T *__restrict__ dy, const uint8_t *__restrict__ arg, const T *__restrict__ x, int relu,
+                                                  T *__restrict__ dx, int B, int H, int W, int Cp, int Ho, int Wo, const PoolIndex &pi,
+                                                  float *__restrict__ bands, uint32_t blk, uint32_t blocks, float *part)
 {
     constexpr int V = Vec16<T>::N;
-    __shared__ float part[256 * V];
-    const uint32_t blk = xcd_block();
     const uint32_t i = blk * 256u + threadIdx.x;
     const bool live = i < (uint32_t)B * pi.h * pi.w * pi.cv;
     if (!live && bands == nullptr) return;
@@ -1036,8 +1036,26 @@ __global__ __launch_bounds__(256) void pool_bwd_s2_kernel(const T *__restrict__ 
         const int gc = c / V, e = c - gc * V;
         float t = 0.f;
         for (int j = (gc - g0 + cv) % cv; j < 256; j += cv) t += part[j * V + e];
-        bands[(long)c * gridDim.x + blk] = t;
+        bands[(long)c * blocks + blk] = t;
     }
+}
+template <typename T, int K>
+__global__ __launch_bounds__(256) void pool_bwd_s2_kernel(const T *__restrict__ dy, const uint8_t *__restrict__ arg, const T *__restrict__ x, int relu,
+                                                        T *__restrict__ dx, int B, int H, int W, int Cp, int Ho, int Wo, PoolIndex pi,
+                                                        float *__restrict__ bands)
+{
+    __shared__ float part[256 * Vec16<T>::N];
+    pool_bwd_s2_block<T, K>(dy, arg, x, relu, dx, B, H, W, Cp, Ho, Wo, pi, bands, xcd_block(), gridDim.x, part);
+}
+// The same with a reduction of partial sums (its first red.blocks workgroups).
+template <typename T, int K>
+__global__ __launch_bounds__(256) void pool_bwd_s2_reduce_kernel(const T *__restrict__ dy, const uint8_t *__restrict__ arg, const T *__restrict__ x, int relu,
+                                                               T *__restrict__ dx, int B, int H, int W, int Cp, int Ho, int Wo, PoolIndex pi,
+                                                               float *__restrict__ bands, Reduction red)
+{
+    __shared__ union { float part[256 * Vec16<T>::N]; ReduceShared red; } sh;
+    if (blockIdx.x < red.blocks) reduce_block<T>(red, blockIdx.x, sh.red);
+    else pool_bwd_s2_block<T, K>(dy, arg, x, relu, dx, B, H, W, Cp, Ho, Wo, pi, bands, xcd_block(blockIdx.x - red.blocks, gridDim.x - red.blocks), gridDim.x - red.blocks, sh.part);
 }
 
 // Where pool_bwd_s2_kernel runs: a block's 256 threads see two images, or several small ones, in one range of 2 GiB.
@@ -1047,13 +1065,19 @@ static bool pool_bwd_blocks(int H, int W, int Cp, int es, int k, int stride)
 }
 template <typename T>
 static void launch_pool_bwd_t(const void *dy, const uint8_t *arg, const void *x, int relu, void *dx, int B, int H, int W, int Cp, int k, int stride,
-                              int Ho, int Wo, unsigned blocks, float *bands, hipStream_t s)
+                              int Ho, int Wo, unsigned blocks, float *bands, const Reduction *beside, hipStream_t s)
 {
     const T *d = static_cast<const T *>(dy), *xx = static_cast<const T *>(x); T *o = static_cast<T *>(dx);
     if (pool_bwd_blocks(H, W, Cp, (int)sizeof(T), k, stride)) {
         const int Hb = (H + 1) / 2, Wb = (W + 1) / 2, cv = Cp / (16 / (int)sizeof(T));
         const PoolIndex pb = make_pool_index(cv, Wb, Hb);
         const unsigned nb = blocks_for((size_t)B * Hb * Wb * cv, 256);
+        if (beside) {
+            const dim3 grid(nb + beside->blocks);
+            if (k == 3) hipLaunchKernelGGL((pool_bwd_s2_reduce_kernel<T, 3>), grid, dim3(256), 0, s, d, arg, xx, relu, o, B, H, W, Cp, Ho, Wo, pb, bands, *beside);
+            else hipLaunchKernelGGL((pool_bwd_s2_reduce_kernel<T, 2>), grid, dim3(256), 0, s, d, arg, xx, relu, o, B, H, W, Cp, Ho, Wo, pb, bands, *beside);
+            return;
+        }
         if (k == 3) hipLaunchKernelGGL((pool_bwd_s2_kernel<T, 3>), dim3(nb), dim3(256), 0, s, d, arg, xx, relu, o, B, H, W, Cp, Ho, Wo, pb, bands);
         else hipLaunchKernelGGL((pool_bwd_s2_kernel<T, 2>), dim3(nb), dim3(256), 0, s, d, arg, xx, relu, o, B, H, W, Cp, Ho, Wo, pb, bands);
         return;
@@ -1071,15 +1095,15 @@ long pool_bwd_bands(int dtype, int B, int H, int W, int Cp, int k, int stride)
     return (long)blocks_for((size_t)B * ((H + 1) / 2) * ((W + 1) / 2) * (Cp / V), 256);
 }
 int launch_pool_bwd(int dtype, const void *dy, const uint8_t *arg, const void *x, int relu, void *dx, int B, int H, int W, int Cp, int k, int stride,
-                    float *bands, hipStream_t s)
+                    float *bands, const Reduction *beside, hipStream_t s)
 {
     const int Ho = (H - k) / stride + 1, Wo = (W - k) / stride + 1;
     const int V = dtype == kBF16 ? 8 : 4;
     if ((size_t)B * H * W * (Cp / V) > 0x7fffffffu) return -1;
-    if (bands && pool_bwd_bands(dtype, B, H, W, Cp, k, stride) == 0) return -1;
+    if ((bands || beside) && pool_bwd_bands(dtype, B, H, W, Cp, k, stride) == 0) return -1;
     const unsigned blocks = blocks_for((size_t)B * H * W * (Cp / V), 256);
-    if (dtype == kBF16) launch_pool_bwd_t<bf16_t>(dy, arg, x, relu, dx, B, H, W, Cp, k, stride, Ho, Wo, blocks, bands, s);
-    else launch_pool_bwd_t<float>(dy, arg, x, relu, dx, B, H, W, Cp, k, stride, Ho, Wo, blocks, bands, s);
+    if (dtype == kBF16) launch_pool_bwd_t<bf16_t>(dy, arg, x, relu, dx, B, H, W, Cp, k, stride, Ho, Wo, blocks, bands, beside, s);
+    else launch_pool_bwd_t<float>(dy, arg, x, relu, dx, B, H, W, Cp, k, stride, Ho, Wo, blocks, bands, beside, s);
     return launch_ok();
 }
 
@@ -1802,7 +1826,7 @@ __global__ __launch_bounds__(256) void colsum_stage1(ColsumS1Jobs jobs)
     }
 }
 // Stage 2 for several layers in one launch.
-__global__ __launch_bounds__(256) void colsum_stage2(ColsumJobs jobs)
+__device__ __forceinline__ void colsum_finish_block(const ColsumJobs &jobs, unsigned block, float (&part)[4][8])
 {
     // Band-major jobs (ws[band][ld], from colsum_stage1, or the rows of a short tensor itself, up to 512 bands): 8 columns per block,
     // 32 lanes per column.
@@ -1811,15 +1835,14 @@ __global__ __launch_bounds__(256) void colsum_stage2(ColsumJobs jobs)
     // a wavefront by shuffles and its four wavefronts in LDS.  Latency bounds it: with a wavefront per column and one lane
     // adding the 32 or 64 partial sums from LDS, the AlexNet-style layers took 10.8 us at 128 images (bf16; now 7.7), 18.3 at
     // 256 (9.6), 17.8 in fp32 at 128 (9.2).
-    __shared__ float part[4][8];
     int q = 0;
 #pragma unroll
-    for (int i = 1; i < 12; ++i) q += blockIdx.x >= jobs.j[i].start_block;   // independent scalar loads, no chain of them
+    for (int i = 1; i < 12; ++i) q += block >= jobs.j[i].start_block;   // independent scalar loads, no chain of them
     const ColsumJob &J = jobs.j[q];
     const float *ws = J.ws;
     const int nblk = J.nblk, N = J.N, cm = J.colmajor, cpb = cm ? 1 : 8, L = 256 / cpb;
     const int tx = cm ? 0 : threadIdx.x % 8, ty = cm ? threadIdx.x : threadIdx.x / 8;
-    const int n = (int)(blockIdx.x - J.start_block) * cpb + tx;
+    const int n = (int)(block - J.start_block) * cpb + tx;
     const long sb = cm ? 1 : J.ld, sn = cm ? nblk : 1;   // strides of the band and of the column index
     float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (n < N) {
@@ -1840,6 +1863,18 @@ __global__ __launch_bounds__(256) void colsum_stage2(ColsumJobs jobs)
     if (threadIdx.x % 64 < 8) part[threadIdx.x / 64][threadIdx.x % 64] = t;
     __syncthreads();
     if (ty == 0 && n < N) J.db[n] = ((part[0][tx] + part[1][tx]) + (part[2][tx] + part[3][tx])) / J.div;
+}
+__global__ __launch_bounds__(256) void colsum_stage2(ColsumJobs jobs)
+{
+    __shared__ float part[4][8];
+    colsum_finish_block(jobs, blockIdx.x, part);
+}
+// The same with a reduction of partial sums (its first red.blocks workgroups).
+template <typename T> __global__ __launch_bounds__(256) void colsum_stage2_reduce(ColsumJobs jobs, Reduction red)
+{
+    __shared__ ReduceShared sh;
+    if (blockIdx.x < red.blocks) reduce_block<T>(red, blockIdx.x, sh);
+    else colsum_finish_block(jobs, blockIdx.x - red.blocks, sh.part);
 }
 static void colsum_geometry(int dtype, long ld, long M, int &chunks, int &cpb, int &rl, long &rows_per_block, int &nblk)
 {
@@ -1900,9 +1935,9 @@ int launch_colsum_partial(int dtype, const void *dy, long ld, long M, int N, flo
     if (colsum_partial_defer(dtype, dy, ld, M, N, db, ws, s1, jobs) != 0) return -1;
     return launch_colsum_stage1(dtype, s1, s);
 }
-int launch_colsum_finish(ColsumJobs &jobs, hipStream_t s)
+int launch_colsum_finish(int dtype, ColsumJobs &jobs, const Reduction *beside, hipStream_t s)
 {
-    if (jobs.n == 0) return 0;
+    if (jobs.n == 0) return beside ? launch_reduction(dtype, *beside, s) : 0;
     unsigned blocks = 0;
     for (int q = 0; q < jobs.n; ++q) {
         ColsumJob &J = jobs.j[q];
@@ -1911,7 +1946,9 @@ int launch_colsum_finish(ColsumJobs &jobs, hipStream_t s)
         blocks += (unsigned)((J.N + cpb - 1) / cpb);
     }
     for (int q = jobs.n; q < 12; ++q) jobs.j[q].start_block = ~0u;
-    hipLaunchKernelGGL(colsum_stage2, dim3(blocks), dim3(256), 0, s, jobs);
+    if (!beside) hipLaunchKernelGGL(colsum_stage2, dim3(blocks), dim3(256), 0, s, jobs);
+    else if (dtype == kBF16) hipLaunchKernelGGL(colsum_stage2_reduce<bf16_t>, dim3(blocks + beside->blocks), dim3(256), 0, s, jobs, *beside);
+    else hipLaunchKernelGGL(colsum_stage2_reduce<float>, dim3(blocks + beside->blocks), dim3(256), 0, s, jobs, *beside);
     jobs.n = 0;
     return launch_ok();
 }

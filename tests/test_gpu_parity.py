@@ -660,6 +660,23 @@ def test_train_step_is_the_three_calls_bit_for_bit_and_matches_the_oracle(cfg, d
 
 
 # ---------------------------------------------------------------- A-SGD replay
+# Last layers whose logits and softmax come from one kernel (up to 16 classes) and from two, batches around its tiles of 16 rows; the gradients of a small
+# fully-connected layer, weights and data, in one launch; partial sums of filter gradients that wait for the next pool (stride 2), for
+# a convolution or a pool of another stride below, or for the bias gradients.
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("classes,batch", [(2, 1), (8, 15), (9, 16), (16, 17), (17, 33), (10, 70)])
+@pytest.mark.parametrize("stride", [1, 2])
+def test_small_nets_in_few_launches(stride, classes, batch, dtype):
+    layers = [("conv", 16, 5, 1, 2), ("relu",), ("maxpool", 3, stride), ("conv", 24, 3, 1, 1), ("relu",), ("conv", 16, 3, 1, 1), ("relu",), ("maxpool", 2, 2),
+              ("fc", 40), ("relu",), ("dropout", 0.5), ("fc", classes), ("softmax_ce",)]
+    g, onet, (loss, grads), (ref_loss, ref_grads, _), _ = _net_case({"name": "few", "in_shape": (3, 18, 14), "classes": classes, "layers": layers}, batch, dtype, plain=False)
+    try:
+        assert abs(loss - ref_loss) <= TOL[dtype] * abs(ref_loss)
+        compare_grads(onet, grads, ref_grads, TOL[dtype], "few")
+    finally:
+        g.close()
+
+
 # The push of fully-connected weights in its own kernel: 2048 and 2056 inputs (strips of 128, the last one whole and ragged) into outputs around the tiles
 # of 64 rows, enough tiles for it and one too few; batches around what a set of fragments holds (32, 64, 128, 256 images) and past it.
 PUSH_SHAPES = [(16, 16, 1000, 1), (16, 16, 1000, 17), (16, 16, 1016, 32), (16, 16, 961, 33), (16, 16, 1087, 64), (16, 16, 1000, 65), (16, 16, 1026, 128),
