@@ -89,7 +89,14 @@ __global__ __launch_bounds__(64 * WM * WN, (MB * NB > 8 ? 1 : 2)) void conv_dire
         const int nb = gridDim.x, q = nb >> 3, r = nb & 7, x = blockIdx.x & 7;
         bid = x * q + (x < r ? x : r) + (blockIdx.x >> 3);
     }
-    const int tiles_row = p.tiles_n * p.groups, tm = bid / tiles_row, col = bid - tm * tiles_row, grp = col / p.tiles_n, tn = col - grp * p.tiles_n;
+    // a tile's place: rows, group, columns.  Found anew for the output: the scalar registers that kept it would be spilled into
+    // vector registers, and tiles of 96 x 96 would lose the second workgroup of a CU (one step at 142 images 1495 -> 1521 us).
+    int tm, grp, tn;
+    auto place = [&](int b) ASGD_INLINE {
+        const int row = p.tiles_n * p.groups, c = b - (tm = b / row) * row;
+        grp = c / p.tiles_n; tn = c - grp * p.tiles_n;
+    };
+    place(bid);
     const int wm = (wave % WM) * (32 * MB), wn = (wave / WM) * (32 * NB);
     const int total = p.nchunks * p.npos;
     const unsigned zero_base = sm + p.patch_off2 + p.patch_bytes;   // a multiple of 256
@@ -263,6 +270,8 @@ __global__ __launch_bounds__(64 * WM * WN, (MB * NB > 8 ? 1 : 2)) void conv_dire
 
     // ---- output: each wave moves its tile through its own part of LDS, 32 rows at a time, so that a lane ends up with 8
     // consecutive columns of a row
+    asm volatile("" : "+s"(bid));
+    place(bid);
     asm volatile("" ::"v"(touch[0]), "v"(touch[1]), "v"(touch[2]), "v"(touch[3]));
     char *smp = reinterpret_cast<char *>(smem4);
     float *sBias = reinterpret_cast<float *>(smp + WM * WN * NB * 4096);
