@@ -1,7 +1,7 @@
 // The push of a fully-connected layer's weights in the kernel that computes their gradient, 16-bit data: for every weight g is a sum over the
 // minibatch, t = g + wd * w, v = mu * v - lr * t, w = w + v, and the new weights go to the replicas' copies.
 //
-// What bounds it is memory: 18 bytes a weight (26 with the sum of a replica's gradients) at the rate of a copy, 5 TB/s.  One workgroup of four
+// What bounds it is memory: 18 bytes a weight at the rate of a copy, 5 TB/s.  One workgroup of four
 // waves a CU is enough for that if loads never pause, and leaves most of the LDS and the registers of a CU to the kernels of the
 // other stream: with tiles of 128 x 128 and two workgroups of 80 KB a CU (what this replaced, as fast when alone) a data gradient found no room
 // until the whole push was over.  So a workgroup walks over tiles of 64 x 128, down a strip of columns whose inputs it keeps as
@@ -31,9 +31,9 @@ struct FcPush {
     unsigned lda, ldb;            // bytes from one image to the next
     int M, N, K, tiles_m, total;  // total: tiles
     unsigned ld;                  // elements from one row of the parameters to the next
-    float *w, *v, *acc, *out;
+    float *w, *v, *out;
     bf16_t *copy[kPushCopies];
-    int copies, acc_first;
+    int copies;
     float lr, mu, wd;
 };
 
@@ -55,7 +55,7 @@ __device__ __forceinline__ void push_barrier() { asm volatile("s_waitcnt lgkmcnt
 
 }  // namespace
 
-template <int KF, bool ACC, int R>   // K steps of 16 images; groups of 8 rows per set of parameters
+template <int KF, int R>   // K steps of 16 images; groups of 8 rows per set of parameters
 __global__ __launch_bounds__(256, 2) void fc_push_kernel(FcPush p)
 {
     constexpr int KL = KF * 16, LA = TransTile<bf16_t, kPushBM>::LINE, LB = TransTile<bf16_t, kPushBN>::LINE;
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256, 2) void fc_push_kernel(FcPush p)
     FragOff<bf16_t, true, kPushBM> foA;
     foA.init(0, lane);
     // ---- parameters: block mb of a tile is 32 rows of this wave's columns; a lane owns 4 columns of the rows r * 8 + lane / 8
-    f32x4 w[2][R], mo[2][R], ac[2][R];
+    f32x4 w[2][R], mo[2][R];
     const int piece = lane & 7, lrow8 = lane >> 3, col = wave * 32 + piece * 4;
     auto range = [&](int tm_, int tn_, bool ok) ASGD_INLINE -> unsigned {   // elements of a tile from its first one on
         return ok ? (unsigned)min(kPushBM, p.M - tm_ * kPushBM) * p.ld - (unsigned)tn_ * kPushBN : 0u;
@@ -127,10 +127,6 @@ __global__ __launch_bounds__(256, 2) void fc_push_kernel(FcPush p)
         const __amdgpu_buffer_rsrc_t rw = rsrc4(p.w, first, n), rv = rsrc4(p.v, first, n);
         static_for<0, R>([&](auto r) ASGD_INLINE { w[set][r] = buf_ldf4(rw, voff(tn_, sub, r)); });
         static_for<0, R>([&](auto r) ASGD_INLINE { mo[set][r] = buf_ldf4(rv, voff(tn_, sub, r)); });
-        if constexpr (ACC) {
-            const __amdgpu_buffer_rsrc_t rc = rsrc4(p.acc, first, p.acc_first ? 0u : n);
-            static_for<0, R>([&](auto r) ASGD_INLINE { ac[set][r] = buf_ldf4(rc, voff(tn_, sub, r)); });
-        }
     };
 
     load_inputs();
@@ -178,10 +174,6 @@ __global__ __launch_bounds__(256, 2) void fc_push_kernel(FcPush p)
                 buf_stf4(rv, voff(tn, sub, r), vo);
                 w[set][r] = wo;
             });
-            if constexpr (ACC) {
-                const __amdgpu_buffer_rsrc_t rc = rsrc4(p.acc, first, n);
-                static_for<0, R>([&](auto r) ASGD_INLINE { buf_stf4(rc, voff(tn, sub, r), p.acc_first ? g[r] : ac[set][r] + g[r]); });
-            }
             if (p.out) {
                 const __amdgpu_buffer_rsrc_t ro = rsrc4(p.out, first, n);
                 static_for<0, R>([&](auto r) ASGD_INLINE { buf_stf4(ro, voff(tn, sub, r), g[r]); });
@@ -207,11 +199,12 @@ __global__ __launch_bounds__(256, 2) void fc_push_kernel(FcPush p)
     }
 }
 
-// Where it runs: 16-bit data, a K that fits the registers (256; 128 with a third parameter array), a tile for every CU (with fewer the small products'
-// kernel and the general one put more workgroups on the chip), offsets within a tile in 31 bits.
+// Where it runs: 16-bit data, a K that fits the registers, a tile for every CU (with fewer the small products' kernel and the general one put more
+// workgroups on the chip), offsets within a tile in 31 bits.  Not with the sum of a replica's gradients, a third array read and written: nothing
+// runs beside the local steps of a replica, and a CU's four waves are not enough for it (4096 x 9216, 32 images 177 us in gemm_kernel, 190 here).
 bool fc_push_applies(int dtype, int M, int N, int K, const Epilogue &ep)
 {
-    return dtype == kBF16 && ep.upd_w && K >= 1 && K <= (ep.upd_acc ? 128 : 256) && N % 8 == 0 && ep.ld % 8 == 0 && ep.ld < (1L << 22) &&
+    return dtype == kBF16 && ep.upd_w && !ep.upd_acc && K >= 1 && K <= 256 && N % 8 == 0 && ep.ld % 8 == 0 && ep.ld < (1L << 22) &&
            ((M + kPushBM - 1) / kPushBM) * (long)((N + kPushBN - 1) / kPushBN) >= 256;
 }
 
@@ -224,20 +217,19 @@ int fc_push(const void *at, long lda, int M, const void *bt, long ldb, int N, in
     p.a = Operand{at, (unsigned)abytes}; p.b = Operand{bt, (unsigned)bbytes};
     p.lda = (unsigned)(lda * 2); p.ldb = (unsigned)(ldb * 2);
     p.M = M; p.N = N; p.K = K; p.tiles_m = (int)tiles_m; p.total = (int)total; p.ld = (unsigned)ep.ld;
-    p.w = ep.upd_w; p.v = ep.upd_v; p.acc = ep.upd_acc; p.out = static_cast<float *>(ep.out);
+    p.w = ep.upd_w; p.v = ep.upd_v; p.out = static_cast<float *>(ep.out);
     for (int c = 0; c < kPushCopies; ++c) p.copy[c] = static_cast<bf16_t *>(ep.upd_copy[c]);
-    p.copies = ep.upd_copies; p.acc_first = ep.upd_acc_first;
+    p.copies = ep.upd_copies;
     p.lr = ep.upd_lr; p.mu = ep.upd_mu; p.wd = ep.upd_wd;
     const unsigned grid = (unsigned)std::min<long>(256, total);
     const auto go = [&](auto kf) {
         constexpr int KF = decltype(kf)::value;
-        if (ep.upd_acc) hipLaunchKernelGGL((fc_push_kernel<KF, true, 4>), dim3(grid), dim3(256), 0, s, p);
-        else hipLaunchKernelGGL((fc_push_kernel<KF, false, 4>), dim3(grid), dim3(256), 0, s, p);
+        hipLaunchKernelGGL((fc_push_kernel<KF, KF == 16 ? 2 : 4>), dim3(grid), dim3(256), 0, s, p);
     };
     if (K <= 32) go(std::integral_constant<int, 2>{});
     else if (K <= 64) go(std::integral_constant<int, 4>{});
     else if (K <= 128) go(std::integral_constant<int, 8>{});
-    else hipLaunchKernelGGL((fc_push_kernel<16, false, 2>), dim3(grid), dim3(256), 0, s, p);
+    else go(std::integral_constant<int, 16>{});
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
