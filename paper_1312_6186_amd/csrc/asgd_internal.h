@@ -143,6 +143,8 @@ int gemm_plain_trans(int dtype, const void *a, long lda, int M, const void *bt, 
 // A stored [K][lda] (rows m contiguous), B stored [K][ldb].
 int gemm_trans_trans(int dtype, const void *at, long lda, int M, const void *bt, long ldb, int N, int K,
                      const Epilogue &ep, const GemmPlan &plan, float *ws, hipStream_t s);
+// Partial sums ws[split][M][N] of A[M][K], M up to 64, times fully-connected weights in 16-bit data, [N][K] (rows past b_rows count as zeros) or trans [K][N] (fc_split.hip)
+int fc_split(bool trans, const void *a, long lda, int M, const void *b, long ldb, int N, int b_rows, int K, int splits, float *ws, hipStream_t s);
 // Small fully-connected products (the kernel for them takes both): the weight gradient of layer w (stored or pushed as we says) and the
 // data gradient of layer d in one launch.  They may be one layer's; not where the push rewrites the weights that d reads.
 struct FcGrads { const void *dy, *x, *w; long ld_dy, ld_x; int batch, in, out; };   // output gradients, inputs, weights [out][in]

@@ -1519,10 +1519,19 @@ int gemm_gather_plain(int dtype, const Gather &a, const void *b, long ldb, int N
     return dtype == kBF16 ? gather_plain_t<bf16_t>(a, b, ldb, N, ep, plan, ws, s) : gather_plain_t<float>(a, b, ldb, N, ep, plan, ws, s);
 }
 
+// Where fc_split runs: 16-bit data, up to 64 rows, more than one K split (as many as have K tiles; otherwise 1).  Its head says why.
+static int fc_splits(int dtype, int M, int N, int K, const GemmPlan &plan)
+{
+    if (dtype != kBF16 || M <= 0 || M > 64 || N <= 0 || N % 8 || K <= 0 || lone_applies(M, N, K)) return 1;
+    const int nkt = (K + Geo<bf16_t>::BK - 1) / Geo<bf16_t>::BK, per = (nkt + plan.splits - 1) / plan.splits;
+    return (nkt + per - 1) / per;
+}
 int gemm_plain_plain(int dtype, const void *a, long lda, int M, const void *b, long ldb, int N, int b_rows, int K, const Epilogue &ep,
                      const GemmPlan &plan, float *ws, hipStream_t s)
 {
     if (b_rows > N) return -1;
+    const int splits = fc_splits(dtype, M, N, K, plan);
+    if (splits > 1) return fc_split(false, a, lda, M, b, ldb, N, b_rows, K, splits, ws, s) == 0 ? splitk_reduce(kBF16, ws, splits, ep, M, N, nullptr, s) : -1;
     if (dtype == kBF16)
         return run<bf16_t>(make_plain_k<bf16_t>(a, lda, M, K), make_plain_k<bf16_t>(b, ldb, b_rows, K), M, N, K, ep, plan, ws, s);
     return run<float>(make_plain_k<float>(a, lda, M, K), make_plain_k<float>(b, ldb, b_rows, K), M, N, K, ep, plan, ws, s);
@@ -1531,6 +1540,8 @@ int gemm_plain_plain(int dtype, const void *a, long lda, int M, const void *b, l
 int gemm_plain_trans(int dtype, const void *a, long lda, int M, const void *bt, long ldb, int N, int K, const Epilogue &ep,
                      const GemmPlan &plan, float *ws, hipStream_t s)
 {
+    const int splits = fc_splits(dtype, M, N, K, plan);
+    if (splits > 1) return fc_split(true, a, lda, M, bt, ldb, N, N, K, splits, ws, s) == 0 ? splitk_reduce(kBF16, ws, splits, ep, M, N, nullptr, s) : -1;
     if (dtype == kBF16)
         return run<bf16_t>(make_plain_k<bf16_t>(a, lda, M, K), make_plain_t<bf16_t>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);
     return run<float>(make_plain_k<float>(a, lda, M, K), make_plain_t<float>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);

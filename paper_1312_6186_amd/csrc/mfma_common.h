@@ -51,9 +51,9 @@ struct Operand {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
     }
 };
-__device__ __forceinline__ uint4 buf_ld16(__amdgpu_buffer_rsrc_t rs, unsigned off)
+template <bool NONTEMPORAL = false> __device__ __forceinline__ uint4 buf_ld16(__amdgpu_buffer_rsrc_t rs, unsigned off)
 {
-    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0);
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, NONTEMPORAL ? 2 : 0);
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 // LDS tile of a row-contiguous operand: BK lines of ROWS elements.  A transposing read makes half a wave touch

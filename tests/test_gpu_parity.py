@@ -677,6 +677,23 @@ def test_small_nets_in_few_launches(stride, classes, batch, dtype):
         g.close()
 
 
+# Fully-connected forward passes and data gradients in K splits with few rows: batches around the blocks of 32 rows and past 64 (the general kernel),
+# outputs and inputs around the tiles of 128 columns and the K tiles of 64, K ranges that no round of four tiles divides, a last layer of odd size.
+FC_SPLIT_SHAPES = [(512, 1000, 1), (520, 1032, 31), (1032, 520, 32), (2056, 264, 33), (1024, 1088, 63), (776, 1160, 64), (512, 1000, 65)]
+
+
+@pytest.mark.parametrize("shape", FC_SPLIT_SHAPES, ids=lambda s: "%dto%d_%d" % s)
+def test_split_fully_connected_shapes(shape):
+    fin, out, batch = shape
+    layers = [("conv", 8, 1, 1, 0), ("relu",), ("fc", out), ("relu",), ("dropout", 0.5), ("fc", 1096), ("relu",), ("fc", 1003), ("softmax_ce",)]
+    g, onet, (loss, grads), (ref_loss, ref_grads, _), _ = _net_case({"name": "fcsplit", "in_shape": (3, 1, fin // 8), "classes": 1003, "layers": layers}, batch, B.BF16, plain=False)
+    try:
+        assert abs(loss - ref_loss) <= TOL[B.BF16] * abs(ref_loss)
+        compare_grads(onet, grads, ref_grads, TOL[B.BF16], "fcsplit")
+    finally:
+        g.close()
+
+
 # The push of fully-connected weights in its own kernel: 2048 and 2056 inputs (strips of 128, the last one whole and ragged) into outputs around the tiles
 # of 64 rows, enough tiles for it and one too few; batches around what a set of fragments holds (32, 64, 128, 256 images) and past it.
 PUSH_SHAPES = [(16, 16, 1000, 1), (16, 16, 1000, 17), (16, 16, 1016, 32), (16, 16, 961, 33), (16, 16, 1087, 64), (16, 16, 1000, 65), (16, 16, 1026, 128),
