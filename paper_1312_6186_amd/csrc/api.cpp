@@ -750,6 +750,7 @@ Epilogue fc_weight_epilogue(const asgd_net *n, int si, float *grads, const Serve
         ew.upd_copies = srv->copies;
         if (srv->acc) { ew.upd_acc = srv->acc + s.w_off; ew.upd_acc_first = srv->acc_first; }
         ew.upd_lr = srv->lr; ew.upd_mu = srv->mu; ew.upd_wd = srv->wd;
+        ew.upd_once = beyond_cache(n->param_count, 3);
     }
     return ew;
 }
@@ -775,6 +776,7 @@ int push_rest(asgd_net *n, const float *grads, const ServerArgs &srv, hipStream_
     p.w = srv.master; p.v = srv.momentum; p.g = grads; p.acc = srv.acc; p.acc_first = srv.acc_first; p.lr = srv.lr; p.mu = srv.mu; p.wd = srv.wd;
     for (int c = 0; c < srv.copies; ++c) { p.copy[c] = srv.copy[c]; p.f32mask |= n->dtype == kF32 ? 1u << c : 0u; }
     p.ncopies = srv.copies;
+    p.total = n->param_count;
     const double es = (double)dtype_size(n->dtype);
     auto flush = [&](bool last) -> int {
         if (last) {
@@ -1572,7 +1574,7 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
             } else {
                 PushRanges p = {};
                 p.w = params; p.v = momentum; p.g = loc->accum[worker[v]]; p.lr = lr; p.mu = mu; p.wd = wd;
-                p.n = 1; p.off[0] = 0; p.cnt[0] = P;
+                p.n = 1; p.off[0] = 0; p.cnt[0] = P; p.total = P;
                 for (int c = 0; c < push.copies; ++c) {   // a fetch fills the compute copy and the replica's own parameters
                     p.copy[p.ncopies] = push.copy[c]; p.f32mask |= n0->dtype == kF32 ? 1u << p.ncopies : 0u; ++p.ncopies;
                     p.copy[p.ncopies] = loc->params[reader[c]]; p.f32mask |= 1u << p.ncopies; ++p.ncopies;

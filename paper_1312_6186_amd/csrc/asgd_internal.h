@@ -49,7 +49,7 @@ struct Epilogue {
     // groups of 8 aligned to 16 bytes.
     float *upd_w = nullptr, *upd_v = nullptr, *upd_acc = nullptr;
     void *upd_copy[kPushCopies] = {};
-    int upd_copies = 0, upd_acc_first = 0;
+    int upd_copies = 0, upd_acc_first = 0, upd_once = 0;   // upd_once: the whole parameter vector is larger than the caches
     float upd_lr = 0.f, upd_mu = 0.f, upd_wd = 0.f;
 };
 
@@ -166,6 +166,11 @@ int gemm_trans_gather(int dtype, const void *at, long lda, int M, const Gather &
 size_t rows_wgrad_ws_floats(int dtype, int M, const Gather &b);
 
 // ---- streaming kernels (kernels_stream.hip) --------------------------------
+// Whether a pass over `arrays` parameter-shaped buffers is larger than the memory-side cache (256 MB): then nothing of them is there at the next
+// pass, and what ordinary loads allocate on their way pushes out what others have written, so that those are non-temporal too.  us, ordinary /
+// non-temporal: 62.4 M parameters, momentum and a bf16 copy 288 / 276; 57 M with the copy in the same pass 237 / 221, Adadelta over 38 M 258 / 241
+// and 41 M 264 / 247; but Adagrad over 14.9 M (178 MB) 65 / 70, Adadelta over 5.4 M 34 / 37.  Steps of 77 images 1097 / 1081.
+inline bool beyond_cache(size_t n, int arrays) { return n * 4 * (size_t)arrays > ((size_t)256 << 20); }
 int launch_update(float *w, float *v, const float *g, size_t n, float lr, float mu, float wd,
                   int *version_counter, hipStream_t s);
 // the update, and the updated parameters written to `copy` (fp32 or bf16) in the same pass
@@ -178,6 +183,8 @@ struct PushRanges {
     float *w, *v; const float *g; float *acc;
     float lr, mu, wd;
     int acc_first, n, ncopies, nlogs;
+    size_t total;                           // parameters of the whole vector, of which the ranges are a part
+    bool once;                              // filled by the launch
     void *copy[2 * kPushCopies];
     unsigned f32mask;                       // bit c: copy c is fp32
     int *counter;

@@ -44,12 +44,18 @@ __device__ __forceinline__ void update1(float &w, float &v, float g, float lr, f
     w = w + v;
 }
 
+template <bool ONCE> __device__ __forceinline__ f32x4 load4(const f32x4 *p)
+{
+    if constexpr (ONCE) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
 // SNAP: 0 = update only, 1 = also write the new parameters to `copy` as fp32, 2 = as bf16 (round to nearest even):
 // the worker copy of the next fetch comes out of the same pass instead of a second read of the parameters.
 __device__ inline uint32_t f32_to_bf16_bits(uint32_t u);
 // The work of block `blk` of an update over n parameters whose buffers are 16-byte aligned (n4 = n / 4 whole vectors;
 // block 0 also takes the n % 4 elements behind them).
-template <int SNAP>
+template <int SNAP, bool ONCE>
 __device__ __forceinline__ void update_block(f32x4 *__restrict__ w, f32x4 *__restrict__ v, const f32x4 *__restrict__ g, size_t n4, float *ws, float *vs,
                                              const float *gs, size_t n, float lr, float mu, float wd, void *__restrict__ copy, size_t blk)
 {
@@ -59,7 +65,7 @@ __device__ __forceinline__ void update_block(f32x4 *__restrict__ w, f32x4 *__res
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const size_t i = i0 + (size_t)u * 256;
-        if (i < n4) { ww[u] = w[i]; vv[u] = v[i]; gg[u] = __builtin_nontemporal_load(&g[i]); }
+        if (i < n4) { ww[u] = load4<ONCE>(&w[i]); vv[u] = load4<ONCE>(&v[i]); gg[u] = __builtin_nontemporal_load(&g[i]); }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -95,12 +101,12 @@ __device__ __forceinline__ void update_block(f32x4 *__restrict__ w, f32x4 *__res
     }
 }
 
-template <int SNAP>
+template <int SNAP, bool ONCE>
 __global__ __launch_bounds__(256) void update_kernel(f32x4 *__restrict__ w, f32x4 *__restrict__ v, const f32x4 *__restrict__ g, size_t n4,
                                                      float *ws, float *vs, const float *gs, size_t n, float lr, float mu, float wd,
                                                      int *version_counter, void *__restrict__ copy)
 {
-    update_block<SNAP>(w, v, g, n4, ws, vs, gs, n, lr, mu, wd, copy, blockIdx.x);
+    update_block<SNAP, ONCE>(w, v, g, n4, ws, vs, gs, n, lr, mu, wd, copy, blockIdx.x);
     if (blockIdx.x == 0 && threadIdx.x == 0 && version_counter) *version_counter += 1;
 }
 
@@ -149,7 +155,9 @@ __global__ __launch_bounds__(256) void push_ranges_kernel(PushRanges p)
     for (int u = 0; u < U; ++u) {
         const size_t i = i0 + (size_t)u * 256;
         if (i < n4) {
-            ww[u] = w[i]; vv[u] = v[i]; gg[u] = __builtin_nontemporal_load(&g[i]);
+            if (p.once) { ww[u] = load4<true>(&w[i]); vv[u] = load4<true>(&v[i]); }
+            else { ww[u] = w[i]; vv[u] = v[i]; }
+            gg[u] = __builtin_nontemporal_load(&g[i]);
             if (add) aa[u] = __builtin_nontemporal_load(&acc[i]);
         }
     }
@@ -199,8 +207,12 @@ static int launch_update_t(float *w, float *v, const float *g, size_t n, float l
         const size_t n4 = n / 4;
         const size_t blocks = (n4 + 1023) / 1024 ? (n4 + 1023) / 1024 : 1;
         if (blocks > 0x7fffffffu) return -1;
-        hipLaunchKernelGGL(update_kernel<SNAP>, dim3((unsigned)blocks), dim3(256), 0, s, reinterpret_cast<f32x4 *>(w), reinterpret_cast<f32x4 *>(v),
-                           reinterpret_cast<const f32x4 *>(g), n4, w, v, g, n, lr, mu, wd, version_counter, copy);
+        const auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, reinterpret_cast<f32x4 *>(w), reinterpret_cast<f32x4 *>(v),
+                               reinterpret_cast<const f32x4 *>(g), n4, w, v, g, n, lr, mu, wd, version_counter, copy);
+        };
+        if (beyond_cache(n, 3)) go(update_kernel<SNAP, true>);
+        else go(update_kernel<SNAP, false>);
     } else {
         unsigned blocks = blocks_for(n ? n : 1, 256);
         if (blocks > 8192) blocks = 8192;
@@ -227,6 +239,7 @@ int launch_push_ranges(PushRanges &p, hipStream_t s)
         if (blocks > 0x7fffffffu) return -1;
     }
     p.blk[p.n] = (unsigned)blocks;
+    p.once = beyond_cache(p.total, 3);
     hipLaunchKernelGGL(push_ranges_kernel, dim3((unsigned)blocks), dim3(256), 0, s, p);
     return launch_ok();
 }
@@ -255,7 +268,7 @@ __device__ __forceinline__ void adadelta1(float &w, float &a, float &b, float g,
     w = w + d;
 }
 // KIND 0: Adagrad (s1 = h, s2 unused, c1 = lr); KIND 1: Adadelta (s1 = a, s2 = b, c1 = rho)
-template <int KIND>
+template <int KIND, bool ONCE>
 __global__ __launch_bounds__(256) void adaptive_update_kernel(float *__restrict__ w, float *__restrict__ s1, float *__restrict__ s2,
                                                              const float *__restrict__ g, size_t n, int vec, float c1, float eps, float wd)
 {
@@ -268,8 +281,8 @@ __global__ __launch_bounds__(256) void adaptive_update_kernel(float *__restrict_
     for (int u = 0; u < U; ++u) {
         const size_t i = i0 + (size_t)u * 256;
         if (i < n4) {
-            ww[u] = reinterpret_cast<f32x4 *>(w)[i]; aa[u] = reinterpret_cast<f32x4 *>(s1)[i];
-            if (KIND == 1) bb[u] = reinterpret_cast<f32x4 *>(s2)[i];
+            ww[u] = load4<ONCE>(&reinterpret_cast<f32x4 *>(w)[i]); aa[u] = load4<ONCE>(&reinterpret_cast<f32x4 *>(s1)[i]);
+            if (KIND == 1) bb[u] = load4<ONCE>(&reinterpret_cast<f32x4 *>(s2)[i]);
             gg[u] = __builtin_nontemporal_load(&reinterpret_cast<const f32x4 *>(g)[i]);
         }
     }
@@ -310,14 +323,16 @@ int launch_adagrad(float *w, float *h, const float *g, size_t n, float lr, float
 {
     const int vec = ((((uintptr_t)w | (uintptr_t)h | (uintptr_t)g) & 15) == 0) ? 1 : 0;
     const unsigned blocks = adaptive_blocks(n, vec);
-    hipLaunchKernelGGL(adaptive_update_kernel<0>, dim3(blocks), dim3(256), 0, s, w, h, static_cast<float *>(nullptr), g, n, vec, lr, eps, wd);
+    if (beyond_cache(n, 3)) hipLaunchKernelGGL((adaptive_update_kernel<0, true>), dim3(blocks), dim3(256), 0, s, w, h, static_cast<float *>(nullptr), g, n, vec, lr, eps, wd);
+    else hipLaunchKernelGGL((adaptive_update_kernel<0, false>), dim3(blocks), dim3(256), 0, s, w, h, static_cast<float *>(nullptr), g, n, vec, lr, eps, wd);
     return launch_ok();
 }
 int launch_adadelta(float *w, float *a, float *b, const float *g, size_t n, float rho, float eps, float wd, hipStream_t s)
 {
     const int vec = ((((uintptr_t)w | (uintptr_t)a | (uintptr_t)b | (uintptr_t)g) & 15) == 0) ? 1 : 0;
     const unsigned blocks = adaptive_blocks(n, vec);
-    hipLaunchKernelGGL(adaptive_update_kernel<1>, dim3(blocks), dim3(256), 0, s, w, a, b, g, n, vec, rho, eps, wd);
+    if (beyond_cache(n, 4)) hipLaunchKernelGGL((adaptive_update_kernel<1, true>), dim3(blocks), dim3(256), 0, s, w, a, b, g, n, vec, rho, eps, wd);
+    else hipLaunchKernelGGL((adaptive_update_kernel<1, false>), dim3(blocks), dim3(256), 0, s, w, a, b, g, n, vec, rho, eps, wd);
     return launch_ok();
 }
 
