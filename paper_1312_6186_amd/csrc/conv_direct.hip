@@ -123,6 +123,8 @@ DirectPlan plan_direct(int dtype, const Gather &a, int N, int groups)
     return d;
 }
 
+DirectPlan plan_direct(int dtype, const Gather &a, int N) { return plan_direct(dtype, a, N, 1); }
+
 // Few columns over few pixels: the general engine in K splits, where it is modelled a quarter faster.
 bool split_is_faster(int dtype, const Gather &a, int N, int groups, const DirectPlan &d, size_t partials)
 {
