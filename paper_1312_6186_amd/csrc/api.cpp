@@ -750,7 +750,6 @@ Epilogue fc_weight_epilogue(const asgd_net *n, int si, float *grads, const Serve
         ew.upd_copies = srv->copies;
         if (srv->acc) { ew.upd_acc = srv->acc + s.w_off; ew.upd_acc_first = srv->acc_first; }
         ew.upd_lr = srv->lr; ew.upd_mu = srv->mu; ew.upd_wd = srv->wd;
-        ew.upd_once = beyond_cache(n->param_count, 3);
     }
     return ew;
 }
@@ -776,7 +775,6 @@ int push_rest(asgd_net *n, const float *grads, const ServerArgs &srv, hipStream_
     p.w = srv.master; p.v = srv.momentum; p.g = grads; p.acc = srv.acc; p.acc_first = srv.acc_first; p.lr = srv.lr; p.mu = srv.mu; p.wd = srv.wd;
     for (int c = 0; c < srv.copies; ++c) { p.copy[c] = srv.copy[c]; p.f32mask |= n->dtype == kF32 ? 1u << c : 0u; }
     p.ncopies = srv.copies;
-    p.total = n->param_count;
     const double es = (double)dtype_size(n->dtype);
     auto flush = [&](bool last) -> int {
         if (last) {
@@ -869,7 +867,7 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
         }
         const size_t off = s.w_off, cnt = s.w_cnt + s.b_cnt;   // weights and bias of a layer are adjacent
         ProfScope ps(n, sd, ASGD_K_UPDATE, 0, (double)cnt * (20.0 + es));
-        if (launch_update_snapshot(srv->master + off, srv->momentum + off, grads + off, cnt, srv->lr, srv->mu, srv->wd,
+        if (launch_update_snapshot(srv->master + off, srv->momentum + off, grads + off, cnt, n->param_count, srv->lr, srv->mu, srv->wd,
                                    static_cast<char *>(srv->copy[0]) + off * dtype_size(dt), dt, sd) != 0)
             return hip_fail(hipGetLastError(), "update kernel");
         return ASGD_OK;
@@ -1311,7 +1309,7 @@ int asgd_apply_update_snapshot(float *params, float *momentum, const float *grad
     if (!params || !momentum || !grads || !worker_copy) return fail(ASGD_EINVAL, "asgd_apply_update_snapshot: null argument");
     if ((((uintptr_t)params | (uintptr_t)momentum | (uintptr_t)grads) & 3) || ((uintptr_t)worker_copy & (dst_dtype == ASGD_BF16 ? 1 : 3)))
         return fail(ASGD_EALIGN, "asgd_apply_update_snapshot: misaligned buffer");
-    if (launch_update_snapshot(params, momentum, grads, n, lr, mu, wd, worker_copy, dst_dtype, static_cast<hipStream_t>(stream)) != 0)
+    if (launch_update_snapshot(params, momentum, grads, n, n, lr, mu, wd, worker_copy, dst_dtype, static_cast<hipStream_t>(stream)) != 0)
         return hip_fail(hipGetLastError(), "update kernel");
     return ASGD_OK;
 }
@@ -1545,7 +1543,7 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
                              dropout_seed, (uint64_t)b, (uint32_t)w, losses + b, worker_grads[w], ws[w], fused ? &step : nullptr);
                 if (loc && !fused && rc == ASGD_OK) {
                     if (launch_accumulate(loc->accum[w], worker_grads[w], P, i == 0, ws[w]) != 0) rc = hip_fail(hipGetLastError(), "accumulate kernel");
-                    else if (launch_update_snapshot(loc->params[w], loc->momentum[w], worker_grads[w], P, lr, mu, wd, worker_copy[w], n0->dtype,
+                    else if (launch_update_snapshot(loc->params[w], loc->momentum[w], worker_grads[w], P, P, lr, mu, wd, worker_copy[w], n0->dtype,
                                                     ws[w]) != 0)
                         rc = hip_fail(hipGetLastError(), "update kernel");
                 }
@@ -1576,7 +1574,7 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
             } else {
                 PushRanges p = {};
                 p.w = params; p.v = momentum; p.g = loc->accum[worker[v]]; p.lr = lr; p.mu = mu; p.wd = wd;
-                p.n = 1; p.off[0] = 0; p.cnt[0] = P; p.total = P;
+                p.n = 1; p.off[0] = 0; p.cnt[0] = P;
                 for (int c = 0; c < push.copies; ++c) {   // a fetch fills the compute copy and the replica's own parameters
                     p.copy[p.ncopies] = push.copy[c]; p.f32mask |= n0->dtype == kF32 ? 1u << p.ncopies : 0u; ++p.ncopies;
                     p.copy[p.ncopies] = loc->params[reader[c]]; p.f32mask |= 1u << p.ncopies; ++p.ncopies;

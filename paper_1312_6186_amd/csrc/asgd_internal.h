@@ -49,7 +49,7 @@ struct Epilogue {
     // groups of 8 aligned to 16 bytes.
     float *upd_w = nullptr, *upd_v = nullptr, *upd_acc = nullptr;
     void *upd_copy[kPushCopies] = {};
-    int upd_copies = 0, upd_acc_first = 0, upd_once = 0;   // upd_once: the whole parameter vector is larger than the caches
+    int upd_copies = 0, upd_acc_first = 0;
     float upd_lr = 0.f, upd_mu = 0.f, upd_wd = 0.f;
 };
 
@@ -167,15 +167,18 @@ int gemm_trans_gather(int dtype, const void *at, long lda, int M, const Gather &
 size_t rows_wgrad_ws_floats(int dtype, int M, const Gather &b);
 
 // ---- streaming kernels (kernels_stream.hip) --------------------------------
-// Whether a pass over `arrays` parameter-shaped buffers is larger than the memory-side cache (256 MB): then nothing of them is there at the next
-// pass, and what ordinary loads allocate on their way pushes out what others have written, so that those are non-temporal too.  us, ordinary /
-// non-temporal: 62.4 M parameters, momentum and a bf16 copy 288 / 276; 57 M with the copy in the same pass 237 / 221, Adadelta over 38 M 258 / 241
-// and 41 M 264 / 247; but Adagrad over 14.9 M (178 MB) 65 / 70, Adadelta over 5.4 M 34 / 37.  Steps of 77 images 1097 / 1081.
-inline bool beyond_cache(size_t n, int arrays) { return n * 4 * (size_t)arrays > ((size_t)256 << 20); }
+// Whether an update over n parameters reads its `arrays` fp32 vectors (parameters and state; the gradient, read once, is non-temporal in any case)
+// by non-temporal loads: where these and the copy of copy_es bytes a parameter that it writes are larger than 384 MiB, one and a half times
+// the memory-side cache.  Up to there some of a vector is still in the cache at the next pass, beyond it ordinary loads only push out what is
+// needed elsewhere.  us, ordinary / non-temporal, the same vectors again / after a copy of 1 GiB: momentum 24 M 70 / 80, 76 / 85; 40 M 126 / 129,
+// 123 / 134; 50 M 175 / 166, 159 / 171; 62 M 225 / 206, 200 / 211; with a bf16 copy 28 M 89 / 98, 97 / 105; 40 M 145 / 135, 141 / 144; 62 M 256 / 211, 228 / 227;
+// with an fp32 copy 28 M 96 / 100, 108 / 112; 36 M 154 / 126, 139 / 143; Adagrad as momentum; Adadelta 24 M 98 / 118, 114 / 122; 36 M 184 / 176, 169 / 180; 50 M
+// 265 / 244, 243 / 249.  Passes with the update behind the gradient: 25.7 M 233 / 243, 38 M 299 / 300, 58.8 M 469 / 432.
+bool beyond_cache(size_t n, int arrays, size_t copy_es);
 int launch_update(float *w, float *v, const float *g, size_t n, float lr, float mu, float wd,
                   int *version_counter, hipStream_t s);
-// the update, and the updated parameters written to `copy` (fp32 or bf16) in the same pass
-int launch_update_snapshot(float *w, float *v, const float *g, size_t n, float lr, float mu, float wd, void *copy,
+// the update, and the updated parameters written to `copy` (fp32 or bf16) in the same pass; n parameters of a vector of total
+int launch_update_snapshot(float *w, float *v, const float *g, size_t n, size_t total, float lr, float mu, float wd, void *copy,
                            int dst_dtype, hipStream_t s);
 // The update of up to 8 ranges [off, off + cnt) of the parameter vector in one launch, with what a replay does beside it in the same
 // pass: the gradient added to acc (or written there if acc_first), the new parameters written to copies in fp32 or
@@ -184,8 +187,6 @@ struct PushRanges {
     float *w, *v; const float *g; float *acc;
     float lr, mu, wd;
     int acc_first, n, ncopies, nlogs;
-    size_t total;                           // parameters of the whole vector, of which the ranges are a part
-    bool once;                              // filled by the launch
     void *copy[2 * kPushCopies];
     unsigned f32mask;                       // bit c: copy c is fp32
     int *counter;

@@ -457,9 +457,8 @@ __device__ __forceinline__ void update_tile(const uint4 *smem, const Epilogue &e
         if (m < M && n0 < N) {
             const long p = (long)m * ep.ld + n0;
             if (add) acc[r] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(__builtin_assume_aligned(ep.upd_acc + p, 16)));
-            const f32x4 *pw = reinterpret_cast<const f32x4 *>(__builtin_assume_aligned(ep.upd_w + p, 16)), *pv = reinterpret_cast<const f32x4 *>(__builtin_assume_aligned(ep.upd_v + p, 16));
-            if (ep.upd_once) { w[r] = __builtin_nontemporal_load(pw); mo[r] = __builtin_nontemporal_load(pv); }
-            else { w[r] = *pw; mo[r] = *pv; }
+            w[r] = *reinterpret_cast<const f32x4 *>(__builtin_assume_aligned(ep.upd_w + p, 16));
+            mo[r] = *reinterpret_cast<const f32x4 *>(__builtin_assume_aligned(ep.upd_v + p, 16));
         }
     });
     __syncthreads();

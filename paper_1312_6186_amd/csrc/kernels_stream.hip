@@ -155,9 +155,7 @@ __global__ __launch_bounds__(256) void push_ranges_kernel(PushRanges p)
     for (int u = 0; u < U; ++u) {
         const size_t i = i0 + (size_t)u * 256;
         if (i < n4) {
-            if (p.once) { ww[u] = load4<true>(&w[i]); vv[u] = load4<true>(&v[i]); }
-            else { ww[u] = w[i]; vv[u] = v[i]; }
-            gg[u] = __builtin_nontemporal_load(&g[i]);
+            ww[u] = w[i]; vv[u] = v[i]; gg[u] = __builtin_nontemporal_load(&g[i]);
             if (add) aa[u] = __builtin_nontemporal_load(&acc[i]);
         }
     }
@@ -198,8 +196,10 @@ __global__ __launch_bounds__(256) void update_scalar_kernel(float *w, float *v, 
     if (blockIdx.x == 0 && threadIdx.x == 0 && version_counter) *version_counter += 1;
 }
 
+bool beyond_cache(size_t n, int arrays, size_t copy_es) { return n * (4 * (size_t)arrays + copy_es) > ((size_t)384 << 20); }
+
 template <int SNAP>
-static int launch_update_t(float *w, float *v, const float *g, size_t n, float lr, float mu, float wd, int *version_counter, void *copy, hipStream_t s)
+static int launch_update_t(float *w, float *v, const float *g, size_t n, size_t total, float lr, float mu, float wd, int *version_counter, void *copy, hipStream_t s)
 {
     const unsigned copy_align = SNAP == 1 ? 15u : SNAP == 2 ? 7u : 0u;
     const bool aligned = (((uintptr_t)w | (uintptr_t)v | (uintptr_t)g) & 15) == 0 && ((uintptr_t)copy & copy_align) == 0;
@@ -211,7 +211,7 @@ static int launch_update_t(float *w, float *v, const float *g, size_t n, float l
             hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, reinterpret_cast<f32x4 *>(w), reinterpret_cast<f32x4 *>(v),
                                reinterpret_cast<const f32x4 *>(g), n4, w, v, g, n, lr, mu, wd, version_counter, copy);
         };
-        if (beyond_cache(n, 3)) go(update_kernel<SNAP, true>);
+        if (beyond_cache(total, 2, SNAP == 1 ? 4 : SNAP == 2 ? 2 : 0)) go(update_kernel<SNAP, true>);
         else go(update_kernel<SNAP, false>);
     } else {
         unsigned blocks = blocks_for(n ? n : 1, 256);
@@ -222,7 +222,7 @@ static int launch_update_t(float *w, float *v, const float *g, size_t n, float l
 }
 int launch_update(float *w, float *v, const float *g, size_t n, float lr, float mu, float wd, int *version_counter, hipStream_t s)
 {
-    return launch_update_t<0>(w, v, g, n, lr, mu, wd, version_counter, nullptr, s);
+    return launch_update_t<0>(w, v, g, n, n, lr, mu, wd, version_counter, nullptr, s);
 }
 int launch_push_ranges(PushRanges &p, hipStream_t s)
 {
@@ -239,13 +239,12 @@ int launch_push_ranges(PushRanges &p, hipStream_t s)
         if (blocks > 0x7fffffffu) return -1;
     }
     p.blk[p.n] = (unsigned)blocks;
-    p.once = beyond_cache(p.total, 3);
     hipLaunchKernelGGL(push_ranges_kernel, dim3((unsigned)blocks), dim3(256), 0, s, p);
     return launch_ok();
 }
-int launch_update_snapshot(float *w, float *v, const float *g, size_t n, float lr, float mu, float wd, void *copy, int dst_dtype, hipStream_t s)
+int launch_update_snapshot(float *w, float *v, const float *g, size_t n, size_t total, float lr, float mu, float wd, void *copy, int dst_dtype, hipStream_t s)
 {
-    return dst_dtype == kBF16 ? launch_update_t<2>(w, v, g, n, lr, mu, wd, nullptr, copy, s) : launch_update_t<1>(w, v, g, n, lr, mu, wd, nullptr, copy, s);
+    return dst_dtype == kBF16 ? launch_update_t<2>(w, v, g, n, total, lr, mu, wd, nullptr, copy, s) : launch_update_t<1>(w, v, g, n, total, lr, mu, wd, nullptr, copy, s);
 }
 
 // ---------------------------------------------------------------- Adagrad / Adadelta server updates
@@ -323,7 +322,7 @@ int launch_adagrad(float *w, float *h, const float *g, size_t n, float lr, float
 {
     const int vec = ((((uintptr_t)w | (uintptr_t)h | (uintptr_t)g) & 15) == 0) ? 1 : 0;
     const unsigned blocks = adaptive_blocks(n, vec);
-    if (beyond_cache(n, 3)) hipLaunchKernelGGL((adaptive_update_kernel<0, true>), dim3(blocks), dim3(256), 0, s, w, h, static_cast<float *>(nullptr), g, n, vec, lr, eps, wd);
+    if (beyond_cache(n, 2, 0)) hipLaunchKernelGGL((adaptive_update_kernel<0, true>), dim3(blocks), dim3(256), 0, s, w, h, static_cast<float *>(nullptr), g, n, vec, lr, eps, wd);
     else hipLaunchKernelGGL((adaptive_update_kernel<0, false>), dim3(blocks), dim3(256), 0, s, w, h, static_cast<float *>(nullptr), g, n, vec, lr, eps, wd);
     return launch_ok();
 }
@@ -331,7 +330,7 @@ int launch_adadelta(float *w, float *a, float *b, const float *g, size_t n, floa
 {
     const int vec = ((((uintptr_t)w | (uintptr_t)a | (uintptr_t)b | (uintptr_t)g) & 15) == 0) ? 1 : 0;
     const unsigned blocks = adaptive_blocks(n, vec);
-    if (beyond_cache(n, 4)) hipLaunchKernelGGL((adaptive_update_kernel<1, true>), dim3(blocks), dim3(256), 0, s, w, a, b, g, n, vec, rho, eps, wd);
+    if (beyond_cache(n, 3, 0)) hipLaunchKernelGGL((adaptive_update_kernel<1, true>), dim3(blocks), dim3(256), 0, s, w, a, b, g, n, vec, rho, eps, wd);
     else hipLaunchKernelGGL((adaptive_update_kernel<1, false>), dim3(blocks), dim3(256), 0, s, w, a, b, g, n, vec, rho, eps, wd);
     return launch_ok();
 }

@@ -237,3 +237,18 @@ def test_side_stream_hides_long_sums_of_few_workgroups():
     for dtype, out, fin, batch in ((B.F32, 10, 1024, 512), (B.BF16, 10, 1024, 512), (B.F32, 8, 3456, 2904)):
         assert f(dtype, out, fin, batch) < 200
     assert f(B.F32, 4096, 4096, 16384) == 0
+
+
+# Updates (arrays of parameters and state, bytes a parameter of the copy, parameters) with the us by ordinary and by non-temporal loads, each the
+# mean over vectors that were swept just before and vectors that were not.
+UPDATES = [(2, 0, 16000000, 51.2, 54.2), (2, 0, 24000000, 72.8, 82.2), (2, 0, 36000000, 106.0, 121.5), (2, 0, 44000000, 142.1, 148.2), (2, 0, 62000000, 212.6, 208.9),
+           (2, 2, 20000000, 69.0, 74.5), (2, 2, 28000000, 93.3, 101.1), (2, 2, 36000000, 122.0, 129.2), (2, 2, 44000000, 166.7, 156.3), (2, 2, 62378344, 242.3, 219.0),
+           (2, 4, 16000000, 60.4, 62.2), (2, 4, 28000000, 102.0, 106.0), (2, 4, 36000000, 146.4, 134.4), (2, 4, 62000000, 267.3, 226.2),
+           (3, 0, 20000000, 89.8, 99.2), (3, 0, 32000000, 142.6, 158.2), (3, 0, 44000000, 219.5, 213.8), (3, 0, 62000000, 316.9, 303.8)]
+
+
+def test_updates_read_their_vectors_by_the_faster_loads():
+    f = B.lib()["_ZN4asgd12beyond_cacheEmim"]
+    f.argtypes, f.restype = [ctypes.c_size_t, ctypes.c_int, ctypes.c_size_t], ctypes.c_bool
+    for arrays, copy_es, n, ordinary, nontemporal in UPDATES:
+        assert f(n, arrays, copy_es) == (nontemporal < ordinary), (arrays, copy_es, n)
