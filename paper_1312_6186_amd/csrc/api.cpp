@@ -100,6 +100,7 @@ struct asgd_net {
     hipStream_t side = nullptr;
     bool in_replay = false;   // replicas of a replay already run beside each other: no side stream then (measured slower)
     bool fork_pays = false;   // the side stream is worth its events (plan_net)
+    double conv_flops = 0;    // operations of the convolutions' gradients
     bool serial = false;      // every kernel on the caller's stream (asgd_net_set_serial, or ASGD_SERIAL=1 at creation)
     // Streams and events of the A-SGD replay, kept by the plan of worker 0 from one replay to the next (created on
     // first use, released with the plan), so that a replay only enqueues.
@@ -349,6 +350,11 @@ int plan_net(asgd_net &n)
     for (const Stage &s : n.stages)
         if (s.kind == ST_FC) lone += lone_fc_wgrad_us(n.dtype, s.out_f, s.in_f, n.batch);
     n.fork_pays = n.param_count >= (size_t)4 << 20 || lone >= 200;
+    n.conv_flops = 0;
+    for (size_t si = 0; si < n.stages.size(); ++si) {
+        const Stage &s = n.stages[si];
+        if (s.kind == ST_CONV) n.conv_flops += (si > 0 ? 4.0 : 2.0) * n.batch * s.outH * s.outW * s.outC * (s.inC / s.groups) * s.k * s.k;
+    }
 
     int rc = size_net(n, {SIZE_MAX, SIZE_MAX}, false);
     if (rc != ASGD_OK || n.ws_bytes <= kStaticWsBytes) return rc;
@@ -713,6 +719,7 @@ struct ServerArgs {
     int copies = 0;
     // with fuse
     bool keep = false;       // ... which stores the gradient too
+    bool slim = false;       // ... and leaves room beside it (fc_push)
     bool later = false;      // the gradient kernels leave the push to push_weights and push_rest
     hipEvent_t ready = nullptr;   // ... and this event says that what push_weights reads and replaces is done with
     float *acc = nullptr;    // the gradient is added up here (written if acc_first)
@@ -748,6 +755,7 @@ Epilogue fc_weight_epilogue(const asgd_net *n, int si, float *grads, const Serve
         ew.upd_w = srv->master + s.w_off; ew.upd_v = srv->momentum + s.w_off;
         for (int c = 0; c < srv->copies; ++c) ew.upd_copy[c] = static_cast<char *>(srv->copy[c]) + s.w_off * dtype_size(n->dtype);
         ew.upd_copies = srv->copies;
+        ew.upd_slim = srv->slim;
         if (srv->acc) { ew.upd_acc = srv->acc + s.w_off; ew.upd_acc_first = srv->acc_first; }
         ew.upd_lr = srv->lr; ew.upd_mu = srv->mu; ew.upd_wd = srv->wd;
     }
@@ -1272,6 +1280,7 @@ int train_step_impl(const char *name, bool fuse, asgd_net_t *net, float *master,
     net->last_seed = dropout_seed; net->last_step = step; net->last_worker = worker; net->ran = true;
     ServerArgs srv{master, momentum, lr, mu, wd, fuse};
     srv.copy[0] = worker_copy; srv.copies = 1;
+    srv.slim = fc_push_pays(net->param_count, net->conv_flops, net->batch, !net->fork_pays, false);
     return backward(net, worker_copy, loss, grads, st, &srv);
 }
 }  // namespace
@@ -1568,6 +1577,7 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
             push.logs = push.copies; push.counter = counter;
             if (!loc) {
                 push.keep = last_push[worker[v]] == v;
+                push.slim = fc_push_pays(P, n0->conv_flops, n0->batch, !n0->fork_pays, n_workers > 1);
                 rc = push_weights(nets[worker[v]], worker_grads[worker[v]], push, server);
                 RP(hipStreamWaitEvent(server, ev_grad[v], 0));
                 if (rc == ASGD_OK) rc = push_rest(nets[worker[v]], worker_grads[worker[v]], push, server);

@@ -49,7 +49,7 @@ struct Epilogue {
     // groups of 8 aligned to 16 bytes.
     float *upd_w = nullptr, *upd_v = nullptr, *upd_acc = nullptr;
     void *upd_copy[kPushCopies] = {};
-    int upd_copies = 0, upd_acc_first = 0;
+    int upd_copies = 0, upd_acc_first = 0, upd_slim = 0;   // upd_slim: in fc_push where it takes the layer
     float upd_lr = 0.f, upd_mu = 0.f, upd_wd = 0.f;
 };
 
@@ -156,6 +156,9 @@ bool fc_softmax_applies(long M, long N, long K);
 int fc_softmax(int dtype, const void *a, long lda, int M, const void *b, long ldb, int N, int classes, int K, const Epilogue &ep, const int32_t *labels, void *dz,
                float *row_loss, hipStream_t s);
 // The push of a fully-connected layer's weights in their gradient kernel (fc_push.hip): operands as in gemm_trans_trans
+// Whether the pushes of a pass are better off there than in the general kernel: parameters of the net, operations of its convolutions' gradients, images,
+// whether the pass stays on one stream for its size, whether other replicas' passes run beside it.
+bool fc_push_pays(size_t params, double conv_flops, long batch, bool one_stream, bool replay);
 bool fc_push_applies(int dtype, int M, int N, int K, const Epilogue &ep);
 int fc_push(const void *at, long lda, int M, const void *bt, long ldb, int N, int K, const Epilogue &ep, hipStream_t s);
 // Filter gradient: A stored [K = B*Ho*Wo][lda] (rows = cout), B gathered with the

@@ -1,18 +1,20 @@
 // The push of a fully-connected layer's weights in the kernel that computes their gradient, 16-bit data: for every weight g is a sum over the
 // minibatch, t = g + wd * w, v = mu * v - lr * t, w = w + v, and the new weights go to the replicas' copies.
 //
-// What bounds it is memory: 18 bytes a weight at the rate of a copy, 5 TB/s.  One workgroup of four
+// What bounds it is memory: 18 bytes a weight.  4096 x 9216 over 128 images take 125 us again and again (5.4 TB/s) and 138 after a copy of 1 GiB (4.9;
+// the copy itself 5.2), in gemm_kernel 123 and 131.  One workgroup of four
 // waves a CU is enough for that if loads never pause, and leaves most of the LDS and the registers of a CU to the kernels of the
-// other stream: with tiles of 128 x 128 and two workgroups of 80 KB a CU (what this replaced, as fast when alone) a data gradient found no room
-// until the whole push was over.  So a workgroup walks over tiles of 64 x 128, down a strip of columns whose inputs it keeps as
+// other stream: with tiles of 128 x 128 and two workgroups of 80 KB a CU (gemm_kernel) a data gradient finds no room
+// until the whole push is over.  So a workgroup walks over tiles of 64 x 128, down a strip of columns whose inputs it keeps as
 // fragments in registers; the rows' output gradients arrive one tile ahead, and the parameters and momenta of a tile (64 KB a
 // workgroup) are on their way while the one before is stored.  Loads return in order, so a tile's output gradients are asked for
 // ahead of its parameters: waiting for the former does not wait for the latter.  A wave owns 32 columns, a line of memory in every row, and
 // turns its sums from the matrix cores' order into rows through 4 KB of LDS of its own, without a barrier.
-// 4096 x 9216, 128 images, alone: 122 -> 125 us (5.4 TB/s); one step of the AlexNet-style net, 128 images 1328 -> 1288 us, the two-column one
-// 1201 -> 1177, 256 images 2280 -> 2238.  With half or a quarter of the parameters on their way: alone 128 and 131 us, steps the same, replays 2 % slower.
-// With 128 or 512 workgroups: alone 170 and 129, steps 1280 and 1270.  On a third stream, beside the filter gradients too: steps 1 % slower.  Non-temporal
-// parameter loads and stores matter beside convolutions (pairs of kernels 5 % slower without), for the copies they cost 15 % alone.
+// One step, gemm_kernel / here, all else the same: AlexNet-style net, 128 images 1276 / 1228 us, 256 images 2195 / 2143, two-column net 1173 / 1132.
+// Workgroups 128, 192, 256, 320, 384, 512 on one box: alone 170, 134, 125, 161, 145, 128; the three steps 1337, 1273, 1266, 1317, 1294, 1291; 2174,
+// 2246, 2212, 2254, 2232, 2236; 1223, 1172, 1162, 1190, 1183, 1173.  With half or a quarter of the parameters on their way it is 3 and 5 %
+// slower alone, on a third stream, beside the filter gradients too, a step 1 %.  Ordinary parameter loads: fc_push_pays; ordinary stores beside
+// convolutions 5 %; non-temporal stores of the copies 15 % alone.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -199,12 +201,27 @@ __global__ __launch_bounds__(256, 2) void fc_push_kernel(FcPush p)
     }
 }
 
-// Where it runs: 16-bit data, a K that fits the registers, a tile for every CU (with fewer the small products' kernel and the general one put more
+// What it is for is the room it leaves, to the kernels of the other stream; its loads, non-temporal in any case, find nothing in the caches.
+// One step, gemm_kernel / here, us.  Convolutions below of 64 and 128 channels on 32 x 32 images: 16.8 M parameters, 64 images 230 / 231, 256 images
+// 334 / 298; 33.6 M, 16 images 260 / 255, 256 images 415 / 380; the two-column net 697 / 655 at 32 images, 1173 / 1132 at 128.  With next to nothing below: 13 M
+// 183 / 189, 19 M 204 / 215, 26 M 230 / 242 at 64 images, 34 M 255 / 254 at 16 and 291 / 278 at 128, 59 M 440 / 403 at 64: there only vectors far
+// beyond the caches.  (Ordinary loads: 19 M 204, 59 M 471; convolutions below, 16.8 M, 256 images 316.)  On one stream the push of a small layer is
+// faster here by itself: 2048 to 1000, cold caches, 16 / 13, hot 9.3 / 7.0.
+// Beside other replicas' passes, eight updates, AlexNet-style net: 2 x 16 images 4759 / 4895, 4 x 32 5606 / 5643, 4 x 64 7010 / 7020, 4 x 96 8427 / 8388,
+// 4 x 128 9872 / 9756; 19 M parameters with next to nothing below, 4 x 16 1212 / 1328.  (Against the rule: 59 M so, 2 x 16 2911 / 2726.)
+bool fc_push_pays(size_t params, double conv_flops, long batch, bool one_stream, bool replay)
+{
+    if (one_stream) return true;
+    const double push_us = 18.0 * params / 5e6, conv_us = conv_flops / 5e8;
+    return (8 * conv_us >= push_us || params * 10 > ((size_t)320 << 20)) && (!replay || batch > 64);
+}
+
+// Which layers it takes: 16-bit data, a K that fits the registers, a tile for every CU (with fewer the small products' kernel and the general one put more
 // workgroups on the chip), offsets within a tile in 31 bits.  Not with the sum of a replica's gradients, a third array read and written: nothing
 // runs beside the local steps of a replica, and a CU's four waves are not enough for it (4096 x 9216, 32 images 177 us in gemm_kernel, 190 here).
 bool fc_push_applies(int dtype, int M, int N, int K, const Epilogue &ep)
 {
-    return dtype == kBF16 && ep.upd_w && !ep.upd_acc && K >= 1 && K <= 256 && N % 8 == 0 && ep.ld % 8 == 0 && ep.ld < (1L << 22) &&
+    return dtype == kBF16 && ep.upd_w && ep.upd_slim && !ep.upd_acc && K >= 1 && K <= 256 && N % 8 == 0 && ep.ld % 8 == 0 && ep.ld < (1L << 22) &&
            ((M + kPushBM - 1) / kPushBM) * (long)((N + kPushBN - 1) / kPushBN) >= 256;
 }
 

@@ -252,3 +252,21 @@ def test_updates_read_their_vectors_by_the_faster_loads():
     f.argtypes, f.restype = [ctypes.c_size_t, ctypes.c_int, ctypes.c_size_t], ctypes.c_bool
     for arrays, copy_es, n, ordinary, nontemporal in UPDATES:
         assert f(n, arrays, copy_es) == (nontemporal < ordinary), (arrays, copy_es, n)
+
+
+# Nets (parameters, operations of the convolutions' gradients, images, whether they stay on one stream, whether other replicas' passes run beside) with
+# the us of a step or a replay by the general gradient kernel's pushes and by those that leave room beside them.
+PUSHES = [(62378344, 4.4e9 * 16, 16, False, False, 660, 630), (62378344, 4.4e9 * 128, 128, False, False, 1280, 1228), (60965224, 2.4e9 * 32, 32, False, False, 697, 655),
+          (16794000, 0.08e9 * 256, 256, False, False, 334, 298), (25200000, 0.08e9 * 128, 128, False, False, 291, 273), (33600000, 0.08e9 * 16, 16, False, False, 260, 255),
+          (58800000, 1e6, 64, False, False, 440, 403), (33600000, 1e6, 128, False, False, 291, 278),
+          (13100000, 1e6, 64, False, False, 183, 189), (18900000, 1e6, 64, False, False, 204, 215), (25700000, 1e6, 16, False, False, 217, 230),
+          (62378344, 4.4e9 * 16, 16, False, True, 4759, 4895), (62378344, 4.4e9 * 32, 32, False, True, 5606, 5643), (62378344, 4.4e9 * 96, 96, False, True, 8427, 8388),
+          (62378344, 4.4e9 * 128, 128, False, True, 9872, 9756), (18900000, 1e6, 16, False, True, 1212, 1328), (18900000, 1e6, 128, False, True, 1398, 1468),
+          (2060000, 1e6, 64, True, False, 99.6, 94.9)]
+
+
+def test_pushes_go_to_the_faster_of_the_two_kernels():
+    f = B.lib()["_ZN4asgd12fc_push_paysEmdlbb"]
+    f.argtypes, f.restype = [ctypes.c_size_t, ctypes.c_double, ctypes.c_long, ctypes.c_bool, ctypes.c_bool], ctypes.c_bool
+    for params, conv_flops, batch, one_stream, replay, general, beside in PUSHES:
+        assert f(params, conv_flops, batch, one_stream, replay) == (beside < general), (params, conv_flops, batch, one_stream, replay)
