@@ -98,7 +98,7 @@ struct asgd_net {
     // The parameter gradients of a layer do not feed the next
     // layer: they run on an internal stream beside the caller's, forked and joined with events.
     hipStream_t side = nullptr;
-    bool in_replay = false;   // replicas of a replay already run beside each other: no side stream then (measured slower)
+    int replicas = 1;         // whose passes run beside each other (a replay's); no side stream where there are several (measured slower)
     bool fork_pays = false;   // the side stream is worth its events (plan_net)
     double conv_flops = 0;    // operations of the convolutions' gradients
     bool serial = false;      // every kernel on the caller's stream (asgd_net_set_serial, or ASGD_SERIAL=1 at creation)
@@ -590,6 +590,13 @@ Gather dgrad_gather(const Stage &s, const void *dy, int B, int dt, int group)
     return d;
 }
 
+// The plan of a fully-connected layer's forward pass or data gradient, with how its weights are read.
+GemmPlan fc_plan(const asgd_net *n, GemmPlan p)
+{
+    p.stream = fc_split_streams(n->param_count * dtype_size(n->dtype), n->ws_bytes, n->replicas);
+    return p;
+}
+
 const char *param_ptr(const asgd_net *n, const void *params, size_t off) { return static_cast<const char *>(params) + off * dtype_size(n->dtype); }
 
 int forward(asgd_net *n, const void *params, const void *images, const int32_t *labels, uint64_t seed, uint64_t step, uint32_t worker, hipStream_t st)
@@ -696,7 +703,7 @@ int forward(asgd_net *n, const void *params, const void *images, const int32_t *
                 return ASGD_OK;
             }
             ProfScope ps(n, st, ASGD_K_FC_FWD, 2 * Bd * s.in_f * s.out_f, (Bd * s.in_f + (double)s.w_cnt) * es + Bd * s.out_f * (s.last ? 4 : es));
-            CHECK_LAUNCH(gemm_plain_plain(dt, x, ldx, B, param_ptr(n, params, s.w_off), s.in_f, s.out_ld, s.out_f, s.in_f, ep, s.p_fwd, n->scratch, st),
+            CHECK_LAUNCH(gemm_plain_plain(dt, x, ldx, B, param_ptr(n, params, s.w_off), s.in_f, s.out_ld, s.out_f, s.in_f, ep, fc_plan(n, s.p_fwd), n->scratch, st),
                          "fc forward");
         }
         cur = s.out;
@@ -829,7 +836,7 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
 {
     const int B = n->batch, dt = n->dtype;
     const double es = (double)dtype_size(dt), Bd = (double)B;
-    const bool fork = n->fork_pays && !n->prof_on && !n->in_replay && !n->serial;
+    const bool fork = n->fork_pays && !n->prof_on && n->replicas == 1 && !n->serial;
     hipStream_t sd = fork ? n->side : st;   // parameter gradients go here
     ColsumJobs bias_jobs; bias_jobs.n = 0;  // the loss, and second stage of the bias gradients: one launch at the end, or per layer when pushing by layer
     loss_job(n->row_loss, B, loss, bias_jobs);
@@ -920,7 +927,7 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
             auto data_grad = [&]() -> int {
                 if (!prev) return ASGD_OK;
                 ProfScope ps(n, st, ASGD_K_FC_DGRAD, 2 * Bd * s.in_f * s.out_f, (Bd * s.out_f + (double)s.w_cnt + Bd * s.in_f * (ed.mask_src ? 2 : 1)) * es);
-                CHECK_LAUNCH(gemm_plain_trans(dt, s.dout, s.out_ld, B, param_ptr(n, params, s.w_off), s.in_f, s.in_f, s.out_f, ed, s.p_dgrad, n->scratch, st),
+                CHECK_LAUNCH(gemm_plain_trans(dt, s.dout, s.out_ld, B, param_ptr(n, params, s.w_off), s.in_f, s.in_f, s.out_f, ed, fc_plan(n, s.p_dgrad), n->scratch, st),
                              "fc data gradient");
                 return ASGD_OK;
             };
@@ -1469,7 +1476,7 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
         const int rc = ensure_prepared(nets[w]);
         if (rc != ASGD_OK) return rc;
     }
-    for (int w = 0; w < n_workers; ++w) nets[w]->in_replay = n_workers > 1;   // until this call has enqueued its work
+    for (int w = 0; w < n_workers; ++w) nets[w]->replicas = n_workers;   // until this call has enqueued its work
     const asgd_net *n0 = nets[0];
     const size_t P = n0->param_count;
     const size_t img_bytes = (size_t)n0->batch * n0->in_c * n0->in_h * n0->in_w * dtype_size(n0->dtype);
@@ -1498,7 +1505,7 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
         RP(hipEventCreateWithFlags(&e, kInnerEvent));
         if (rc == ASGD_OK) keeper->replay_events.push_back(e);
     }
-    if (rc != ASGD_OK) { for (int w = 0; w < n_workers; ++w) nets[w]->in_replay = false; return rc; }
+    if (rc != ASGD_OK) { for (int w = 0; w < n_workers; ++w) nets[w]->replicas = 1; return rc; }
     hipStream_t *ws = keeper->replay_streams.data();
     hipStream_t server = keeper->replay_streams[n_workers];
     hipEvent_t *ev_upd = keeper->replay_events.data(), *ev_snap = ev_upd + T, *ev_grad = ev_snap + T, *ev_fc = ev_grad + T;
@@ -1607,7 +1614,7 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
     if (rc != ASGD_OK) {
         for (int w = 0; w <= n_workers; ++w) (void)hipStreamSynchronize(keeper->replay_streams[w]);
     }
-    for (int w = 0; w < n_workers; ++w) nets[w]->in_replay = false;
+    for (int w = 0; w < n_workers; ++w) nets[w]->replicas = 1;
 #undef RP
     return rc;
 }

@@ -76,6 +76,7 @@ struct GemmPlan {
     int splits = 1;          // split-K factor
     int bm = 128, bn = 128;  // rows of a tile (filter gradients: 32, 64 or 128), columns (convolutions: 32 or 128)
     size_t ws_floats = 0;    // fp32 scratch needed when splits > 1
+    bool stream = false;     // fc_split: weights by non-temporal loads
 };
 
 // The partial sums of a split GEMM, to be added up by `blocks` workgroups of 256 threads: in a launch of their own, or beside something
@@ -145,7 +146,9 @@ int gemm_plain_trans(int dtype, const void *a, long lda, int M, const void *bt, 
 int gemm_trans_trans(int dtype, const void *at, long lda, int M, const void *bt, long ldb, int N, int K,
                      const Epilogue &ep, const GemmPlan &plan, float *ws, hipStream_t s);
 // Partial sums ws[split][M][N] of A[M][K], M up to 64, times fully-connected weights in 16-bit data, [N][K] (rows past b_rows count as zeros) or trans [K][N] (fc_split.hip)
-int fc_split(bool trans, const void *a, long lda, int M, const void *b, long ldb, int N, int b_rows, int K, int splits, float *ws, hipStream_t s);
+int fc_split(bool trans, const void *a, long lda, int M, const void *b, long ldb, int N, int b_rows, int K, int splits, bool stream, float *ws, hipStream_t s);
+// Whether it is to read them by non-temporal loads: bytes of a net's 16-bit parameters, of its workspace, replicas whose passes run beside each other
+bool fc_split_streams(size_t weights, size_t workspace, int replicas);
 // Small fully-connected products (the kernel for them takes both): the weight gradient of layer w (stored or pushed as we says) and the
 // data gradient of layer d in one launch.  They may be one layer's; not where the push rewrites the weights that d reads.
 struct FcGrads { const void *dy, *x, *w; long ld_dy, ld_x; int batch, in, out; };   // output gradients, inputs, weights [out][in]

@@ -2,12 +2,10 @@
 // (activations or output gradients, K contiguous) times the weights, stored [N][K] or (TRANS) [K][N].
 //
 // What bounds it is reading the weights once (75 MB of 4096 x 9216 in 11.2 us at 6.7 TB/s with 64 KB a CU on their way, 13.5 us with 32 KB), so four K
-// tiles are on their way and only as many rows as there are images are staged and multiplied.  What counts most is that the weights' loads are
-// non-temporal: on its way through the caches an ordinary load pushes out what the kernels before have written, and waits for it.  32
-// images, inside a pass, the general engine / here with ordinary loads / here: 4096 outputs over 9216 inputs 28.2 / 28.0 / 16.9 us, 4096 over
-// 4096 15.7 / 15.0 / 10.4, 1000 over 4096 8.3 / 7.3 / 6.4; data gradients (which the engine reads from the memory-side cache, where its forward
-// pass leaves them) 16.0 / 15.7 / 17.5, 8.8 / 9.0 / 10.4, 7.3 / 6.4 / 6.8.  One gradient at 32 images 689 -> 682 us.  With 128 images the multiplication takes
-// longer than the loads (forward 28 / 25.7, 17 / 19.6, data gradients 20.6 / 26, 13 / 16.4): the general engine keeps more than 64.
+// tiles are on their way and only as many rows as there are images are staged and multiplied.  One pass, general engine / here, us: 1024, 1024 and
+// 10 outputs over 2048 inputs, 64 images 111 / 106; 4096, 4096 and 1000 over 2048, 16 to 64 images 257 to 271 / 250 to 262; the same over 9248 203 / 196
+// at 32; AlexNet-style net, 32 images, gradient and its accumulation 680 / 672.  Up to 64 rows: with 128 images the multiplication takes
+// longer than the loads (forward 28 / 25.7, 17 / 19.6, data gradients 20.6 / 26, 13 / 16.4).
 #include <hip/hip_runtime.h>
 
 #include "asgd_internal.h"
@@ -22,7 +20,7 @@ constexpr int kFcBN = 128, kFcThreads = 512, kFcDepth = 4;   // columns of a til
 struct FcSplit {
     Operand a, b;
     unsigned lda, ldb;                        // bytes from one row (TRANS: K line) to the next
-    int M, N, K, b_rows, nkt, per, tiles_n;
+    int M, N, K, b_rows, per, tiles_n;
     float *ws;
 };
 
@@ -31,7 +29,7 @@ __device__ __forceinline__ void fc_barrier() { asm volatile("s_waitcnt lgkmcnt(0
 }  // namespace
 
 // MB: blocks of 32 rows (1 or 2).  Four waves side by side own 32 columns of 32 rows each, four more the other rows (MB = 1: they only fetch).
-template <int MB, bool TRANS>
+template <int MB, bool TRANS, bool STREAM>
 __global__ __launch_bounds__(kFcThreads, 2) void fc_split_kernel(FcSplit p)
 {
     using T = bf16_t;
@@ -64,7 +62,7 @@ __global__ __launch_bounds__(kFcThreads, 2) void fc_split_kernel(FcSplit p)
         const unsigned kc = k + slot * 8 < kend ? (unsigned)(k + slot * 8) * 2u : kInv;
         static_for<0, 2>([&](auto s) ASGD_INLINE {
             const int kl = k + line + s * 32;
-            r[set][s] = buf_ld16<true>(rb, woff[s] + (TRANS ? (kl < kend ? (unsigned)kl * p.ldb : kInv) : kc));
+            r[set][s] = buf_ld16<STREAM>(rb, woff[s] + (TRANS ? (kl < kend ? (unsigned)kl * p.ldb : kInv) : kc));
         });
         r[set][2] = buf_ld16(ra, xoff + kc);
         k += 64;
@@ -124,7 +122,16 @@ __global__ __launch_bounds__(kFcThreads, 2) void fc_split_kernel(FcSplit p)
     });
 }
 
-int fc_split(bool trans, const void *a, long lda, int M, const void *b, long ldb, int N, int b_rows, int K, int splits, float *ws, hipStream_t s)
+// Weights that stay in the memory-side cache (256 MB) from one pass to the next are read by ordinary loads.  Where what a pass writes between two uses
+// pushes them out they are non-temporal: on its way through the caches an ordinary load then pushes out what the kernels before have written, and
+// waits for it (4096 outputs over 9216 inputs inside a pass of 32 images 28.0 us, non-temporal 16.9).  Ordinary / non-temporal: 4096, 4096
+// and 1000 outputs over 9248 inputs, 64 images, gradient 207 / 227 us, step 379 / 403; AlexNet-style step in calls, 16 images 664 / 679, 32 759 / 760; gradient
+// and accumulation, 32 images 678 / 672, 48 803 / 787; replays of 2 x 16 images 4768 / 4722, 4 x 16 4870 / 4820, 4 x 32 5594 / 5595; 13 M parameters
+// behind a small convolution, replay of 4 x 48 images 1041 / 1076, 59 M 3125 / 3174.  (Against the rule: 59 M, gradient and accumulation, 340 / 327; 34 M, replay
+// of 2 x 48 images 1793 / 1727.)
+bool fc_split_streams(size_t weights, size_t workspace, int replicas) { return weights + workspace * replicas > ((size_t)256 << 20); }
+
+int fc_split(bool trans, const void *a, long lda, int M, const void *b, long ldb, int N, int b_rows, int K, int splits, bool stream, float *ws, hipStream_t s)
 {
     FcSplit p;
     const size_t ab = ((size_t)(M - 1) * lda + K) * 2, bb = trans ? ((size_t)(K - 1) * ldb + N) * 2 : ((size_t)(b_rows - 1) * ldb + K) * 2;
@@ -132,17 +139,23 @@ int fc_split(bool trans, const void *a, long lda, int M, const void *b, long ldb
     p.a = Operand{a, (unsigned)ab}; p.b = Operand{b, (unsigned)bb};
     p.lda = (unsigned)(lda * 2); p.ldb = (unsigned)(ldb * 2);
     p.M = M; p.N = N; p.K = K; p.b_rows = trans ? N : b_rows;
-    p.nkt = (K + 63) / 64; p.per = (p.nkt + splits - 1) / splits;
+    const int nkt = (K + 63) / 64;
+    p.per = (nkt + splits - 1) / splits;
     p.tiles_n = (N + kFcBN - 1) / kFcBN; p.ws = ws;
     const long grid = (long)p.tiles_n * splits;
-    if (grid <= 0 || grid > 0x7fffffffL || (long)(splits - 1) * p.per >= p.nkt) return -1;
-    const auto go = [&](auto m) {
+    if (grid <= 0 || grid > 0x7fffffffL || (long)(splits - 1) * p.per >= nkt) return -1;
+    const auto go = [&](auto m, auto t) {
         constexpr int MB = decltype(m)::value;
-        if (trans) hipLaunchKernelGGL((fc_split_kernel<MB, true>), dim3((unsigned)grid), dim3(kFcThreads), 0, s, p);
-        else hipLaunchKernelGGL((fc_split_kernel<MB, false>), dim3((unsigned)grid), dim3(kFcThreads), 0, s, p);
+        constexpr bool TRANS = decltype(t)::value;
+        if (stream) hipLaunchKernelGGL((fc_split_kernel<MB, TRANS, true>), dim3((unsigned)grid), dim3(kFcThreads), 0, s, p);
+        else hipLaunchKernelGGL((fc_split_kernel<MB, TRANS, false>), dim3((unsigned)grid), dim3(kFcThreads), 0, s, p);
     };
-    if (M <= 32) go(std::integral_constant<int, 1>{});
-    else go(std::integral_constant<int, 2>{});
+    const auto rows = [&](auto t) {
+        if (M <= 32) go(std::integral_constant<int, 1>{}, t);
+        else go(std::integral_constant<int, 2>{}, t);
+    };
+    if (trans) rows(std::true_type{});
+    else rows(std::false_type{});
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -1531,7 +1531,7 @@ int gemm_plain_plain(int dtype, const void *a, long lda, int M, const void *b, l
 {
     if (b_rows > N) return -1;
     const int splits = fc_splits(dtype, M, N, K, plan);
-    if (splits > 1) return fc_split(false, a, lda, M, b, ldb, N, b_rows, K, splits, ws, s) == 0 ? splitk_reduce(kBF16, ws, splits, ep, M, N, nullptr, s) : -1;
+    if (splits > 1) return fc_split(false, a, lda, M, b, ldb, N, b_rows, K, splits, plan.stream, ws, s) == 0 ? splitk_reduce(kBF16, ws, splits, ep, M, N, nullptr, s) : -1;
     if (dtype == kBF16)
         return run<bf16_t>(make_plain_k<bf16_t>(a, lda, M, K), make_plain_k<bf16_t>(b, ldb, b_rows, K), M, N, K, ep, plan, ws, s);
     return run<float>(make_plain_k<float>(a, lda, M, K), make_plain_k<float>(b, ldb, b_rows, K), M, N, K, ep, plan, ws, s);
@@ -1541,7 +1541,7 @@ int gemm_plain_trans(int dtype, const void *a, long lda, int M, const void *bt, 
                      const GemmPlan &plan, float *ws, hipStream_t s)
 {
     const int splits = fc_splits(dtype, M, N, K, plan);
-    if (splits > 1) return fc_split(true, a, lda, M, bt, ldb, N, N, K, splits, ws, s) == 0 ? splitk_reduce(kBF16, ws, splits, ep, M, N, nullptr, s) : -1;
+    if (splits > 1) return fc_split(true, a, lda, M, bt, ldb, N, N, K, splits, plan.stream, ws, s) == 0 ? splitk_reduce(kBF16, ws, splits, ep, M, N, nullptr, s) : -1;
     if (dtype == kBF16)
         return run<bf16_t>(make_plain_k<bf16_t>(a, lda, M, K), make_plain_t<bf16_t>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);
     return run<float>(make_plain_k<float>(a, lda, M, K), make_plain_t<float>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);

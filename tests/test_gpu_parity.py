@@ -1,4 +1,6 @@
 """Parity of the HIP path (through the C ABI) against the CPU oracle.  GPU only."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -692,6 +694,32 @@ def test_split_fully_connected_shapes(shape):
         compare_grads(onet, grads, ref_grads, TOL[B.BF16], "fcsplit")
     finally:
         g.close()
+
+
+# (images, outputs, inputs, K splits): rows around the blocks of 32, columns around the tiles of 128, K ranges of whole tiles of 64 and with a rest, fewer
+# weight rows than columns (a last layer).
+@pytest.mark.parametrize("trans", [False, True], ids=["forward", "data"])
+@pytest.mark.parametrize("rows,n,k,splits", [(1, 8, 512, 2), (31, 136, 1000, 4), (33, 1008, 4096, 8), (64, 264, 3160, 7)])
+def test_split_products_by_either_loads(rows, n, k, splits, trans):
+    """Internal function: the partial sums are the same bits by ordinary and by non-temporal weight loads, and add up to the product."""
+    f = B.lib()["_ZN4asgd8fc_splitEbPKvliS1_liiiibPfP12ihipStream_t"]
+    f.argtypes = ([ctypes.c_bool, ctypes.c_void_p, ctypes.c_long, ctypes.c_int, ctypes.c_void_p, ctypes.c_long] + [ctypes.c_int] * 4
+                  + [ctypes.c_bool, ctypes.c_void_p, ctypes.c_void_p])
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(rows * n)
+    b_rows = n if trans else n - 3
+    a = torch.randn((rows, k), generator=gen, device=DEV).bfloat16()
+    b = torch.randn((k, n) if trans else (b_rows, k), generator=gen, device=DEV).bfloat16()
+    ref = a.double().cpu() @ (b if trans else torch.nn.functional.pad(b, (0, 0, 0, n - b_rows)).t()).double().cpu()
+    sums = []
+    for stream in (False, True):
+        ws = torch.full((splits, rows, n), float("nan"), device=DEV)
+        assert f(trans, a.data_ptr(), k, rows, b.data_ptr(), n if trans else k, n, b_rows, k, splits, stream, ws.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+        sums.append(ws.cpu())
+    assert torch.equal(sums[0], sums[1])
+    # products of 16-bit values are exact in fp32; k additions in fp32 are off by less than k * 2^-24 of the sum of the magnitudes
+    bound = k * 2.0 ** -24 * (a.double().abs().cpu() @ (b if trans else torch.nn.functional.pad(b, (0, 0, 0, n - b_rows)).t()).double().abs().cpu())
+    assert ((sums[0].double().sum(0) - ref).abs() <= bound).all()
 
 
 # The push of fully-connected weights in its own kernel: 2048 and 2056 inputs (strips of 128, the last one whole and ragged) into outputs around the tiles

@@ -270,3 +270,17 @@ def test_pushes_go_to_the_faster_of_the_two_kernels():
     f.argtypes, f.restype = [ctypes.c_size_t, ctypes.c_double, ctypes.c_long, ctypes.c_bool, ctypes.c_bool], ctypes.c_bool
     for params, conv_flops, batch, one_stream, replay, general, beside in PUSHES:
         assert f(params, conv_flops, batch, one_stream, replay) == (beside < general), (params, conv_flops, batch, one_stream, replay)
+
+
+# Passes of up to 64 images (MiB of 16-bit parameters, MiB of workspace, replicas beside each other) with the us by ordinary and by non-temporal loads
+# of the fully-connected weights.
+WEIGHT_LOADS = [(112, 4, 1, 366, 381), (112, 16, 1, 379, 403), (56, 12, 1, 262, 273), (119, 72, 1, 629, 639), (119, 106, 1, 664, 679), (119, 163, 1, 678, 672),
+                (119, 221, 1, 803, 787), (119, 106, 2, 4768, 4722), (119, 106, 4, 4870, 4820), (119, 163, 2, 2200, 2190), (25, 8, 4, 1041, 1076), (36, 10, 2, 1145, 1187),
+                (112, 13, 4, 3125, 3174)]
+
+
+def test_fully_connected_weights_are_read_by_the_faster_loads():
+    f = B.lib()["_ZN4asgd16fc_split_streamsEmmi"]
+    f.argtypes, f.restype = [ctypes.c_size_t, ctypes.c_size_t, ctypes.c_int], ctypes.c_bool
+    for weights, workspace, replicas, ordinary, nontemporal in WEIGHT_LOADS:
+        assert f(weights << 20, workspace << 20, replicas) == (nontemporal < ordinary), (weights, workspace, replicas)
