@@ -110,7 +110,6 @@ struct DirectPlan {
 };
 // All groups of a layer run in one launch: a and ep of the first group (N columns each), the groups' packed filters one after the other.
 DirectPlan plan_direct(int dtype, const Gather &a, int N, int groups);   // none where the general engine is the faster one
-DirectPlan plan_direct(int dtype, const Gather &a, int N);               // one group
 // whether the general engine in K splits (plan_conv) is faster than plan d
 bool split_is_faster(int dtype, const Gather &a, int N, int groups, const DirectPlan &d, size_t partials);
 int conv_direct(int dtype, const Gather &a, const void *wpack, int N, int groups, const Epilogue &ep, const DirectPlan &plan, hipStream_t s);

@@ -169,11 +169,13 @@ class _DirectPlan(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int) for n in ("ks", "nchunks", "tile", "npl")] + [(n, ctypes.c_size_t) for n in ("nblk_elems", "pack_elems")]
 
 
-def _plan_direct(dtype, batch, h, w, cin, cout, k):
+def _plan_direct(dtype, batch, h, w, cin, cout, k, groups=1):
+    """cin and cout of one group, as the gather of a layer's first group describes it"""
     es = 2 if dtype == B.BF16 else 4
-    f = B.lib()["_ZN4asgd11plan_directEiRKNS_6GatherEi"]
-    f.argtypes, f.restype = [ctypes.c_int, ctypes.POINTER(_Gather), ctypes.c_int], _DirectPlan
-    return f(dtype, ctypes.byref(_Gather(None, batch, h, w, cin, h, w, k, k, 1, 1, k // 2, batch * h * w * cin * es, 0, 0)), cout)
+    f = B.lib()["_ZN4asgd11plan_directEiRKNS_6GatherEii"]
+    f.argtypes, f.restype = [ctypes.c_int, ctypes.POINTER(_Gather), ctypes.c_int, ctypes.c_int], _DirectPlan
+    pix = cin * groups * es if groups > 1 else 0
+    return f(dtype, ctypes.byref(_Gather(None, batch, h, w, cin, h, w, k, k, 1, 1, k // 2, batch * h * w * cin * groups * es, w * pix, pix)), cout, groups)
 
 
 def _pieces_stored(ks, npos):
@@ -188,18 +190,22 @@ def _pieces_stored(ks, npos):
                 stored, on_its_way = stored | {on_its_way}, pos
 
 
+@pytest.mark.parametrize("groups", [1, 2, 4])
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
-def test_stride1_convolution_plans_copy_every_piece_of_a_patch(dtype):
+def test_stride1_convolution_plans_copy_every_piece_of_a_patch(dtype, groups):
     wide = chunked = 0
     for k in (3, 5):
         for cin in list(range(8, 200, 8)) + [256, 384, 400, 512]:
             for cout in (8, 48, 64, 96, 128, 256):
                 for w in list(range(5, 64, 9)) + list(range(64, 560, 5)) + [111, 112, 191, 192, 223, 224, 225, 240, 255, 256, 447, 448, 479, 480, 511, 512]:
                     for h, batch in ((3, 1), (w, 4)):
-                        p = _plan_direct(dtype, batch, h, w, cin, cout, k)
+                        p = _plan_direct(dtype, batch, h, w, cin, cout, k, groups)
                         if p.ks == 0:
                             continue
                         assert p.nchunks == -(-cin // (16 * p.ks)) and p.npl > 0
+                        # a group's filters whole, and those of all groups within what an operand may hold
+                        assert p.pack_elems == -(-cout // 32) * p.nblk_elems and p.nblk_elems == p.nchunks * k * k * p.ks * 512
+                        assert p.pack_elems * groups * (2 if dtype == B.BF16 else 4) <= 1 << 30
                         if p.nchunks > 1:
                             chunked += 1
                             missing = set(range(p.npl)) - _pieces_stored(p.ks, k * k)
@@ -218,12 +224,19 @@ DIRECT_FASTER = [(B.F32, (32, 32, 5, 16, 16, 128)), (B.F32, (256, 384, 3, 13, 13
                  (B.BF16, (32, 32, 5, 16, 16, 93)), (B.BF16, (96, 256, 5, 27, 27, 128)), (B.BF16, (256, 384, 3, 13, 13, 32)), (B.BF16, (384, 256, 3, 13, 13, 256)),
                  (B.BF16, (48, 128, 5, 64, 64, 101)), (B.BF16, (192, 192, 3, 13, 13, 77))]
 
+# The same of grouped layers: channels of one group, and groups; us of a pass with the engine's launches, one a group, and with the one launch
+GROUPED_DIRECT_FASTER = [(B.F32, (16, 96, 5, 8, 16, 10), 2, 178, 143), (B.F32, (96, 24, 3, 21, 20, 60), 2, 239, 204), (B.F32, (168, 56, 5, 25, 66, 2), 4, 1356, 541),
+                         (B.F32, (16, 16, 5, 9, 99, 37), 8, 652, 465), (B.BF16, (8, 8, 5, 13, 7, 103), 2, 98, 87), (B.BF16, (48, 152, 5, 18, 9, 5), 2, 176, 127),
+                         (B.BF16, (16, 8, 3, 49, 152, 186), 4, 1480, 1127), (B.BF16, (56, 48, 3, 6, 7, 4), 4, 147, 90), (B.BF16, (56, 96, 5, 56, 7, 27), 8, 464, 195)]
+
 
 def test_stride1_layers_go_to_the_faster_of_the_two_kernels():
     for dtype, (cin, cout, k, h, w, batch), engine, direct in ENGINE_FASTER:
         assert engine < direct and _plan_direct(dtype, batch, h, w, cin, cout, k).ks == 0, (dtype, cin, cout, k, h, w, batch)
     for dtype, (cin, cout, k, h, w, batch) in DIRECT_FASTER:
         assert _plan_direct(dtype, batch, h, w, cin, cout, k).ks > 0, (dtype, cin, cout, k, h, w, batch)
+    for dtype, (cin, cout, k, h, w, batch), groups, engine, direct in GROUPED_DIRECT_FASTER:
+        assert direct < engine and _plan_direct(dtype, batch, h, w, cin, cout, k, groups).ks > 0, (dtype, cin, cout, k, h, w, batch, groups)
 
 
 def test_side_stream_hides_long_sums_of_few_workgroups():
