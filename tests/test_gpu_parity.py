@@ -726,53 +726,115 @@ def test_split_products_by_either_loads(rows, n, k, splits, trans):
 # of 64 rows, enough tiles for it and one too few; batches around what a set of fragments holds (32, 64, 128, 256 images) and past it.
 PUSH_SHAPES = [(16, 16, 1000, 1), (16, 16, 1000, 17), (16, 16, 1016, 32), (16, 16, 961, 33), (16, 16, 1087, 64), (16, 16, 1000, 65), (16, 16, 1026, 128),
                (16, 16, 1000, 129), (16, 16, 1000, 256), (16, 16, 1000, 257), (16, 16, 960, 20), (1, 257, 1000, 8), (1, 257, 968, 72), (1, 257, 2048, 136)]
+# Convolutions worth the room beside the push of 8192 inputs into 552 outputs, which takes a side stream in a step; more images than a replay's rule asks for.
+CONV_STACK = [("conv", 64, 3, 1, 1), ("relu",), ("maxpool", 2, 2), ("conv", 128, 3, 1, 1), ("relu",), ("maxpool", 2, 2), ("fc", 552), ("relu",), ("fc", 10), ("softmax_ce",)]
+
+
+def _in_push_kernel(net, outputs, inputs, batch, conv_flops, replay):
+    """What the library's rules say of the largest layer of a net (internal functions): whether its push has a kernel of its own."""
+    f = B.lib()["_ZN4asgd12fc_push_paysEmdlbb"]
+    f.argtypes, f.restype = [ctypes.c_size_t, ctypes.c_double, ctypes.c_long, ctypes.c_bool, ctypes.c_bool], ctypes.c_bool
+    params = B.asgd_param_count(net)
+    return f(params, conv_flops, batch, params < 4 << 20, replay) and batch <= 256 and -(-outputs // 64) * -(-inputs // 128) >= 256
+
+
+def _bits(tensors):
+    torch.cuda.synchronize()
+    return [t.cpu().contiguous().view(torch.uint8).numpy() for t in tensors]
+
+
+def _push_inputs(layers, in_shape, batch, replicas, minibatches):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(5)
+    nets = [B.asgd_net_create(layers, batch, in_shape, B.BF16) for _ in range(replicas)]
+    P = B.asgd_param_count(nets[0])
+    return (nets, torch.randn(P, generator=gen, device=DEV) * 0.05, torch.randn(P, generator=gen, device=DEV) * 0.01,
+            torch.randn((minibatches, batch) + in_shape, generator=gen, device=DEV).bfloat16(),
+            torch.randint(0, 10, (minibatches, batch), generator=gen, device=DEV, dtype=torch.int32))
+
+
+def _step_bits(net, params0, mom0, images, labels, fused):
+    w, v, copy, grads, loss = params0.clone(), mom0.clone(), torch.empty_like(params0, dtype=torch.bfloat16), torch.zeros_like(params0), torch.zeros(1, device=DEV)
+    B.asgd_snapshot(w, copy, B.BF16)
+    if fused:
+        B.asgd_train_step_fused(net, w, v, copy, images[0], labels[0], 3, 0, 0, loss, grads, 0.01, 0.9, 5e-4)
+    else:
+        B.asgd_fwd_bwd(net, copy, images[0], labels[0], 3, 0, 0, loss, grads)
+        B.asgd_apply_update_snapshot(w, v, grads, 0.01, 0.9, 5e-4, copy, B.BF16)
+    return _bits([w, v, copy, loss])
+
+
+def _replay_bits(nets, params0, mom0, images, labels, offset):
+    """Six updates of three replicas: the first two pushes are fetched by none, the third by all three, the last three leave their gradients.
+    offset: parameters that many floats behind a 16-byte boundary."""
+    P, W, T = params0.numel(), 3, 6
+
+    def vec(src):
+        t = torch.zeros(P + offset, device=DEV)[offset:]
+        t.copy_(src)
+        return t
+    params, mom = vec(params0), vec(mom0)
+    copies, grads = [torch.zeros(P, dtype=torch.bfloat16, device=DEV) for _ in range(W)], [torch.zeros(P, device=DEV) for _ in range(W)]
+    losses, log = torch.zeros(T, device=DEV), torch.zeros((T, 3), dtype=torch.int32, device=DEV)
+    B.asgd_replay_run(nets, params, mom, copies, grads, images, labels, np.array([0, 1, 2, 0, 1, 2], np.int32), np.array([0, 0, 0, 3, 3, 3], np.int32), 0.01, 0.9, 5e-4, 9,
+                      losses, log)
+    return _bits([params.clone(), mom.clone(), losses, log] + copies + grads)
 
 
 @pytest.mark.parametrize("shape", PUSH_SHAPES, ids=lambda s: "%dx%d_%d_%d" % s)
 def test_pushed_weights_are_the_calls_bit_for_bit(shape):
-    """One fused step against the separate calls, and a replay of local steps, whose gradients are summed up too, against the separate kernels that
-    parameters at a 4-byte offset take."""
+    """One fused step against the separate calls, and a replay against the separate kernels that parameters at a 4-byte offset take: parameters, momenta, the
+    copies of several fetches at once, the gradients left."""
     h, w_, out, batch = shape
-    layers, tdt = [("conv", 8, 1, 1, 0), ("relu",), ("fc", out), ("softmax_ce",)], torch.bfloat16
-    gen = torch.Generator(device=DEV)
-    gen.manual_seed(5)
-    nets = [B.asgd_net_create(layers, batch, (3, h, w_), B.BF16) for _ in range(2)]
-    P = B.asgd_param_count(nets[0])
-    params0 = torch.randn(P, generator=gen, device=DEV) * 0.05
-    mom0 = torch.randn(P, generator=gen, device=DEV) * 0.01
-    images = torch.randn((4, batch, 3, h, w_), generator=gen, device=DEV).to(tdt)
-    labels = torch.randint(0, 10, (4, batch), generator=gen, device=DEV, dtype=torch.int32)
-
-    def bits(tensors):
-        torch.cuda.synchronize()
-        return [t.cpu().contiguous().view(torch.uint8).numpy() for t in tensors]
-
+    layers = [("conv", 8, 1, 1, 0), ("relu",), ("fc", out), ("softmax_ce",)]
+    nets, params0, mom0, images, labels = _push_inputs(layers, (3, h, w_), batch, 3, 6)
     try:
-        steps = []
-        for fused in (True, False):
-            w, v, copy, grads, loss = params0.clone(), mom0.clone(), torch.empty(P, dtype=tdt, device=DEV), torch.zeros(P, device=DEV), torch.zeros(1, device=DEV)
-            B.asgd_snapshot(w, copy, B.BF16)
-            if fused:
-                B.asgd_train_step_fused(nets[0], w, v, copy, images[0], labels[0], 3, 0, 0, loss, grads, 0.01, 0.9, 5e-4)
-            else:
-                B.asgd_fwd_bwd(nets[0], copy, images[0], labels[0], 3, 0, 0, loss, grads)
-                B.asgd_apply_update_snapshot(w, v, grads, 0.01, 0.9, 5e-4, copy, B.BF16)
-            steps.append(bits([w, v, copy, loss]))
-        for a, b in zip(*steps):
+        inside = out > 960 and out < 2048 and batch <= 256   # 2048 outputs: a net with a side stream and nothing to run beside the push
+        assert all(_in_push_kernel(nets[0], out, 8 * h * w_, batch, 0.0, r) == inside for r in (False, True))
+        for a, b in zip(_step_bits(nets[0], params0, mom0, images, labels, True), _step_bits(nets[0], params0, mom0, images, labels, False)):
             np.testing.assert_array_equal(a, b)
-        if (images[0].numel() * 2) % 16:
-            return   # the second minibatch would not be aligned
+        for a, b in zip(_replay_bits(nets, params0, mom0, images, labels, 0), _replay_bits(nets, params0, mom0, images, labels, 1)):
+            np.testing.assert_array_equal(a, b)
+    finally:
+        for n in nets:
+            B.asgd_net_destroy(n)
+
+
+@pytest.mark.parametrize("batch", [65, 136])
+def test_pushes_beside_convolutions_are_the_calls_bit_for_bit(batch):
+    nets, params0, mom0, images, labels = _push_inputs(CONV_STACK, (3, 32, 32), batch, 3, 6)
+    try:
+        assert B.asgd_param_count(nets[0]) >= 4 << 20
+        flops = 2.0 * batch * (1024 * 64 * 27 + 2 * 256 * 128 * 576)   # filter gradients, and the second layer's data gradient
+        assert all(_in_push_kernel(nets[0], 552, 8192, batch, flops, r) for r in (False, True))
+        for a, b in zip(_step_bits(nets[0], params0, mom0, images, labels, True), _step_bits(nets[0], params0, mom0, images, labels, False)):
+            np.testing.assert_array_equal(a, b)
+        for a, b in zip(_replay_bits(nets, params0, mom0, images, labels, 0), _replay_bits(nets, params0, mom0, images, labels, 1)):
+            np.testing.assert_array_equal(a, b)
+    finally:
+        for n in nets:
+            B.asgd_net_destroy(n)
+
+
+@pytest.mark.parametrize("shape", [(16, 16, 1000, 65), (1, 257, 968, 72)], ids=lambda s: "%dx%d_%d_%d" % s)
+def test_pushes_of_local_steps_are_the_calls_bit_for_bit(shape):
+    """Local steps, whose gradients are summed up too (in the general gradient kernel), against the separate kernels that parameters at a 4-byte offset take."""
+    h, w_, out, batch = shape
+    layers = [("conv", 8, 1, 1, 0), ("relu",), ("fc", out), ("softmax_ce",)]
+    nets, params0, mom0, images, labels = _push_inputs(layers, (3, h, w_), batch, 2, 4)
+    P = params0.numel()
+    try:
         replays = []
         for offset in (0, 1):
             def vec():
                 return torch.zeros(P + offset, device=DEV)[offset:]
             params, mom, local = vec(), vec(), [[vec() for _ in range(2)] for _ in range(3)]
             params.copy_(params0)
-            copies, grads = [torch.zeros(P, dtype=tdt, device=DEV) for _ in range(2)], [torch.zeros(P, device=DEV) for _ in range(2)]
+            copies, grads = [torch.zeros(P, dtype=torch.bfloat16, device=DEV) for _ in range(2)], [torch.zeros(P, device=DEV) for _ in range(2)]
             losses, log = torch.zeros(4, device=DEV), torch.zeros((2, 3), dtype=torch.int32, device=DEV)
             B.asgd_replay_nsync_run(nets, 2, params, mom, local[0], local[1], local[2], copies, grads, images, labels, np.array([0, 1], np.int32), np.array([0, 1], np.int32),
                                     0.01, 0.9, 5e-4, 9, losses, log)
-            replays.append(bits([params.clone(), mom.clone(), losses, log] + copies + grads + [t.clone() for l in local for t in l]))
+            replays.append(_bits([params.clone(), mom.clone(), losses, log] + copies + grads + [t.clone() for l in local for t in l]))
         for a, b in zip(*replays):
             np.testing.assert_array_equal(a, b)
     finally:
