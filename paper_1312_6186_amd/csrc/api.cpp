@@ -921,13 +921,15 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
             auto pair = [&](int w, bool &done) -> int {
                 done = w >= 0 && prev && !fork && !n->prof_on && fc_pair_applies(fc_grads(n, w, params), fc_grads(n, si, params));
                 if (!done) return ASGD_OK;
-                CHECK_LAUNCH(fc_pair(dt, fc_grads(n, w, params), fc_grads(n, si, params), fc_weight_epilogue(n, w, grads, fused ? srv : nullptr), ed, st), "fc gradients");
+                CHECK_LAUNCH(fc_pair(dt, fc_grads(n, w, params), fc_grads(n, si, params), fc_weight_epilogue(n, w, grads, fused ? srv : nullptr), ed, st),
+                             "fc gradients");
                 return ASGD_OK;
             };
             auto data_grad = [&]() -> int {
                 if (!prev) return ASGD_OK;
                 ProfScope ps(n, st, ASGD_K_FC_DGRAD, 2 * Bd * s.in_f * s.out_f, (Bd * s.out_f + (double)s.w_cnt + Bd * s.in_f * (ed.mask_src ? 2 : 1)) * es);
-                CHECK_LAUNCH(gemm_plain_trans(dt, s.dout, s.out_ld, B, param_ptr(n, params, s.w_off), s.in_f, s.in_f, s.out_f, ed, fc_plan(n, s.p_dgrad), n->scratch, st),
+                CHECK_LAUNCH(gemm_plain_trans(dt, s.dout, s.out_ld, B, param_ptr(n, params, s.w_off), s.in_f, s.in_f, s.out_f, ed, fc_plan(n, s.p_dgrad),
+                                              n->scratch, st),
                              "fc data gradient");
                 return ASGD_OK;
             };
@@ -1043,7 +1045,8 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                     Epilogue ew;   // the groups' filters follow each other: one matrix of groups * Og rows
                     ew.out = grads + s.w_off; ew.mode = 1; ew.out_f32 = 1;
                     ew.cw_cout = s.outC; ew.cw_cin = Cg; ew.cw_cinp = s.groups > 1 ? Cg : s.inCp; ew.cw_kh = s.k; ew.cw_kw = s.k;
-                    CHECK_LAUNCH(conv_wgrad(s.dout, s.outCp, Ogp, s.groups, conv_gather(s, xin, B, dt), ew, s.d_wgrad, n->scratch_side, join ? &partial : nullptr, sd),
+                    CHECK_LAUNCH(conv_wgrad(s.dout, s.outCp, Ogp, s.groups, conv_gather(s, xin, B, dt), ew, s.d_wgrad, n->scratch_side,
+                                            join ? &partial : nullptr, sd),
                                  "conv filter gradient");
                 } else if (s.groups > 1) {
                     for (int gi = 0; gi < s.groups; ++gi) {
@@ -1060,7 +1063,8 @@ int backward(asgd_net *n, const void *params, float *loss, float *grads, hipStre
                     Epilogue ew;
                     ew.out = grads + s.w_off; ew.mode = s.rw ? 2 : 1; ew.out_f32 = 1;
                     ew.cw_cout = s.outC; ew.cw_cin = s.inC; ew.cw_cinp = s.rw ? s.rwKW : s.inCp; ew.cw_kh = s.k; ew.cw_kw = s.k; ew.cw_rwc = s.rw ? s.rwC : 4;
-                    CHECK_LAUNCH(gemm_trans_gather(dt, s.dout, s.outCp, s.outCp, g, ew, s.p_wgrad, n->scratch_side, join ? &partial : nullptr, sd), "conv filter gradient");
+                    CHECK_LAUNCH(gemm_trans_gather(dt, s.dout, s.outCp, s.outCp, g, ew, s.p_wgrad, n->scratch_side, join ? &partial : nullptr, sd),
+                                 "conv filter gradient");
                 }
                 return ASGD_OK;
             };

@@ -144,7 +144,8 @@ int gemm_plain_trans(int dtype, const void *a, long lda, int M, const void *bt, 
 // A stored [K][lda] (rows m contiguous), B stored [K][ldb].
 int gemm_trans_trans(int dtype, const void *at, long lda, int M, const void *bt, long ldb, int N, int K,
                      const Epilogue &ep, const GemmPlan &plan, float *ws, hipStream_t s);
-// Partial sums ws[split][M][N] of A[M][K], M up to 64, times fully-connected weights in 16-bit data, [N][K] (rows past b_rows count as zeros) or trans [K][N] (fc_split.hip)
+// Partial sums ws[split][M][N] of A[M][K], M up to 64, times fully-connected weights in 16-bit data, [N][K] (rows past b_rows count as zeros) or
+// trans [K][N] (fc_split.hip)
 int fc_split(bool trans, const void *a, long lda, int M, const void *b, long ldb, int N, int b_rows, int K, int splits, bool stream, float *ws, hipStream_t s);
 // Whether it is to read them by non-temporal loads: bytes of a net's 16-bit parameters, of its workspace, replicas whose passes run beside each other
 bool fc_split_streams(size_t weights, size_t workspace, int replicas);

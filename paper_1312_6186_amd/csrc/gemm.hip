@@ -698,7 +698,8 @@ struct LoneShared { f32x4 part[kLoneWaves][64]; float sums[16][20]; };
 // softmax cross-entropy over the logits of a tile (all classes in its 16 columns): labels, gradient at the logits [M][ld], loss per row
 struct LoneCe { const int32_t *labels; void *dz; float *row_loss; int classes; };
 template <typename T, bool CE, class LA, class LB>
-__device__ __forceinline__ void lone_tile(LoneShared &sh, const LA &la, const LB &lb, const Epilogue &ep, int M, int N, int K, int tiles_n, int block, const LoneCe &ce)
+__device__ __forceinline__ void lone_tile(LoneShared &sh, const LA &la, const LB &lb, const Epilogue &ep, int M, int N, int K, int tiles_n, int block,
+                                          const LoneCe &ce)
 {
     auto &part = sh.part;
     auto &sums = sh.sums;
@@ -1531,7 +1532,10 @@ int gemm_plain_plain(int dtype, const void *a, long lda, int M, const void *b, l
 {
     if (b_rows > N) return -1;
     const int splits = fc_splits(dtype, M, N, K, plan);
-    if (splits > 1) return fc_split(false, a, lda, M, b, ldb, N, b_rows, K, splits, plan.stream, ws, s) == 0 ? splitk_reduce(kBF16, ws, splits, ep, M, N, nullptr, s) : -1;
+    if (splits > 1) {
+        if (fc_split(false, a, lda, M, b, ldb, N, b_rows, K, splits, plan.stream, ws, s) != 0) return -1;
+        return splitk_reduce(kBF16, ws, splits, ep, M, N, nullptr, s);
+    }
     if (dtype == kBF16)
         return run<bf16_t>(make_plain_k<bf16_t>(a, lda, M, K), make_plain_k<bf16_t>(b, ldb, b_rows, K), M, N, K, ep, plan, ws, s);
     return run<float>(make_plain_k<float>(a, lda, M, K), make_plain_k<float>(b, ldb, b_rows, K), M, N, K, ep, plan, ws, s);
@@ -1541,7 +1545,10 @@ int gemm_plain_trans(int dtype, const void *a, long lda, int M, const void *bt, 
                      const GemmPlan &plan, float *ws, hipStream_t s)
 {
     const int splits = fc_splits(dtype, M, N, K, plan);
-    if (splits > 1) return fc_split(true, a, lda, M, bt, ldb, N, N, K, splits, plan.stream, ws, s) == 0 ? splitk_reduce(kBF16, ws, splits, ep, M, N, nullptr, s) : -1;
+    if (splits > 1) {
+        if (fc_split(true, a, lda, M, bt, ldb, N, N, K, splits, plan.stream, ws, s) != 0) return -1;
+        return splitk_reduce(kBF16, ws, splits, ep, M, N, nullptr, s);
+    }
     if (dtype == kBF16)
         return run<bf16_t>(make_plain_k<bf16_t>(a, lda, M, K), make_plain_t<bf16_t>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);
     return run<float>(make_plain_k<float>(a, lda, M, K), make_plain_t<float>(bt, ldb, N, K), M, N, K, ep, plan, ws, s);
@@ -1601,7 +1608,8 @@ template <typename T> static int launch_lone_pair(const FcGrads &w, const FcGrad
     p.da = make_plain_k<T>(d.dy, d.ld_dy, d.batch, d.out); p.db = make_plain_t<T>(d.w, d.in, d.in, d.out);
     p.d_ep = de; p.d_m = d.batch; p.d_n = d.in; p.d_k = d.out; p.d_tiles_n = (d.in + 15) / 16;
     if (p.wa.op.bytes == 0 || p.wb.op.bytes == 0 || p.da.op.bytes == 0 || p.db.op.bytes == 0) return -1;
-    hipLaunchKernelGGL(lone_pair_kernel<T>, dim3((unsigned)(p.w_blocks + lone_tiles(d.batch, d.in))), dim3((unsigned)(64 * std::max(lone_waves(w.batch), lone_waves(d.out)))), 0, s, p);
+    const unsigned blocks = (unsigned)(p.w_blocks + lone_tiles(d.batch, d.in)), threads = (unsigned)(64 * std::max(lone_waves(w.batch), lone_waves(d.out)));
+    hipLaunchKernelGGL(lone_pair_kernel<T>, dim3(blocks), dim3(threads), 0, s, p);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 bool fc_pair_applies(const FcGrads &w, const FcGrads &d)

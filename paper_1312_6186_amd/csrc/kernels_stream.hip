@@ -244,7 +244,8 @@ int launch_push_ranges(PushRanges &p, hipStream_t s)
 }
 int launch_update_snapshot(float *w, float *v, const float *g, size_t n, size_t total, float lr, float mu, float wd, void *copy, int dst_dtype, hipStream_t s)
 {
-    return dst_dtype == kBF16 ? launch_update_t<2>(w, v, g, n, total, lr, mu, wd, nullptr, copy, s) : launch_update_t<1>(w, v, g, n, total, lr, mu, wd, nullptr, copy, s);
+    if (dst_dtype == kBF16) return launch_update_t<2>(w, v, g, n, total, lr, mu, wd, nullptr, copy, s);
+    return launch_update_t<1>(w, v, g, n, total, lr, mu, wd, nullptr, copy, s);
 }
 
 // ---------------------------------------------------------------- Adagrad / Adadelta server updates
@@ -322,16 +323,16 @@ int launch_adagrad(float *w, float *h, const float *g, size_t n, float lr, float
 {
     const int vec = ((((uintptr_t)w | (uintptr_t)h | (uintptr_t)g) & 15) == 0) ? 1 : 0;
     const unsigned blocks = adaptive_blocks(n, vec);
-    if (beyond_cache(n, 2, 0)) hipLaunchKernelGGL((adaptive_update_kernel<0, true>), dim3(blocks), dim3(256), 0, s, w, h, static_cast<float *>(nullptr), g, n, vec, lr, eps, wd);
-    else hipLaunchKernelGGL((adaptive_update_kernel<0, false>), dim3(blocks), dim3(256), 0, s, w, h, static_cast<float *>(nullptr), g, n, vec, lr, eps, wd);
+    const auto kernel = beyond_cache(n, 2, 0) ? adaptive_update_kernel<0, true> : adaptive_update_kernel<0, false>;
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, w, h, static_cast<float *>(nullptr), g, n, vec, lr, eps, wd);
     return launch_ok();
 }
 int launch_adadelta(float *w, float *a, float *b, const float *g, size_t n, float rho, float eps, float wd, hipStream_t s)
 {
     const int vec = ((((uintptr_t)w | (uintptr_t)a | (uintptr_t)b | (uintptr_t)g) & 15) == 0) ? 1 : 0;
     const unsigned blocks = adaptive_blocks(n, vec);
-    if (beyond_cache(n, 3, 0)) hipLaunchKernelGGL((adaptive_update_kernel<1, true>), dim3(blocks), dim3(256), 0, s, w, a, b, g, n, vec, rho, eps, wd);
-    else hipLaunchKernelGGL((adaptive_update_kernel<1, false>), dim3(blocks), dim3(256), 0, s, w, a, b, g, n, vec, rho, eps, wd);
+    const auto kernel = beyond_cache(n, 3, 0) ? adaptive_update_kernel<1, true> : adaptive_update_kernel<1, false>;
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, w, a, b, g, n, vec, rho, eps, wd);
     return launch_ok();
 }
 
@@ -1069,7 +1070,8 @@ __global__ __launch_bounds__(256) void pool_bwd_s2_reduce_kernel(const T *__rest
 {
     __shared__ union { float part[256 * Vec16<T>::N]; ReduceShared red; } sh;
     if (blockIdx.x < red.blocks) reduce_block<T>(red, blockIdx.x, sh.red);
-    else pool_bwd_s2_block<T, K>(dy, arg, x, relu, dx, B, H, W, Cp, Ho, Wo, pi, bands, xcd_block(blockIdx.x - red.blocks, gridDim.x - red.blocks), gridDim.x - red.blocks, sh.part);
+    else pool_bwd_s2_block<T, K>(dy, arg, x, relu, dx, B, H, W, Cp, Ho, Wo, pi, bands, xcd_block(blockIdx.x - red.blocks, gridDim.x - red.blocks),
+                                 gridDim.x - red.blocks, sh.part);
 }
 
 // Where pool_bwd_s2_kernel runs: a block's 256 threads see two images, or several small ones, in one range of 2 GiB.

@@ -44,7 +44,8 @@ template <typename T> __device__ __forceinline__ void reduce_plain(const float *
 // to 256 partials each): L = 8 or 32 neighbouring lanes, or with L = 256 a workgroup, share a group, lane l adds partials l, l+L,
 // ... in that order, and the L sums are combined in a fixed butterfly (and the four wavefronts' in their order), so the
 // result does not depend on anything but the inputs.
-template <typename T, int L> __device__ __forceinline__ void reduce_wide(const float *ws, int splits, const Epilogue &ep, int M, int N, unsigned block, float (&part)[4][8])
+template <typename T, int L>
+__device__ __forceinline__ void reduce_wide(const float *ws, int splits, const Epilogue &ep, int M, int N, unsigned block, float (&part)[4][8])
 {
     static_assert(L == 8 || L == 32 || L == 256, "lanes per group of outputs");
     constexpr int SH = L == 8 ? 3 : L == 32 ? 5 : 8;
@@ -103,7 +104,8 @@ template <typename T, int L> __device__ __forceinline__ void reduce_wide(const f
 // 3 x 3): 384 -> 384 channels, 7 partials (42 MB) 14.4 us there, 8.5 here; 256 -> 384, 10 partials 10.8 and 8.2; 384 -> 256, 14
 // partials 13.8 and 10.7; 5 x 5, 96 -> 256, 17 partials 10.6 and 9.0.
 constexpr int kReduceLds = 2048;   // floats: window positions times channels of a workgroup
-__device__ __forceinline__ void reduce_filters(const float *ws, int splits, const Epilogue &ep, int M, int N, int npos, int cb_max, int chunks, unsigned block, float *sums)
+__device__ __forceinline__ void reduce_filters(const float *ws, int splits, const Epilogue &ep, int M, int N, int npos, int cb_max, int chunks,
+                                               unsigned block, float *sums)
 {
     const int m = (int)block / chunks, c0 = ((int)block - m * chunks) * cb_max;
     if (m >= ep.cw_cout) return;
