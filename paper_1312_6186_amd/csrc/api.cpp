@@ -1588,7 +1588,9 @@ static int replay_impl(asgd_net_t *const *nets, int n_workers, float *params, fl
             push.logs = push.copies; push.counter = counter;
             if (!loc) {
                 push.keep = last_push[worker[v]] == v;
-                push.slim = fc_push_pays(P, n0->conv_flops, n0->batch, !n0->fork_pays, n_workers > 1);
+                bool others = false;   // gradients on earlier versions, of other replicas, run beside the push
+                for (int a = v + 1; a < T && !others; ++a) others = read_version[a] <= v;
+                push.slim = fc_push_pays(P, n0->conv_flops, n0->batch, !n0->fork_pays, others);
                 rc = push_weights(nets[worker[v]], worker_grads[worker[v]], push, server);
                 RP(hipStreamWaitEvent(server, ev_grad[v], 0));
                 if (rc == ASGD_OK) rc = push_rest(nets[worker[v]], worker_grads[worker[v]], push, server);

@@ -161,7 +161,7 @@ int fc_softmax(int dtype, const void *a, long lda, int M, const void *b, long ld
 // The push of a fully-connected layer's weights in their gradient kernel (fc_push.hip): operands as in gemm_trans_trans
 // Whether the pushes of a pass are better off there than in the general kernel: parameters of the net, operations of its convolutions' gradients, images,
 // whether the pass stays on one stream for its size, whether other replicas' passes run beside it.
-bool fc_push_pays(size_t params, double conv_flops, long batch, bool one_stream, bool replay);
+bool fc_push_pays(size_t params, double conv_flops, long batch, bool one_stream, bool others);
 bool fc_push_applies(int dtype, int M, int N, int K, const Epilogue &ep);
 int fc_push(const void *at, long lda, int M, const void *bt, long ldb, int N, int K, const Epilogue &ep, hipStream_t s);
 // Filter gradient: A stored [K = B*Ho*Wo][lda] (rows = cout), B gathered with the

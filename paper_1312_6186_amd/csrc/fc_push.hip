@@ -208,12 +208,14 @@ __global__ __launch_bounds__(256, 2) void fc_push_kernel(FcPush p)
 // beyond the caches.  (Ordinary loads: 19 M 204, 59 M 471; convolutions below, 16.8 M, 256 images 316.)  On one stream the push of a small layer is
 // faster here by itself: 2048 to 1000, cold caches, 16 / 13, hot 9.3 / 7.0.
 // Beside other replicas' passes, eight updates, AlexNet-style net: 2 x 16 images 4759 / 4895, 4 x 32 5606 / 5643, 4 x 64 7010 / 7020, 4 x 96 8427 / 8388,
-// 4 x 128 9872 / 9756; 19 M parameters with next to nothing below, 4 x 16 1212 / 1328.  (Against the rule: 59 M so, 2 x 16 2911 / 2726.)
-bool fc_push_pays(size_t params, double conv_flops, long batch, bool one_stream, bool replay)
+// 4 x 128 9872 / 9756; 19 M parameters with next to nothing below, 4 x 16 1212 / 1328.  An update of a replay that no other replica's gradient runs beside
+// is a step: every gradient on the newest version, 2 x 16 images 5632 / 5594, 2 x 20 5758 / 5752, 2 x 26 6004 / 6065; 59 M 3219 / 2982; both kinds in one
+// schedule, 4 x 16 (one update stale at most) 4959 / 4964, 4 x 32 5656 / 5628; 59 M 3053 / 2943.
+bool fc_push_pays(size_t params, double conv_flops, long batch, bool one_stream, bool others)
 {
     if (one_stream) return true;
     const double push_us = 18.0 * params / 5e6, conv_us = conv_flops / 5e8;
-    return (8 * conv_us >= push_us || params * 10 > ((size_t)320 << 20)) && (!replay || batch > 64);
+    return (8 * conv_us >= push_us || params * 10 > ((size_t)320 << 20)) && (!others || batch > 64);
 }
 
 // Which layers it takes: 16-bit data, a K that fits the registers, a tile for every CU (with fewer the small products' kernel and the general one put more

@@ -275,14 +275,14 @@ PUSHES = [(62378344, 4.4e9 * 16, 16, False, False, 660, 630), (62378344, 4.4e9 *
           (13100000, 1e6, 64, False, False, 183, 189), (18900000, 1e6, 64, False, False, 204, 215), (25700000, 1e6, 16, False, False, 217, 230),
           (62378344, 4.4e9 * 16, 16, False, True, 4759, 4895), (62378344, 4.4e9 * 32, 32, False, True, 5606, 5643), (62378344, 4.4e9 * 96, 96, False, True, 8427, 8388),
           (62378344, 4.4e9 * 128, 128, False, True, 9872, 9756), (18900000, 1e6, 16, False, True, 1212, 1328), (18900000, 1e6, 128, False, True, 1398, 1468),
-          (2060000, 1e6, 64, True, False, 99.6, 94.9)]
+          (62378344, 4.4e9 * 16, 16, False, False, 5632, 5594), (58800000, 1e6, 16, False, False, 3219, 2982), (2060000, 1e6, 64, True, False, 99.6, 94.9)]
 
 
 def test_pushes_go_to_the_faster_of_the_two_kernels():
     f = B.lib()["_ZN4asgd12fc_push_paysEmdlbb"]
     f.argtypes, f.restype = [ctypes.c_size_t, ctypes.c_double, ctypes.c_long, ctypes.c_bool, ctypes.c_bool], ctypes.c_bool
-    for params, conv_flops, batch, one_stream, replay, general, beside in PUSHES:
-        assert f(params, conv_flops, batch, one_stream, replay) == (beside < general), (params, conv_flops, batch, one_stream, replay)
+    for params, conv_flops, batch, one_stream, others, general, beside in PUSHES:
+        assert f(params, conv_flops, batch, one_stream, others) == (beside < general), (params, conv_flops, batch, one_stream, others)
 
 
 # Passes of up to 64 images (MiB of 16-bit parameters, MiB of workspace, replicas beside each other) with the us by ordinary and by non-temporal loads
